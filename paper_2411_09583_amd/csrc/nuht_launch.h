@@ -29,6 +29,24 @@ struct Arena {
     int32_t node_cap, l_cap, a_cap, d_cap, q_cap, litem_cap, aitem_cap, pad;
 };
 
+// Most partitions planned together (launch_planning_many).
+constexpr int kMaxPlanParts = 8;
+
+// What the planning kernels of one partition need.
+struct PlanArgs {
+    PlanDev P;
+    Arena A;
+    int32_t* K;          // staircases (m and n entries)
+    int32_t* Jc;
+    int32_t* a_cells;    // cells of each asymptotic item
+    int64_t min_size;
+    int32_t ncand, dft_max;
+    double sigma;
+    Summary* sum;
+    const int32_t* errs; // the input check's flags
+    int32_t n_errs, pad;
+};
+
 // planning (plan.hip)
 // Keys (bit patterns) of r (na values) and w (nb values) sorted into (k0, v0)
 // with their caller indices, (k1, v1) and hist (sort_hist_len ints) as
@@ -44,9 +62,10 @@ hipError_t launch_reduce_errs(const int32_t* errs, int32_t n, int32_t* flag, hip
 // offsets, all on the device; counts and totals are left in *sum.
 // The summary is cleared first; its domain_error is set from the input
 // check's tile flags (errs, n_errs entries).
-hipError_t launch_planning(const PlanDev& P, const Arena& A, int32_t* K, int32_t* Jc, int32_t* a_cells,
-                           int64_t min_size, int32_t ncand, int32_t dft_max, double sigma, Summary* sum,
-                           const int32_t* errs, int32_t n_errs, hipStream_t s);
+hipError_t launch_planning(const PlanArgs& a, hipStream_t s);
+// The same for `count` partitions whose arguments are in device memory, every
+// stage one launch over all of them; nm: the largest n + m.
+hipError_t launch_planning_many(const PlanArgs* args_dev, int count, int64_t nm, hipStream_t s);
 
 // execution (exec.hip)
 struct ExecBuffers {

@@ -1211,12 +1211,12 @@ __device__ __forceinline__ void staircase_body(const double* __restrict__ sorted
 // first nba workgroups count, for each sorted frequency, the sorted points
 // whose product with it is at most z (K); the rest count, for each sorted
 // point, the sorted frequencies (Jc).  One launch fewer on the plan's path.
-__global__ __launch_bounds__(256) void k_staircase(const double* __restrict__ rs, int32_t n,
-                                                   const double* __restrict__ ws, int32_t m, double z,
-                                                   int32_t* __restrict__ K, int32_t* __restrict__ Jc, int32_t nba)
+__device__ __forceinline__ void staircases(const PlanArgs& a)
 {
-    if ((int32_t)blockIdx.x < nba) staircase_body(rs, n, ws, m, z, K, blockIdx.x);
-    else staircase_body(ws, m, rs, n, z, Jc, blockIdx.x - nba);
+    const PlanDev& P = a.P;
+    const int32_t nba = (P.m + 255) / 256;
+    if ((int32_t)blockIdx.x < nba) staircase_body(P.rs, P.n, P.ws, P.m, P.z, a.K, blockIdx.x);
+    else staircase_body(P.ws, P.m, P.rs, P.n, P.z, a.Jc, blockIdx.x - nba);
 }
 
 // ---------------------------------------------------------------------------
@@ -1319,11 +1319,15 @@ constexpr int kSubThreads = 256;
 // past them go to the global queues at the same index.
 constexpr int kSubLds = 1920;
 
-__global__ __launch_bounds__(kSubThreads) void k_subdivide(const int32_t* __restrict__ K, const int32_t* __restrict__ Jc,
-                                                    int32_t m, int32_t n, int64_t min_size, int32_t ncand, Arena A,
-                                                    Summary* __restrict__ sum, const int32_t* __restrict__ errs,
-                                                    int32_t n_errs)
+__device__ __forceinline__ void subdivide(const PlanArgs& a)
 {
+    const int32_t* __restrict__ K = a.K;
+    const int32_t* __restrict__ Jc = a.Jc;
+    const int32_t* __restrict__ errs = a.errs;
+    Summary* __restrict__ sum = a.sum;
+    const Arena& A = a.A;
+    const int32_t m = a.P.m, n = a.P.n, ncand = a.ncand, n_errs = a.n_errs;
+    const int64_t min_size = a.min_size;
     __shared__ int32_t wsum[4][16];
     __shared__ Rect lq[2][kSubLds];
     int tid = threadIdx.x;
@@ -1457,8 +1461,13 @@ __global__ __launch_bounds__(kSubThreads) void k_subdivide(const int32_t* __rest
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int32_t iceil(double x) { return (int32_t)ceil(x); }
 
-__global__ void k_block_params(PlanDev P, Arena A, int32_t dft_max, double sigma, Summary* __restrict__ sum)
+__device__ __forceinline__ void block_params(const PlanArgs& a)
 {
+    const PlanDev& P = a.P;
+    const Arena& A = a.A;
+    Summary* __restrict__ sum = a.sum;
+    const int32_t dft_max = a.dft_max;
+    const double sigma = a.sigma;
     if (sum->overflow) return;
     const int32_t n_l = sum->n_l, n_a = sum->n_a;
     const int w = P.w;
@@ -1527,8 +1536,11 @@ __global__ void k_block_params(PlanDev P, Arena A, int32_t dft_max, double sigma
 // ---------------------------------------------------------------------------
 constexpr int kPlanScanThreads = 256;
 
-__global__ __launch_bounds__(kPlanScanThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_plan_scan(PlanDev P, Arena A, Summary* __restrict__ sum)
+__device__ __forceinline__ void plan_scan(const PlanArgs& a)
 {
+    const PlanDev& P = a.P;
+    const Arena& A = a.A;
+    Summary* __restrict__ sum = a.sum;
     __shared__ int64_t wsum[2][16];
     __shared__ int32_t cls_cnt[kMaxFftLog2 + 1];
     __shared__ int32_t cls_first[kMaxFftLog2 + 1];
@@ -1659,8 +1671,12 @@ __global__ __launch_bounds__(kPlanScanThreads) __attribute__((amdgpu_waves_per_e
 // An item is a chunk of one block's columns; an asymptotic item also carries
 // the subgrid of cells its points can reach (one cell of margin each side).
 // ---------------------------------------------------------------------------
-__global__ void k_items(PlanDev P, Arena A, Summary* __restrict__ sum, int32_t* __restrict__ a_cells)
+__device__ __forceinline__ void items(const PlanArgs& a)
 {
+    const PlanDev& P = a.P;
+    const Arena& A = a.A;
+    Summary* __restrict__ sum = a.sum;
+    int32_t* __restrict__ a_cells = a.a_cells;
     if (sum->overflow) return;
     const int32_t n_l = sum->n_l, n_a = sum->n_a;
     const int32_t n_li = sum->n_litems, n_ai = sum->n_aitems;
@@ -1717,9 +1733,12 @@ __global__ void k_items(PlanDev P, Arena A, Summary* __restrict__ sum, int32_t* 
 // dense items at alist[0 ..), medium ones after them, and the others at
 // alist[n_ai - 1], alist[n_ai - 2], ..., each list in item order (one
 // workgroup).
-__global__ __launch_bounds__(kPlanScanThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_item_scan(
-    PlanDev P, Arena A, Summary* __restrict__ sum, const int32_t* __restrict__ a_cells)
+__device__ __forceinline__ void item_scan(const PlanArgs& a)
 {
+    const PlanDev& P = a.P;
+    const Arena& A = a.A;
+    Summary* __restrict__ sum = a.sum;
+    const int32_t* __restrict__ a_cells = a.a_cells;
     __shared__ int64_t wsum[3][16];
     __shared__ int32_t n_dense_total;
     if (sum->overflow) return;
@@ -1775,6 +1794,30 @@ __global__ __launch_bounds__(kPlanScanThreads) __attribute__((amdgpu_waves_per_e
         sum->n_amed = (int32_t)run_med;
     }
 }
+
+// ---------------------------------------------------------------------------
+// The planning kernels: for one partition, its arguments passed by value; for
+// several (k_*_many), read from device memory through the constant address
+// space, partition blockIdx.y.
+// ---------------------------------------------------------------------------
+typedef const __attribute__((address_space(4))) PlanArgs ConstPlanArgs;
+__device__ __forceinline__ const PlanArgs& args_of(const PlanArgs* args)
+{
+    return *(const PlanArgs*)((ConstPlanArgs*)args + blockIdx.y);
+}
+
+#define NUHT_PLANNING_KERNEL(name, ...)                                                      \
+    __global__ __VA_ARGS__ void k_##name(PlanArgs a) { name(a); }                            \
+    __global__ __VA_ARGS__ void k_##name##_many(const PlanArgs* args) { name(args_of(args)); }
+
+NUHT_PLANNING_KERNEL(staircases, __launch_bounds__(256))
+NUHT_PLANNING_KERNEL(subdivide, __launch_bounds__(kSubThreads))
+NUHT_PLANNING_KERNEL(block_params, __launch_bounds__(128))
+NUHT_PLANNING_KERNEL(plan_scan, __launch_bounds__(kPlanScanThreads) __attribute__((amdgpu_waves_per_eu(4))))
+NUHT_PLANNING_KERNEL(items, __launch_bounds__(128))
+NUHT_PLANNING_KERNEL(item_scan, __launch_bounds__(kPlanScanThreads) __attribute__((amdgpu_waves_per_eu(4))))
+
+#undef NUHT_PLANNING_KERNEL
 
 // ---------------------------------------------------------------------------
 // Host-side launchers.
@@ -1900,18 +1943,30 @@ int sort_hist_len(int32_t na, int32_t nb)
     }
 }
 
-hipError_t launch_planning(const PlanDev& P, const Arena& A, int32_t* K, int32_t* Jc, int32_t* a_cells,
-                           int64_t min_size, int32_t ncand, int32_t dft_max, double sigma, Summary* sum,
-                           const int32_t* errs, int32_t n_errs, hipStream_t s)
+constexpr int kParamBlocks = 256, kItemBlocks = 512;
+
+hipError_t launch_planning(const PlanArgs& a, hipStream_t s)
 {
-    const int32_t n = P.n, m = P.m;
-    hipLaunchKernelGGL(k_staircase, dim3(cdiv(m, 256) + cdiv(n, 256)), dim3(256), 0, s, P.rs, n, P.ws, m, P.z, K,
-                       Jc, cdiv(m, 256));
-    hipLaunchKernelGGL(k_subdivide, dim3(1), dim3(kSubThreads), 0, s, K, Jc, m, n, min_size, ncand, A, sum, errs, n_errs);
-    hipLaunchKernelGGL(k_block_params, dim3(256), dim3(128), 0, s, P, A, dft_max, sigma, sum);
-    hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(kPlanScanThreads), 0, s, P, A, sum);
-    hipLaunchKernelGGL(k_items, dim3(512), dim3(128), 0, s, P, A, sum, a_cells);
-    hipLaunchKernelGGL(k_item_scan, dim3(1), dim3(kPlanScanThreads), 0, s, P, A, sum, a_cells);
+    const int32_t n = a.P.n, m = a.P.m;
+    hipLaunchKernelGGL(k_staircases, dim3(cdiv(m, 256) + cdiv(n, 256)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_subdivide, dim3(1), dim3(kSubThreads), 0, s, a);
+    hipLaunchKernelGGL(k_block_params, dim3(kParamBlocks), dim3(128), 0, s, a);
+    hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(kPlanScanThreads), 0, s, a);
+    hipLaunchKernelGGL(k_items, dim3(kItemBlocks), dim3(128), 0, s, a);
+    hipLaunchKernelGGL(k_item_scan, dim3(1), dim3(kPlanScanThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_planning_many(const PlanArgs* args_dev, int count, int64_t nm, hipStream_t s)
+{
+    // cdiv(m) + cdiv(n) workgroups of staircases, at most cdiv(n + m) + 1;
+    // their kernel ignores workgroups past a partition's queries
+    hipLaunchKernelGGL(k_staircases_many, dim3(cdiv(nm, 256) + 1, count), dim3(256), 0, s, args_dev);
+    hipLaunchKernelGGL(k_subdivide_many, dim3(1, count), dim3(kSubThreads), 0, s, args_dev);
+    hipLaunchKernelGGL(k_block_params_many, dim3(kParamBlocks, count), dim3(128), 0, s, args_dev);
+    hipLaunchKernelGGL(k_plan_scan_many, dim3(1, count), dim3(kPlanScanThreads), 0, s, args_dev);
+    hipLaunchKernelGGL(k_items_many, dim3(kItemBlocks, count), dim3(128), 0, s, args_dev);
+    hipLaunchKernelGGL(k_item_scan_many, dim3(1, count), dim3(kPlanScanThreads), 0, s, args_dev);
     return hipGetLastError();
 }
 
