@@ -72,7 +72,11 @@ typedef struct nuht_plan_s *nuht_plan_t;
  *   dft_max           asymptotic blocks whose spread grid has at most this
  *                     many cells are evaluated by a direct sum over the grid
  *                     instead of an FFT and interpolation (0 -> built-in default,
- *                     negative -> always use the FFT path).
+ *                     negative -> always use the FFT path).  In FP64 plans with
+ *                     eps at or below about 1e-8 and dft_max >= 0, blocks of a
+ *                     small (r range) x (omega range) are applied through
+ *                     Chebyshev expansions in r and omega instead (to eps /
+ *                     1000) and have no spread grid.
  *   spread_chunk      points per spreading work item, 64 .. 16384 (0 -> 1024).
  *   tune              nonzero: nuht_plan_many picks min_size, dft_max,
  *                     spread_chunk and split_candidates per size class with
@@ -136,15 +140,16 @@ typedef struct {
     int64_t local_row_members, local_col_members;
     int64_t asy_row_members, asy_col_members;
     int64_t direct_entries;
-    int64_t grid_cells;               /* sum of spread-grid sizes N1 over asymptotic blocks */
+    int64_t grid_cells;               /* sum of spread-grid sizes N1 over asymptotic blocks that have a grid */
     int64_t fft_points;               /* sum of FFT sizes N2 over FFT-path blocks */
     int64_t dft_row_cells;            /* sum of rows x N1 over direct-sum-path blocks */
     int64_t fft_row_members;          /* sum of rows over FFT-path blocks */
     int64_t workspace_bytes;          /* device memory held by the plan */
     int64_t min_size;                 /* options in use (after defaults and tuning) */
     int32_t dft_max, spread_chunk;
-    int32_t spread_items;             /* spreading work items of the asymptotic blocks */
-    int32_t dense_items;              /* of which spread on the matrix cores */
+    int32_t spread_items;             /* column work items of the asymptotic blocks */
+    int32_t dense_items;              /* of which dense: spread on the matrix cores unless their
+                                         block is applied through Chebyshev expansions */
     int32_t split_candidates;         /* candidate rows of SplitIndices in use (-1: exact) */
     int32_t half_order;               /* 1: the order is nu + 1/2 (nuht_plan_half) */
 } nuht_info;

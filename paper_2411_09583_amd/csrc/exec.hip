@@ -20,6 +20,15 @@
 
 namespace nuht {
 
+// Orders the LDS accesses of the wave's lanes around it (the region is
+// written and read by different lanes of the same wave).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------
 // Every execution kernel is a body taking the transform (P) and the index of
 // its workgroup within that transform's work.  A single transform's kernel
@@ -95,15 +104,6 @@ __global__ void k_zero_output_many(const PlanDev* __restrict__ plans, const Work
     const WorkSeg w = find_seg(segs, nseg);
     const int64_t i = (int64_t)w.g0 * blockDim.x + threadIdx.x;
     if (i < plan_of(plans, w.t).m) g_table[w.t][i] = 0.0;
-}
-
-// gd = 0 ahead of the direct blocks.
-__global__ void k_zero_gd_many(const PlanDev* __restrict__ plans, const WorkSeg* __restrict__ segs, int nseg)
-{
-    const WorkSeg w = find_seg(segs, nseg);
-    const PlanDev& P = plan_of(plans, w.t);
-    const int64_t i = (int64_t)w.g0 * blockDim.x + threadIdx.x;
-    if (i < P.m) P.gd[i] = 0.0;
 }
 
 __global__ void k_fill_value(double* __restrict__ x, int64_t n, double v)
@@ -314,6 +314,506 @@ __global__ void k_lmom_reduce_many(const PlanDev* __restrict__ plans, const Work
 {
     const WorkSeg w = find_seg(segs, nseg);
     lmom_reduce_body(plan_of(plans, w.t), w.g0);
+}
+
+// ---------------------------------------------------------------------------
+// Rank blocks: asymptotic blocks whose (half r range) x (half omega range) is
+// small enough (a few times kRankPanels) that their kernel, without its fast
+// phases, is a smooth function of both variables.  With r = C + b,
+// omega = D + a,
+//   J_nu(omega r) = sqrt(2/pi) (omega r)^(-1/2) Re( e^{i (omega C + phi)} e^{i D b} F(r, omega) ),
+//   F = H(omega r) e^{i a b},   H(x) = sum_p beta_p x^(-p)  (Hankel's M terms),
+// and F is its Chebyshev interpolant in both variables, K terms in each
+// (rank_terms bounds the error).  In place of 2M type-3 transforms per block:
+//   moments      t_m = sum_k c_k sqrt(r0 / r_k) e^{i D b_k} T_m(y_k), one set per
+//                panel of points (y in [-1, 1] across the panel);
+//   weights      the sums at the panel's K nodes, a cosine transform of t;
+//   translation  u_t = sum over panels and nodes s of F(r_s, omega_t) weight_s at
+//                the K nodes of each panel of frequencies, then the
+//                coefficients v_m of the function through them;
+//   rows         (omega r0)^(-1/2) Re( e^{i (omega C + phi)} sum_m v_m T_m(eta) ).
+// A point or row costs its phase and 3 K operations, where spreading costs w
+// taps x 4M sums and a row N1 >= w + 2 cells x (4M + 2).
+// ---------------------------------------------------------------------------
+// Moments of one item, four waves, a point per lane and step, 2 KC sums in
+// registers.  At the end of a panel each wave adds its lanes' sums: half-wave
+// and row exchanges leave a quarter of the sums in each row of 16 lanes, and
+// the rows are added through LDS.  Where the waves share a panel, the four
+// waves' sums are added in order.  Bound by FP64 issue: the phase is about 70
+// instructions and a term 3.  The next step's point is loaded a step ahead.
+constexpr int kRankWaves = 4;
+
+// What the moments of a rank block need of it.
+struct RankCols {
+    double C, D, r0, cw;
+    int32_t pc, cpan0;
+};
+
+// a <- a + a of the other half-wave in lanes 0 .. 31, b likewise in 32 .. 63.
+__device__ __forceinline__ double add_halves(double a, double b)
+{
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+
+// The same for rows of 16 lanes: a in rows 0 and 2 (with the row above), b in
+// rows 1 and 3 (with the row below).
+__device__ __forceinline__ double add_rows(double a, double b)
+{
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+
+// Sum over the wave of acc[v], in lane v < N (N a multiple of 8, at most 64);
+// s: the wave's N / 4 x 64 doubles of LDS.
+template <int N>
+__device__ __forceinline__ double wave_sums(double (&acc)[N], double* s, int lane)
+{
+    constexpr int Q = N / 4;
+    #pragma unroll
+    for (int i = 0; i < 2 * Q; ++i) acc[i] = add_halves(acc[i], acc[i + 2 * Q]);   // values i | i + 2Q
+    #pragma unroll
+    for (int i = 0; i < Q; ++i) s[i * 64 + lane] = add_rows(acc[i], acc[i + Q]);   // row h: value i + h Q
+    wave_sync();
+    const int v = lane < N ? lane : 0, h = v / Q, j = v - h * Q;
+    const double* row = s + j * 64 + h * 16;
+    double sum = 0.0;
+    #pragma unroll
+    for (int l = 0; l < 16; ++l) sum += row[(l + lane) & 15];
+    wave_sync();
+    return sum;
+}
+
+// Sums over the wave of columns first + 64 stride j + lane < kb of panel q,
+// in lane v < 2 KC.
+template <int KC>
+__device__ __forceinline__ double rank_moments_wave(const PlanDev& P, const RankCols B, int q, int first, int stride,
+                                                    int kb, double* s)
+{
+    const double* __restrict__ cs = P.cs;
+    const double* __restrict__ rs = P.rs;
+    const int lane = threadIdx.x & 63;
+    const double inv_r0 = rcp_refined(B.r0);
+    const double inv_w = B.cw > 0.0 ? rcp_refined(B.cw) : 0.0;
+    const double mid = rank_mid(q, B.pc, B.cw);
+    double acc[2 * KC];
+    #pragma unroll
+    for (int m = 0; m < 2 * KC; ++m) acc[m] = 0.0;
+    int k = first + lane;
+    double r_nx = B.r0, c_nx = 0.0;
+    if (k < kb) { r_nx = rs[k]; c_nx = cs[k]; }
+    for (int k0 = first; k0 < kb; k0 += 64 * stride) {
+        const double r = r_nx, c = c_nx;
+        k += 64 * stride;
+        r_nx = B.r0; c_nx = 0.0;
+        if (k < kb) { r_nx = rs[k]; c_nx = cs[k]; }
+        const dd tp = two_sum(r, -B.C);
+        const dd ph = two_prod(B.D, tp.hi);
+        double cth, sth;
+        cis_dd(ph.hi, __builtin_fma(B.D, tp.lo, ph.lo), cth, sth);
+        const double w0 = c * rsqrt_refined(r * inv_r0);
+        const double xr = w0 * cth, xi = w0 * sth;
+        const double y = ((tp.hi - mid) + tp.lo) * inv_w, y2 = y + y;
+        double t0 = 1.0, t1 = y;
+        #pragma unroll
+        for (int m = 0; m < KC; ++m) {
+            acc[2 * m] = __builtin_fma(xr, t0, acc[2 * m]);
+            acc[2 * m + 1] = __builtin_fma(xi, t0, acc[2 * m + 1]);
+            const double t2 = __builtin_fma(y2, t1, -t0);
+            t0 = t1;
+            t1 = t2;
+        }
+    }
+    return wave_sums<2 * KC>(acc, s, lane);
+}
+
+// A large item (four waves) within one or two panels: the waves share each
+// panel's points.  Over more panels: a panel per wave in turn.  A small item's
+// wave takes its panels one after the other.
+// The K-term instance for an item's block.
+template <class F>
+__device__ __forceinline__ void rank_dispatch(int K, F&& f)
+{
+    if (K <= 12) f(std::integral_constant<int, 12>());
+    else if (K <= 16) f(std::integral_constant<int, 16>());
+    else if (K <= 20) f(std::integral_constant<int, 20>());
+    else f(std::integral_constant<int, 24>());
+}
+
+// Workgroups 0 .. n_ritems - 1: a large item each; then four small items
+// each, one per wave.
+__device__ __forceinline__ void rank_moments_body(const PlanDev& P, int bid)
+{
+    __shared__ double s_m[kRankWaves][2 * kRankK];
+    __shared__ double s_wave[kRankWaves * (kRankK / 2 * 64)];
+    const bool large = bid < P.n_ritems;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int i = large ? bid : (bid - P.n_ritems) * kRankWaves + wave;
+    if (!large && i >= P.n_rsmall) return;
+    const RankItem I = P.rlist[large ? i : P.rlist_cap - 1 - i];
+    const ABlock& A = P.ab[I.blk];
+    const int K = A.K;
+    const RankCols B{A.C, A.D, A.r0, A.cw, A.pc, A.cpan0};
+    double* s = s_wave + wave * (kRankK / 2 * 64);
+    const bool shared = large && I.nq <= 2;
+    const int first = large && !shared ? wave : 0, step = large && !shared ? kRankWaves : 1;
+    rank_dispatch(K, [&](auto kc) {
+        constexpr int KC = decltype(kc)::value;
+        for (int h = first; h < I.nq; h += step) {
+            const int q = I.q0 + h;
+            int ka = I.ka, kb = I.kb;
+            if (B.pc > 1) {
+                const Panel T = P.cpans[B.cpan0 + q];
+                ka = T.ka > ka ? T.ka : ka;
+                kb = T.kb < kb ? T.kb : kb;
+            }
+            double* out = (double*)(P.rmom + (int64_t)(I.slot + q) * kRankK);
+            const double v = rank_moments_wave<KC>(P, B, q, shared ? ka + 64 * wave : ka, shared ? kRankWaves : 1, kb, s);
+            if (!shared) {
+                if (lane < 2 * KC) out[lane] = v;
+                continue;
+            }
+            if (lane < 2 * KC) s_m[wave][lane] = v;
+            __syncthreads();
+            if (threadIdx.x < 2 * KC) {
+                double t = s_m[0][lane];
+                #pragma unroll
+                for (int w = 1; w < kRankWaves; ++w) t += s_m[w][lane];
+                out[lane] = t;
+            }
+            __syncthreads();
+        }
+    });
+}
+
+static inline int rank_moments_blocks(const Summary& S) { return S.n_ritems + (S.n_rsmall + kRankWaves - 1) / kRankWaves; }
+
+__global__ __launch_bounds__(64 * kRankWaves) void k_rank_moments(PlanDev P) { rank_moments_body(P, blockIdx.x); }
+
+__global__ __launch_bounds__(64 * kRankWaves) void k_rank_moments_many(const PlanDev* __restrict__ plans,
+                                                                       const WorkSeg* __restrict__ segs, int nseg)
+{
+    const WorkSeg w = find_seg(segs, nseg);
+    rank_moments_body(plan_of(plans, w.t), w.g0);
+}
+
+// Sum over items i0 .. i1 - 1 (step `step`) of moment `lane` of panel `pan`,
+// in item order within eight running sums.
+__device__ __forceinline__ double rank_moment_sum(const PlanDev& P, int pan, int i0, int i1, int step, int lane)
+{
+    const double* __restrict__ src = (const double*)(P.rmom + (int64_t)pan * kRankK) + lane;
+    constexpr int kStride = 2 * kRankK;
+    double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    int i = i0;
+    for (; i + 7 * step < i1; i += 8 * step) {
+        #pragma unroll
+        for (int u = 0; u < 8; ++u) a[u] += src[(int64_t)(i + u * step) * kStride];
+    }
+    #pragma unroll
+    for (int u = 0; u < 7; ++u)
+        if (i + u * step < i1) a[u] += src[(int64_t)(i + u * step) * kStride];
+    return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+}
+
+// v of lane `src` (the same in every lane), through the scalar unit.
+__device__ __forceinline__ double read_lane(double v, int src)
+{
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, src), hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), src);
+    return __longlong_as_double(((long long)hi << 32) | lo);
+}
+
+// Lane s < K: weight_s = (1/K) (t_0 + 2 sum_{m>=1} t_m cos(pi m (2 s + 1) / (2 K))),
+// t the moment of lane 2m (real) and 2m + 1 (imaginary).
+__device__ __forceinline__ double2 rank_nodal_weight(const double* __restrict__ tab, int K, double t, int lane)
+{
+    const int s = lane < K ? lane : K - 1;
+    double wr = 0.0, wi = 0.0;
+    for (int m0 = 0; m0 < K; m0 += 4) {      // m = 0 with factor 1 (taken off below)
+        double c[4];
+        #pragma unroll
+        for (int u = 0; u < 4; ++u) c[u] = tab[(m0 + u) * K + s];
+        #pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            wr = __builtin_fma(read_lane(t, 2 * (m0 + u)), c[u], wr);
+            wi = __builtin_fma(read_lane(t, 2 * (m0 + u) + 1), c[u], wi);
+        }
+    }
+    const double inv = 1.0 / K;
+    return make_double2((wr + wr - read_lane(t, 0)) * inv, (wi + wi - read_lane(t, 1)) * inv);
+}
+
+// Lane m < K: v_m = (2 - [m = 0]) / K sum_t u_t cos(pi m (2 t + 1) / (2 K)),
+// u_t in lane t.
+__device__ __forceinline__ void rank_store_coefs(const PlanDev& P, const double* __restrict__ tab, int K, int pan,
+                                                 double ur, double ui, int lane)
+{
+    const int m = lane < K ? lane : K - 1;
+    const double* __restrict__ col = tab + K * K + m;
+    double vr = 0.0, vi = 0.0;
+    for (int h0 = 0; h0 < K; h0 += 4) {
+        double c[4];
+        #pragma unroll
+        for (int u = 0; u < 4; ++u) c[u] = col[(h0 + u) * K];
+        #pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            vr = __builtin_fma(read_lane(ur, h0 + u), c[u], vr);
+            vi = __builtin_fma(read_lane(ui, h0 + u), c[u], vi);
+        }
+    }
+    const double f = (m == 0 ? 1.0 : 2.0) / K;
+    if (lane < K) P.rcoef[(int64_t)pan * kRankK + lane] = make_double2(vr * f, vi * f);
+}
+
+// Hankel's terms H(x), from MP >= M pairs of channel factors held in (scalar)
+// registers (the factors beyond 2M are zero); MP = 0: from memory.
+template <int MP>
+struct Hankel {
+    const PlanDev& P;
+    double f[MP > 0 ? 2 * MP : 1];
+    __device__ __forceinline__ Hankel(const PlanDev& plan) : P(plan)
+    {
+        #pragma unroll
+        for (int i = 0; i < 2 * MP; ++i) f[i] = plan.chan[i];
+    }
+    __device__ __forceinline__ void at(double x, double& hr, double& hi) const
+    {
+        const double inv = rcp_refined(x), inv2 = inv * inv;
+        if constexpr (MP > 0) {
+            hr = f[2 * MP - 2];
+            hi = f[2 * MP - 1];
+            #pragma unroll
+            for (int l = MP - 2; l >= 0; --l) {
+                hr = __builtin_fma(hr, inv2, f[2 * l]);
+                hi = __builtin_fma(hi, inv2, f[2 * l + 1]);
+            }
+        } else {
+            hr = 0.0;
+            hi = 0.0;
+            for (int l = P.M - 1; l >= 0; --l) {
+                hr = __builtin_fma(hr, inv2, P.chan[2 * l]);
+                hi = __builtin_fma(hi, inv2, P.chan[2 * l + 1]);
+            }
+        }
+        hi *= inv;
+    }
+};
+
+// The instance for a plan's M: 4 and 8 pairs in registers, beyond from memory.
+template <class F>
+__device__ __forceinline__ void hankel_dispatch(int M, F&& f)
+{
+    if (M <= 4) f(std::integral_constant<int, 4>());
+    else if (M <= 8) f(std::integral_constant<int, 8>());
+    else f(std::integral_constant<int, 0>());
+}
+
+// e^{i a b}, to the rounding of a and b's low parts
+__device__ __forceinline__ void rank_phase(dd a, dd b, double& c, double& s)
+{
+    const dd ph = two_prod(a.hi, b.hi);
+    cis_dd(ph.hi, __builtin_fma(a.hi, b.lo, __builtin_fma(a.lo, b.hi, ph.lo)), c, s);
+}
+
+// Nodal weights of one panel of points of a block of several panels or many
+// items: the four waves each sum every fourth item, the four sums are added
+// in order, and the first wave forms the weights.
+__device__ __forceinline__ void rank_weights_panel(const PlanDev& P, const Panel& T, double (*s_t)[64])
+{
+    const ABlock B = P.ab[T.blk];
+    const int pan = B.cpan0 + T.q;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, K = B.K;
+    double t = 0.0;
+    if (T.kb > T.ka && lane < 2 * K) {
+        const int i0 = B.item0 + (T.ka - B.k0) / P.spread_chunk, i1 = B.item0 + (T.kb - 1 - B.k0) / P.spread_chunk + 1;
+        t = rank_moment_sum(P, pan, i0 + wave, i1, 4, lane);
+    }
+    s_t[wave][lane] = t;
+    __syncthreads();
+    if (wave > 0) return;
+    t = ((s_t[0][lane] + s_t[1][lane]) + s_t[2][lane]) + s_t[3][lane];
+    const double2 w = rank_nodal_weight(P.rank_tab + rank_tab_off(K), K, t, lane);
+    if (lane < K) P.rwts[(int64_t)pan * kRankK + lane] = w;
+}
+
+// One panel of frequencies of a block of one panel of points and few items,
+// a wave: moments summed, weights, translation, coefficients.  Groups of 8,
+// 16 or 32 lanes hold the frequency nodes and share the point nodes.
+__device__ __forceinline__ void rank_translate_single(const PlanDev& P, const Panel& T)
+{
+    const ABlock B = P.ab[T.blk];
+    const int pan = B.rpan0 + T.q;
+    const int lane = threadIdx.x & 63, K = B.K;
+    const double* __restrict__ tab = P.rank_tab + rank_tab_off(K);   // row m = 1: the nodes
+    const double tm = lane < 2 * K ? rank_moment_sum(P, B.cpan0, B.item0, B.item0 + B.nitems, 1, lane) : 0.0;
+    const double2 w = rank_nodal_weight(tab, K, tm, lane);
+    const int logt = K <= 8 ? 3 : K <= 16 ? 4 : 5, groups = 64 >> logt;
+    const int t = lane & ((1 << logt) - 1), g = lane >> logt;
+    const dd a = two_sum(rank_mid(T.q, B.pr, B.rw), B.rw * tab[K + (t < K ? t : K - 1)]);
+    const double om = B.D + a.hi;
+    double ur = 0.0, ui = 0.0;
+    hankel_dispatch(P.M, [&](auto mp) {
+        const Hankel<decltype(mp)::value> H(P);
+        for (int s0 = 0; s0 < K; s0 += groups) {
+            const int s = s0 + g < K ? s0 + g : K - 1;
+            double wr = __shfl(w.x, s), wi = __shfl(w.y, s);
+            if (s0 + g >= K) { wr = 0.0; wi = 0.0; }
+            const double d = B.cw * tab[K + s];
+            double hr, hi, c, sn;
+            H.at(om * (B.C + d), hr, hi);
+            rank_phase(a, dd{d, 0.0}, c, sn);
+            const double fr = __builtin_fma(hr, c, -hi * sn), fi = __builtin_fma(hr, sn, hi * c);
+            ur = __builtin_fma(fr, wr, __builtin_fma(-fi, wi, ur));
+            ui = __builtin_fma(fr, wi, __builtin_fma(fi, wr, ui));
+        }
+    });
+    for (int o = 32; o >= (1 << logt); o >>= 1) { ur += __shfl_xor(ur, o); ui += __shfl_xor(ui, o); }
+    rank_store_coefs(P, tab, K, pan, ur, ui, lane);
+}
+
+// Workgroups 0 .. n_wmulti - 1: the weights of a panel of points each; then
+// four panels of frequencies of one-wave blocks each, one per wave.
+__device__ __forceinline__ void rank_weights_body(const PlanDev& P, int bid)
+{
+    __shared__ double s_t[4][64];
+    if (bid < P.n_wmulti) {
+        rank_weights_panel(P, P.wlist[bid], s_t);
+        return;
+    }
+    const int i = (bid - P.n_wmulti) * 4 + (threadIdx.x >> 6);
+    if (i < P.n_tsingle) rank_translate_single(P, P.tlist[i]);
+}
+
+static inline int rank_weights_blocks(const Summary& S) { return S.n_wmulti + (S.n_tsingle + 3) / 4; }
+
+__global__ __launch_bounds__(256) void k_rank_weights(PlanDev P) { rank_weights_body(P, blockIdx.x); }
+
+__global__ __launch_bounds__(256) void k_rank_weights_many(const PlanDev* __restrict__ plans,
+                                                           const WorkSeg* __restrict__ segs, int nseg)
+{
+    const WorkSeg w = find_seg(segs, nseg);
+    rank_weights_body(plan_of(plans, w.t), w.g0);
+}
+
+// One panel of frequencies of the other rank blocks, a workgroup of 512
+// threads: 16 groups of 32 lanes, a lane per frequency node.  A group takes
+// point nodes s of every panel; from panel to panel the phase turns by the
+// same angle (restarted every 8 panels, so that the rotations' rounding stays
+// at that of one phase).
+constexpr int kRankTransThreads = 512;
+
+__device__ __forceinline__ void rank_translate_body(const PlanDev& P, int bid)
+{
+    // the block's nodal weights first, the groups' sums afterwards
+    __shared__ double2 s_w[kRankPanels * kRankK];
+    static_assert(kRankPanels * kRankK >= kRankTransThreads, "room for the groups' sums");
+    const Panel T = P.tlist[P.tlist_cap - 1 - bid];
+    const ABlock B = P.ab[T.blk];
+    const int pan = B.rpan0 + T.q;
+    constexpr int kGroups = kRankTransThreads / 32;
+    const int K = B.K, t = threadIdx.x & 31, g = threadIdx.x >> 5;
+    const double* __restrict__ tab = P.rank_tab + rank_tab_off(K);
+    const double2* __restrict__ wts = P.rwts + (int64_t)B.cpan0 * kRankK;
+    for (int e = threadIdx.x; e < B.pc * kRankK; e += kRankTransThreads) s_w[e] = wts[e];
+    const dd a = two_sum(rank_mid(T.q, B.pr, B.rw), B.rw * tab[K + (t < K ? t : K - 1)]);
+    const double om = B.D + a.hi;
+    double er, ei;
+    rank_phase(a, dd{2.0 * B.cw, 0.0}, er, ei);
+    __syncthreads();
+    double ur = 0.0, ui = 0.0;
+    // (node, run of 8 panels) pairs, dealt to the groups in turn
+    const int runs = (B.pc + 7) >> 3;
+    hankel_dispatch(P.M, [&](auto mp) {
+        const Hankel<decltype(mp)::value> H(P);
+        for (int j = g; j < K * runs; j += kGroups) {
+            const int run = j / K, s = j - run * K;
+            const int q1 = 8 * run + 8 < B.pc ? 8 * run + 8 : B.pc;
+            const double d = B.cw * tab[K + s];
+            double c, sn;
+            rank_phase(a, two_sum(rank_mid(8 * run, B.pc, B.cw), d), c, sn);
+            for (int q = 8 * run; q < q1; ++q) {
+                double hr, hi;
+                H.at(om * (B.C + (rank_mid(q, B.pc, B.cw) + d)), hr, hi);
+                const double2 w = s_w[q * kRankK + s];
+                const double fr = __builtin_fma(hr, c, -hi * sn), fi = __builtin_fma(hr, sn, hi * c);
+                ur = __builtin_fma(fr, w.x, __builtin_fma(-fi, w.y, ur));
+                ui = __builtin_fma(fr, w.y, __builtin_fma(fi, w.x, ui));
+                const double cn = __builtin_fma(c, er, -sn * ei);
+                sn = __builtin_fma(c, ei, sn * er);
+                c = cn;
+            }
+        }
+    });
+    __syncthreads();
+    double2* s_sum = s_w;
+    s_sum[threadIdx.x] = make_double2(ur, ui);
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    ur = 0.0; ui = 0.0;
+    for (int h = 0; h < kGroups; ++h) {
+        const double2 v = s_sum[32 * h + t];
+        ur += v.x;
+        ui += v.y;
+    }
+    rank_store_coefs(P, tab, K, pan, ur, ui, threadIdx.x);
+}
+
+__global__ __launch_bounds__(kRankTransThreads) void k_rank_translate(PlanDev P) { rank_translate_body(P, blockIdx.x); }
+
+__global__ __launch_bounds__(kRankTransThreads) void k_rank_translate_many(const PlanDev* __restrict__ plans,
+                                                                           const WorkSeg* __restrict__ segs, int nseg)
+{
+    const WorkSeg w = find_seg(segs, nseg);
+    rank_translate_body(plan_of(plans, w.t), w.g0);
+}
+
+// A rank block's contribution at frequency om.  UNI: the block is the same in
+// every lane; where the panel is too, its coefficients come through the
+// scalar unit.
+__device__ __forceinline__ double rank_series(const double2* __restrict__ v, int K, double eta, double cr, double ci)
+{
+    double t0 = 1.0, t1 = eta, ar = 0.0, ai = 0.0;
+    const double e2 = eta + eta;
+    for (int m = 0; m < K; m += 4) {
+        #pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double2 c = v[m + u];
+            ar = __builtin_fma(c.x, t0, ar);
+            ai = __builtin_fma(c.y, t0, ai);
+            const double t2 = __builtin_fma(e2, t1, -t0);
+            t0 = t1;
+            t1 = t2;
+        }
+    }
+    return __builtin_fma(cr, ar, -ci * ai);
+}
+
+template <bool UNI>
+__device__ __forceinline__ double rank_eval(const PlanDev& P, const ABlock& B, double om)
+{
+    const double rs = rsqrt_refined(om * B.r0);
+    const dd pc = two_prod(om, B.C);
+    const dd ph = two_sum(pc.hi, P.phi_hi);
+    double cr, ci;
+    cis_dd(ph.hi, ph.lo + pc.lo + P.phi_lo, cr, ci);
+    const double inv = B.rw > 0.0 ? rcp_refined(B.rw) : 0.0;
+    const dd a = two_sum(om, -B.D);
+    int q = (int)(0.5 * __builtin_fma(a.hi, inv, (double)B.pr));
+    q = q < 0 ? 0 : q > B.pr - 1 ? B.pr - 1 : q;
+    const double eta = ((a.hi - rank_mid(q, B.pr, B.rw)) + a.lo) * inv;
+    double v;
+    if constexpr (UNI) {
+        const int qu = __builtin_amdgcn_readfirstlane(q);
+        if (__all(q == qu)) v = rank_series(P.rcoef + (int64_t)(B.rpan0 + qu) * kRankK, B.K, eta, cr, ci);
+        else v = rank_series(P.rcoef + (int64_t)(B.rpan0 + q) * kRankK, B.K, eta, cr, ci);
+    } else {
+        v = rank_series(P.rcoef + (int64_t)(B.rpan0 + q) * kRankK, B.K, eta, cr, ci);
+    }
+    return kSqrt2OverPi * rs * v;
 }
 
 // ---------------------------------------------------------------------------
@@ -563,15 +1063,6 @@ struct SpreadMfma {
     static constexpr size_t wave_bytes = ((size_t)WPTS * point_bytes + 15) / 16 * 16 + fold_bytes;
     static constexpr size_t lds_bytes = 4 * wave_bytes;   // the workgroup's four waves
 };
-
-// Orders the LDS accesses of the wave's lanes around it (the region is
-// written and read by different lanes of the same wave).
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // Points g_lo .. g_hi-1 of the step (g_lo a multiple of 8) into the tile of
 // anchor a, two groups of four points per iteration (two independent kernel
@@ -1571,6 +2062,7 @@ template <int NCH, bool UNI>
 __device__ double asym_eval(const PlanDev& P, int ablk, double om, const double2* __restrict__ grids)
 {
     const ABlock B = P.ab[ablk];
+    if (B.K > 0) return rank_eval<UNI>(P, B, om);
     const int w = P.w;
     // gamma = 1/(om r0) and its square root (om r0 > z > 0 on an asymptotic block)
     const double rs = rsqrt_refined(om * B.r0);
@@ -1753,7 +2245,8 @@ __device__ __forceinline__ void besselj_table2(const PlanDev& P, Tab tab, double
 // power of two up to 64, as many as fit), the lanes of a row sum strided
 // entries and combine by shuffles.  A
 // row lies in at most one direct block (the last block of its path down the
-// subdivision tree), so the per-row sums are stored, not accumulated.
+// subdivision tree), so the per-row sums are stored, not accumulated; rows in
+// none are never read, and gd needs no clearing.
 constexpr int kDirectThreads = 256;
 // Tables of up to kJtabLdsPanels panels (z up to about 240 with the
 // default range) are copied into LDS by each workgroup and read from there:
@@ -1830,12 +2323,6 @@ __global__ __launch_bounds__(kDirectThreads) void k_direct_blocks_many(const Pla
 {
     const WorkSeg w = find_seg(segs, nseg);
     direct_body(plan_of(plans, w.t), w.g0);
-}
-
-__global__ void k_fill_zero(double* __restrict__ x, int64_t n)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) x[i] = 0.0;
 }
 
 // Row pass, two kernels; each has one thread per sorted frequency and walks
@@ -1966,7 +2453,7 @@ static inline int cdiv64(int64_t a, int64_t b) { return (int)((a + b - 1) / b); 
 template <int NCH>
 static void launch_spread(const PlanDev& P, const Summary& S, hipStream_t s)
 {
-    const int32_t n_dense = S.n_adense, n_med = S.n_amed, n_rest = S.n_aitems - S.n_adense - S.n_amed;
+    const int32_t n_dense = S.n_adense, n_med = S.n_amed, n_rest = S.n_aspread - S.n_adense - S.n_amed;
     if constexpr (NCH <= kMfmaMaxChannels) {
         if (n_dense > 0)
             hipLaunchKernelGGL((k_spread_mfma<NCH, kSpreadAnchors>), dim3(n_dense), dim3(256), 0, s, P);
@@ -2156,7 +2643,6 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
     }
     auto launch_direct = [&](hipStream_t st) {
         if (P.n_d > 0) {
-            hipLaunchKernelGGL(k_fill_zero, dim3(cdiv64(P.m, 256)), dim3(256), 0, st, P.gd, (int64_t)P.m);
             hipLaunchKernelGGL(k_direct_blocks, dim3(P.n_d), dim3(kDirectThreads), 0, st, P);
         }
     };
@@ -2166,8 +2652,15 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
         if (e != hipSuccess) return e;
     }
     mark(marks, 2, s);
+    if (rank_moments_blocks(S) > 0)
+        hipLaunchKernelGGL(k_rank_moments, dim3(rank_moments_blocks(S)), dim3(64 * kRankWaves), 0, s, P);
     dispatch_channels(P.nch, [&](auto k) { launch_spread<decltype(k)::value>(P, S, s); });
     mark(marks, 3, s);
+    if (S.n_cpan > 0) {
+        hipLaunchKernelGGL(k_rank_weights, dim3(rank_weights_blocks(S)), dim3(256), 0, s, P);
+        if (S.n_tmulti > 0)
+            hipLaunchKernelGGL(k_rank_translate, dim3(S.n_tmulti), dim3(kRankTransThreads), 0, s, P);
+    }
     if (P.grid_cells > 0) {
         if (P.fp32)
             hipLaunchKernelGGL(k_spread_reduce<float2>, dim3(cdiv64(P.grid_cells * P.nch, 256)), dim3(256), 0, s, P);
@@ -2217,8 +2710,8 @@ void small_fft_table(PlanDev& P, const FftClass* cls, int ncls)
 // its channel count (spreading, grid rows) or local-row mode.
 // ---------------------------------------------------------------------------
 enum BatchKind : int32_t {
-    kZeroOut, kGather, kLmom, kLmomReduce, kSpreadMfma, kSpreadMfmaMed, kSpreadVec, kSpreadReduce, kFftSmall,
-    kFftPass0, kFftPass1, kFftPass2, kZeroGd, kDirect, kRowsAsy, kRowsLocal
+    kZeroOut, kGather, kLmom, kLmomReduce, kRankMoments, kRankWeights, kRankTranslate, kSpreadMfma, kSpreadMfmaMed, kSpreadVec, kSpreadReduce, kFftSmall,
+    kFftPass0, kFftPass1, kFftPass2, kDirect, kRowsAsy, kRowsLocal
 };
 
 void build_batch_schedule(const BatchTransform* tr, int count, const int* order, BatchSchedule& out)
@@ -2260,6 +2753,15 @@ void build_batch_schedule(const BatchTransform* tr, int count, const int* order,
     add(kLmomReduce, 0, 0, 256, [&](const BatchTransform& T, size_t&) -> int64_t {
         return live(*T.P) && T.S->n_litems > 0 ? cdiv64((int64_t)T.S->n_l * (T.P->L + 1), 256) : 0;
     });
+    add(kRankMoments, 0, 0, 64 * kRankWaves, [&](const BatchTransform& T, size_t&) -> int64_t {
+        return live(*T.P) ? rank_moments_blocks(*T.S) : 0;
+    });
+    add(kRankWeights, 0, 0, 256, [&](const BatchTransform& T, size_t&) -> int64_t {
+        return live(*T.P) ? rank_weights_blocks(*T.S) : 0;
+    });
+    add(kRankTranslate, 0, 0, kRankTransThreads, [&](const BatchTransform& T, size_t&) -> int64_t {
+        return live(*T.P) ? T.S->n_tmulti : 0;
+    });
     // the channel counts and precisions present
     std::vector<std::pair<int, int>> variants;
     for (int t = 0; t < count; ++t) {
@@ -2281,7 +2783,7 @@ void build_batch_schedule(const BatchTransform* tr, int count, const int* order,
         add(kSpreadVec, nch, fp32, 256, [&](const BatchTransform& T, size_t& lds) -> int64_t {
             if (!same(*T.P)) return 0;
             lds = fp32 ? spread_lds_bytes<float>(T.P->w) : spread_lds_bytes<double>(T.P->w);
-            return T.S->n_aitems - T.S->n_adense - T.S->n_amed;
+            return T.S->n_aspread - T.S->n_adense - T.S->n_amed;
         });
     }
     for (int fp32 = 0; fp32 <= 1; ++fp32)
@@ -2321,9 +2823,6 @@ void build_batch_schedule(const BatchTransform* tr, int count, const int* order,
         L.blocks = (int32_t)g;
         if (L.nseg > 0) out.launches.push_back(L);
     }
-    add(kZeroGd, 0, 0, 256, [&](const BatchTransform& T, size_t&) -> int64_t {
-        return live(*T.P) && T.P->n_d > 0 ? cdiv64(T.P->m, 256) : 0;
-    });
     add(kDirect, 0, 0, kDirectThreads, [&](const BatchTransform& T, size_t&) -> int64_t {
         return live(*T.P) ? T.P->n_d : 0;
     });
@@ -2378,7 +2877,7 @@ hipError_t launch_execute_many(const BatchSchedule& S, const void* table_dev, vo
     };
     for (const BatchLaunch& L : S.launches) {
         const dim3 grid(L.blocks), block(L.threads);
-        const bool side_kind = L.kind == kLmom || L.kind == kLmomReduce || L.kind == kZeroGd || L.kind == kDirect;
+        const bool side_kind = L.kind == kLmom || L.kind == kLmomReduce || L.kind == kDirect;
         hipStream_t st = s;
         if (fork && side_kind && !joined) {
             if (!forked) {
@@ -2403,6 +2902,11 @@ hipError_t launch_execute_many(const BatchSchedule& S, const void* table_dev, vo
             else hipLaunchKernelGGL(k_lmom_many<64>, grid, block, 0, st, plans, sg, L.nseg);
             break;
         case kLmomReduce: hipLaunchKernelGGL(k_lmom_reduce_many, grid, block, 0, st, plans, sg, L.nseg); break;
+        case kRankMoments:
+            hipLaunchKernelGGL(k_rank_moments_many, grid, block, 0, s, plans, sg, L.nseg);
+            break;
+        case kRankWeights: hipLaunchKernelGGL(k_rank_weights_many, grid, block, 0, s, plans, sg, L.nseg); break;
+        case kRankTranslate: hipLaunchKernelGGL(k_rank_translate_many, grid, block, 0, s, plans, sg, L.nseg); break;
         case kSpreadMfma:
         case kSpreadMfmaMed:
             dispatch_channels(L.variant, [&](auto k) {
@@ -2434,7 +2938,6 @@ hipError_t launch_execute_many(const BatchSchedule& S, const void* table_dev, vo
         case kFftPass0:
         case kFftPass1: hipLaunchKernelGGL(k_fft_col_many, grid, block, L.lds, s, plans, fs, L.nseg); break;
         case kFftPass2: hipLaunchKernelGGL(k_fft_row_many, grid, block, L.lds, s, plans, fs, L.nseg); break;
-        case kZeroGd: hipLaunchKernelGGL(k_zero_gd_many, grid, block, 0, st, plans, sg, L.nseg); break;
         case kDirect: hipLaunchKernelGGL(k_direct_blocks_many, grid, block, 0, st, plans, sg, L.nseg); break;
         case kRowsAsy:
             dispatch_channels(L.variant, [&](auto k) {

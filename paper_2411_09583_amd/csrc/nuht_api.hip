@@ -731,6 +731,61 @@ static const double2* fft_twiddles_device()
     return table[dev];
 }
 
+// Cosine tables of the rank blocks' expansion lengths (rank_tab_off), one copy
+// per device.
+static const double* rank_tables_device()
+{
+    static std::mutex mu;
+    static const double* table[64] = {};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) { (void)hipGetLastError(); return nullptr; }
+    std::lock_guard<std::mutex> lock(mu);
+    if (!table[dev]) {
+        std::vector<double> host(rank_tab_off(kRankK + 4));
+        const long double pi = 3.141592653589793238462643383279502884L;
+        for (int K = 4; K <= kRankK; K += 4) {
+            double* t = host.data() + rank_tab_off(K);
+            for (int m = 0; m < K; ++m)
+                for (int s = 0; s < K; ++s) {
+                    const double c = (double)cosl(pi * ((long double)((m * (2 * s + 1)) % (4 * K)) / (2.0L * K)));
+                    t[m * K + s] = c;
+                    t[K * K + s * K + m] = c;
+                }
+        }
+        void* p = nullptr;
+        const size_t bytes = sizeof(double) * host.size();
+        if (hipMalloc(&p, bytes) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
+        if (hipMemcpy(p, host.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipFree(p);
+            return nullptr;
+        }
+        table[dev] = (const double*)p;
+    }
+    return table[dev];
+}
+
+// The largest xi = (half r range) x (half omega range) whose exponential
+// e^{i xi x y} kRankK Chebyshev terms give to exp(ltol) (the bound of
+// rank_terms with constant Hankel terms).
+static double rank_largest_xi(double ltol)
+{
+    auto fits = [&](double xi) {
+        for (int l = 0; l < 16; ++l) {
+            const double lr = kRankLr0 + kRankLrStep * l, rho = std::exp(lr);
+            const double k = (std::log(4.0) + 0.5 * xi * (rho - 1.0 / rho) - std::log(rho - 1.0) - ltol) / lr + 1.0;
+            if (k <= (double)kRankK) return true;
+        }
+        return false;
+    };
+    double lo = 0.0, hi = 64.0;
+    for (int it = 0; it < 40; ++it) {
+        const double mid = 0.5 * (lo + hi);
+        if (fits(mid)) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
 // -(2nu+1) pi/4 modulo 2 pi as a double-double in (0, 2 pi], from the
 // integer t = 2 nu + 1 (odd for integer orders, even for half-integers).
 static void phase_offset2(int t, double& hi, double& lo)
@@ -1122,6 +1177,14 @@ static int fill_params(PlanDev& P, int nu2, double eps_req, const nuht_opts& o)
     for (int p = 0; p < 2 * M + 2; ++p) P.hank[p] = hankel_coef(nu, p);
     for (int p = 0; p < kMaxChannels; ++p)
         P.chan[p] = p < 2 * M ? (((p >> 1) & 1) ? -P.hank[p] : P.hank[p]) : 0.0;
+    // rank blocks where the ES transforms are accurate enough for the two
+    // forms to agree; a caller who asks for FFTs everywhere (dft_max < 0) gets them
+    P.rank = (!P.fp32 && P.w >= kRankMinWidth && o.dft_max >= 0) ? 1 : 0;
+    P.rank_const = 1;
+    for (int p = 1; p < 2 * M; ++p)
+        if (P.chan[p] != 0.0) P.rank_const = 0;
+    P.rank_ltol = std::log(std::max(0.001 * eps, 2e-16));
+    P.rank_xi = P.rank ? rank_largest_xi(P.rank_ltol) : 1.0;
     phase_offset2(half ? nu2 + 1 : 2 * anu + 1, P.phi_hi, P.phi_lo);
     P.kappa_max = P.w * M_PI / 4.0 * (1.0 + 1e-9);
     P.eshat_s = 2.0 / (P.kappa_max * P.kappa_max);
@@ -1215,6 +1278,7 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
     A = Arena{};
     A.node_cap = pp.cap; A.l_cap = pp.cap; A.a_cap = pp.cap; A.d_cap = 2 * pp.cap; A.q_cap = pp.cap;
     A.litem_cap = pp.icap; A.aitem_cap = pp.icap;
+    A.pan_cap = P.rank ? 2 * pp.cap : 0;
     int32_t *K = nullptr, *Jc = nullptr, *a_cells = nullptr;
     Slab slab;
     slab.add(K, (size_t)G.m);
@@ -1231,9 +1295,15 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
     slab.add(A.alist, (size_t)A.aitem_cap);
     slab.add(A.fft_list, (size_t)A.a_cap);
     slab.add(A.gslot, (size_t)A.a_cap + 1);
+    slab.add(A.cpans, (size_t)A.pan_cap);
+    slab.add(A.tlist, (size_t)A.pan_cap);
+    slab.add(A.wlist, (size_t)A.pan_cap);
+    slab.add(A.rlist, P.rank ? (size_t)A.aitem_cap : 0);
     NUHT_TRY(slab.commit(pp.tmp));
     P.nodes = A.nodes; P.lb = A.lb; P.ab = A.ab; P.db = A.db;
     P.litems = A.litems; P.aitems = A.aitems; P.alist = A.alist; P.fft_list = A.fft_list; P.gslot = A.gslot;
+    P.cpans = A.cpans; P.rlist = A.rlist; P.tlist = A.tlist; P.wlist = A.wlist;
+    P.tlist_cap = A.pan_cap; P.rlist_cap = A.aitem_cap;
     a.P = P; a.A = A; a.K = K; a.Jc = Jc; a.a_cells = a_cells;
     a.min_size = min_size; a.ncand = ncand; a.dft_max = dft_max; a.sigma = sigma;
     a.sum = pl->d_sum; a.errs = pl->errs; a.n_errs = pl->n_errs; a.pad = 0;
@@ -1279,7 +1349,8 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     if (S.grid_error) return NUHT_ECAPACITY;
     if (S.overflow) {
         if (++pp.attempt >= 6) return NUHT_ECAPACITY;
-        int64_t need = std::max<int64_t>({(int64_t)S.n_nodes, (int64_t)S.n_l, (int64_t)S.n_a, (int64_t)S.n_d / 2});
+        int64_t need = std::max<int64_t>({(int64_t)S.n_nodes, (int64_t)S.n_l, (int64_t)S.n_a, (int64_t)S.n_d / 2,
+                                          (int64_t)S.n_cpan / 2, (int64_t)S.n_rpan / 2});
         if (need >= pp.cap) pp.cap = (int32_t)std::min<int64_t>(2 * need + 1024, 1 << 29);
         int64_t ineed = std::max<int64_t>((int64_t)S.n_litems, (int64_t)S.n_aitems);
         if (ineed >= pp.icap) pp.icap = (int32_t)std::min<int64_t>(2 * ineed + 1024, 1 << 29);
@@ -1295,6 +1366,8 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     Pt.A = pp.A;
     P.n_nodes = S.n_nodes; P.n_l = S.n_l; P.n_a = S.n_a; P.n_d = S.n_d;
     P.n_litems = S.n_litems; P.n_aitems = S.n_aitems; P.n_adense = S.n_adense; P.n_amed = S.n_amed;
+    P.n_tsingle = S.n_tsingle; P.n_tmulti = S.n_tmulti; P.n_wmulti = S.n_wmulti;
+    P.n_ritems = S.n_ritems; P.n_rsmall = S.n_rsmall;
 
     // execution buffers
     ExecBuffers& B = Pt.B;
@@ -1306,6 +1379,11 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     slab.add(B.grids, (size_t)S.grid_cells * P.nch);
     slab.add(B.gd, (size_t)G.m);
     slab.add(B.ga, (size_t)G.m);
+    if (S.n_cpan > 0) {
+        slab.add(B.rmom, (size_t)kRankK * ((size_t)S.n_aitems + S.n_cpan));
+        slab.add(B.rwts, (size_t)kRankK * S.n_cpan);
+        slab.add(B.rcoef, (size_t)kRankK * S.n_rpan);
+    }
     B.grid_cells = S.grid_cells;
     int64_t scratch = 0;
     for (int c = 6; c <= kMaxFftLog2; ++c) {
@@ -1322,7 +1400,12 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     if (!B.es_poly) return NUHT_ENOMEM;
     B.fft_tw = fft_twiddles_device();
     if (!B.fft_tw) return NUHT_ENOMEM;
+    if (P.rank) {
+        P.rank_tab = rank_tables_device();
+        if (!P.rank_tab) return NUHT_ENOMEM;
+    }
     P.es_poly = B.es_poly;
+    P.rmom = B.rmom; P.rwts = B.rwts; P.rcoef = B.rcoef;
     P.cs = B.cs; P.lpart = B.lpart; P.lmom = B.lmom; P.part = B.part; P.grids = B.grids;
     P.scratch = B.scratch; P.gd = B.gd; P.ga = B.ga; P.fft_tw = B.fft_tw;
     P.grid_cells = B.grid_cells;
@@ -2537,7 +2620,7 @@ int nuht_plan_info(nuht_plan_t p, nuht_info* info)
     info->dft_max = p->opts.dft_max == 0 ? 48 : p->opts.dft_max;
     info->spread_chunk = P.spread_chunk;
     info->spread_items = S.n_aitems;
-    info->dense_items = S.n_adense + S.n_amed;
+    info->dense_items = S.n_dense_info;
     info->split_candidates = p->opts.split_candidates == -1 ? -1
                              : (p->opts.split_candidates > 1 ? p->opts.split_candidates : 16);
     return NUHT_OK;

@@ -42,6 +42,28 @@ constexpr double kHalfWidth = 4.0;     // panel width (in omega R) of those coef
 constexpr int kJtabCoef = 16;          // coefficients per panel of the direct-block J_nu table (degree 15)
 constexpr double kJtabWidth = 2.0;     // panel width (in x = omega r) of that table
 
+// Asymptotic blocks applied through Chebyshev expansions in r and omega
+// instead of type-3 transforms (rank blocks; see exec.hip).  An expansion has
+// K terms, a multiple of 4 up to kRankK; the points and the frequencies of a
+// block are cut into equal-width panels, at most kRankPanels of points.
+constexpr int kRankK = 24;
+constexpr int kRankPanels = 40;
+// The narrowest ES kernel at which plans have rank blocks: the expansions are
+// good to eps / 100 and the ES transforms to about 10^(1-w), so the two forms
+// of a block agree to 1e-9 or better from this width (eps <= 1e-8) on; wider
+// tolerances keep the ES transforms, whose own error is part of their results.
+constexpr int kRankMinWidth = 11;
+// Items of at most this many columns take one wave, larger ones four.
+constexpr int kRankWaveCols = 256;
+// Blocks with one panel of points and at most this many items are translated
+// by the wave that adds up their moments.
+constexpr int kRankSingleItems = 16;
+// log rho of the ellipses the expansions' length is bounded on (16 of them).
+constexpr double kRankLr0 = 0.1, kRankLrStep = 0.28;
+// Cosine tables of the expansion lengths K = 4, 8, .., kRankK, one after the
+// other: cos(pi m (2 s + 1) / (2 K)) as [m][s], then as [s][m].
+__host__ __device__ inline int rank_tab_off(int K) { const int i = K / 4 - 1; return 2 * 16 * (i * (i + 1) * (2 * i + 1) / 6); }
+
 // A mixed block of Alg. 1 and the split chosen for it.  Rows j0..js and
 // columns k0..ks are the local (upper-left) side.  A wholly local block is
 // stored with (js, ks) = (j1, k1), a wholly asymptotic one with
@@ -78,11 +100,37 @@ struct ABlock {
     int32_t item0, nitems;
     int64_t part_off;     // first partial-subgrid element of its items (complex)
     int32_t level, fft_slot;  // fft_slot: position in the FFT size-class list
+    // rank blocks (K > 0): expansion length, panels of points and frequencies
+    // with their half-widths and first panel numbers
+    int32_t K, pc, pr, cpan0, rpan0, pad;
+    double cw, rw;
 };
+
+// A panel of a rank block's points (columns ka .. kb - 1) or frequencies
+// (ka, kb unused), panel q of its block.
+struct Panel {
+    int32_t blk, q, ka, kb;
+};
+
+// A rank block's item: columns ka .. kb - 1 of block blk, in panels q0 .. q0 +
+// nq - 1; its moments of panel q are number `slot` + q.
+struct RankItem {
+    int32_t blk, slot, ka, kb, q0, nq;
+};
+
+// Panels are laid out about the block's centres: left edge (q = pc: the right
+// end) and middle of panel q of the points, as offsets from C, and middle of
+// panel q of the frequencies, as an offset from D.  (Offsets keep the panels'
+// places exact to their own size, whatever the size of r and omega.)
+__host__ __device__ inline double rank_edge(const ABlock& B, int q) { return (2 * q - B.pc) * B.cw; }
+__host__ __device__ inline double rank_mid(int q, int panels, double half) { return (2 * q + 1 - panels) * half; }
 
 struct DBlock {
     int32_t j0, j1, k0, k1;
 };
+
+// Whether one wave adds up a rank block's moments and translates them.
+__host__ __device__ inline bool rank_one_wave(const ABlock& B) { return B.pc == 1 && B.nitems <= kRankSingleItems; }
 
 // Work item of the column-side kernels: a chunk of one block's columns.
 struct Item {
@@ -102,6 +150,12 @@ struct Summary {
     int32_t n_litems, n_aitems;
     int32_t n_fft, max_nch;
     int32_t n_adense, n_amed;  // dense and medium spread items (the first n_adense, then n_amed, of the item list)
+    int32_t n_aspread;         // spread items (the items of blocks that are not rank blocks)
+    int32_t n_dense_info;      // items of all asymptotic blocks that are dense or medium by their cells
+    int32_t n_ritems, n_rsmall;    // items of rank blocks: of more than kRankWaveCols columns, of at most that many
+    int32_t n_cpan, n_rpan;    // panels of the rank blocks
+    int32_t n_tsingle, n_tmulti;   // their panels of frequencies: of blocks translated by one wave, of others
+    int32_t n_wmulti;              // panels of points of those others
     int64_t l_row, l_col, a_row, a_col, d_ent;
     int64_t grid_cells;     // sum N1 (all asymptotic blocks)
     int64_t dft_cells;      // sum N1 over direct-sum-path blocks
@@ -134,6 +188,10 @@ struct PlanDev {
     int32_t half_ns, pad0;           // leading panels holding the coefficients divided by x^nu
     int32_t nch, sign;               // channels (2M padded to a kernel instance); (-1)^nu for negative orders, else 1
     int32_t fp32;                    // FP32 spreading (weights, kernel values and channel sums in float)
+    int32_t rank, rank_const;        // plan has rank blocks; the Hankel terms beyond the first vanish
+    double rank_ltol, rank_xi;       // log of the expansions' tolerance; largest (half r range) x (half
+                                     // omega range) that kRankK terms cover
+    const double* rank_tab;          // cosine tables (rank_tab_off)
     int32_t mfma;                    // dense spreading items go to the matrix cores (FP64, w <= 16, nch <= 32)
     double z, beta, eps;
     double phi_hi, phi_lo;           // -(2nu+1) pi/4 reduced to [0, 2pi), double-double
@@ -163,10 +221,19 @@ struct PlanDev {
     double jtab_x0;
     int32_t jtab_np, pad2;
     int32_t n_nodes, n_l, n_a, n_d, n_litems, n_aitems, n_adense, n_amed;
+    int32_t n_tsingle, n_tmulti, n_wmulti, n_ritems, n_rsmall, rpad;
+    const Panel* cpans;              // panels of the rank blocks' points
+    const RankItem* rlist;           // items of rank blocks: large ones from the front, small ones from the back
+    const Panel* tlist;              // panels of frequencies: blocks of one wave from the front, others from the back
+    const Panel* wlist;              // panels of points of the latter blocks
+    int32_t tlist_cap, rlist_cap;
     // execution buffers of the partition
     double* cs;                      // weights gathered into sorted point order (n)
     double* lpart;                   // local-moment partial sums (items x (L + 1))
     double* lmom;                    // local moments (local blocks x (L + 1))
+    double2* rmom;                   // rank blocks: moments of (item i, panel q) at (i + q) kRankK
+    double2* rwts;                   // their nodal weights per panel of points
+    double2* rcoef;                  // their expansion coefficients per panel of frequencies
     double2* part;                   // spread partial subgrids
     double2* grids;                  // spread grids (direct-sum path) and FFT buffers (FFT path)
     double2* scratch;                // second buffer of the multi-pass FFTs

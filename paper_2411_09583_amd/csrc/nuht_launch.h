@@ -26,6 +26,11 @@ struct Arena {
     int32_t* alist;      // spreading order of the asymptotic items (aitem_cap)
     int32_t* fft_list;
     int64_t* gslot;      // first grid slot of each asymptotic block, then the total (a_cap + 1)
+    Panel* cpans;        // panels of the rank blocks' points (pan_cap)
+    RankItem* rlist;     // items of rank blocks (aitem_cap)
+    Panel* tlist;        // panels of frequencies to translate (pan_cap)
+    Panel* wlist;        // panels of points weighted on their own (pan_cap)
+    int32_t pan_cap;
     int32_t node_cap, l_cap, a_cap, d_cap, q_cap, litem_cap, aitem_cap, pad;
 };
 
@@ -72,6 +77,9 @@ struct ExecBuffers {
     double* cs;         // gathered weights (sorted point order)
     double* lpart;      // local-moment partial sums, n_litems x (L+1)
     double* lmom;       // local moments, n_l x (L+1)
+    double2* rmom;      // moments of the rank blocks' (item, panel) pairs
+    double2* rwts;      // nodal weights of their panels of points
+    double2* rcoef;     // expansion coefficients of their panels of frequencies
     double2* part;      // spread partial subgrids
     double2* grids;     // spread grids (direct-sum path) and FFT buffers (FFT path)
     double2* scratch;   // second buffer of the two-pass FFTs

@@ -1457,9 +1457,69 @@ __device__ __forceinline__ void subdivide(const PlanArgs& a)
 }
 
 // ---------------------------------------------------------------------------
-// Per-block parameters (grid-stride over the blocks the subdivision made).
+// Per-block parameters: 16 lanes per asymptotic block, a lane per local block
+// (grid-stride over the blocks the subdivision made).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int32_t iceil(double x) { return (int32_t)ceil(x); }
+
+// Terms of a Chebyshev expansion of  H(omega r) e^{i (omega - D)(r - C)}  (H:
+// Hankel's terms) over an interval of one of the two variables, centre `cen`
+// and half-width `half` > 0, the other at least `other` and off its centre by
+// at most xi / half.  On the ellipse with foci at the interval's ends and
+// semi-axes summing to rho the exponential is at most e^{xi (rho - 1/rho)/2}
+// and H at most its terms' sum at the smallest omega r there, so the
+// interpolant of K terms is off by at most 4 max / ((rho - 1) rho^(K-1))
+// (Trefethen, Approximation Theory and Approximation Practice, Thm. 8.2).
+// Sixteen lanes take a rho each; the result is the smallest K over them.
+__device__ __forceinline__ double rank_terms(const PlanDev& P, double cen, double half, double other, double xi)
+{
+    if (!(half > 0.0)) return 1.0;
+    const double lr = kRankLr0 + kRankLrStep * (threadIdx.x & 15);
+    const double rho = exp(lr), inv = 1.0 / rho;
+    double H = fabs(P.chan[0]);
+    bool ok = true;
+    if (!P.rank_const) {
+        const double x = (cen - 0.5 * half * (rho + inv)) * other;
+        ok = x > 0.0;
+        const double ix = ok ? 1.0 / x : 0.0;
+        double v = 0.0;
+        for (int p = 2 * P.M - 1; p >= 0; --p) v = v * ix + fabs(P.chan[p]);
+        H = v;
+    }
+    double k = (log(4.0 * H) + 0.5 * xi * (rho - inv) - log(rho - 1.0) - P.rank_ltol) / lr + 1.0;
+    if (!ok || !(k < 1e9)) k = 1e9;
+    if (k < 1.0) k = 1.0;
+    for (int o = 8; o >= 1; o >>= 1) k = fmin(k, __shfl_xor(k, o));
+    return k;
+}
+
+// Panels of one variable: the fewest equal panels (from xi on) whose
+// expansions need at most kRankK terms -- the panel at the smallest values is
+// the worst, as H varies fastest there.  Returns the panels (0: more than
+// `most`), their terms in *terms.
+__device__ __forceinline__ int rank_panels(const PlanDev& P, double lo, double span_half, double other, double xi,
+                                           int32_t most, double* terms)
+{
+    int pc = (int)ceil(fmin(xi / P.rank_xi, 1e6));
+    if (pc < 1) pc = 1;
+    while (pc <= most) {
+        const double half = span_half / pc;
+        const double k = rank_terms(P, lo + half, half, other, xi / pc);
+        if (k <= (double)kRankK) { *terms = k; return pc; }
+        pc += (pc + 1) / 2;
+    }
+    return 0;
+}
+
+// Half-width of each of `panels` panels over a half-range: rounded up to 40
+// bits, so that the panels' middles (small integers times it) are exact and
+// evenly spaced.
+__device__ __forceinline__ double rank_half_width(double half_range, int panels)
+{
+    const double h = half_range / panels;
+    if (panels == 1 || h == 0.0) return h;
+    return __longlong_as_double((__double_as_longlong(h) + ((1ll << 12) - 1)) & ~((1ll << 12) - 1));
+}
 
 __device__ __forceinline__ void block_params(const PlanArgs& a)
 {
@@ -1471,58 +1531,71 @@ __device__ __forceinline__ void block_params(const PlanArgs& a)
     if (sum->overflow) return;
     const int32_t n_l = sum->n_l, n_a = sum->n_a;
     const int w = P.w;
-    const int32_t nb = n_l > n_a ? n_l : n_a;
-    for (int32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += gridDim.x * blockDim.x) {
-        if (b < n_a) {
-            ABlock B = A.ab[b];
-            double rlo = P.rs[B.k0], rhi = P.rs[B.k1];
-            double wlo = P.ws[B.j0], whi = P.ws[B.j1];
-            double C = 0.5 * (rlo + rhi);
-            double X = fmax(rhi - C, C - rlo);
-            double D = 0.5 * (wlo + whi);
-            double S = fmax(whi - D, D - wlo);
-            if (!(S > 1e-280)) S = 1e-280;
-            // grid spacing: the largest power of two with S h <= pi / sigma
-            double h = exp2(floor(log2(kPi / (sigma * S))));
-            if (S * h > kPi / sigma) h *= 0.5;
-            double span = X / h;
-            if (!(span < (double)(1 << (kMaxFftLog2 - 3)))) {   // grid too large for the FFT sizes
-                atomicOr(&sum->grid_error, 1);
-                span = 0.0;
+    const int lane = threadIdx.x & 15;
+    const int32_t group = (int32_t)((blockIdx.x * blockDim.x + threadIdx.x) >> 4), groups = (int32_t)((gridDim.x * blockDim.x) >> 4);
+    for (int32_t b = group; b < n_a; b += groups) {
+        ABlock B = A.ab[b];
+        double rlo = P.rs[B.k0], rhi = P.rs[B.k1];
+        double wlo = P.ws[B.j0], whi = P.ws[B.j1];
+        double C = 0.5 * (rlo + rhi);
+        double X = fmax(rhi - C, C - rlo);
+        double D = 0.5 * (wlo + whi);
+        double S = fmax(whi - D, D - wlo);
+        B.K = 0; B.pc = 0; B.pr = 0; B.cw = 0.0; B.rw = 0.0;
+        // (half-widths too small for their reciprocals stay on the ES path)
+        if (P.rank && (X == 0.0 || X > 1e-290) && (S == 0.0 || S > 1e-290)) {
+            const double xi = X * S;
+            double kc = 1.0, kr = 1.0;
+            const int pc = rank_panels(P, rlo, X, wlo, xi, kRankPanels, &kc);
+            const int pr = pc > 0 ? rank_panels(P, wlo, S, rlo, xi, 64, &kr) : 0;
+            if (pc > 0 && pr > 0) {
+                int K = ((int)ceil(fmax(kc, kr)) + 3) & ~3;
+                B.K = K < 4 ? 4 : K;
+                B.pc = pc; B.pr = pr;
+                B.cw = rank_half_width(X, pc); B.rw = rank_half_width(S, pr);
             }
-            int32_t llo = iceil(-span - 0.5 * w) - 1;
-            int32_t lhi = iceil(span - 0.5 * w) + w;
-            int32_t N1 = lhi - llo + 1;
-            B.C = C; B.D = D; B.h = h; B.r0 = rlo; B.alpha = 0.5 * w * h;
-            B.llo = llo; B.N1 = N1;
-            int32_t fft = (dft_max >= 0 && N1 <= dft_max) ? 0 : 1;
-            int32_t N2 = 0;
-            if (fft) {
-                int32_t maxl = llo < 0 ? -llo : llo;
-                if (lhi > maxl) maxl = lhi;
-                N2 = 64;
-                while (N2 < 4 * maxl + 4) N2 <<= 1;
-                // h N2 / (2 pi): exact scaling of the double-double 1/(2 pi)
-                B.Khi = h * (double)N2 * kInvTwoPi;
-                B.Klo = h * (double)N2 * kInvTwoPiLo;
-            }
-            B.fft = fft; B.N2 = N2;
-            int32_t ncol = B.k1 - B.k0 + 1;
-            B.nitems = (ncol + P.spread_chunk - 1) / P.spread_chunk;
-            A.ab[b] = B;
         }
-        if (b < n_l) {
-            LBlock L = A.lb[b];
-            double R = P.rs[L.k1];
-            if (R == 0.0) {
-                double wm = P.ws[L.j1];
-                R = wm > 0.0 ? P.z / wm : 1.0;
-            }
-            L.R = R;
-            int32_t ncol = L.k1 - L.k0 + 1;
-            L.nitems = (ncol + kLocalChunk - 1) / kLocalChunk;
-            A.lb[b] = L;
+        if (!(S > 1e-280)) S = 1e-280;
+        // grid spacing: the largest power of two with S h <= pi / sigma
+        double h = exp2(floor(log2(kPi / (sigma * S))));
+        if (S * h > kPi / sigma) h *= 0.5;
+        double span = X / h;
+        if (!(span < (double)(1 << (kMaxFftLog2 - 3)))) {   // grid too large for the FFT sizes
+            if (lane == 0) atomicOr(&sum->grid_error, 1);
+            span = 0.0;
         }
+        int32_t llo = iceil(-span - 0.5 * w) - 1;
+        int32_t lhi = iceil(span - 0.5 * w) + w;
+        int32_t N1 = lhi - llo + 1;
+        B.C = C; B.D = D; B.h = h; B.r0 = rlo; B.alpha = 0.5 * w * h;
+        B.llo = llo; B.N1 = N1;
+        int32_t fft = (B.K > 0 || (dft_max >= 0 && N1 <= dft_max)) ? 0 : 1;
+        int32_t N2 = 0;
+        if (fft) {
+            int32_t maxl = llo < 0 ? -llo : llo;
+            if (lhi > maxl) maxl = lhi;
+            N2 = 64;
+            while (N2 < 4 * maxl + 4) N2 <<= 1;
+            // h N2 / (2 pi): exact scaling of the double-double 1/(2 pi)
+            B.Khi = h * (double)N2 * kInvTwoPi;
+            B.Klo = h * (double)N2 * kInvTwoPiLo;
+        }
+        B.fft = fft; B.N2 = N2;
+        int32_t ncol = B.k1 - B.k0 + 1;
+        B.nitems = (ncol + P.spread_chunk - 1) / P.spread_chunk;
+        if (lane == 0) A.ab[b] = B;
+    }
+    for (int32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < n_l; b += gridDim.x * blockDim.x) {
+        LBlock L = A.lb[b];
+        double R = P.rs[L.k1];
+        if (R == 0.0) {
+            double wm = P.ws[L.j1];
+            R = wm > 0.0 ? P.z / wm : 1.0;
+        }
+        L.R = R;
+        int32_t ncol = L.k1 - L.k0 + 1;
+        L.nitems = (ncol + kLocalChunk - 1) / kLocalChunk;
+        A.lb[b] = L;
     }
 }
 
@@ -1541,7 +1614,7 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
     const PlanDev& P = a.P;
     const Arena& A = a.A;
     Summary* __restrict__ sum = a.sum;
-    __shared__ int64_t wsum[2][16];
+    __shared__ int64_t wsum[3][16];
     __shared__ int32_t cls_cnt[kMaxFftLog2 + 1];
     __shared__ int32_t cls_first[kMaxFftLog2 + 1];
     __shared__ long long red[9][kPlanScanThreads / 64];
@@ -1580,31 +1653,33 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
         l_items += tot[0];
     }
     int64_t a_items = 0, grid = 0;
+    int64_t pans = 0;                                // panels of points + 2^32 panels of frequencies
     for (int32_t c0 = 0; c0 < n_a; c0 += kPlanScanThreads * kVpt) {
         const int32_t i0 = c0 + tid * kVpt;
-        int64_t v[kVpt][2];
+        int64_t v[kVpt][3];
         bool fft[kVpt];
         int32_t n2[kVpt];
         #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
-            v[k][0] = v[k][1] = 0;
+            v[k][0] = v[k][1] = v[k][2] = 0;
             fft[k] = false;
             n2[k] = 0;
             if (i0 + k < n_a) {
                 const ABlock B = A.ab[i0 + k];
                 v[k][0] = B.nitems;
-                v[k][1] = B.fft ? (int64_t)B.N2 : (int64_t)B.N1;
+                v[k][1] = B.K > 0 ? 0 : B.fft ? (int64_t)B.N2 : (int64_t)B.N1;
+                v[k][2] = B.K > 0 ? (int64_t)B.pc + ((int64_t)B.pr << 32) : 0;
                 fft[k] = B.fft != 0;
                 n2[k] = B.N2;
                 const long long rows = B.j1 - B.j0 + 1;
                 st[2] += rows;
                 st[3] += B.k1 - B.k0 + 1;
                 if (B.fft) { st[6] += B.N2; st[8] += rows; }
-                else { st[5] += B.N1; st[7] += rows * B.N1; }
+                else if (B.K == 0) { st[5] += B.N1; st[7] += rows * B.N1; }
             }
         }
-        int64_t tot[2];
-        block_scan_vpt<2, kVpt, kPlanScanThreads / 64>(v, tot, wsum);
+        int64_t tot[3];
+        block_scan_vpt<3, kVpt, kPlanScanThreads / 64>(v, tot, wsum);
         #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
             const int32_t i = i0 + k;
@@ -1612,11 +1687,15 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
                 A.ab[i].item0 = (int32_t)(a_items + v[k][0]);
                 A.ab[i].grid_off = (grid + v[k][1]) * nch;
                 A.gslot[i] = grid + v[k][1];
+                const int64_t pq = pans + v[k][2];
+                A.ab[i].cpan0 = (int32_t)(pq & 0xffffffff);
+                A.ab[i].rpan0 = (int32_t)(pq >> 32);
                 if (fft[k]) atomicAdd(&cls_cnt[31 - __clz(n2[k])], 1);
             }
         }
         a_items += tot[0];
         grid += tot[1];
+        pans += tot[2];
     }
     if (tid == 0) A.gslot[n_a] = grid;
     __syncthreads();
@@ -1662,15 +1741,96 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
         sum->n_litems = (int32_t)l_items; sum->n_aitems = (int32_t)a_items;
         sum->max_nch = nch;
         sum->grid_cells = grid;
-        if (l_items > A.litem_cap || a_items > A.aitem_cap) sum->overflow = 1;
+        const int32_t n_cp = (int32_t)(pans & 0xffffffff), n_rp = (int32_t)(pans >> 32);
+        sum->n_cpan = n_cp; sum->n_rpan = n_rp;
+        if (l_items > A.litem_cap || a_items > A.aitem_cap || n_cp > A.pan_cap || n_rp > A.pan_cap) sum->overflow = 1;
     }
 }
 
 // ---------------------------------------------------------------------------
-// Work items (grid-stride over all items: local first, then asymptotic).
-// An item is a chunk of one block's columns; an asymptotic item also carries
-// the subgrid of cells its points can reach (one cell of margin each side).
+// Work items (grid-stride over all items: local, asymptotic, then the rank
+// blocks' panels of points and of frequencies).
+// An item is a chunk of one block's columns; a spread item also carries the
+// subgrid of cells its points can reach (one cell of margin each side), an
+// item of a rank block the panels its points lie in.
 // ---------------------------------------------------------------------------
+// Last block b with first_of(b) <= i (first_of nondecreasing, first_of(0) <= i),
+// for the 64 consecutive values i0 .. i0 + 63 of a wave (lane l: i = i0 + l;
+// every lane calls it).  The wave finds the block of i0 by 64-ary steps; when
+// the next 63 blocks reach past the wave's last value each lane then searches
+// their first values, loaded once, through lane reads.
+template <class F>
+__device__ __forceinline__ int32_t block_of(int32_t n, int32_t i0, F&& first_of)
+{
+    const int lane = threadIdx.x & 63;
+    const int32_t i = i0 + lane;
+    int32_t lo = 0, hi = n;                          // the block of i0 lies in [lo, hi)
+    while (hi - lo > 1) {
+        const int32_t step = (hi - lo + 63) / 64;
+        const int32_t p = lo + (lane + 1) * step;    // first_of(p) <= i0 for the first c lanes
+        const int c = __popcll(__ballot(p < hi && first_of(p) <= i0));
+        lo += c * step;
+        hi = lo + step < hi ? lo + step : hi;
+    }
+    const int32_t b = lo + 1 + lane;
+    const int32_t f = b < n ? first_of(b) : INT32_MAX;
+    if (__shfl(f, 63) > i0 + 63) {
+        int c = 0;                                   // blocks after lo that start at or before i
+        #pragma unroll
+        for (int o = 32; o >= 1; o >>= 1)
+            if (__shfl(f, c + o - 1) <= i) c += o;
+        return lo + c;
+    }
+    int32_t a = lo, e = n - 1;
+    while (a < e) {
+        const int32_t mid = (a + e + 1) >> 1;
+        if (first_of(mid) <= i) a = mid; else e = mid - 1;
+    }
+    return a;
+}
+
+// Panel of the rank block's point r: the one with edge(q) <= r - C < edge(q + 1),
+// the outer panels open-ended.
+__device__ __forceinline__ int32_t rank_panel_of(const ABlock& B, double r)
+{
+    if (B.pc == 1) return 0;
+    const double b = r - B.C;
+    int32_t q = (int32_t)((b - rank_edge(B, 0)) / (2.0 * B.cw));
+    q = q < 0 ? 0 : q >= B.pc ? B.pc - 1 : q;
+    while (q > 0 && b < rank_edge(B, q)) --q;
+    while (q + 1 < B.pc && b >= rank_edge(B, q + 1)) ++q;
+    return q;
+}
+
+// First column of panel q of a rank block (q = pc: one past its last).
+__device__ __forceinline__ int32_t rank_panel_col(const ABlock& B, const double* __restrict__ rs, int32_t q)
+{
+    if (q <= 0) return B.k0;
+    if (q >= B.pc) return B.k1 + 1;
+    const double e = rank_edge(B, q);
+    int32_t lo = B.k0, hi = B.k1 + 1;
+    while (lo < hi) {
+        const int32_t mid = lo + ((hi - lo) >> 1);
+        if (rs[mid] - B.C < e) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+// Appends the calling lanes with `take` set to a list whose length is *count:
+// one atomic per wave.  The order of a list depends on timing; nothing that is
+// computed from it does.
+__device__ __forceinline__ int32_t wave_append(bool take, int32_t* count)
+{
+    const uint64_t m = __ballot(take);
+    if (m == 0) return 0;
+    const int lane = threadIdx.x & 63;
+    const int lead = __builtin_ctzll(m);
+    int32_t base = 0;
+    if (lane == lead) base = atomicAdd(count, (int32_t)__popcll(m));
+    base = __shfl(base, lead);
+    return base + (int32_t)__popcll(m & (lane == 0 ? 0ull : (~0ull >> (64 - lane))));
+}
+
 __device__ __forceinline__ void items(const PlanArgs& a)
 {
     const PlanDev& P = a.P;
@@ -1679,119 +1839,175 @@ __device__ __forceinline__ void items(const PlanArgs& a)
     int32_t* __restrict__ a_cells = a.a_cells;
     if (sum->overflow) return;
     const int32_t n_l = sum->n_l, n_a = sum->n_a;
-    const int32_t n_li = sum->n_litems, n_ai = sum->n_aitems;
+    const int32_t n_li = sum->n_litems, n_ai = sum->n_aitems, n_cp = sum->n_cpan, n_rp = sum->n_rpan;
     const int w = P.w;
-    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n_li + n_ai; i += gridDim.x * blockDim.x) {
-        if (i < n_li) {
-            int32_t lo = 0, hi = n_l - 1;             // last block with item0 <= i
-            while (lo < hi) {
-                int32_t mid = (lo + hi + 1) >> 1;
-                if (A.lb[mid].item0 <= i) lo = mid; else hi = mid - 1;
+    // the four kinds of work, each rounded up to whole waves
+    const int32_t w_li = (n_li + 63) & ~63, w_ai = (n_ai + 63) & ~63, w_cp = (n_cp + 63) & ~63, w_rp = (n_rp + 63) & ~63;
+    const int32_t total = w_li + w_ai + w_cp + w_rp;
+    for (int32_t j0 = blockIdx.x * blockDim.x + (threadIdx.x & ~63); j0 < total; j0 += gridDim.x * blockDim.x) {
+        const int lane = threadIdx.x & 63;
+        bool ritem = false;                           // an item of a rank block
+        bool tone = false, tmany = false;             // a panel of frequencies of a block of one wave / of another
+        bool wmany = false;                           // a panel of points of another
+        RankItem R{};
+        Panel T{};
+        if (j0 < w_li) {
+            const int32_t i = j0 + lane;
+            const int32_t lo = block_of(n_l, j0, [&](int32_t b) { return A.lb[b].item0; });
+            if (i < n_li) {
+                const LBlock L = A.lb[lo];
+                int32_t it = i - L.item0;
+                int32_t ka = L.k0 + it * kLocalChunk;
+                int32_t kb = ka + kLocalChunk;
+                if (kb > L.k1 + 1) kb = L.k1 + 1;
+                Item I;
+                I.blk = lo; I.ka = ka; I.kb = kb; I.sub_lo = 0; I.sub_n = 0; I.dense = 0; I.off = 0;
+                A.litems[i] = I;
             }
-            const LBlock L = A.lb[lo];
-            int32_t it = i - L.item0;
-            int32_t ka = L.k0 + it * kLocalChunk;
-            int32_t kb = ka + kLocalChunk;
-            if (kb > L.k1 + 1) kb = L.k1 + 1;
-            Item I;
-            I.blk = lo; I.ka = ka; I.kb = kb; I.sub_lo = 0; I.sub_n = 0; I.dense = 0; I.off = 0;
-            A.litems[i] = I;
+        } else if (j0 < w_li + w_ai) {
+            const int32_t i0 = j0 - w_li, ia = i0 + lane;
+            const int32_t lo = block_of(n_a, i0, [&](int32_t b) { return A.ab[b].item0; });
+            if (ia < n_ai) {
+                const ABlock B = A.ab[lo];
+                int32_t it = ia - B.item0;
+                int32_t ka = B.k0 + it * P.spread_chunk;
+                int32_t kb = ka + P.spread_chunk - 1;
+                if (kb > B.k1) kb = B.k1;
+                int32_t lhi = B.llo + B.N1 - 1;
+                const double ra = P.rs[ka], rb = P.rs[kb];
+                double u0 = (ra - B.C) / B.h, u1 = (rb - B.C) / B.h;
+                int32_t s0 = iceil(u0 - 0.5 * w) - 1;
+                int32_t s1 = iceil(u1 - 0.5 * w) + w;
+                if (s0 < B.llo) s0 = B.llo;
+                if (s1 > lhi) s1 = lhi;
+                Item I;
+                I.blk = lo; I.ka = ka; I.kb = kb + 1; I.sub_lo = s0; I.sub_n = s1 - s0 + 1; I.off = 0;
+                // first cells of the points lie in s0 .. s1 - w + 1 (one cell of
+                // margin each side for rounding): dense if at most kSpreadAnchors,
+                // medium if at most kSpreadAnchorsMed
+                const int32_t anchors = I.sub_n - w + 1;
+                I.dense = !P.mfma ? 0
+                        : anchors <= kSpreadAnchors ? 1
+                        : (anchors <= kSpreadAnchorsMed && P.nch <= kMfmaMedMaxChannels) ? 2 : 0;
+                int32_t cells = I.sub_n;
+                if (B.K > 0) {
+                    ritem = true;
+                    R.blk = lo; R.slot = ia + B.cpan0; R.ka = ka; R.kb = kb + 1;
+                    R.q0 = rank_panel_of(B, ra);
+                    R.nq = rank_panel_of(B, rb) - R.q0 + 1;
+                    cells = 0;
+                }
+                A.aitems[ia] = I;
+                // cells, the item's kind and whether its block is a rank block
+                a_cells[ia] = cells | (I.dense << 28) | (B.K > 0 ? (1 << 30) : 0);
+            }
+        } else if (j0 < w_li + w_ai + w_cp) {
+            const int32_t i0 = j0 - w_li - w_ai, ip = i0 + lane;
+            const int32_t lo = block_of(n_a, i0, [&](int32_t b) { return A.ab[b].cpan0; });
+            if (ip < n_cp) {
+                const ABlock B = A.ab[lo];
+                T.blk = lo; T.q = ip - B.cpan0;
+                T.ka = rank_panel_col(B, P.rs, T.q);
+                T.kb = rank_panel_col(B, P.rs, T.q + 1);
+                A.cpans[ip] = T;
+                wmany = !rank_one_wave(B);
+            }
         } else {
-            int32_t ia = i - n_li;
-            int32_t lo = 0, hi = n_a - 1;
-            while (lo < hi) {
-                int32_t mid = (lo + hi + 1) >> 1;
-                if (A.ab[mid].item0 <= ia) lo = mid; else hi = mid - 1;
+            const int32_t i0 = j0 - w_li - w_ai - w_cp, ip = i0 + lane;
+            const int32_t lo = block_of(n_a, i0, [&](int32_t b) { return A.ab[b].rpan0; });
+            if (ip < n_rp) {
+                const ABlock B = A.ab[lo];
+                T.blk = lo; T.q = ip - B.rpan0;
+                tone = rank_one_wave(B);
+                tmany = !tone;
             }
-            const ABlock B = A.ab[lo];
-            int32_t it = ia - B.item0;
-            int32_t ka = B.k0 + it * P.spread_chunk;
-            int32_t kb = ka + P.spread_chunk - 1;
-            if (kb > B.k1) kb = B.k1;
-            int32_t lhi = B.llo + B.N1 - 1;
-            double u0 = (P.rs[ka] - B.C) / B.h, u1 = (P.rs[kb] - B.C) / B.h;
-            int32_t s0 = iceil(u0 - 0.5 * w) - 1;
-            int32_t s1 = iceil(u1 - 0.5 * w) + w;
-            if (s0 < B.llo) s0 = B.llo;
-            if (s1 > lhi) s1 = lhi;
-            Item I;
-            I.blk = lo; I.ka = ka; I.kb = kb + 1; I.sub_lo = s0; I.sub_n = s1 - s0 + 1; I.off = 0;
-            // first cells of the points lie in s0 .. s1 - w + 1 (one cell of
-            // margin each side for rounding): dense if at most kSpreadAnchors,
-            // medium if at most kSpreadAnchorsMed
-            const int32_t anchors = I.sub_n - w + 1;
-            I.dense = !P.mfma ? 0
-                    : anchors <= kSpreadAnchors ? 1
-                    : (anchors <= kSpreadAnchorsMed && P.nch <= kMfmaMedMaxChannels) ? 2 : 0;
-            A.aitems[ia] = I;
-            a_cells[ia] = I.sub_n;
         }
+        const bool small = ritem && R.kb - R.ka <= kRankWaveCols;
+        const int32_t p0 = wave_append(ritem && !small, &sum->n_ritems), p4 = wave_append(small, &sum->n_rsmall);
+        if (ritem) A.rlist[small ? A.aitem_cap - 1 - p4 : p0] = R;
+        const int32_t p3 = wave_append(wmany, &sum->n_wmulti);
+        if (wmany) A.wlist[p3] = T;
+        const int32_t p1 = wave_append(tone, &sum->n_tsingle);
+        if (tone) A.tlist[p1] = T;
+        const int32_t p2 = wave_append(tmany, &sum->n_tmulti);
+        if (tmany) A.tlist[A.pan_cap - 1 - p2] = T;
     }
 }
 
 // Partial-subgrid offsets of the asymptotic items, and the spreading order:
 // dense items at alist[0 ..), medium ones after them, and the others at
 // alist[n_ai - 1], alist[n_ai - 2], ..., each list in item order (one
-// workgroup).
+// workgroup).  Items of rank blocks are not spread and in none of them.
 __device__ __forceinline__ void item_scan(const PlanArgs& a)
 {
     const PlanDev& P = a.P;
     const Arena& A = a.A;
     Summary* __restrict__ sum = a.sum;
     const int32_t* __restrict__ a_cells = a.a_cells;
-    __shared__ int64_t wsum[3][16];
-    __shared__ int32_t n_dense_total;
+    __shared__ int64_t wsum[4][16];
+    __shared__ int32_t n_dense_total, n_dense_all;
     if (sum->overflow) return;
     const int32_t n_ai = sum->n_aitems;
     const int nch = P.nch;
     constexpr int kVpt = 8;                          // items per thread per pass (2048 per pass)
     // the dense items' total first: the medium ones follow them in the list
     {
-        int32_t nd = 0;
-        for (int32_t i = threadIdx.x; i < n_ai; i += kPlanScanThreads) nd += A.aitems[i].dense == 1 ? 1 : 0;
-        for (int o = 32; o >= 1; o >>= 1) nd += __shfl_xor(nd, o);
-        if (threadIdx.x == 0) n_dense_total = 0;
+        int32_t nd = 0, all = 0;
+        for (int32_t i = threadIdx.x; i < n_ai; i += kPlanScanThreads) {
+            const int32_t c = a_cells[i];
+            const int kind = (c >> 28) & 3;
+            all += kind != 0 ? 1 : 0;
+            nd += (kind == 1 && !(c >> 30)) ? 1 : 0;
+        }
+        for (int o = 32; o >= 1; o >>= 1) { nd += __shfl_xor(nd, o); all += __shfl_xor(all, o); }
+        if (threadIdx.x == 0) { n_dense_total = 0; n_dense_all = 0; }
         __syncthreads();
-        if ((threadIdx.x & 63) == 0) atomicAdd(&n_dense_total, nd);
+        if ((threadIdx.x & 63) == 0) { atomicAdd(&n_dense_total, nd); atomicAdd(&n_dense_all, all); }
         __syncthreads();
     }
     const int64_t nd_total = n_dense_total;
-    int64_t run = 0, run_dense = 0, run_med = 0;
+    int64_t run = 0, run_dense = 0, run_med = 0, run_rank = 0;
     for (int32_t c0 = 0; c0 < n_ai; c0 += kPlanScanThreads * kVpt) {
         const int32_t i0 = c0 + threadIdx.x * kVpt;
-        int64_t v[kVpt][3];
-        int cls[kVpt];
+        int64_t v[kVpt][4];
+        int cls[kVpt];                               // 1 dense, 2 medium, 0 vector, 3 an item of a rank block
         #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
-            const bool act = i0 + k < n_ai;
-            v[k][0] = act ? (int64_t)a_cells[i0 + k] : 0;
-            cls[k] = act ? A.aitems[i0 + k].dense : 0;
+            const int32_t c = i0 + k < n_ai ? a_cells[i0 + k] : (1 << 30);
+            v[k][0] = c & ((1 << 28) - 1);
+            cls[k] = (c >> 30) ? 3 : (c >> 28) & 3;
             v[k][1] = cls[k] == 1 ? 1 : 0;
             v[k][2] = cls[k] == 2 ? 1 : 0;
+            v[k][3] = cls[k] == 3 ? 1 : 0;
         }
-        int64_t tot[3];
-        block_scan_vpt<3, kVpt, kPlanScanThreads / 64>(v, tot, wsum);
+        int64_t tot[4];
+        block_scan_vpt<4, kVpt, kPlanScanThreads / 64>(v, tot, wsum);
         #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
             const int32_t i = i0 + k;
-            if (i < n_ai) {
+            if (i < n_ai && cls[k] != 3) {
                 A.aitems[i].off = (run + v[k][0]) * nch;
                 // dense from the front, then medium, the others from the back
                 const int64_t nd_before = run_dense + v[k][1], nm_before = run_med + v[k][2];
                 const int64_t pos = cls[k] == 1 ? nd_before
                                   : cls[k] == 2 ? nd_total + nm_before
-                                                : n_ai - 1 - (i - nd_before - nm_before);
+                                                : n_ai - 1 - (i - nd_before - nm_before - (run_rank + v[k][3]));
                 A.alist[pos] = i;
             }
         }
         run += tot[0];
         run_dense += tot[1];
         run_med += tot[2];
+        run_rank += tot[3];
     }
     if (threadIdx.x == 0) {
+        // the last pass counted its unused places as items of rank blocks
+        const int64_t pass = kPlanScanThreads * kVpt, unused = (n_ai + pass - 1) / pass * pass - n_ai;
         sum->part_cells = run;
         sum->n_adense = (int32_t)run_dense;
         sum->n_amed = (int32_t)run_med;
+        sum->n_aspread = (int32_t)(n_ai - (run_rank - unused));
+        sum->n_dense_info = n_dense_all;
     }
 }
 
@@ -1943,7 +2159,7 @@ int sort_hist_len(int32_t na, int32_t nb)
     }
 }
 
-constexpr int kParamBlocks = 256, kItemBlocks = 512;
+constexpr int kParamBlocks = 512, kItemBlocks = 512;
 
 hipError_t launch_planning(const PlanArgs& a, hipStream_t s)
 {
