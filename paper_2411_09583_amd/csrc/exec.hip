@@ -177,13 +177,23 @@ __device__ __forceinline__ double reduce_chunk(const double (&acc)[NQ], int off,
     return mine;
 }
 
-// Stores the chunk of C moments starting at s0 + off (those up to L).
+// A moment as the row evaluations use it: u_0 = t_0, u_l = 2 (-1)^l t_l
+// (integer orders), t_l itself (half-integer orders: the factors are in the
+// table).
+__device__ __forceinline__ double moment_as_used(const PlanDev& P, int l, double t)
+{
+    return (l == 0 || P.half) ? t : ((l & 1) ? -2.0 * t : 2.0 * t);
+}
+
+// Stores the chunk of C moments starting at s0 + off (those up to L); `whole`:
+// they are a block's only item, stored as used.
 template <int C, int NQ>
-__device__ __forceinline__ void store_chunk(const double (&acc)[NQ], int off, int s0, int L, int lane,
-                                            double* __restrict__ dst)
+__device__ __forceinline__ void store_chunk(const PlanDev& P, const double (&acc)[NQ], int off, int s0, int lane,
+                                            bool whole, double* __restrict__ dst)
 {
     const double mine = reduce_chunk<C>(acc, off, lane);
-    if (lane < C && s0 + off + lane <= L) dst[s0 + off + lane] = mine;
+    const int l = s0 + off + lane;
+    if (lane < C && l <= P.L) dst[l] = whole ? moment_as_used(P, l, mine) : mine;
 }
 
 // Moments s0 .. s0 + NQ - 1 of the item (those up to L are stored); NQ a
@@ -229,12 +239,13 @@ __device__ __forceinline__ void lmom_pass(const PlanDev& P, const Item& I, const
         }
     }
     // the pass's moments in chunks of 64, 32, 16 and 8 (NQ's binary digits)
-    double* __restrict__ dst = lpart + (int64_t)bid * (L + 1);
+    const bool whole = B.nitems == 1;
+    double* __restrict__ dst = whole ? P.lmom + (int64_t)I.blk * (L + 1) : lpart + (int64_t)bid * (L + 1);
     constexpr int c64 = NQ & 64, c32 = NQ & 32, c16 = NQ & 16, c8 = NQ & 8;
-    if constexpr (c64) store_chunk<64>(acc, 0, s0, L, lane, dst);
-    if constexpr (c32) store_chunk<32>(acc, c64, s0, L, lane, dst);
-    if constexpr (c16) store_chunk<16>(acc, c64 + c32, s0, L, lane, dst);
-    if constexpr (c8) store_chunk<8>(acc, c64 + c32 + c16, s0, L, lane, dst);
+    if constexpr (c64) store_chunk<64>(P, acc, 0, s0, lane, whole, dst);
+    if constexpr (c32) store_chunk<32>(P, acc, c64, s0, lane, whole, dst);
+    if constexpr (c16) store_chunk<16>(P, acc, c64 + c32, s0, lane, whole, dst);
+    if constexpr (c8) store_chunk<8>(P, acc, c64 + c32 + c16, s0, lane, whole, dst);
 }
 
 // MAXQ: the widest pass (32 or 64).  A kernel's registers follow its widest
@@ -280,7 +291,7 @@ __global__ __launch_bounds__(64) void k_lmom_many(const PlanDev* __restrict__ pl
     lmom_body<MAXQ>(plan_of(plans, w.t), w.g0);
 }
 
-// Sum of a local block's item partials, in a fixed order: eight running sums
+// Sum of a local block's item partials (blocks of several items), in a fixed order: eight running sums
 // over the items (item i into sum i mod 8), combined pairwise.  A block can
 // hold a few hundred items (the top-level local block spans most columns),
 // and eight independent sums keep eight loads in flight instead of one.
@@ -292,6 +303,7 @@ __device__ __forceinline__ void lmom_reduce_body(const PlanDev& P, int bid)
     const int32_t b = t / Lp;
     const int32_t l = t - b * Lp;
     const LBlock B = P.lb[b];
+    if (B.nitems == 1) return;                       // stored by its item
     const double* __restrict__ col = P.lpart + (int64_t)B.item0 * Lp + l;
     double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     int32_t it = 0;
@@ -303,9 +315,7 @@ __device__ __forceinline__ void lmom_reduce_body(const PlanDev& P, int bid)
     for (int q = 0; q < 7; ++q)
         if (it + q < B.nitems) a[q] += col[(int64_t)(it + q) * Lp];
     const double s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-    // stored as the row pass uses them: u_0 = t_0, u_l = 2 (-1)^l t_l (integer
-    // orders), t_l itself (half-integer orders: the factors are in the table)
-    P.lmom[t] = (l == 0 || P.half) ? s : ((l & 1) ? -2.0 * s : 2.0 * s);
+    P.lmom[t] = moment_as_used(P, l, s);
 }
 
 __global__ void k_lmom_reduce(PlanDev P) { lmom_reduce_body(P, blockIdx.x); }
@@ -1998,6 +2008,7 @@ __device__ double local_eval(const PlanDev& P, int lblk, double om, const double
 // with beta from the plan's table: panel p = floor(x / h), Horner's rule in the
 // panel variable tau = 2 (x / h - p) - 1 for each l; the leading panels
 // (below x = n + 10) hold beta / x^n, accurate relative to beta itself there.
+// The factor sqrt(2x/pi), not smooth at 0, is left to the row pass.
 __device__ double local_eval_half(const PlanDev& P, int lblk, double om, const double* __restrict__ lmom)
 {
     const LBlock B = P.lb[lblk];
@@ -2017,7 +2028,7 @@ __device__ double local_eval_half(const PlanDev& P, int lblk, double om, const d
         acc = __builtin_fma(b, t[l], acc);
     }
     if (pn < P.half_ns && P.nu > 0) acc *= pow(x, (double)P.nu);
-    return sqrt(2.0 * x / kPi) * acc;
+    return acc;
 }
 
 // Asymptotic block contribution at frequency om (Sec. 3.2):
@@ -2325,68 +2336,124 @@ __global__ __launch_bounds__(kDirectThreads) void k_direct_blocks_many(const Pla
     direct_body(plan_of(plans, w.t), w.g0);
 }
 
-// Row pass, two kernels; each has one thread per sorted frequency and walks
-// the block tree from the root.  At a node the row lies either in the local
-// side (rows j0..js) -- local block, then the upper-right child -- or in the
-// asymptotic side -- asymptotic block, then the lower-left child; a direct
-// child ends the walk.  k_rows_asy adds the row's asymptotic blocks (no LDS,
-// so it runs at the occupancy its registers allow) into ga; k_rows_local adds
-// the local blocks, the direct-block sum from k_direct_blocks and ga, and
-// writes g once in the caller's order.
-template <int NCH>
-__device__ __forceinline__ void rows_asy_body(const PlanDev& P, int bid)
+// The local blocks' rows.  In omega a block's sum sum_l C_l(omega R) t_l is
+// entire and no wider than R, so on a panel of frequencies its Chebyshev
+// interpolant of K terms stands for it: k_local_nodes evaluates the sum at
+// each panel's K nodes (Miller's recurrence, or the half-integer table), a
+// wave per 64 / K panels of a block, and turns the values into coefficients;
+// the row pass then spends 2 K operations on a row instead of a recurrence
+// of tens of steps with its products.  A block with fewer rows than nodes has
+// the sum evaluated at its rows and the values kept.
+template <int MODE>
+__device__ __forceinline__ void local_nodes_body(const PlanDev& P, int bid, double* ring_all)
 {
-    const double2* __restrict__ grids = P.grids;
-    int j = bid * blockDim.x + threadIdx.x;
-    if (j >= P.m) return;
-    double om = P.ws[j];
-    double acc = 0.0;
-    int node = P.n_nodes > 0 ? 0 : -1;
-    while (node >= 0) {
-        const Node nd = P.nodes[node];
-        int child;
-        if (j <= nd.js) {
-            child = nd.ur;
-        } else {
-            if (nd.ablk >= 0) {
-                int ab = nd.ablk;
-                int abu = __builtin_amdgcn_readfirstlane(ab);
-                if (__all(ab == abu)) acc += asym_eval<NCH, true>(P, abu, om, grids);
-                else acc += asym_eval<NCH, false>(P, ab, om, grids);
-            }
-            child = nd.ll;
-        }
-        node = child;
+    const LocalWork W = P.lwork[bid];
+    const LBlock& B = P.lb[W.blk];
+    const int lane = threadIdx.x;
+    const int K = B.K, per = local_wave_slots(K), slots = local_slots(B);
+    const int n = slots - W.q < per ? slots - W.q : per;       // slots of this wave
+    double* __restrict__ out = P.lcoef + (int64_t)(B.slot0 + W.q) * kRankK;
+    int rows = 0, p = 0, t = 0;
+    double om;
+    const double* __restrict__ tab = P.rank_tab + rank_tab_off(K > 0 ? K : 4);
+    if (K > 0) {
+        p = lane / K;
+        t = lane - p * K;
+        if (p >= n) { p = n - 1; t = K - 1; }
+        om = B.D + (rank_mid(W.q + p, B.pr, B.rw) + B.rw * tab[K + t]);
+        if (om < 0.0) om = 0.0;                                 // the lowest node at omega = 0, rounded
+    } else {
+        rows = B.j1 - B.j0 + 1 - W.q * kRankK;
+        if (rows > n * kRankK) rows = n * kRankK;
+        om = P.ws[B.j0 + W.q * kRankK + (lane < rows ? lane : rows - 1)];
     }
-    P.ga[j] = acc;
-}
-
-template <int NCH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_rows_asy(PlanDev P)
-{
-    rows_asy_body<NCH>(P, blockIdx.x);
-}
-
-template <int NCH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_rows_asy_many(
-    const PlanDev* __restrict__ plans, const WorkSeg* __restrict__ segs, int nseg)
-{
-    const WorkSeg w = find_seg(segs, nseg);
-    rows_asy_body<NCH>(plan_of(plans, w.t), w.g0);
+    double v;
+    if constexpr (MODE == 3) v = local_eval_half(P, W.blk, om, P.lmom);
+    else v = local_eval<MODE>(P, W.blk, om, P.lmom, ring_all + lane, 64);
+    if (K == 0) {
+        if (lane < rows) out[lane] = v;
+        return;
+    }
+    // lane p K + m: coefficient m = t of panel p
+    const double* __restrict__ col = tab + K * K + t;
+    double c = 0.0;
+    for (int h = 0; h < K; ++h) c = __builtin_fma(__shfl(v, p * K + h), col[h * K], c);
+    if (lane < n * K) out[p * kRankK + t] = c * ((t == 0 ? 1.0 : 2.0) / K);
 }
 
 template <int MODE>
-__device__ __forceinline__ void rows_local_body(const PlanDev& P, int bid, double* g)
+__global__ __launch_bounds__(64) void k_local_nodes(PlanDev P)
 {
-    const double* __restrict__ gd = P.gd;
-    const double* __restrict__ ga = P.ga;
-    const double* __restrict__ lmom = P.lmom;
     extern __shared__ double ring_all[];
-    int j = bid * blockDim.x + threadIdx.x;
+    local_nodes_body<MODE>(P, blockIdx.x, ring_all);
+}
+
+template <int MODE>
+__global__ __launch_bounds__(64) void k_local_nodes_many(const PlanDev* __restrict__ plans,
+                                                         const WorkSeg* __restrict__ segs, int nseg)
+{
+    extern __shared__ double ring_all[];
+    const WorkSeg w = find_seg(segs, nseg);
+    local_nodes_body<MODE>(plan_of(plans, w.t), w.g0, ring_all);
+}
+
+__device__ __forceinline__ double local_series(const double* __restrict__ v, int K, double eta)
+{
+    double t0 = 1.0, t1 = eta, a = 0.0;
+    const double e2 = eta + eta;
+    for (int m = 0; m < K; m += 4) {
+        #pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            a = __builtin_fma(v[m + u], t0, a);
+            const double t2 = __builtin_fma(e2, t1, -t0);
+            t0 = t1;
+            t1 = t2;
+        }
+    }
+    return a;
+}
+
+// Local block lb's contribution at row j, frequency om (lb the same in every
+// lane with UNI).
+template <bool UNI>
+__device__ __forceinline__ double local_row(const PlanDev& P, int lb, int j, double om)
+{
+    const LBlock& B = P.lb[lb];
+    const double* __restrict__ slots = P.lcoef + (int64_t)B.slot0 * kRankK;
+    double v;
+    if (B.K == 0) {
+        v = slots[j - B.j0];
+    } else {
+        const double inv = B.rw > 0.0 ? rcp_refined(B.rw) : 0.0;
+        const dd a = two_sum(om, -B.D);
+        int q = (int)(0.5 * __builtin_fma(a.hi, inv, (double)B.pr));
+        q = q < 0 ? 0 : q > B.pr - 1 ? B.pr - 1 : q;
+        const double eta = ((a.hi - rank_mid(q, B.pr, B.rw)) + a.lo) * inv;
+        if constexpr (UNI) {
+            const int qu = __builtin_amdgcn_readfirstlane(q);
+            if (__all(q == qu)) v = local_series(slots + qu * kRankK, B.K, eta);
+            else v = local_series(slots + q * kRankK, B.K, eta);
+        } else {
+            v = local_series(slots + q * kRankK, B.K, eta);
+        }
+    }
+    if (P.half) v *= sqrt(2.0 / kPi * (om * B.R));
+    return v;
+}
+
+// Row pass: one thread per sorted frequency walks the block tree from the
+// root.  At a node the row lies either in the local side (rows j0..js) --
+// local block, then the upper-right child -- or in the asymptotic side --
+// asymptotic block, then the lower-left child; a direct child ends the walk
+// and adds the row's sum from k_direct_blocks.  g is written once, in the
+// caller's order.
+template <int NCH>
+__device__ __forceinline__ void rows_body(const PlanDev& P, int bid, double* g)
+{
+    const double2* __restrict__ grids = P.grids;
+    const int j = bid * blockDim.x + threadIdx.x;
     if (j >= P.m) return;
-    double* ring = ring_all + threadIdx.x;
-    const int stride = blockDim.x;
-    double om = P.ws[j];
+    const double om = P.ws[j];
     double acc = 0.0;
     int node = P.n_nodes > 0 ? 0 : -1;
     while (node >= 0) {
@@ -2394,42 +2461,41 @@ __device__ __forceinline__ void rows_local_body(const PlanDev& P, int bid, doubl
         int child;
         if (j <= nd.js) {
             if (nd.lblk >= 0) {
-                int lb = nd.lblk;
-                int lbu = __builtin_amdgcn_readfirstlane(lb);
-                if constexpr (MODE == 3) {
-                    if (__all(lb == lbu)) acc += local_eval_half(P, lbu, om, lmom);
-                    else acc += local_eval_half(P, lb, om, lmom);
-                } else {
-                    if (__all(lb == lbu)) acc += local_eval<MODE>(P, lbu, om, lmom, ring, stride);
-                    else acc += local_eval<MODE>(P, lb, om, lmom, ring, stride);
-                }
+                const int lb = nd.lblk, lbu = __builtin_amdgcn_readfirstlane(lb);
+                if (__all(lb == lbu)) acc += local_row<true>(P, lbu, j, om);
+                else acc += local_row<false>(P, lb, j, om);
             }
             child = nd.ur;
         } else {
+            if (nd.ablk >= 0) {
+                const int ab = nd.ablk, abu = __builtin_amdgcn_readfirstlane(ab);
+                if (__all(ab == abu)) acc += asym_eval<NCH, true>(P, abu, om, grids);
+                else acc += asym_eval<NCH, false>(P, ab, om, grids);
+            }
             child = nd.ll;
         }
         if (child <= -2) {
-            acc += gd[j];
+            acc += P.gd[j];
             break;
         }
         node = child;
     }
-    g[P.perm_w[j]] = P.sign * (acc + ga[j]);
+    g[P.perm_w[j]] = P.sign * acc;
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256) void k_rows_local(PlanDev P, double* g, double* const* g_slot)
+template <int NCH>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_rows(PlanDev P, double* g,
+                                                                                     double* const* g_slot)
 {
-    rows_local_body<MODE>(P, blockIdx.x, g_slot ? *g_slot : g);
+    rows_body<NCH>(P, blockIdx.x, g_slot ? *g_slot : g);
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256) void k_rows_local_many(const PlanDev* __restrict__ plans,
-                                                         const WorkSeg* __restrict__ segs, int nseg,
-                                                         double* const* g_table)
+template <int NCH>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_rows_many(
+    const PlanDev* __restrict__ plans, const WorkSeg* __restrict__ segs, int nseg, double* const* g_table)
 {
     const WorkSeg w = find_seg(segs, nseg);
-    rows_local_body<MODE>(plan_of(plans, w.t), w.g0, g_table[w.t]);
+    rows_body<NCH>(plan_of(plans, w.t), w.g0, g_table[w.t]);
 }
 
 // Brute-force reference: one thread per frequency, all points.
@@ -2470,39 +2536,22 @@ static void launch_spread(const PlanDev& P, const Summary& S, hipStream_t s)
     }
 }
 
-template <int NCH>
-static void launch_rows_asy(const PlanDev& P, hipStream_t s)
+// local_eval keeps J_{nu-a .. nu}, a = floor(nu/2), per lane in LDS at orders
+// 2 and up.
+static size_t local_nodes_lds(const PlanDev& P)
 {
-    hipLaunchKernelGGL(k_rows_asy<NCH>, dim3(cdiv64(P.m, 256)), dim3(256), 0, s, P);
+    return P.half || P.nu <= 1 ? 0 : (size_t)((P.nu >> 1) + 1) * 64 * sizeof(double);
 }
 
-// local_eval keeps J_{nu-a .. nu}, a = floor(nu/2), per thread in LDS: the
-// block size and LDS bytes of the local-row kernel of order nu (MODE 2).
-static int rows_local_block(int nu)
-{
-    const int slots = (nu >> 1) + 1;
-    return slots * 256 * 8 <= 65536 ? 256 : 64;
-}
+// The instance of k_local_nodes: orders 0 and 1, the general one, half-integer
+// orders.
+static int local_mode(const PlanDev& P) { return P.half ? 3 : P.nu <= 1 ? P.nu : 2; }
 
-static size_t rows_local_lds(int nu, int bs)
+static void launch_local_nodes(const PlanDev& P, hipStream_t s)
 {
-    return nu <= 1 ? 0 : (size_t)((nu >> 1) + 1) * bs * sizeof(double);
-}
-
-static void launch_rows_local(const PlanDev& P, const IoArgs& io, hipStream_t s)
-{
-    if (P.half) {      // half-integer orders: coefficients from the table
-        hipLaunchKernelGGL(k_rows_local<3>, dim3(cdiv64(P.m, 256)), dim3(256), 0, s, P, io.g, io.g_slot);
-        return;
-    }
-    if (P.nu <= 1) {   // no ring of earlier values needed
-        auto k = P.nu == 0 ? k_rows_local<0> : k_rows_local<1>;
-        hipLaunchKernelGGL(k, dim3(cdiv64(P.m, 256)), dim3(256), 0, s, P, io.g, io.g_slot);
-        return;
-    }
-    const int bs = rows_local_block(P.nu);
-    hipLaunchKernelGGL(k_rows_local<2>, dim3(cdiv64(P.m, bs)), dim3(bs), rows_local_lds(P.nu, bs), s, P, io.g,
-                       io.g_slot);
+    const int mode = local_mode(P);
+    auto k = mode == 0 ? k_local_nodes<0> : mode == 1 ? k_local_nodes<1> : mode == 2 ? k_local_nodes<2> : k_local_nodes<3>;
+    hipLaunchKernelGGL(k, dim3(P.n_lwork), dim3(64), local_nodes_lds(P), s, P);
 }
 
 // Calls f with std::integral_constant<int, nch>; nch is one of the instantiated
@@ -2616,6 +2665,9 @@ static void launch_fft_large(const PlanDev& P, const FftClass& K, hipStream_t s)
     }
 }
 
+// Transforms of at most this many points and frequencies run on one stream.
+constexpr int64_t kForkMin = 1 << 14;
+
 hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers& B, const FftClass* cls, int ncls,
                           const IoArgs& io, hipStream_t s, hipEvent_t* marks, const ExecFork* fork)
 {
@@ -2628,8 +2680,11 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
     hipLaunchKernelGGL(k_gather, dim3(cdiv64(P.n, 256)), dim3(256), 0, s, P, io.c, io.c_slot,
                        io.scale_by_points ? 1 : 0);
     mark(marks, 1, s);
-    // the local moments and direct blocks read only the gathered weights
-    const bool forked = fork && fork->side && (S.n_litems > 0 || P.n_d > 0);
+    // the local moments and direct blocks read only the gathered weights; a
+    // small transform's kernels are shorter than the fork's events and waits
+    // take the host (a pass at 500 x 500: 56 us on one stream, 77 forked; plan
+    // and pass at 2000 x 2000: 173 and 220)
+    const bool forked = fork && fork->side && (S.n_litems > 0 || P.n_d > 0) && (int64_t)P.n + P.m > kForkMin;
     const hipStream_t ls = forked ? fork->side : s;
     if (forked) {
         hipError_t e = hipEventRecord(fork->ev_fork, s);
@@ -2639,7 +2694,9 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
     if (S.n_litems > 0) {
         if (lmom_width(P.L) == 32) hipLaunchKernelGGL(k_lmom<32>, dim3(S.n_litems), dim3(64), 0, ls, P);
         else hipLaunchKernelGGL(k_lmom<64>, dim3(S.n_litems), dim3(64), 0, ls, P);
-        hipLaunchKernelGGL(k_lmom_reduce, dim3(cdiv64((int64_t)S.n_l * (P.L + 1), 256)), dim3(256), 0, ls, P);
+        if (S.n_litems > S.n_l)   // some block has several items
+            hipLaunchKernelGGL(k_lmom_reduce, dim3(cdiv64((int64_t)S.n_l * (P.L + 1), 256)), dim3(256), 0, ls, P);
+        launch_local_nodes(P, ls);
     }
     auto launch_direct = [&](hipStream_t st) {
         if (P.n_d > 0) {
@@ -2676,13 +2733,14 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
     mark(marks, 5, s);
     if (!forked) launch_direct(s);
     mark(marks, 6, s);
-    dispatch_channels(P.nch, [&](auto k) { launch_rows_asy<decltype(k)::value>(P, s); });
-    mark(marks, 7, s);
     if (forked) {
         const hipError_t e = hipStreamWaitEvent(s, fork->ev_join, 0);
         if (e != hipSuccess) return e;
     }
-    launch_rows_local(P, io, s);
+    dispatch_channels(P.nch, [&](auto k) {
+        hipLaunchKernelGGL(k_rows<decltype(k)::value>, dim3(cdiv64(P.m, 256)), dim3(256), 0, s, P, io.g, io.g_slot);
+    });
+    mark(marks, 7, s);
     mark(marks, 8, s);
     return hipGetLastError();
 }
@@ -2710,8 +2768,8 @@ void small_fft_table(PlanDev& P, const FftClass* cls, int ncls)
 // its channel count (spreading, grid rows) or local-row mode.
 // ---------------------------------------------------------------------------
 enum BatchKind : int32_t {
-    kZeroOut, kGather, kLmom, kLmomReduce, kRankMoments, kRankWeights, kRankTranslate, kSpreadMfma, kSpreadMfmaMed, kSpreadVec, kSpreadReduce, kFftSmall,
-    kFftPass0, kFftPass1, kFftPass2, kDirect, kRowsAsy, kRowsLocal
+    kZeroOut, kGather, kLmom, kLmomReduce, kLocalNodes, kRankMoments, kRankWeights, kRankTranslate, kSpreadMfma, kSpreadMfmaMed, kSpreadVec, kSpreadReduce, kFftSmall,
+    kFftPass0, kFftPass1, kFftPass2, kDirect, kRows
 };
 
 void build_batch_schedule(const BatchTransform* tr, int count, const int* order, BatchSchedule& out)
@@ -2751,8 +2809,14 @@ void build_batch_schedule(const BatchTransform* tr, int count, const int* order,
             return live(*T.P) && lmom_width(T.P->L) == width ? T.S->n_litems : 0;
         });
     add(kLmomReduce, 0, 0, 256, [&](const BatchTransform& T, size_t&) -> int64_t {
-        return live(*T.P) && T.S->n_litems > 0 ? cdiv64((int64_t)T.S->n_l * (T.P->L + 1), 256) : 0;
+        return live(*T.P) && T.S->n_litems > T.S->n_l ? cdiv64((int64_t)T.S->n_l * (T.P->L + 1), 256) : 0;
     });
+    for (int mode = 0; mode < 4; ++mode)
+        add(kLocalNodes, mode, 0, 64, [&](const BatchTransform& T, size_t& lds) -> int64_t {
+            if (!live(*T.P) || local_mode(*T.P) != mode) return 0;
+            lds = local_nodes_lds(*T.P);
+            return T.S->n_lwork;
+        });
     add(kRankMoments, 0, 0, 64 * kRankWaves, [&](const BatchTransform& T, size_t&) -> int64_t {
         return live(*T.P) ? rank_moments_blocks(*T.S) : 0;
     });
@@ -2830,22 +2894,9 @@ void build_batch_schedule(const BatchTransform* tr, int count, const int* order,
     for (const auto& v : variants)
         if (std::find(chans.begin(), chans.end(), v.first) == chans.end()) chans.push_back(v.first);
     for (int nch : chans)
-        add(kRowsAsy, nch, 0, 256, [&](const BatchTransform& T, size_t&) -> int64_t {
+        add(kRows, nch, 0, 256, [&](const BatchTransform& T, size_t&) -> int64_t {
             return live(*T.P) && T.P->nch == nch ? cdiv64(T.P->m, 256) : 0;
         });
-    // local rows: orders 0 and 1, the general mode at 256 and at 64 lanes,
-    // half-integer orders
-    for (int mode = 0; mode < 5; ++mode) {
-        const int bs = mode == 3 ? 64 : 256;
-        const int variant = mode < 2 ? mode : (mode == 4 ? 3 : 2);
-        add(kRowsLocal, variant, 0, bs, [&](const BatchTransform& T, size_t& lds) -> int64_t {
-            const int nu = T.P->nu;
-            if (!live(*T.P) || (T.P->half != 0) != (mode == 4)) return 0;
-            if (mode < 2 ? nu != mode : (mode < 4 && (nu <= 1 || rows_local_block(nu) != bs))) return 0;
-            lds = mode == 4 ? 0 : rows_local_lds(nu, bs);
-            return cdiv64(T.P->m, bs);
-        });
-    }
     // the device tables: PlanDev[count], WorkSeg[], FftSeg[] (each 256-byte aligned)
     auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
     out.segs_off = align(sizeof(PlanDev) * (size_t)count);
@@ -2877,7 +2928,7 @@ hipError_t launch_execute_many(const BatchSchedule& S, const void* table_dev, vo
     };
     for (const BatchLaunch& L : S.launches) {
         const dim3 grid(L.blocks), block(L.threads);
-        const bool side_kind = L.kind == kLmom || L.kind == kLmomReduce || L.kind == kDirect;
+        const bool side_kind = L.kind == kLmom || L.kind == kLmomReduce || L.kind == kLocalNodes || L.kind == kDirect;
         hipStream_t st = s;
         if (fork && side_kind && !joined) {
             if (!forked) {
@@ -2888,7 +2939,7 @@ hipError_t launch_execute_many(const BatchSchedule& S, const void* table_dev, vo
             }
             st = fork->side;
         }
-        if (forked && !joined && L.kind == kRowsLocal) {
+        if (forked && !joined && L.kind == kRows) {
             const hipError_t e = join();
             if (e != hipSuccess) return e;
         }
@@ -2902,6 +2953,12 @@ hipError_t launch_execute_many(const BatchSchedule& S, const void* table_dev, vo
             else hipLaunchKernelGGL(k_lmom_many<64>, grid, block, 0, st, plans, sg, L.nseg);
             break;
         case kLmomReduce: hipLaunchKernelGGL(k_lmom_reduce_many, grid, block, 0, st, plans, sg, L.nseg); break;
+        case kLocalNodes:
+            if (L.variant == 0) hipLaunchKernelGGL(k_local_nodes_many<0>, grid, block, L.lds, st, plans, sg, L.nseg);
+            else if (L.variant == 1) hipLaunchKernelGGL(k_local_nodes_many<1>, grid, block, L.lds, st, plans, sg, L.nseg);
+            else if (L.variant == 2) hipLaunchKernelGGL(k_local_nodes_many<2>, grid, block, L.lds, st, plans, sg, L.nseg);
+            else hipLaunchKernelGGL(k_local_nodes_many<3>, grid, block, L.lds, st, plans, sg, L.nseg);
+            break;
         case kRankMoments:
             hipLaunchKernelGGL(k_rank_moments_many, grid, block, 0, s, plans, sg, L.nseg);
             break;
@@ -2939,18 +2996,10 @@ hipError_t launch_execute_many(const BatchSchedule& S, const void* table_dev, vo
         case kFftPass1: hipLaunchKernelGGL(k_fft_col_many, grid, block, L.lds, s, plans, fs, L.nseg); break;
         case kFftPass2: hipLaunchKernelGGL(k_fft_row_many, grid, block, L.lds, s, plans, fs, L.nseg); break;
         case kDirect: hipLaunchKernelGGL(k_direct_blocks_many, grid, block, 0, st, plans, sg, L.nseg); break;
-        case kRowsAsy:
+        case kRows:
             dispatch_channels(L.variant, [&](auto k) {
-                hipLaunchKernelGGL((k_rows_asy_many<decltype(k)::value>), grid, block, 0, s, plans, sg, L.nseg);
+                hipLaunchKernelGGL((k_rows_many<decltype(k)::value>), grid, block, 0, s, plans, sg, L.nseg, gout);
             });
-            break;
-        case kRowsLocal:
-            if (L.variant == 0) hipLaunchKernelGGL(k_rows_local_many<0>, grid, block, L.lds, s, plans, sg, L.nseg, gout);
-            else if (L.variant == 1)
-                hipLaunchKernelGGL(k_rows_local_many<1>, grid, block, L.lds, s, plans, sg, L.nseg, gout);
-            else if (L.variant == 3)
-                hipLaunchKernelGGL(k_rows_local_many<3>, grid, block, L.lds, s, plans, sg, L.nseg, gout);
-            else hipLaunchKernelGGL(k_rows_local_many<2>, grid, block, L.lds, s, plans, sg, L.nseg, gout);
             break;
         default: return hipErrorInvalidValue;
         }

@@ -766,15 +766,17 @@ static const double* rank_tables_device()
 }
 
 // The largest xi = (half r range) x (half omega range) whose exponential
-// e^{i xi x y} kRankK Chebyshev terms give to exp(ltol) (the bound of
-// rank_terms with constant Hankel terms).
-static double rank_largest_xi(double ltol)
+// e^{i xi x y} `terms` Chebyshev terms give to exp(ltol) (the bound of
+// rank_terms with constant Hankel terms).  The same bound holds for a local
+// block's rows: in omega they are sums of J_nu(omega r), r <= R, entire and at
+// most e^{R |Im omega|}.
+static double rank_largest_xi(double ltol, int terms = kRankK)
 {
     auto fits = [&](double xi) {
         for (int l = 0; l < 16; ++l) {
             const double lr = kRankLr0 + kRankLrStep * l, rho = std::exp(lr);
             const double k = (std::log(4.0) + 0.5 * xi * (rho - 1.0 / rho) - std::log(rho - 1.0) - ltol) / lr + 1.0;
-            if (k <= (double)kRankK) return true;
+            if (k <= (double)terms) return true;
         }
         return false;
     };
@@ -1185,6 +1187,13 @@ static int fill_params(PlanDev& P, int nu2, double eps_req, const nuht_opts& o)
         if (P.chan[p] != 0.0) P.rank_const = 0;
     P.rank_ltol = std::log(std::max(0.001 * eps, 2e-16));
     P.rank_xi = P.rank ? rank_largest_xi(P.rank_ltol) : 1.0;
+    // local rows: far below the tolerance, so that the expansions add nothing
+    // to the error of the L + 1 terms they go through (x the amplitude
+    // sqrt(2z/pi) that half-integer orders keep outside)
+    {
+        const double lt = std::log(std::max(1e-5 * eps, 2e-16));
+        for (int i = 0; i < kRankK / 4; ++i) P.local_xi[i] = rank_largest_xi(lt, 4 * (i + 1));
+    }
     phase_offset2(half ? nu2 + 1 : 2 * anu + 1, P.phi_hi, P.phi_lo);
     P.kappa_max = P.w * M_PI / 4.0 * (1.0 + 1e-9);
     P.eshat_s = 2.0 / (P.kappa_max * P.kappa_max);
@@ -1279,6 +1288,7 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
     A.node_cap = pp.cap; A.l_cap = pp.cap; A.a_cap = pp.cap; A.d_cap = 2 * pp.cap; A.q_cap = pp.cap;
     A.litem_cap = pp.icap; A.aitem_cap = pp.icap;
     A.pan_cap = P.rank ? 2 * pp.cap : 0;
+    A.lslot_cap = 2 * pp.cap;
     int32_t *K = nullptr, *Jc = nullptr, *a_cells = nullptr;
     Slab slab;
     slab.add(K, (size_t)G.m);
@@ -1295,6 +1305,7 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
     slab.add(A.alist, (size_t)A.aitem_cap);
     slab.add(A.fft_list, (size_t)A.a_cap);
     slab.add(A.gslot, (size_t)A.a_cap + 1);
+    slab.add(A.lwork, (size_t)A.lslot_cap);
     slab.add(A.cpans, (size_t)A.pan_cap);
     slab.add(A.tlist, (size_t)A.pan_cap);
     slab.add(A.wlist, (size_t)A.pan_cap);
@@ -1303,6 +1314,7 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
     P.nodes = A.nodes; P.lb = A.lb; P.ab = A.ab; P.db = A.db;
     P.litems = A.litems; P.aitems = A.aitems; P.alist = A.alist; P.fft_list = A.fft_list; P.gslot = A.gslot;
     P.cpans = A.cpans; P.rlist = A.rlist; P.tlist = A.tlist; P.wlist = A.wlist;
+    P.lwork = A.lwork;
     P.tlist_cap = A.pan_cap; P.rlist_cap = A.aitem_cap;
     a.P = P; a.A = A; a.K = K; a.Jc = Jc; a.a_cells = a_cells;
     a.min_size = min_size; a.ncand = ncand; a.dft_max = dft_max; a.sigma = sigma;
@@ -1350,7 +1362,7 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     if (S.overflow) {
         if (++pp.attempt >= 6) return NUHT_ECAPACITY;
         int64_t need = std::max<int64_t>({(int64_t)S.n_nodes, (int64_t)S.n_l, (int64_t)S.n_a, (int64_t)S.n_d / 2,
-                                          (int64_t)S.n_cpan / 2, (int64_t)S.n_rpan / 2});
+                                          (int64_t)S.n_cpan / 2, (int64_t)S.n_rpan / 2, (int64_t)S.n_lslots / 2});
         if (need >= pp.cap) pp.cap = (int32_t)std::min<int64_t>(2 * need + 1024, 1 << 29);
         int64_t ineed = std::max<int64_t>((int64_t)S.n_litems, (int64_t)S.n_aitems);
         if (ineed >= pp.icap) pp.icap = (int32_t)std::min<int64_t>(2 * ineed + 1024, 1 << 29);
@@ -1368,6 +1380,7 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     P.n_litems = S.n_litems; P.n_aitems = S.n_aitems; P.n_adense = S.n_adense; P.n_amed = S.n_amed;
     P.n_tsingle = S.n_tsingle; P.n_tmulti = S.n_tmulti; P.n_wmulti = S.n_wmulti;
     P.n_ritems = S.n_ritems; P.n_rsmall = S.n_rsmall;
+    P.n_lwork = S.n_lwork;
 
     // execution buffers
     ExecBuffers& B = Pt.B;
@@ -1375,10 +1388,10 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     slab.add(B.cs, (size_t)G.n);
     slab.add(B.lpart, (size_t)S.n_litems * (P.L + 1));
     slab.add(B.lmom, (size_t)S.n_l * (P.L + 1));
+    slab.add(B.lcoef, (size_t)S.n_lslots * kRankK);
     slab.add(B.part, (size_t)S.part_cells * P.nch);
     slab.add(B.grids, (size_t)S.grid_cells * P.nch);
     slab.add(B.gd, (size_t)G.m);
-    slab.add(B.ga, (size_t)G.m);
     if (S.n_cpan > 0) {
         slab.add(B.rmom, (size_t)kRankK * ((size_t)S.n_aitems + S.n_cpan));
         slab.add(B.rwts, (size_t)kRankK * S.n_cpan);
@@ -1400,14 +1413,12 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     if (!B.es_poly) return NUHT_ENOMEM;
     B.fft_tw = fft_twiddles_device();
     if (!B.fft_tw) return NUHT_ENOMEM;
-    if (P.rank) {
-        P.rank_tab = rank_tables_device();
-        if (!P.rank_tab) return NUHT_ENOMEM;
-    }
+    P.rank_tab = rank_tables_device();
+    if (!P.rank_tab) return NUHT_ENOMEM;
     P.es_poly = B.es_poly;
     P.rmom = B.rmom; P.rwts = B.rwts; P.rcoef = B.rcoef;
-    P.cs = B.cs; P.lpart = B.lpart; P.lmom = B.lmom; P.part = B.part; P.grids = B.grids;
-    P.scratch = B.scratch; P.gd = B.gd; P.ga = B.ga; P.fft_tw = B.fft_tw;
+    P.cs = B.cs; P.lpart = B.lpart; P.lmom = B.lmom; P.lcoef = B.lcoef; P.part = B.part; P.grids = B.grids;
+    P.scratch = B.scratch; P.gd = B.gd; P.fft_tw = B.fft_tw;
     P.grid_cells = B.grid_cells;
     small_fft_table(P, Pt.cls.data(), (int)Pt.cls.size());
     Pt.built = true;

@@ -84,7 +84,21 @@ struct LBlock {
     int32_t j0, j1, k0, k1;
     double R;             // expansion radius: r_{k1}, or z / omega_{j1} when r_{k1} = 0
     int32_t item0, nitems;
-    int32_t level, pad;
+    int32_t level;
+    // its rows: a Chebyshev expansion of K terms on each of pr panels of
+    // frequencies (middles about D, half-width rw), or (K = 0) one value per
+    // row; both from slot slot0 on, kRankK values a slot
+    int32_t K, pr, slot0;
+    double D, rw;
+};
+
+// Slots of a local block's rows, and those evaluated by one wave.
+__host__ __device__ inline int32_t local_slots(const LBlock& B) { return B.K > 0 ? B.pr : (B.j1 - B.j0 + kRankK) / kRankK; }
+__host__ __device__ inline int32_t local_wave_slots(int32_t K) { return K > 0 ? 64 / K : 64 / kRankK; }
+
+// A wave's slots q .. of local block blk.
+struct LocalWork {
+    int32_t blk, q;
 };
 
 struct ABlock {
@@ -156,6 +170,7 @@ struct Summary {
     int32_t n_cpan, n_rpan;    // panels of the rank blocks
     int32_t n_tsingle, n_tmulti;   // their panels of frequencies: of blocks translated by one wave, of others
     int32_t n_wmulti;              // panels of points of those others
+    int32_t n_lslots, n_lwork;     // slots of the local blocks' rows; waves that fill them
     int64_t l_row, l_col, a_row, a_col, d_ent;
     int64_t grid_cells;     // sum N1 (all asymptotic blocks)
     int64_t dft_cells;      // sum N1 over direct-sum-path blocks
@@ -189,6 +204,7 @@ struct PlanDev {
     int32_t nch, sign;               // channels (2M padded to a kernel instance); (-1)^nu for negative orders, else 1
     int32_t fp32;                    // FP32 spreading (weights, kernel values and channel sums in float)
     int32_t rank, rank_const;        // plan has rank blocks; the Hankel terms beyond the first vanish
+    double local_xi[kRankK / 4];     // largest (half omega range) x R that 4, 8, .. terms of a local panel cover
     double rank_ltol, rank_xi;       // log of the expansions' tolerance; largest (half r range) x (half
                                      // omega range) that kRankK terms cover
     const double* rank_tab;          // cosine tables (rank_tab_off)
@@ -221,7 +237,8 @@ struct PlanDev {
     double jtab_x0;
     int32_t jtab_np, pad2;
     int32_t n_nodes, n_l, n_a, n_d, n_litems, n_aitems, n_adense, n_amed;
-    int32_t n_tsingle, n_tmulti, n_wmulti, n_ritems, n_rsmall, rpad;
+    int32_t n_tsingle, n_tmulti, n_wmulti, n_ritems, n_rsmall, n_lwork;
+    const LocalWork* lwork;          // the local blocks' rows by waves
     const Panel* cpans;              // panels of the rank blocks' points
     const RankItem* rlist;           // items of rank blocks: large ones from the front, small ones from the back
     const Panel* tlist;              // panels of frequencies: blocks of one wave from the front, others from the back
@@ -231,6 +248,7 @@ struct PlanDev {
     double* cs;                      // weights gathered into sorted point order (n)
     double* lpart;                   // local-moment partial sums (items x (L + 1))
     double* lmom;                    // local moments (local blocks x (L + 1))
+    double* lcoef;                   // expansions or values of the local blocks' rows, by slot
     double2* rmom;                   // rank blocks: moments of (item i, panel q) at (i + q) kRankK
     double2* rwts;                   // their nodal weights per panel of points
     double2* rcoef;                  // their expansion coefficients per panel of frequencies
@@ -238,7 +256,6 @@ struct PlanDev {
     double2* grids;                  // spread grids (direct-sum path) and FFT buffers (FFT path)
     double2* scratch;                // second buffer of the multi-pass FFTs
     double* gd;                      // per-row direct-block sums (m)
-    double* ga;                      // per-row asymptotic sums (m)
     const double2* fft_tw;           // FFT twiddles (8192 entries)
     int64_t grid_cells;              // grid slots (without the channel factor)
     SmallFfts small;                 // the FFT size classes up to 4096 points

@@ -30,7 +30,8 @@ struct Arena {
     RankItem* rlist;     // items of rank blocks (aitem_cap)
     Panel* tlist;        // panels of frequencies to translate (pan_cap)
     Panel* wlist;        // panels of points weighted on their own (pan_cap)
-    int32_t pan_cap;
+    LocalWork* lwork;    // the local blocks' rows by waves (lslot_cap)
+    int32_t pan_cap, lslot_cap;
     int32_t node_cap, l_cap, a_cap, d_cap, q_cap, litem_cap, aitem_cap, pad;
 };
 
@@ -77,6 +78,7 @@ struct ExecBuffers {
     double* cs;         // gathered weights (sorted point order)
     double* lpart;      // local-moment partial sums, n_litems x (L+1)
     double* lmom;       // local moments, n_l x (L+1)
+    double* lcoef;      // the local blocks' rows, n_lslots x kRankK
     double2* rmom;      // moments of the rank blocks' (item, panel) pairs
     double2* rwts;      // nodal weights of their panels of points
     double2* rcoef;     // expansion coefficients of their panels of frequencies
@@ -84,7 +86,6 @@ struct ExecBuffers {
     double2* grids;     // spread grids (direct-sum path) and FFT buffers (FFT path)
     double2* scratch;   // second buffer of the two-pass FFTs
     double* gd;         // per-row direct-block sums (m)
-    double* ga;         // per-row asymptotic sums (m)
     const double* es_poly;  // ES kernel pieces (w x (kEsDeg + 1)), shared by all plans on the device
     const double2* fft_tw;  // FFT twiddles (8192 entries), shared by all plans on the device
     int64_t grid_cells; // grid slots (without the channel factor)
@@ -97,7 +98,7 @@ struct FftClass {
 
 // Execution stages, timed between consecutive events of `marks` (kStages + 1
 // events, or null; a null entry records nothing).
-constexpr int kStages = 8;   // gather, local moments, spread, grid assembly, FFT, direct, asymptotic rows, local rows
+constexpr int kStages = 8;   // gather, local moments and row expansions, spread, grid assembly, FFT, direct, rows, (none)
 // Input and output of one transform.  When the slots are set, the kernels
 // read the input and output pointers from those device locations at run time
 // (so a captured graph serves any buffers); otherwise c and g are used.  With

@@ -1419,7 +1419,8 @@ __device__ __forceinline__ void subdivide(const PlanArgs& a)
                     if (l_slot < A.l_cap) {
                         LBlock b;
                         b.j0 = Rq.j0; b.j1 = o.js; b.k0 = Rq.k0; b.k1 = o.ks;
-                        b.R = 0.0; b.item0 = 0; b.nitems = 0; b.level = level; b.pad = 0;
+                        b.R = 0.0; b.item0 = 0; b.nitems = 0; b.level = level;
+                        b.K = 0; b.pr = 0; b.slot0 = 0; b.D = 0.0; b.rw = 0.0;
                         A.lb[l_slot] = b;
                     }
                     ++l_slot;
@@ -1595,6 +1596,21 @@ __device__ __forceinline__ void block_params(const PlanArgs& a)
         L.R = R;
         int32_t ncol = L.k1 - L.k0 + 1;
         L.nitems = (ncol + kLocalChunk - 1) / kLocalChunk;
+        // rows: panels of as many terms as their share of xi = S R needs,
+        // unless they have more nodes than the block has rows
+        const double wlo = P.ws[L.j0], whi = P.ws[L.j1];
+        const double D = 0.5 * (wlo + whi), S = fmax(whi - D, D - wlo), xi = S * R;
+        const double pr = ceil(xi / P.local_xi[kRankK / 4 - 1]);
+        L.D = D;
+        L.K = 0; L.pr = 0; L.rw = 0.0;
+        if (pr < 1e6 && (S == 0.0 || S > 1e-290)) {
+            L.pr = pr < 1.0 ? 1 : (int32_t)pr;
+            int i = 0;
+            while (i < kRankK / 4 - 1 && xi / L.pr > P.local_xi[i]) ++i;
+            L.K = 4 * (i + 1);
+            L.rw = rank_half_width(S, L.pr);
+            if ((int64_t)L.K * L.pr > L.j1 - L.j0 + 1) L.K = 0;
+        }
         A.lb[b] = L;
     }
 }
@@ -1631,7 +1647,7 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
     constexpr int kStats = 9;
     long long st[kStats] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     constexpr int kVpt = 8;                          // blocks per thread per pass (2048 per pass)
-    int64_t l_items = 0;
+    int64_t l_items = 0;                             // items + 2^32 slots
     for (int32_t c0 = 0; c0 < n_l; c0 += kPlanScanThreads * kVpt) {
         const int32_t i0 = c0 + tid * kVpt;
         int64_t v[kVpt][1];
@@ -1640,7 +1656,7 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
             v[k][0] = 0;
             if (i0 + k < n_l) {
                 const LBlock L = A.lb[i0 + k];
-                v[k][0] = L.nitems;
+                v[k][0] = L.nitems + ((int64_t)local_slots(L) << 32);
                 st[0] += L.j1 - L.j0 + 1;
                 st[1] += L.k1 - L.k0 + 1;
             }
@@ -1649,9 +1665,15 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
         block_scan_vpt<1, kVpt, kPlanScanThreads / 64>(v, tot, wsum);
         #pragma unroll
         for (int k = 0; k < kVpt; ++k)
-            if (i0 + k < n_l) A.lb[i0 + k].item0 = (int32_t)(l_items + v[k][0]);
+            if (i0 + k < n_l) {
+                const int64_t x = l_items + v[k][0];
+                A.lb[i0 + k].item0 = (int32_t)(x & 0xffffffff);
+                A.lb[i0 + k].slot0 = (int32_t)(x >> 32);
+            }
         l_items += tot[0];
     }
+    const int32_t n_lslots = (int32_t)(l_items >> 32);
+    l_items &= 0xffffffff;
     int64_t a_items = 0, grid = 0;
     int64_t pans = 0;                                // panels of points + 2^32 panels of frequencies
     for (int32_t c0 = 0; c0 < n_a; c0 += kPlanScanThreads * kVpt) {
@@ -1742,14 +1764,16 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
         sum->max_nch = nch;
         sum->grid_cells = grid;
         const int32_t n_cp = (int32_t)(pans & 0xffffffff), n_rp = (int32_t)(pans >> 32);
-        sum->n_cpan = n_cp; sum->n_rpan = n_rp;
-        if (l_items > A.litem_cap || a_items > A.aitem_cap || n_cp > A.pan_cap || n_rp > A.pan_cap) sum->overflow = 1;
+        sum->n_cpan = n_cp; sum->n_rpan = n_rp; sum->n_lslots = n_lslots;
+        if (l_items > A.litem_cap || a_items > A.aitem_cap || n_cp > A.pan_cap || n_rp > A.pan_cap ||
+            n_lslots > A.lslot_cap)
+            sum->overflow = 1;
     }
 }
 
 // ---------------------------------------------------------------------------
-// Work items (grid-stride over all items: local, asymptotic, then the rank
-// blocks' panels of points and of frequencies).
+// Work items (grid-stride over all items: local, asymptotic, the rank blocks'
+// panels of points and of frequencies, the slots of the local blocks' rows).
 // An item is a chunk of one block's columns; a spread item also carries the
 // subgrid of cells its points can reach (one cell of margin each side), an
 // item of a rank block the panels its points lie in.
@@ -1839,16 +1863,19 @@ __device__ __forceinline__ void items(const PlanArgs& a)
     int32_t* __restrict__ a_cells = a.a_cells;
     if (sum->overflow) return;
     const int32_t n_l = sum->n_l, n_a = sum->n_a;
-    const int32_t n_li = sum->n_litems, n_ai = sum->n_aitems, n_cp = sum->n_cpan, n_rp = sum->n_rpan;
+    const int32_t n_li = sum->n_litems, n_ai = sum->n_aitems, n_cp = sum->n_cpan, n_rp = sum->n_rpan, n_ls = sum->n_lslots;
     const int w = P.w;
-    // the four kinds of work, each rounded up to whole waves
+    // the five kinds of work, each rounded up to whole waves
     const int32_t w_li = (n_li + 63) & ~63, w_ai = (n_ai + 63) & ~63, w_cp = (n_cp + 63) & ~63, w_rp = (n_rp + 63) & ~63;
-    const int32_t total = w_li + w_ai + w_cp + w_rp;
+    const int32_t w_ls = (n_ls + 63) & ~63;
+    const int32_t total = w_li + w_ai + w_cp + w_rp + w_ls;
     for (int32_t j0 = blockIdx.x * blockDim.x + (threadIdx.x & ~63); j0 < total; j0 += gridDim.x * blockDim.x) {
         const int lane = threadIdx.x & 63;
         bool ritem = false;                           // an item of a rank block
         bool tone = false, tmany = false;             // a panel of frequencies of a block of one wave / of another
         bool wmany = false;                           // a panel of points of another
+        bool lwork = false;                           // the first slot of a wave of local rows
+        LocalWork W{};
         RankItem R{};
         Panel T{};
         if (j0 < w_li) {
@@ -1912,6 +1939,14 @@ __device__ __forceinline__ void items(const PlanArgs& a)
                 A.cpans[ip] = T;
                 wmany = !rank_one_wave(B);
             }
+        } else if (j0 >= w_li + w_ai + w_cp + w_rp) {
+            const int32_t i0 = j0 - w_li - w_ai - w_cp - w_rp, is = i0 + lane;
+            const int32_t lo = block_of(n_l, i0, [&](int32_t b) { return A.lb[b].slot0; });
+            if (is < n_ls) {
+                W.blk = lo;
+                W.q = is - A.lb[lo].slot0;
+                lwork = W.q % local_wave_slots(A.lb[lo].K) == 0;
+            }
         } else {
             const int32_t i0 = j0 - w_li - w_ai - w_cp, ip = i0 + lane;
             const int32_t lo = block_of(n_a, i0, [&](int32_t b) { return A.ab[b].rpan0; });
@@ -1927,6 +1962,8 @@ __device__ __forceinline__ void items(const PlanArgs& a)
         if (ritem) A.rlist[small ? A.aitem_cap - 1 - p4 : p0] = R;
         const int32_t p3 = wave_append(wmany, &sum->n_wmulti);
         if (wmany) A.wlist[p3] = T;
+        const int32_t p5 = wave_append(lwork, &sum->n_lwork);
+        if (lwork) A.lwork[p5] = W;
         const int32_t p1 = wave_append(tone, &sum->n_tsingle);
         if (tone) A.tlist[p1] = T;
         const int32_t p2 = wave_append(tmany, &sum->n_tmulti);
