@@ -2259,8 +2259,8 @@ __device__ __forceinline__ void besselj_table2(const PlanDev& P, Tab tab, double
 // subdivision tree), so the per-row sums are stored, not accumulated; rows in
 // none are never read, and gd needs no clearing.
 constexpr int kDirectThreads = 256;
-// Tables of up to kJtabLdsPanels panels (z up to about 240 with the
-// default range) are copied into LDS by each workgroup and read from there:
+// The panels that a block's arguments lie on, where they are at most
+// kJtabLdsPanels, are copied into LDS by its workgroup and read from there:
 // shorter latency than the cache hierarchy for the eight 16-byte loads per
 // entry.  A panel takes kJtabLdsStride double2 (one more than its
 // coefficients), so that lanes on neighbouring panels read different banks.
@@ -2309,22 +2309,131 @@ __device__ __forceinline__ void direct_rows(const PlanDev& P, const DBlock& D, c
     }
 }
 
+// A direct block through expansions, a wave: with x = omega r its kernel
+// J_nu(x) (x^{-1/2} J_nu(x) at half-integer orders, the square roots going to
+// the weights and the rows) is entire in r and in omega, and the blocks lie so
+// close to the curve omega r = z that a few terms give it to full precision.
+// Moments of the weights, nodal weights, the kernel at K x K node pairs (to
+// full precision, as an entry), coefficients of the rows' series.
+template <int KC>
+__device__ __forceinline__ void direct_expand(const PlanDev& P, int d, double* s)
+{
+    const DBlock& B = P.db[d];
+    const int lane = threadIdx.x & 63, K = B.K;
+    const double inv = B.cw > 0.0 ? rcp_refined(B.cw) : 0.0;
+    double acc[KC];
+    #pragma unroll
+    for (int m = 0; m < KC; ++m) acc[m] = 0.0;
+    const int kb = B.k1 + 1;
+    double r_nx = B.C, c_nx = 0.0;
+    if (B.k0 + lane < kb) { r_nx = P.rs[B.k0 + lane]; c_nx = P.cs[B.k0 + lane]; }
+    for (int k0 = B.k0; k0 < kb; k0 += 64) {
+        const double r = r_nx;
+        double c = c_nx;
+        const int k = k0 + 64 + lane;
+        r_nx = B.C; c_nx = 0.0;
+        if (k < kb) { r_nx = P.rs[k]; c_nx = P.cs[k]; }
+        if (P.half) c *= sqrt(r);
+        const dd b = two_sum(r, -B.C);
+        const double y = (b.hi + b.lo) * inv, y2 = y + y;
+        double t0 = 1.0, t1 = y;
+        #pragma unroll
+        for (int m = 0; m < KC; ++m) {
+            acc[m] = __builtin_fma(c, t0, acc[m]);
+            const double t2 = __builtin_fma(y2, t1, -t0);
+            t0 = t1;
+            t1 = t2;
+        }
+    }
+    const double tm = wave_sums<KC>(acc, s, lane);
+    const double* __restrict__ tab = P.rank_tab + rank_tab_off(K);
+    double w = 0.0;
+    {
+        const int q = lane < K ? lane : K - 1;
+        for (int m0 = 0; m0 < K; m0 += 4) {
+            double c[4];
+            #pragma unroll
+            for (int i = 0; i < 4; ++i) c[i] = tab[(m0 + i) * K + q];
+            #pragma unroll
+            for (int i = 0; i < 4; ++i) w = __builtin_fma(read_lane(tm, m0 + i), c[i], w);
+        }
+        w = (w + w - read_lane(tm, 0)) / K;
+    }
+    const int logt = K <= 8 ? 3 : K <= 16 ? 4 : 5, groups = 64 >> logt;
+    const int t = lane & ((1 << logt) - 1), g = lane >> logt;
+    const dd om = two_sum(B.D, B.rw * tab[K + (t < K ? t : K - 1)]);
+    double u = 0.0;
+    for (int s0 = 0; s0 < K; s0 += groups) {
+        const int q = s0 + g < K ? s0 + g : K - 1;
+        const double wq = __shfl(w, q);
+        const dd r = two_sum(B.C, B.cw * tab[K + q]);
+        const dd x = two_prod(om.hi, r.hi);
+        const double xl = __builtin_fma(om.hi, r.lo, __builtin_fma(om.lo, r.hi, x.lo));
+        double v = 0.0;
+        if (x.hi > 0.0) {
+            v = besselj_direct(P, x.hi, xl);
+            if (P.half) v *= rsqrt_refined(x.hi);
+        } else if (P.nu == 0 && !P.half) {
+            v = 1.0;
+        }
+        u = __builtin_fma(s0 + g < K ? wq : 0.0, v, u);
+    }
+    for (int o = 32; o >= (1 << logt); o >>= 1) u += __shfl_xor(u, o);
+    const int m = lane < K ? lane : K - 1;
+    const double* __restrict__ col = tab + K * K + m;
+    double v = 0.0;
+    for (int h0 = 0; h0 < K; h0 += 4) {
+        double c[4];
+        #pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] = col[(h0 + i) * K];
+        #pragma unroll
+        for (int i = 0; i < 4; ++i) v = __builtin_fma(read_lane(u, h0 + i), c[i], v);
+    }
+    if (lane < K) P.dcoef[(int64_t)d * kRankK + lane] = v * ((m == 0 ? 1.0 : 2.0) / K);
+}
+
+// Workgroups 0 .. n_dentry - 1: a block entry by entry each; then four blocks
+// through expansions each, one per wave.
 __device__ __forceinline__ void direct_body(const PlanDev& P, int bid)
 {
+    constexpr int kWaveSums = kRankK / 4 * 64;
     __shared__ double2 s_tab[kJtabLdsPanels * kJtabLdsStride];
-    const DBlock D = P.db[bid];
-    if (P.jtab_np > 0 && P.jtab_np <= kJtabLdsPanels) {
-        const double2* __restrict__ g = (const double2*)P.jtab;
+    static_assert(sizeof(s_tab) >= sizeof(double) * kWaveSums * (kDirectThreads / 64) / 2, "LDS of the waves' sums");
+    __shared__ double s_more[kWaveSums * (kDirectThreads / 64) / 2];
+    if (bid >= P.n_dentry) {
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int i = (bid - P.n_dentry) * (kDirectThreads / 64) + wave;
+        if (i >= P.n_drank) return;
+        const int d = P.dlist[P.n_d - 1 - i];
+        double* s = (wave < 2 ? reinterpret_cast<double*>(s_tab) : s_more) + (wave & 1) * kWaveSums;
+        const int K = P.db[d].K;
+        if (K <= 8) direct_expand<8>(P, d, s);
+        else if (K <= 16) direct_expand<16>(P, d, s);
+        else direct_expand<24>(P, d, s);
+        return;
+    }
+    const DBlock D = P.db[P.dlist[bid]];
+    // the panels of the table that the block's arguments can lie on
+    const double x0 = P.ws[D.j0] * P.rs[D.k0], x1 = P.ws[D.j1] * P.rs[D.k1];
+    const int p0 = (int)fmax(fmin((x0 - P.jtab_x0) * (1.0 / kJtabWidth) - 1e-6, (double)P.jtab_np), 0.0);
+    const int p1 = (int)fmax(fmin((x1 - P.jtab_x0) * (1.0 / kJtabWidth) + 1e-6, (double)(P.jtab_np - 1)), -1.0) + 1;
+    if (p0 < p1 && p1 - p0 <= kJtabLdsPanels) {
+        const double2* __restrict__ g = (const double2*)P.jtab + (int64_t)p0 * (kJtabCoef / 2);
         constexpr int per = kJtabCoef / 2;
-        for (int e = threadIdx.x; e < P.jtab_np * per; e += kDirectThreads) {
+        for (int e = threadIdx.x; e < (p1 - p0) * per; e += kDirectThreads) {
             const int pn = e / per;
             s_tab[pn * kJtabLdsStride + (e - pn * per)] = g[e];
         }
         __syncthreads();
-        direct_rows<true>(P, D, s_tab);
+        direct_rows<true>(P, D, s_tab - p0 * kJtabLdsStride);
     } else {
         direct_rows<false>(P, D, nullptr);
     }
+}
+
+static inline int direct_workgroups(const Summary& S)
+{
+    return S.n_dentry + (S.n_drank + kDirectThreads / 64 - 1) / (kDirectThreads / 64);
 }
 
 __global__ __launch_bounds__(kDirectThreads) void k_direct_blocks(PlanDev P) { direct_body(P, blockIdx.x); }
@@ -2441,12 +2550,26 @@ __device__ __forceinline__ double local_row(const PlanDev& P, int lb, int j, dou
     return v;
 }
 
+// The direct block's contribution at row j, frequency om.
+__device__ __forceinline__ double direct_row(const PlanDev& P, int d, int j, double om)
+{
+    const DBlock& B = P.db[d];
+    if (B.K == 0) return P.gd[j];
+    const dd a = two_sum(om, -B.D);
+    const double eta = (a.hi + a.lo) * (B.rw > 0.0 ? rcp_refined(B.rw) : 0.0);
+    const double v = local_series(P.dcoef + (int64_t)d * kRankK, B.K, eta);
+    return P.half ? v * sqrt(om) : v;
+}
+
 // Row pass: one thread per sorted frequency walks the block tree from the
 // root.  At a node the row lies either in the local side (rows j0..js) --
 // local block, then the upper-right child -- or in the asymptotic side --
 // asymptotic block, then the lower-left child; a direct child ends the walk
-// and adds the row's sum from k_direct_blocks.  g is written once, in the
+// and adds the row's part from k_direct_blocks.  g is written once, in the
 // caller's order.
+// NCH: the plan's channels, or 0 where every asymptotic block is a rank block
+// (no grid): then one instance serves every order, so that a batch's
+// transforms share a launch.
 template <int NCH>
 __device__ __forceinline__ void rows_body(const PlanDev& P, int bid, double* g)
 {
@@ -2469,13 +2592,18 @@ __device__ __forceinline__ void rows_body(const PlanDev& P, int bid, double* g)
         } else {
             if (nd.ablk >= 0) {
                 const int ab = nd.ablk, abu = __builtin_amdgcn_readfirstlane(ab);
-                if (__all(ab == abu)) acc += asym_eval<NCH, true>(P, abu, om, grids);
-                else acc += asym_eval<NCH, false>(P, ab, om, grids);
+                if constexpr (NCH == 0) {
+                    if (__all(ab == abu)) acc += rank_eval<true>(P, P.ab[abu], om);
+                    else acc += rank_eval<false>(P, P.ab[ab], om);
+                } else {
+                    if (__all(ab == abu)) acc += asym_eval<NCH, true>(P, abu, om, grids);
+                    else acc += asym_eval<NCH, false>(P, ab, om, grids);
+                }
             }
             child = nd.ll;
         }
         if (child <= -2) {
-            acc += P.gd[j];
+            acc += direct_row(P, decode_direct(child), j, om);
             break;
         }
         node = child;
@@ -2575,6 +2703,16 @@ static void dispatch_channels(int nch, F&& f)
     case 36: f(std::integral_constant<int, 36>()); break;
     default: f(std::integral_constant<int, 40>()); break;
     }
+}
+
+// The row pass's channel count: 0 without grids.
+static int rows_channels(const PlanDev& P) { return P.grid_cells > 0 ? P.nch : 0; }
+
+template <class F>
+static void dispatch_rows(int nch, F&& f)
+{
+    if (nch == 0) f(std::integral_constant<int, 0>());
+    else dispatch_channels(nch, f);
 }
 
 static inline void mark(hipEvent_t* marks, int i, hipStream_t s)
@@ -2700,7 +2838,7 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
     }
     auto launch_direct = [&](hipStream_t st) {
         if (P.n_d > 0) {
-            hipLaunchKernelGGL(k_direct_blocks, dim3(P.n_d), dim3(kDirectThreads), 0, st, P);
+            hipLaunchKernelGGL(k_direct_blocks, dim3(direct_workgroups(S)), dim3(kDirectThreads), 0, st, P);
         }
     };
     if (forked) {
@@ -2737,7 +2875,7 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
         const hipError_t e = hipStreamWaitEvent(s, fork->ev_join, 0);
         if (e != hipSuccess) return e;
     }
-    dispatch_channels(P.nch, [&](auto k) {
+    dispatch_rows(rows_channels(P), [&](auto k) {
         hipLaunchKernelGGL(k_rows<decltype(k)::value>, dim3(cdiv64(P.m, 256)), dim3(256), 0, s, P, io.g, io.g_slot);
     });
     mark(marks, 7, s);
@@ -2888,14 +3026,17 @@ void build_batch_schedule(const BatchTransform* tr, int count, const int* order,
         if (L.nseg > 0) out.launches.push_back(L);
     }
     add(kDirect, 0, 0, kDirectThreads, [&](const BatchTransform& T, size_t&) -> int64_t {
-        return live(*T.P) ? T.P->n_d : 0;
+        return live(*T.P) ? direct_workgroups(*T.S) : 0;
     });
     std::vector<int> chans;
-    for (const auto& v : variants)
-        if (std::find(chans.begin(), chans.end(), v.first) == chans.end()) chans.push_back(v.first);
+    for (int t = 0; t < count; ++t) {
+        const int c = rows_channels(*tr[t].P);
+        if (live(*tr[t].P) && std::find(chans.begin(), chans.end(), c) == chans.end()) chans.push_back(c);
+    }
+    std::sort(chans.begin(), chans.end());
     for (int nch : chans)
         add(kRows, nch, 0, 256, [&](const BatchTransform& T, size_t&) -> int64_t {
-            return live(*T.P) && T.P->nch == nch ? cdiv64(T.P->m, 256) : 0;
+            return live(*T.P) && rows_channels(*T.P) == nch ? cdiv64(T.P->m, 256) : 0;
         });
     // the device tables: PlanDev[count], WorkSeg[], FftSeg[] (each 256-byte aligned)
     auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
@@ -2997,7 +3138,7 @@ hipError_t launch_execute_many(const BatchSchedule& S, const void* table_dev, vo
         case kFftPass2: hipLaunchKernelGGL(k_fft_row_many, grid, block, L.lds, s, plans, fs, L.nseg); break;
         case kDirect: hipLaunchKernelGGL(k_direct_blocks_many, grid, block, 0, st, plans, sg, L.nseg); break;
         case kRows:
-            dispatch_channels(L.variant, [&](auto k) {
+            dispatch_rows(L.variant, [&](auto k) {
                 hipLaunchKernelGGL((k_rows_many<decltype(k)::value>), grid, block, 0, s, plans, sg, L.nseg, gout);
             });
             break;

@@ -1,6 +1,7 @@
 // nuht_api.hip -- host side of libnuht: expansion parameters (Sec. 3.3), ES
 // kernel set-up, plan construction (sort, staircase, Alg. 1) and the C ABI.
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cmath>
 #include <cstdio>
@@ -772,20 +773,21 @@ static const double* rank_tables_device()
 // most e^{R |Im omega|}.
 static double rank_largest_xi(double ltol, int terms = kRankK)
 {
-    auto fits = [&](double xi) {
+    struct Ellipse {
+        double lr, lrm1, w;                          // log rho, log(rho - 1), (rho - 1 / rho) / 2
+    };
+    static const auto ellipses = [] {
+        std::array<Ellipse, 16> e;
         for (int l = 0; l < 16; ++l) {
             const double lr = kRankLr0 + kRankLrStep * l, rho = std::exp(lr);
-            const double k = (std::log(4.0) + 0.5 * xi * (rho - 1.0 / rho) - std::log(rho - 1.0) - ltol) / lr + 1.0;
-            if (k <= (double)terms) return true;
+            e[l] = Ellipse{lr, std::log(rho - 1.0), 0.5 * (rho - 1.0 / rho)};
         }
-        return false;
-    };
-    double lo = 0.0, hi = 64.0;
-    for (int it = 0; it < 40; ++it) {
-        const double mid = 0.5 * (lo + hi);
-        if (fits(mid)) lo = mid; else hi = mid;
-    }
-    return lo;
+        return e;
+    }();
+    double xi = 0.0;
+    for (const Ellipse& e : ellipses)                // K >= (log 4 + xi w - log(rho - 1) - ltol) / log rho + 1
+        xi = std::max(xi, ((terms - 1) * e.lr + e.lrm1 + ltol - std::log(4.0)) / e.w);
+    return xi;
 }
 
 // -(2nu+1) pi/4 modulo 2 pi as a double-double in (0, 2 pi], from the
@@ -1192,7 +1194,10 @@ static int fill_params(PlanDev& P, int nu2, double eps_req, const nuht_opts& o)
     // sqrt(2z/pi) that half-integer orders keep outside)
     {
         const double lt = std::log(std::max(1e-5 * eps, 2e-16));
-        for (int i = 0; i < kRankK / 4; ++i) P.local_xi[i] = rank_largest_xi(lt, 4 * (i + 1));
+        for (int i = 0; i < kRankK / 4; ++i) {
+            P.local_xi[i] = rank_largest_xi(lt, 4 * (i + 1));
+            P.direct_xi[i] = rank_largest_xi(std::log(2e-16), 4 * (i + 1));
+        }
     }
     phase_offset2(half ? nu2 + 1 : 2 * anu + 1, P.phi_hi, P.phi_lo);
     P.kappa_max = P.w * M_PI / 4.0 * (1.0 + 1e-9);
@@ -1306,6 +1311,7 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
     slab.add(A.fft_list, (size_t)A.a_cap);
     slab.add(A.gslot, (size_t)A.a_cap + 1);
     slab.add(A.lwork, (size_t)A.lslot_cap);
+    slab.add(A.dlist, (size_t)A.d_cap);
     slab.add(A.cpans, (size_t)A.pan_cap);
     slab.add(A.tlist, (size_t)A.pan_cap);
     slab.add(A.wlist, (size_t)A.pan_cap);
@@ -1314,7 +1320,7 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
     P.nodes = A.nodes; P.lb = A.lb; P.ab = A.ab; P.db = A.db;
     P.litems = A.litems; P.aitems = A.aitems; P.alist = A.alist; P.fft_list = A.fft_list; P.gslot = A.gslot;
     P.cpans = A.cpans; P.rlist = A.rlist; P.tlist = A.tlist; P.wlist = A.wlist;
-    P.lwork = A.lwork;
+    P.lwork = A.lwork; P.dlist = A.dlist;
     P.tlist_cap = A.pan_cap; P.rlist_cap = A.aitem_cap;
     a.P = P; a.A = A; a.K = K; a.Jc = Jc; a.a_cells = a_cells;
     a.min_size = min_size; a.ncand = ncand; a.dft_max = dft_max; a.sigma = sigma;
@@ -1380,7 +1386,7 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     P.n_litems = S.n_litems; P.n_aitems = S.n_aitems; P.n_adense = S.n_adense; P.n_amed = S.n_amed;
     P.n_tsingle = S.n_tsingle; P.n_tmulti = S.n_tmulti; P.n_wmulti = S.n_wmulti;
     P.n_ritems = S.n_ritems; P.n_rsmall = S.n_rsmall;
-    P.n_lwork = S.n_lwork;
+    P.n_lwork = S.n_lwork; P.n_dentry = S.n_dentry; P.n_drank = S.n_drank;
 
     // execution buffers
     ExecBuffers& B = Pt.B;
@@ -1389,6 +1395,7 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     slab.add(B.lpart, (size_t)S.n_litems * (P.L + 1));
     slab.add(B.lmom, (size_t)S.n_l * (P.L + 1));
     slab.add(B.lcoef, (size_t)S.n_lslots * kRankK);
+    slab.add(B.dcoef, S.n_drank > 0 ? (size_t)S.n_d * kRankK : 0);
     slab.add(B.part, (size_t)S.part_cells * P.nch);
     slab.add(B.grids, (size_t)S.grid_cells * P.nch);
     slab.add(B.gd, (size_t)G.m);
@@ -1417,7 +1424,7 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     if (!P.rank_tab) return NUHT_ENOMEM;
     P.es_poly = B.es_poly;
     P.rmom = B.rmom; P.rwts = B.rwts; P.rcoef = B.rcoef;
-    P.cs = B.cs; P.lpart = B.lpart; P.lmom = B.lmom; P.lcoef = B.lcoef; P.part = B.part; P.grids = B.grids;
+    P.cs = B.cs; P.lpart = B.lpart; P.lmom = B.lmom; P.lcoef = B.lcoef; P.dcoef = B.dcoef; P.part = B.part; P.grids = B.grids;
     P.scratch = B.scratch; P.gd = B.gd; P.fft_tw = B.fft_tw;
     P.grid_cells = B.grid_cells;
     small_fft_table(P, Pt.cls.data(), (int)Pt.cls.size());

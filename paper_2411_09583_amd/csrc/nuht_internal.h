@@ -141,6 +141,10 @@ __host__ __device__ inline double rank_mid(int q, int panels, double half) { ret
 
 struct DBlock {
     int32_t j0, j1, k0, k1;
+    // K > 0: applied through K-term expansions about (C, D), half-widths cw of
+    // its points and rw of its frequencies; 0: entry by entry
+    int32_t K, pad;
+    double C, cw, D, rw;
 };
 
 // Whether one wave adds up a rank block's moments and translates them.
@@ -171,6 +175,7 @@ struct Summary {
     int32_t n_tsingle, n_tmulti;   // their panels of frequencies: of blocks translated by one wave, of others
     int32_t n_wmulti;              // panels of points of those others
     int32_t n_lslots, n_lwork;     // slots of the local blocks' rows; waves that fill them
+    int32_t n_dentry, n_drank;     // direct blocks applied entry by entry, through expansions
     int64_t l_row, l_col, a_row, a_col, d_ent;
     int64_t grid_cells;     // sum N1 (all asymptotic blocks)
     int64_t dft_cells;      // sum N1 over direct-sum-path blocks
@@ -205,6 +210,7 @@ struct PlanDev {
     int32_t fp32;                    // FP32 spreading (weights, kernel values and channel sums in float)
     int32_t rank, rank_const;        // plan has rank blocks; the Hankel terms beyond the first vanish
     double local_xi[kRankK / 4];     // largest (half omega range) x R that 4, 8, .. terms of a local panel cover
+    double direct_xi[kRankK / 4];    // the same for the two expansions of a direct block, to full precision
     double rank_ltol, rank_xi;       // log of the expansions' tolerance; largest (half r range) x (half
                                      // omega range) that kRankK terms cover
     const double* rank_tab;          // cosine tables (rank_tab_off)
@@ -239,6 +245,8 @@ struct PlanDev {
     int32_t n_nodes, n_l, n_a, n_d, n_litems, n_aitems, n_adense, n_amed;
     int32_t n_tsingle, n_tmulti, n_wmulti, n_ritems, n_rsmall, n_lwork;
     const LocalWork* lwork;          // the local blocks' rows by waves
+    const int32_t* dlist;            // direct blocks: entry by entry from the front, expansions from the back
+    int32_t n_dentry, n_drank;
     const Panel* cpans;              // panels of the rank blocks' points
     const RankItem* rlist;           // items of rank blocks: large ones from the front, small ones from the back
     const Panel* tlist;              // panels of frequencies: blocks of one wave from the front, others from the back
@@ -249,6 +257,7 @@ struct PlanDev {
     double* lpart;                   // local-moment partial sums (items x (L + 1))
     double* lmom;                    // local moments (local blocks x (L + 1))
     double* lcoef;                   // expansions or values of the local blocks' rows, by slot
+    double* dcoef;                   // expansions of the direct blocks' rows, kRankK a block
     double2* rmom;                   // rank blocks: moments of (item i, panel q) at (i + q) kRankK
     double2* rwts;                   // their nodal weights per panel of points
     double2* rcoef;                  // their expansion coefficients per panel of frequencies

@@ -31,6 +31,7 @@ struct Arena {
     Panel* tlist;        // panels of frequencies to translate (pan_cap)
     Panel* wlist;        // panels of points weighted on their own (pan_cap)
     LocalWork* lwork;    // the local blocks' rows by waves (lslot_cap)
+    int32_t* dlist;      // direct blocks by the way they are applied (d_cap)
     int32_t pan_cap, lslot_cap;
     int32_t node_cap, l_cap, a_cap, d_cap, q_cap, litem_cap, aitem_cap, pad;
 };
@@ -79,6 +80,7 @@ struct ExecBuffers {
     double* lpart;      // local-moment partial sums, n_litems x (L+1)
     double* lmom;       // local moments, n_l x (L+1)
     double* lcoef;      // the local blocks' rows, n_lslots x kRankK
+    double* dcoef;      // the direct blocks' rows, n_d x kRankK
     double2* rmom;      // moments of the rank blocks' (item, panel) pairs
     double2* rwts;      // nodal weights of their panels of points
     double2* rcoef;     // expansion coefficients of their panels of frequencies

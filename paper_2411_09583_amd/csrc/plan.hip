@@ -1319,6 +1319,11 @@ constexpr int kSubThreads = 256;
 // past them go to the global queues at the same index.
 constexpr int kSubLds = 1920;
 
+__device__ __forceinline__ DBlock direct_block(int32_t j0, int32_t j1, int32_t k0, int32_t k1)
+{
+    return DBlock{j0, j1, k0, k1, 0, 0, 0.0, 0.0, 0.0, 0.0};
+}
+
 __device__ __forceinline__ void subdivide(const PlanArgs& a)
 {
     const int32_t* __restrict__ K = a.K;
@@ -1405,7 +1410,7 @@ __device__ __forceinline__ void subdivide(const PlanArgs& a)
                     nd.ur = next_base + m_slot;
                     ++m_slot;
                 }
-                if (o.ur_d) { if (d_slot < A.d_cap) A.db[d_slot] = DBlock{Rq.j0, o.js, o.ks + 1, Rq.k1}; nd.ur = encode_direct(d_slot); ++d_slot; }
+                if (o.ur_d) { if (d_slot < A.d_cap) A.db[d_slot] = direct_block(Rq.j0, o.js, o.ks + 1, Rq.k1); nd.ur = encode_direct(d_slot); ++d_slot; }
                 if (o.ll_m) {
                     const Rect c = Rect{o.js + 1, Rq.j1, Rq.k0, o.ks};
                     if (m_slot < kSubLds) lq[cb ^ 1][m_slot] = c;
@@ -1413,7 +1418,7 @@ __device__ __forceinline__ void subdivide(const PlanArgs& a)
                     nd.ll = next_base + m_slot;
                     ++m_slot;
                 }
-                if (o.ll_d) { if (d_slot < A.d_cap) A.db[d_slot] = DBlock{o.js + 1, Rq.j1, Rq.k0, o.ks}; nd.ll = encode_direct(d_slot); ++d_slot; }
+                if (o.ll_d) { if (d_slot < A.d_cap) A.db[d_slot] = direct_block(o.js + 1, Rq.j1, Rq.k0, o.ks); nd.ll = encode_direct(d_slot); ++d_slot; }
                 if (node < A.node_cap) A.nodes[node] = nd;
                 if (o.cl) {
                     if (l_slot < A.l_cap) {
@@ -1530,7 +1535,7 @@ __device__ __forceinline__ void block_params(const PlanArgs& a)
     const int32_t dft_max = a.dft_max;
     const double sigma = a.sigma;
     if (sum->overflow) return;
-    const int32_t n_l = sum->n_l, n_a = sum->n_a;
+    const int32_t n_l = sum->n_l, n_a = sum->n_a, n_d = sum->n_d;
     const int w = P.w;
     const int lane = threadIdx.x & 15;
     const int32_t group = (int32_t)((blockIdx.x * blockDim.x + threadIdx.x) >> 4), groups = (int32_t)((gridDim.x * blockDim.x) >> 4);
@@ -1585,6 +1590,28 @@ __device__ __forceinline__ void block_params(const PlanArgs& a)
         int32_t ncol = B.k1 - B.k0 + 1;
         B.nitems = (ncol + P.spread_chunk - 1) / P.spread_chunk;
         if (lane == 0) A.ab[b] = B;
+    }
+    for (int32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < n_d; b += gridDim.x * blockDim.x) {
+        DBlock E = A.db[b];
+        const double rlo = P.rs[E.k0], rhi = P.rs[E.k1], wlo = P.ws[E.j0], whi = P.ws[E.j1];
+        E.C = 0.5 * (rlo + rhi);
+        E.D = 0.5 * (wlo + whi);
+        E.cw = fmax(rhi - E.C, E.C - rlo);
+        E.rw = fmax(whi - E.D, E.D - wlo);
+        // J_nu(omega r) is entire in either variable and at most e^{|Im|}, so
+        // the width of an expansion is its half-range times the largest value
+        // of the other variable.  Taken when its work -- a point 2 K + 20
+        // operations, a node pair about 60, a row 2 K -- is less than half of
+        // the entries' 45 each.
+        const double xi = fmax(E.cw * whi, E.rw * rhi);
+        const bool ok = (E.cw == 0.0 || E.cw > 1e-290) && (E.rw == 0.0 || E.rw > 1e-290);
+        if (ok && xi <= P.direct_xi[kRankK / 4 - 1]) {
+            int i = 0;
+            while (i < kRankK / 4 - 1 && xi > P.direct_xi[i]) ++i;
+            const double K = 4.0 * (i + 1), mb = E.j1 - E.j0 + 1, nb = E.k1 - E.k0 + 1;
+            if (2.0 * (nb * (2.0 * K + 20.0) + 60.0 * K * K + 2.0 * K * mb) < 45.0 * mb * nb) E.K = (int32_t)K;
+        }
+        A.db[b] = E;
     }
     for (int32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < n_l; b += gridDim.x * blockDim.x) {
         LBlock L = A.lb[b];
@@ -1773,7 +1800,8 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
 
 // ---------------------------------------------------------------------------
 // Work items (grid-stride over all items: local, asymptotic, the rank blocks'
-// panels of points and of frequencies, the slots of the local blocks' rows).
+// panels of points and of frequencies, the slots of the local blocks' rows,
+// the direct blocks).
 // An item is a chunk of one block's columns; a spread item also carries the
 // subgrid of cells its points can reach (one cell of margin each side), an
 // item of a rank block the panels its points lie in.
@@ -1862,19 +1890,21 @@ __device__ __forceinline__ void items(const PlanArgs& a)
     Summary* __restrict__ sum = a.sum;
     int32_t* __restrict__ a_cells = a.a_cells;
     if (sum->overflow) return;
-    const int32_t n_l = sum->n_l, n_a = sum->n_a;
+    const int32_t n_l = sum->n_l, n_a = sum->n_a, n_d = sum->n_d;
     const int32_t n_li = sum->n_litems, n_ai = sum->n_aitems, n_cp = sum->n_cpan, n_rp = sum->n_rpan, n_ls = sum->n_lslots;
     const int w = P.w;
-    // the five kinds of work, each rounded up to whole waves
+    // the six kinds of work, each rounded up to whole waves
     const int32_t w_li = (n_li + 63) & ~63, w_ai = (n_ai + 63) & ~63, w_cp = (n_cp + 63) & ~63, w_rp = (n_rp + 63) & ~63;
-    const int32_t w_ls = (n_ls + 63) & ~63;
-    const int32_t total = w_li + w_ai + w_cp + w_rp + w_ls;
+    const int32_t w_ls = (n_ls + 63) & ~63, w_d = (n_d + 63) & ~63;
+    const int32_t total = w_li + w_ai + w_cp + w_rp + w_ls + w_d;
     for (int32_t j0 = blockIdx.x * blockDim.x + (threadIdx.x & ~63); j0 < total; j0 += gridDim.x * blockDim.x) {
         const int lane = threadIdx.x & 63;
         bool ritem = false;                           // an item of a rank block
         bool tone = false, tmany = false;             // a panel of frequencies of a block of one wave / of another
         bool wmany = false;                           // a panel of points of another
         bool lwork = false;                           // the first slot of a wave of local rows
+        bool drank = false, dentry = false;           // a direct block through expansions / entry by entry
+        int32_t id = 0;
         LocalWork W{};
         RankItem R{};
         Panel T{};
@@ -1939,6 +1969,12 @@ __device__ __forceinline__ void items(const PlanArgs& a)
                 A.cpans[ip] = T;
                 wmany = !rank_one_wave(B);
             }
+        } else if (j0 >= total - w_d) {
+            id = j0 - (total - w_d) + lane;
+            if (id < n_d) {
+                drank = A.db[id].K > 0;
+                dentry = !drank;
+            }
         } else if (j0 >= w_li + w_ai + w_cp + w_rp) {
             const int32_t i0 = j0 - w_li - w_ai - w_cp - w_rp, is = i0 + lane;
             const int32_t lo = block_of(n_l, i0, [&](int32_t b) { return A.lb[b].slot0; });
@@ -1962,6 +1998,9 @@ __device__ __forceinline__ void items(const PlanArgs& a)
         if (ritem) A.rlist[small ? A.aitem_cap - 1 - p4 : p0] = R;
         const int32_t p3 = wave_append(wmany, &sum->n_wmulti);
         if (wmany) A.wlist[p3] = T;
+        const int32_t p6 = wave_append(dentry, &sum->n_dentry), p7 = wave_append(drank, &sum->n_drank);
+        if (dentry) A.dlist[p6] = id;
+        if (drank) A.dlist[n_d - 1 - p7] = id;
         const int32_t p5 = wave_append(lwork, &sum->n_lwork);
         if (lwork) A.lwork[p5] = W;
         const int32_t p1 = wave_append(tone, &sum->n_tsingle);
