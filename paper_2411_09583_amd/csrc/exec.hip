@@ -845,6 +845,14 @@ __device__ __forceinline__ double rank_eval(const PlanDev& P, const ABlock& B, d
 // those with l - w < l0 <= l, a contiguous range (points are sorted), found by
 // binary search; slices of one cell are adjacent lanes and are summed with
 // cross-lane shuffles after the last sub-chunk.
+//
+// Where points are sparse an item's cells take several turns of the threads.
+// A turn only takes the sub-chunks that reach its cells, and the last one of
+// a turn, which also reaches the next turn's, is kept in LDS: every sub-chunk
+// goes through phase 1 about once, whatever the number of turns.  (All of an
+// item's sub-chunks in every turn took 462 us for the 1e6 log-spaced points of
+// order 0, one point a cell, and takes 98 so; 276 and 147 at the first 1e6
+// zeros of J_0.)
 // ---------------------------------------------------------------------------
 constexpr int kSpreadSub = 256;
 
@@ -876,6 +884,20 @@ struct PointEval {
     int l0;
 };
 
+// First cell reached by the point at offset tp = r - C; frac: its distance
+// from the cell before.
+__device__ __forceinline__ int first_cell(const dd& tp, double inv_h, double hw, double& frac)
+{
+    // u - w/2 = (tp.hi + tp.lo)/h - w/2
+    dd a = two_sum(tp.hi * inv_h, -hw);
+    double lo = a.lo + tp.lo * inv_h;
+    double fl = floor(a.hi);
+    frac = (a.hi - fl) + lo;          // a.hi - fl is exact
+    if (frac < 0.0) { fl -= 1.0; frac += 1.0; }
+    else if (frac >= 1.0) { fl += 1.0; frac -= 1.0; }
+    return (int)fl + 1;
+}
+
 __device__ __forceinline__ PointEval eval_point(const ABlock& B, double r, double c, double inv_h, double hw)
 {
     dd tp = two_sum(r, -B.C);
@@ -886,18 +908,13 @@ __device__ __forceinline__ PointEval eval_point(const ABlock& B, double r, doubl
     // estimates (within an ulp or two; no IEEE division or square root)
     const double q = B.r0 * rcp_refined(r);
     const double w0 = c * (q * rsqrt_refined(q));
-    // u - w/2 = (tp.hi + tp.lo)/h - w/2
-    dd a = two_sum(tp.hi * inv_h, -hw);
-    double lo = a.lo + tp.lo * inv_h;
-    double fl = floor(a.hi);
-    double frac = (a.hi - fl) + lo;          // a.hi - fl is exact
-    if (frac < 0.0) { fl -= 1.0; frac += 1.0; }
-    else if (frac >= 1.0) { fl += 1.0; frac -= 1.0; }
+    double frac;
+    const int l0 = first_cell(tp, inv_h, hw, frac);
     PointEval e;
     e.wr = w0 * cth;
     e.wi = w0 * sth;
     e.q = q;
-    e.l0 = (int)fl + 1;
+    e.l0 = l0;
     e.s = 1.0 - 2.0 * frac;                  // s = 2 f - 1, f = 1 - frac
     return e;
 }
@@ -926,19 +943,28 @@ __device__ __forceinline__ void spread_body(const PlanDev& P, int bid)
     int slices = 1;
     while (slices < 64 && slices * 2 * sub_n <= 256) slices <<= 1;
     const int cells_par = 256 / slices;
+    auto cell_of = [&](int k) {
+        double frac;
+        return first_cell(two_sum(P.rs[k], -B.C), inv_h, hw, frac);
+    };
+    int k_begin = I.ka, in_lds = -1;     // first sub-chunk that reaches the turn's cells; the one in LDS
     for (int cbase = 0; cbase < sub_n; cbase += cells_par) {
+        const int l_lo = I.sub_lo + cbase;
+        const int l_hi = I.sub_lo + (cbase + cells_par < sub_n ? cbase + cells_par : sub_n) - 1;
+        while (k_begin + kSpreadSub < I.kb && cell_of(k_begin + kSpreadSub - 1) <= l_lo - w) k_begin += kSpreadSub;
         const int cell = cbase + tid / slices;
         const int sl = tid & (slices - 1);
         const int l = I.sub_lo + cell;
         T ar[NCH], ai[NCH];
         #pragma unroll
         for (int p = 0; p < NCH; ++p) { ar[p] = T(0); ai[p] = T(0); }
-        for (int k0 = I.ka; k0 < I.kb; k0 += kSpreadSub) {
+        for (int k0 = k_begin; k0 < I.kb; k0 += kSpreadSub) {
+            if (cell_of(k0) > l_hi) break;
             const int np = (I.kb - k0) < kSpreadSub ? (I.kb - k0) : kSpreadSub;
-            __syncthreads();
             // every thread evaluates a point (the last one when tid >= np) so
             // that the coefficient loads below stay wave-uniform (scalar)
-            {
+            if (k0 != in_lds) {
+                __syncthreads();
                 const bool own = tid < np;
                 const int k = k0 + (own ? tid : np - 1);
                 const PointEval e = eval_point(B, P.rs[k], cs[k], inv_h, hw);
@@ -970,8 +996,9 @@ __device__ __forceinline__ void spread_body(const PlanDev& P, int bid)
                     double v = __builtin_fma(spow[kHalf], vhi, vlo);
                     if (own) kv[t] = (T)v;
                 }
+                in_lds = k0;
+                __syncthreads();
             }
-            __syncthreads();
             if (cell < sub_n) {
                 // points with l0 in (l - w, l]
                 int lo = 0, hi = np;
