@@ -291,31 +291,35 @@ __global__ __launch_bounds__(64) void k_lmom_many(const PlanDev* __restrict__ pl
     lmom_body<MAXQ>(plan_of(plans, w.t), w.g0);
 }
 
-// Sum of a local block's item partials (blocks of several items), in a fixed order: eight running sums
-// over the items (item i into sum i mod 8), combined pairwise.  A block can
-// hold a few hundred items (the top-level local block spans most columns),
-// and eight independent sums keep eight loads in flight instead of one.
+// Sum of a local block's item partials (blocks of several items), in a fixed
+// order.  A block can hold a thousand items (the top-level local block spans
+// most columns) and a sum's loads are a chain of latencies, so a wave takes
+// eight moments and eight lanes share each: lane group s adds items s, s + 8,
+// .., four loads in flight, and the groups' sums are combined pairwise.
 __device__ __forceinline__ void lmom_reduce_body(const PlanDev& P, int bid)
 {
-    const int32_t t = bid * (int32_t)blockDim.x + (int32_t)threadIdx.x;
+    const int lane = threadIdx.x & 63, sub = lane >> 3;
     const int32_t Lp = P.L + 1;
-    if (t >= P.n_l * Lp) return;
+    const int32_t t = ((bid * (int32_t)blockDim.x + (int32_t)threadIdx.x) >> 6) * 8 + (lane & 7);
+    if (t >= P.n_l * Lp) return;                     // all eight lanes of a moment
     const int32_t b = t / Lp;
     const int32_t l = t - b * Lp;
-    const LBlock B = P.lb[b];
-    if (B.nitems == 1) return;                       // stored by its item
-    const double* __restrict__ col = P.lpart + (int64_t)B.item0 * Lp + l;
-    double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    int32_t it = 0;
-    for (; it + 8 <= B.nitems; it += 8) {
+    const int32_t nitems = P.lb[b].nitems;
+    if (nitems == 1) return;                         // stored by its item
+    const double* __restrict__ col = P.lpart + (int64_t)P.lb[b].item0 * Lp + l;
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    int32_t it = sub;
+    for (; it + 24 < nitems; it += 32) {
         #pragma unroll
-        for (int q = 0; q < 8; ++q) a[q] += col[(int64_t)(it + q) * Lp];
+        for (int q = 0; q < 4; ++q) a[q] += col[(int64_t)(it + 8 * q) * Lp];
     }
     #pragma unroll
-    for (int q = 0; q < 7; ++q)
-        if (it + q < B.nitems) a[q] += col[(int64_t)(it + q) * Lp];
-    const double s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-    P.lmom[t] = moment_as_used(P, l, s);
+    for (int q = 0; q < 3; ++q)
+        if (it + 8 * q < nitems) a[q] += col[(int64_t)(it + 8 * q) * Lp];
+    double s = (a[0] + a[1]) + (a[2] + a[3]);
+    #pragma unroll
+    for (int o = 8; o < 64; o <<= 1) s += __shfl_xor(s, o);
+    if (sub == 0) P.lmom[t] = moment_as_used(P, l, s);
 }
 
 __global__ void k_lmom_reduce(PlanDev P) { lmom_reduce_body(P, blockIdx.x); }
@@ -2670,6 +2674,7 @@ __global__ void k_direct_all(PlanDev P, const double* __restrict__ r, const doub
 
 // ---------------------------------------------------------------------------
 static inline int cdiv64(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+static inline int lmom_reduce_blocks(const PlanDev& P, const Summary& S) { return cdiv64((int64_t)S.n_l * (P.L + 1), 32); }
 
 template <int NCH>
 static void launch_spread(const PlanDev& P, const Summary& S, hipStream_t s)
@@ -2860,7 +2865,7 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
         if (lmom_width(P.L) == 32) hipLaunchKernelGGL(k_lmom<32>, dim3(S.n_litems), dim3(64), 0, ls, P);
         else hipLaunchKernelGGL(k_lmom<64>, dim3(S.n_litems), dim3(64), 0, ls, P);
         if (S.n_litems > S.n_l)   // some block has several items
-            hipLaunchKernelGGL(k_lmom_reduce, dim3(cdiv64((int64_t)S.n_l * (P.L + 1), 256)), dim3(256), 0, ls, P);
+            hipLaunchKernelGGL(k_lmom_reduce, dim3(lmom_reduce_blocks(P, S)), dim3(256), 0, ls, P);
         launch_local_nodes(P, ls);
     }
     auto launch_direct = [&](hipStream_t st) {
@@ -2974,7 +2979,7 @@ void build_batch_schedule(const BatchTransform* tr, int count, const int* order,
             return live(*T.P) && lmom_width(T.P->L) == width ? T.S->n_litems : 0;
         });
     add(kLmomReduce, 0, 0, 256, [&](const BatchTransform& T, size_t&) -> int64_t {
-        return live(*T.P) && T.S->n_litems > T.S->n_l ? cdiv64((int64_t)T.S->n_l * (T.P->L + 1), 256) : 0;
+        return live(*T.P) && T.S->n_litems > T.S->n_l ? lmom_reduce_blocks(*T.P, *T.S) : 0;
     });
     for (int mode = 0; mode < 4; ++mode)
         add(kLocalNodes, mode, 0, 64, [&](const BatchTransform& T, size_t& lds) -> int64_t {

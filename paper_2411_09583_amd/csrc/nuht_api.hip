@@ -1277,7 +1277,7 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
         pp.Pt = &Pt; pp.G = &G; pp.s = s;
         int64_t tot = (int64_t)G.n + G.m;
         pp.cap = (int32_t)std::min<int64_t>(tot / 32 + 4096, 1 << 28);
-        pp.icap = (int32_t)std::min<int64_t>(64 * (tot / P.spread_chunk) + 2 * (int64_t)pp.cap, 1 << 28);
+        pp.icap = (int32_t)std::min<int64_t>(64 * (tot / std::min(P.spread_chunk, local_chunk(G.n))) + 2 * (int64_t)pp.cap, 1 << 28);
     }
     if (G.n == 0 || G.m == 0) return NUHT_OK;
     const nuht_opts& o = pl->opts;

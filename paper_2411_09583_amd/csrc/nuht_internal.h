@@ -12,7 +12,14 @@ namespace nuht {
 
 constexpr int kMaxChannels = 40;       // 2M with M <= 20 (eq. num-asy-terms caps M at 20)
 constexpr int kMaxFftLog2 = 24;        // largest FFT of an asymptotic block: 2^24 = 4096^2 points (two passes)
-constexpr int kLocalChunk = 4096;      // columns per local-moment work item
+// Columns per local-moment work item (one wave) of a transform of n points.
+// A wave's points are a serial chain, so items are short enough for the waves
+// to cover the chip at every n, and long enough that adding up the items of
+// the largest block stays cheap.  Against items of 4096 columns: k_lmom at n =
+// 5229, order 18: 10 us (93); at 1e6, order 0, 31 (48); 40 transforms of 1e3
+// to 1e5 points in one batch 113 (343); the sums 4 to 9 us (5 to 8) through
+// the split of lmom_reduce_body.
+inline __host__ __device__ int32_t local_chunk(int32_t n) { return n <= (1 << 17) ? 256 : n <= (1 << 19) ? 512 : 1024; }
 constexpr int kSpreadChunk = 1024;     // default points per spreading work item (a plan option)
 // Default direct-block threshold of Alg. 1 for an n x m transform.  The
 // paper leaves min_size to numerical experiments (its example: 1024).  On

@@ -1622,7 +1622,7 @@ __device__ __forceinline__ void block_params(const PlanArgs& a)
         }
         L.R = R;
         int32_t ncol = L.k1 - L.k0 + 1;
-        L.nitems = (ncol + kLocalChunk - 1) / kLocalChunk;
+        L.nitems = (ncol + local_chunk(P.n) - 1) / local_chunk(P.n);
         // rows: panels of as many terms as their share of xi = S R needs,
         // unless they have more nodes than the block has rows
         const double wlo = P.ws[L.j0], whi = P.ws[L.j1];
@@ -1914,8 +1914,8 @@ __device__ __forceinline__ void items(const PlanArgs& a)
             if (i < n_li) {
                 const LBlock L = A.lb[lo];
                 int32_t it = i - L.item0;
-                int32_t ka = L.k0 + it * kLocalChunk;
-                int32_t kb = ka + kLocalChunk;
+                int32_t ka = L.k0 + it * local_chunk(P.n);
+                int32_t kb = ka + local_chunk(P.n);
                 if (kb > L.k1 + 1) kb = L.k1 + 1;
                 Item I;
                 I.blk = lo; I.ka = ka; I.kb = kb; I.sub_lo = 0; I.sub_n = 0; I.dense = 0; I.off = 0;
