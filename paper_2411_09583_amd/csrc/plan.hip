@@ -377,19 +377,20 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const uint64_t* _
 // Sorts with fewer launches for short segments (same stable order as the LSD
 // sort above, whose 25 launches dominate planning there):
 // * both segments up to kSsCap keys: k_sort_small, one workgroup per segment
-//   sorting it in LDS (LSD on 8-bit digits over the bits that vary);
-// * both up to 2^18 keys: a splitter sort in five launches (64 bucket slots
+//   sorting it in LDS (bin_sort, or LSD on 8-bit digits over the bits that
+//   vary where the keys crowd a few bins);
+// * both up to 2^20 keys (kSsLargeMax): a splitter sort in five launches (64 bucket slots
 //   per array up to 65536 keys, 1024 above) --
-//   1. k_ss_sample: one workgroup per segment sorts a stratified sample of the
-//      keys in LDS (bitonic for 1024 keys, LSD radix for 16384) and keeps its
-//      quantiles, without repeats, as the
+//   1. k_ss_sample (1024 slots: after k_ss_gather): one workgroup per segment sorts a stratified sample of the
+//      keys in LDS (bin_sort; where that fails bitonic for 1024 keys, LSD
+//      radix for 16384) and keeps its quantiles, without repeats, as the
 //      splitters u_0 < ... < u_{U-1};
 //   2. k_ss_count: each tile of kSsTile keys counts its keys per bucket (range
 //      bucket 2p: the keys strictly between u_{p-1} and u_p; equality bucket
 //      2p + 1: the keys equal to u_p, which never need sorting) and checks its
 //      inputs;
-//   3. k_ss_scan: per bucket, exclusive offsets over the tiles, the bucket
-//      sizes and the bucket starts;
+//   3. k_ss_scan: per bucket, exclusive offsets over the tiles and the bucket
+//      sizes;
 //   4. k_ss_scatter: each tile scatters its keys, stably, into the buckets;
 //   5. k_ss_local: one workgroup per bucket sorts it in LDS like k_sort_small;
 //      a bucket beyond the LDS capacity (only when the sample misrepresents
@@ -400,8 +401,11 @@ constexpr int kSsOversample = 32;        // sample keys per range bucket
 constexpr int kSsThreads = 512;          // count and scatter workgroups: 8 waves
 constexpr int kSsRounds = 16;            // 64-key rounds per wave
 constexpr int kSsTile = kSsThreads * kSsRounds;
-constexpr int kSsLocalThreads = 256;     // LDS sort workgroups: 4 waves
-constexpr int kSsCap = kSsLocalThreads * kSsRounds;   // longest run sorted in LDS
+// LDS sort workgroups: 8 waves of 8 rounds (LDS holds two workgroups to a
+// compute unit whatever their waves).
+constexpr int kSsLocalThreads = 512;
+constexpr int kSsLocalRounds = 8;
+constexpr int kSsCap = kSsLocalThreads * kSsLocalRounds;   // longest run sorted in LDS
 
 // The splitter sort with NB bucket slots per segment (2 U + 1 <= NB - 1
 // used): 64 for segments up to 65536 keys, 1024 up to 2^20.
@@ -464,23 +468,27 @@ __device__ __forceinline__ int64_t ss_sample_pos(int s, int ns, int64_t n)
 {
     uint32_t h = (uint32_t)s * 0x9E3779B9u;
     h ^= h >> 16; h *= 0x85EBCA6Bu; h ^= h >> 13; h *= 0xC2B2AE35u; h ^= h >> 16;
-    const int64_t lo = ((int64_t)s * n) / ns, hi = ((int64_t)(s + 1) * n) / ns;
+    // floor(s n / ns) in double, exactly: s n < 2^53, and a quotient that is
+    // no integer is at least 1/ns away from one (a 64-bit integer division
+    // takes ten times as long)
+    const double dn = (double)n, dns = (double)ns;
+    const int64_t lo = (int64_t)floor((double)s * dn / dns), hi = (int64_t)floor((double)(s + 1) * dn / dns);
     return lo + (int64_t)(((uint64_t)h * (uint64_t)(hi - lo)) >> 32);
 }
 
 // Stable ranks of the 8-bit digits (key >> shift) of a workgroup's keys, held
-// kSsRounds per lane in (wave, round, lane) order with `rounds` rounds per
-// wave, n_valid of them: rk[q] receives the key's offset among the equal
+// R per lane in (wave, round, lane) order with `rounds` rounds per wave, n_valid of them: rk[q] receives the key's offset among the equal
 // digits before it in its wave, wcnt[v][d] (zeroed by the caller) the count
 // of digit d in wave v's keys.
-__device__ __forceinline__ void ss_rank_digits(const uint64_t (&kr)[kSsRounds], int shift, int rounds, int n_valid,
-                                               int32_t (*wcnt)[256], int (&dg)[kSsRounds], int (&rk)[kSsRounds])
+template <int R>
+__device__ __forceinline__ void ss_rank_digits(const uint64_t (&kr)[R], int shift, int rounds, int n_valid,
+                                               int32_t (*wcnt)[256], int (&dg)[R], int (&rk)[R])
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     int32_t* cw = wcnt[wave];
     #pragma unroll
-    for (int q = 0; q < kSsRounds; ++q) {
+    for (int q = 0; q < R; ++q) {
         dg[q] = -1;
         if (q < rounds) {
             const int i = (wave * rounds + q) * 64 + lane;
@@ -498,38 +506,40 @@ __device__ __forceinline__ void ss_rank_digits(const uint64_t (&kr)[kSsRounds], 
     }
 }
 
-// Thread d of the 256: the waves' starts of digit d in wcnt (counts in,
-// starts out), after the digit's start among all the keys plus base.
-// Returns the digit's total.
+// Thread d < 256: the waves' starts of digit d in wcnt (counts in, starts
+// out), after the digit's start among all the keys plus base.  Returns the
+// digit's total (0 in the other threads).
 __device__ __forceinline__ int32_t ss_digit_starts(int32_t (*wcnt)[256], int32_t base, int32_t* wtot)
 {
     constexpr int kWaves = kSsLocalThreads / 64;
     const int d = threadIdx.x, lane = d & 63, wave = d >> 6;
     int32_t c = 0;
-    #pragma unroll
-    for (int v = 0; v < kWaves; ++v) c += wcnt[v][d];
+    if (d < 256)
+        for (int v = 0; v < kWaves; ++v) c += wcnt[v][d];
     const int32_t incl = wave_incl_scan(c);
     if (lane == 63) wtot[wave] = incl;
     __syncthreads();
-    int32_t run = base + incl - c;
-    for (int v = 0; v < wave; ++v) run += wtot[v];
-    #pragma unroll
-    for (int v = 0; v < kWaves; ++v) {
-        const int32_t a = wcnt[v][d];
-        wcnt[v][d] = run;
-        run += a;
+    if (d < 256) {
+        int32_t run = base + incl - c;
+        for (int v = 0; v < wave; ++v) run += wtot[v];
+        #pragma unroll
+        for (int v = 0; v < kWaves; ++v) {
+            const int32_t a = wcnt[v][d];
+            wcnt[v][d] = run;
+            run += a;
+        }
     }
     return c;
 }
 
 // Smallest and largest of the valid keys kr[q] over the block.
-__device__ __forceinline__ void ss_key_range(const uint64_t (&kr)[kSsRounds], int rounds, int n_valid,
+__device__ __forceinline__ void ss_key_range(const uint64_t (&kr)[kSsLocalRounds], int rounds, int n_valid,
                                              uint64_t* red, uint64_t& kmin, uint64_t& kmax)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint64_t lo = ~0ull, hi = 0ull;
     #pragma unroll
-    for (int q = 0; q < kSsRounds; ++q) {
+    for (int q = 0; q < kSsLocalRounds; ++q) {
         const int i = (wave * rounds + q) * 64 + lane;
         if (q < rounds && i < n_valid) { lo = kr[q] < lo ? kr[q] : lo; hi = kr[q] > hi ? kr[q] : hi; }
     }
@@ -550,28 +560,168 @@ __device__ __forceinline__ void ss_key_range(const uint64_t (&kr)[kSsRounds], in
     __syncthreads();
 }
 
+// ---------------------------------------------------------------------------
+// Sort of a workgroup's keys by bins: a key's place among kBins equal bins
+// between the smallest and the largest key is nearly its rank where the keys
+// are spread evenly, and the few keys that share a bin are compared with each
+// other.  Keys go to the bins in any order (LDS counters); the comparison by
+// (key, value) then makes the order the stable one.  One pass over LDS where
+// a radix sort needs one per eight bits of the keys (up to eight).
+//
+// Bins divide the values (uniform, clustered at the ends) or, where a quarter
+// or more of the keys lie in the lowest sixteenth of the range (points over
+// several decades), the bit patterns, which grow like the logarithm.  Both are
+// nondecreasing in the key.
+// ---------------------------------------------------------------------------
+constexpr int kBins = 4096;
+// Fullest bin sorted by comparisons; fuller ones (clusters, many repeats)
+// leave the keys to the radix sorts.
+constexpr int32_t kBinMax = 96;
+
+struct BinMap {
+    uint64_t kmin;
+    double vmin, scale;
+    bool by_value;
+};
+
+__device__ __forceinline__ int bin_of(const BinMap& B, uint64_t k)
+{
+    const double d = B.by_value ? __longlong_as_double((long long)k) - B.vmin : (double)(k - B.kmin);
+    const double t = d * B.scale;
+    return t < kBins - 1 ? (int)t : kBins - 1;
+}
+
+// LDS words of bin_sort besides keys, values and bins.
+template <int WAVES>
+struct BinLds {
+    uint64_t red[2 * WAVES];
+    int32_t wtot[WAVES], wmax[WAVES];
+    int32_t low;
+};
+
+// Sorts the block's n >= 1 keys kr[q] (with their values vr[q]; key i =
+// (wave rounds + q) 64 + lane for q < rounds, i < n) and hands each to
+// emit(rank, key, value).  key, val (n entries) and bin (kBins): LDS.  False,
+// with nothing emitted, if a bin is too full.  val may be null: equal keys
+// then rank in any order.
+template <int WAVES, int R, class Emit>
+__device__ bool bin_sort(const uint64_t (&kr)[R], const int32_t (&vr)[R], int rounds, int n, uint64_t* key,
+                         int32_t* val, int32_t* bin, BinLds<WAVES>& L, Emit emit)
+{
+    constexpr int kThreads = 64 * WAVES, kPer = kBins / kThreads;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    auto valid = [&](int q) { return q < rounds && (wave * rounds + q) * 64 + lane < n; };
+    uint64_t lo = ~0ull, hi = 0ull;
+    #pragma unroll
+    for (int q = 0; q < R; ++q)
+        if (valid(q)) { lo = kr[q] < lo ? kr[q] : lo; hi = kr[q] > hi ? kr[q] : hi; }
+    #pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint64_t a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
+        lo = a < lo ? a : lo;
+        hi = b > hi ? b : hi;
+    }
+    if (lane == 0) { L.red[2 * wave] = lo; L.red[2 * wave + 1] = hi; }
+    if (t == 0) L.low = 0;
+    for (int i = t; i < kBins; i += kThreads) bin[i] = 0;
+    __syncthreads();
+    for (int v = 0; v < WAVES; ++v) {
+        lo = L.red[2 * v] < lo ? L.red[2 * v] : lo;
+        hi = L.red[2 * v + 1] > hi ? L.red[2 * v + 1] : hi;
+    }
+    BinMap B;
+    B.kmin = lo;
+    B.vmin = __longlong_as_double((long long)lo);
+    const double vrange = __longlong_as_double((long long)hi) - B.vmin;
+    const double cut = B.vmin + 0.0625 * vrange;
+    int low = 0;
+    #pragma unroll
+    for (int q = 0; q < R; ++q)
+        low += __popcll(__ballot(valid(q) && __longlong_as_double((long long)kr[q]) < cut));
+    if (lane == 0) atomicAdd(&L.low, low);
+    __syncthreads();
+    const double vscale = kBins / vrange;
+    B.by_value = 4 * L.low < n && vscale <= 1.7976931348623157e308;
+    B.scale = B.by_value ? vscale : hi > lo ? kBins / (double)(hi - lo) : 0.0;
+    int place[R];
+    #pragma unroll
+    for (int q = 0; q < R; ++q)
+        if (valid(q)) place[q] = atomicAdd(&bin[bin_of(B, kr[q])], 1);
+    __syncthreads();
+    // the bins' starts (thread t: bins kPer t ..)
+    {
+        int32_t c[kPer], sum = 0, most = 0;
+        #pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            c[j] = bin[kPer * t + j];
+            sum += c[j];
+            most = c[j] > most ? c[j] : most;
+        }
+        const int32_t incl = wave_incl_scan(sum);
+        #pragma unroll
+        for (int o = 32; o > 0; o >>= 1) { const int32_t u = __shfl_xor(most, o); most = u > most ? u : most; }
+        if (lane == 63) { L.wtot[wave] = incl; L.wmax[wave] = most; }
+        __syncthreads();
+        int32_t run = incl - sum;
+        for (int v = 0; v < WAVES; ++v) {
+            if (v < wave) run += L.wtot[v];
+            most = L.wmax[v] > most ? L.wmax[v] : most;
+        }
+        if (most > kBinMax) return false;          // the same in every thread
+        #pragma unroll
+        for (int j = 0; j < kPer; ++j) { bin[kPer * t + j] = run; run += c[j]; }
+    }
+    __syncthreads();
+    #pragma unroll
+    for (int q = 0; q < R; ++q)
+        if (valid(q)) {
+            const int at = bin[bin_of(B, kr[q])] + place[q];
+            key[at] = kr[q];
+            if (val) val[at] = vr[q];
+        }
+    __syncthreads();
+    for (int i = t; i < n; i += kThreads) {
+        const uint64_t k = key[i];
+        const int32_t v = val ? val[i] : i;
+        const int b = bin_of(B, k);
+        const int first = bin[b], last = b + 1 < kBins ? bin[b + 1] : n;
+        int rank = first;
+        for (int j = first; j < last; ++j) {
+            const uint64_t o = key[j];
+            rank += o < k ? 1 : 0;
+            if (o == k) rank += (val ? val[j] : j) < v ? 1 : 0;
+        }
+        emit(rank, k, v);
+    }
+    return true;
+}
+
 // LDS of a block sort of up to kSsCap keys.
 struct SsBlockLds {
     uint64_t key[kSsCap];
     int32_t val[kSsCap];
-    int32_t wcnt[kSsLocalThreads / 64][256];
+    union {
+        int32_t bin[kBins];
+        int32_t wcnt[kSsLocalThreads / 64][256];
+    };
+    BinLds<kSsLocalThreads / 64> bl;
     int32_t wtot[kSsLocalThreads / 64];
     uint64_t red[2 * (kSsLocalThreads / 64)];
 };
 
-// Rounds per wave for n keys over the block's four waves (wave-major order:
+// Rounds per wave for n keys over the block's waves (wave-major order:
 // key i sits in wave i / (64 rounds), round (i / 64) % rounds, lane i % 64).
-__device__ __forceinline__ int ss_rounds(int n) { return (n + 4 * 64 - 1) / (4 * 64); }
+__device__ __forceinline__ int ss_rounds(int n) { return (n + kSsLocalThreads - 1) / kSsLocalThreads; }
 
 // Stable sort of the block's n <= kSsCap keys (with their values) held in
 // registers as ss_rounds(n) rounds per wave: LSD passes of 8 bits over the
 // bits in which the keys differ, each ranking the keys in registers and
 // exchanging them through LDS.
-__device__ void ss_block_sort(uint64_t (&kr)[kSsRounds], int32_t (&vr)[kSsRounds], int n, SsBlockLds& L)
+__device__ void ss_block_sort(uint64_t (&kr)[kSsLocalRounds], int32_t (&vr)[kSsLocalRounds], int n, SsBlockLds& L)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int rounds = ss_rounds(n);
-    int dg[kSsRounds], rk[kSsRounds];
+    int dg[kSsLocalRounds], rk[kSsLocalRounds];
     uint64_t kmin, kmax;
     ss_key_range(kr, rounds, n, L.red, kmin, kmax);
     const uint64_t diff = kmin ^ kmax;
@@ -584,7 +734,7 @@ __device__ void ss_block_sort(uint64_t (&kr)[kSsRounds], int32_t (&vr)[kSsRounds
         ss_digit_starts(L.wcnt, 0, L.wtot);
         __syncthreads();
         #pragma unroll
-        for (int q = 0; q < kSsRounds; ++q) {
+        for (int q = 0; q < kSsLocalRounds; ++q) {
             if (dg[q] >= 0) {
                 const int off = L.wcnt[wave][dg[q]] + rk[q];
                 L.key[off] = kr[q];
@@ -593,7 +743,7 @@ __device__ void ss_block_sort(uint64_t (&kr)[kSsRounds], int32_t (&vr)[kSsRounds
         }
         __syncthreads();
         #pragma unroll
-        for (int q = 0; q < kSsRounds; ++q) {
+        for (int q = 0; q < kSsLocalRounds; ++q) {
             const int i = (wave * rounds + q) * 64 + lane;
             if (q < rounds && i < n) { kr[q] = L.key[i]; vr[q] = L.val[i]; }
         }
@@ -615,11 +765,11 @@ __global__ __launch_bounds__(kSsLocalThreads) void k_sort_small(const double* __
     const double* __restrict__ x = seg ? w : r;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int rounds = ss_rounds(n);
-    uint64_t kr[kSsRounds];
-    int32_t vr[kSsRounds];
+    uint64_t kr[kSsLocalRounds];
+    int32_t vr[kSsLocalRounds];
     bool bad = false;
     #pragma unroll
-    for (int q = 0; q < kSsRounds; ++q) {
+    for (int q = 0; q < kSsLocalRounds; ++q) {
         const int i = (wave * rounds + q) * 64 + lane;
         kr[q] = 0ull; vr[q] = 0;
         if (q < rounds && i < n) {
@@ -632,26 +782,30 @@ __global__ __launch_bounds__(kSsLocalThreads) void k_sort_small(const double* __
     const int any_bad = __syncthreads_or(bad ? 1 : 0);
     if (threadIdx.x == 0) errs[seg] = any_bad ? 1 : 0;
     if (n == 0) return;
+    if (bin_sort<kSsLocalThreads / 64>(kr, vr, rounds, n, L.key, L.val, L.bin, L.bl,
+                                       [&](int i, uint64_t k, int32_t v) { k0[base + i] = k; v0[base + i] = v; }))
+        return;
+    __syncthreads();
     ss_block_sort(kr, vr, n, L);
     #pragma unroll
-    for (int q = 0; q < kSsRounds; ++q) {
+    for (int q = 0; q < kSsLocalRounds; ++q) {
         const int i = (wave * rounds + q) * 64 + lane;
         if (q < rounds && i < n) { k0[base + i] = kr[q]; v0[base + i] = vr[q]; }
     }
 }
 
-// The B - 1 quantiles of the sorted sample sk (ns keys), each kept if it
-// differs from the one before, as the segment's splitters (threads t < B - 1
-// of a 1024-thread block; every thread calls it).
-__device__ __forceinline__ void ss_pick_splitters(const uint64_t* sk, int ns, int B, uint64_t* spl_seg,
+// The B - 1 quantiles sk[step], sk[2 step], .. of the sorted sample, each kept
+// if it differs from the one before, as the segment's splitters (threads
+// t < B - 1 of a 1024-thread block; every thread calls it).
+__device__ __forceinline__ void ss_pick_splitters(const uint64_t* sk, int step, int B, uint64_t* spl_seg,
                                                   int32_t* nspl_seg, int32_t* wtot)
 {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     uint64_t c = 0;
     bool keep = false;
     if (t < B - 1) {
-        c = sk[((int64_t)(t + 1) * ns) / B];
-        keep = t == 0 || c != sk[((int64_t)t * ns) / B];
+        c = sk[(t + 1) * step];
+        keep = t == 0 || c != sk[t * step];
     }
     const uint64_t kb = __ballot(keep);
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -667,18 +821,39 @@ __device__ __forceinline__ void ss_pick_splitters(const uint64_t* sk, int ns, in
     }
 }
 
+// The sample's keys of NB = 1024 into samp, from the segment's offset on: a
+// thread a key, so that the loads, a cache line each, come from many compute
+// units (16384 of them by the one workgroup that sorts them: 30 us).
+__global__ __launch_bounds__(256) void k_ss_gather(const double* __restrict__ r, const double* __restrict__ w,
+                                                   SortSegs S, uint64_t* __restrict__ samp)
+{
+    const int seg = blockIdx.y;
+    const int64_t n = S.off[seg + 1] - S.off[seg];
+    const int ns = kSsOversample * (int)((n + kSsBucketMean - 1) / kSsBucketMean);
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (n <= kSsBucketMean || i >= ns) return;
+    bool ok;
+    samp[S.off[seg] + i] = sort_key((seg ? w : r)[ss_sample_pos(i, ns, n)], ok);
+}
+
 // One workgroup of 1024 threads per segment: a stratified sample of the keys
-// sorted in LDS (bitonic for the 1024-key samples of NB = 64; LSD on 8-bit
-// digits over the bits that vary, 16 waves of up to 16 rounds, for the
-// 16384-key samples of NB = 1024), then its quantiles as splitters.
+// sorted in LDS (by bins; where those are too full, bitonic for the 1024-key
+// samples of NB = 64 and LSD on 8-bit digits over the bits that vary, 16 waves
+// of up to 16 rounds, for the 16384-key samples of NB = 1024), then its
+// quantiles as splitters.
 template <int NB>
 __global__ __launch_bounds__(1024) void k_ss_sample(const double* __restrict__ r, const double* __restrict__ w,
-                                                    SortSegs S, uint64_t* __restrict__ spl,
+                                                    const uint64_t* __restrict__ samp, SortSegs S,
+                                                    uint64_t* __restrict__ spl,
                                                     int32_t* __restrict__ nspl)
 {
     using C = SsCfg<NB>;
+    constexpr int kRounds = (C::kSample + 1023) / 1024;
     __shared__ uint64_t sk[C::kSample];
-    __shared__ int32_t wtot[16];
+    __shared__ uint64_t quant[C::kMaxSpl + 1];
+    __shared__ int32_t bin[kBins];             // also the radix sort's digit counts
+    __shared__ BinLds<16> bl;
+    int32_t* const wtot = bl.wtot;
     const int seg = blockIdx.x;
     const int64_t n = S.off[seg + 1] - S.off[seg];
     const double* __restrict__ x = seg ? w : r;
@@ -687,19 +862,37 @@ __global__ __launch_bounds__(1024) void k_ss_sample(const double* __restrict__ r
         if (threadIdx.x == 0) nspl[seg] = 0;
         return;
     }
-    const int ns = (int)(n < (int64_t)kSsOversample * B ? n : (int64_t)kSsOversample * B);
+    const int ns = kSsOversample * B;          // below n: a bucket has kSsBucketMean keys
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int rounds = (ns + 1024 - 1) / 1024;
+    uint64_t kr[kRounds];
+    int32_t none[kRounds];
+    #pragma unroll
+    for (int q = 0; q < kRounds; ++q) {
+        const int i = (wave * rounds + q) * 64 + lane;
+        kr[q] = 0ull;
+        none[q] = 0;
+        if (q < rounds && i < ns) {
+            if constexpr (NB == 64) {
+                bool ok;
+                kr[q] = sort_key(x[ss_sample_pos(i, ns, n)], ok);
+            } else {
+                kr[q] = samp[S.off[seg] + i];
+            }
+        }
+    }
+    if (bin_sort<16>(kr, none, rounds, ns, sk, (int32_t*)nullptr, bin, bl, [&](int i, uint64_t k, int32_t) {
+            if (i % kSsOversample == 0) quant[i / kSsOversample] = k;
+        })) {
+        __syncthreads();
+        ss_pick_splitters(quant, 1, B, spl + seg * C::kMaxSpl, nspl + seg, wtot);
+        return;
+    }
+    __syncthreads();
     if constexpr (NB == 64) {
         int np2 = 1;
         while (np2 < ns) np2 <<= 1;
-        {
-            uint64_t k = ~0ull;
-            if (t < ns) {
-                bool ok;
-                k = sort_key(x[ss_sample_pos(t, ns, n)], ok);
-            }
-            sk[t] = k;
-        }
+        sk[t] = t < ns ? kr[0] : ~0ull;        // one round: lane and wave in order
         __syncthreads();
         for (int k = 2; k <= np2; k <<= 1)
             for (int j = k >> 1; j > 0; j >>= 1) {
@@ -711,39 +904,18 @@ __global__ __launch_bounds__(1024) void k_ss_sample(const double* __restrict__ r
                 __syncthreads();
             }
     } else {
-        __shared__ int32_t wcnt[16][256];
-        __shared__ uint64_t red[32];
-        const int rounds = (ns + 1024 - 1) / 1024;
-        uint64_t kr[kSsRounds];
+        int32_t (*wcnt)[256] = reinterpret_cast<int32_t (*)[256]>(bin);
+        static_assert(kBins == 16 * 256, "digit counts of 16 waves");
         #pragma unroll
         for (int q = 0; q < kSsRounds; ++q) {
             const int i = (wave * rounds + q) * 64 + lane;
-            kr[q] = 0ull;
-            if (q < rounds && i < ns) {
-                bool ok;
-                kr[q] = sort_key(x[ss_sample_pos(i, ns, n)], ok);
-                sk[i] = kr[q];
-            }
+            if (q < rounds && i < ns) sk[i] = kr[q];
         }
         // the bits in which the sample's keys differ
-        uint64_t lo = ~0ull, hi = 0ull;
-        #pragma unroll
-        for (int q = 0; q < kSsRounds; ++q) {
-            const int i = (wave * rounds + q) * 64 + lane;
-            if (q < rounds && i < ns) { lo = kr[q] < lo ? kr[q] : lo; hi = kr[q] > hi ? kr[q] : hi; }
-        }
-        #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const uint64_t a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
-            lo = a < lo ? a : lo;
-            hi = b > hi ? b : hi;
-        }
-        if (lane == 0) { red[2 * wave] = lo; red[2 * wave + 1] = hi; }
-        __syncthreads();
         uint64_t kmin = ~0ull, kmax = 0ull;
         for (int v = 0; v < 16; ++v) {
-            kmin = red[2 * v] < kmin ? red[2 * v] : kmin;
-            kmax = red[2 * v + 1] > kmax ? red[2 * v + 1] : kmax;
+            kmin = bl.red[2 * v] < kmin ? bl.red[2 * v] : kmin;
+            kmax = bl.red[2 * v + 1] > kmax ? bl.red[2 * v + 1] : kmax;
         }
         const uint64_t diff = kmin ^ kmax;
         const int passes = diff ? (64 - __clzll((long long)diff) + 7) / 8 : 0;
@@ -783,7 +955,7 @@ __global__ __launch_bounds__(1024) void k_ss_sample(const double* __restrict__ r
         }
         __syncthreads();
     }
-    ss_pick_splitters(sk, ns, B, spl + seg * C::kMaxSpl, nspl + seg, wtot);
+    ss_pick_splitters(sk, kSsOversample, B, spl + seg * C::kMaxSpl, nspl + seg, wtot);
 }
 
 // Per tile: the bucket counts (tile-major, NB per tile) and errs[tile] (1 if
@@ -841,36 +1013,42 @@ __global__ __launch_bounds__(kSsThreads) void k_ss_count(const double* __restric
     if (threadIdx.x == 0) errs[tile] = any_bad ? 1 : 0;
 }
 
-// Per segment, one thread per bucket: the bucket's counts over the segment's
-// tiles become exclusive offsets, btot receives the bucket sizes and bstart
-// their exclusive scan over the buckets (NB = 64: one wave; NB = 1024: one
-// 1024-thread workgroup).
+// A workgroup takes 64 buckets of one segment: their counts over the segment's
+// tiles become exclusive offsets, and btot receives the bucket sizes.  Its
+// waves split the tiles, all of a wave's loads in flight at once (a bucket's
+// counts one after the other are a chain of latencies: 17 us at 123 tiles).
+constexpr int kSsScanWaves = 8;
+
 template <int NB>
-__global__ __launch_bounds__(NB) void k_ss_scan(SortSegs S, int32_t* __restrict__ cnt,
-                                                int32_t* __restrict__ bstart, int32_t* __restrict__ btot)
+__global__ __launch_bounds__(64 * kSsScanWaves) void k_ss_scan(SortSegs S, int32_t* __restrict__ cnt,
+                                                               int32_t* __restrict__ btot)
 {
-    const int seg = blockIdx.x, b = threadIdx.x;
-    const int t0 = S.tile0[seg], nt = S.tile0[seg + 1] - t0;
+    constexpr int kTiles = (SsCfg<NB>::kMaxLen + kSsTile - 1) / kSsTile;    // of a segment, at most
+    constexpr int kPer = (kTiles + kSsScanWaves - 1) / kSsScanWaves;
+    __shared__ int32_t part[kSsScanWaves][64];
+    const int seg = blockIdx.x / (NB / 64), lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int b = (blockIdx.x % (NB / 64)) * 64 + lane;
+    const int nt = S.tile0[seg + 1] - S.tile0[seg];
+    int32_t* c = cnt + (int64_t)S.tile0[seg] * NB + b;
+    int32_t v[kPer], sum = 0;
+    #pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int t = wave * kPer + q;
+        v[q] = t < nt ? c[(int64_t)t * NB] : 0;
+    }
+    #pragma unroll
+    for (int q = 0; q < kPer; ++q) sum += v[q];
+    part[wave][lane] = sum;
+    __syncthreads();
     int32_t run = 0;
-    for (int t = 0; t < nt; t += 16) {
-        int32_t v[16];
-        #pragma unroll
-        for (int q = 0; q < 16; ++q) v[q] = t + q < nt ? cnt[(int64_t)(t0 + t + q) * NB + b] : 0;
-        #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            if (t + q < nt) cnt[(int64_t)(t0 + t + q) * NB + b] = run;
-            run += v[q];
-        }
+    for (int u = 0; u < wave; ++u) run += part[u][lane];
+    #pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int t = wave * kPer + q;
+        if (t < nt) c[(int64_t)t * NB] = run;
+        run += v[q];
     }
-    btot[seg * NB + b] = run;
-    if constexpr (NB == 64) {
-        bstart[seg * NB + b] = wave_incl_scan(run) - run;
-    } else {
-        __shared__ int32_t wsum[1][16];
-        int32_t e[1] = {run}, tot[1];
-        block_scan<int32_t, 1, NB / 64>(e, tot, wsum);
-        bstart[seg * NB + b] = e[0];
-    }
+    if (wave == kSsScanWaves - 1) btot[seg * NB + b] = run;
 }
 
 // Stable scatter of a tile into the buckets, through LDS: wave v owns the
@@ -878,14 +1056,16 @@ __global__ __launch_bounds__(NB) void k_ss_scan(SortSegs S, int32_t* __restrict_
 // among the equal buckets of their round plus the wave's earlier keys of that
 // bucket; one block step turns the waves' counts into LDS starts; the staged
 // tile is written out with consecutive threads on consecutive addresses of
-// each bucket's run.
+// each bucket's run.  Every tile adds up the buckets' starts from their sizes;
+// a segment's first tile stores them.
 template <int NB>
 __global__ __launch_bounds__(kSsThreads) void k_ss_scatter(const double* __restrict__ r,
                                                            const double* __restrict__ w, SortSegs S,
                                                            const uint64_t* __restrict__ spl,
                                                            const int32_t* __restrict__ nspl,
                                                            const int32_t* __restrict__ cnt,
-                                                           const int32_t* __restrict__ bstart,
+                                                           const int32_t* __restrict__ btot,
+                                                           int32_t* __restrict__ bstart,
                                                            uint64_t* __restrict__ kout, int32_t* __restrict__ vout)
 {
     using C = SsCfg<NB>;
@@ -898,7 +1078,7 @@ __global__ __launch_bounds__(kSsThreads) void k_ss_scatter(const double* __restr
     __shared__ int32_t wcnt[kWaves][NB];
     __shared__ int32_t gbase[NB];
     __shared__ int32_t lstart[NB];
-    __shared__ int32_t wtot[kWaves];
+    __shared__ int32_t wtot[kWaves], btsum[kWaves];
     const int tile = blockIdx.x;
     const int seg = tile_segment(S, tile);
     const int lt = tile - S.tile0[seg];
@@ -953,25 +1133,29 @@ __global__ __launch_bounds__(kSsThreads) void k_ss_scatter(const double* __restr
                 wcnt[v][b] = run;
                 run += a;
             }
-            gbase[b] = base + bstart[seg * NB + b] + cnt[(int64_t)tile * NB + b];
+            const int32_t size = btot[seg * NB + b], at = wave_incl_scan(size) - size;
+            if (lt == 0) bstart[seg * NB + b] = at;
+            gbase[b] = base + at + cnt[(int64_t)tile * NB + b];
         }
     } else {
         // thread t: buckets BPT t .. BPT t + BPT - 1
         constexpr int BPT = NB / kSsThreads;
         const int b0 = BPT * threadIdx.x;
-        int32_t c[BPT], sum = 0;
+        int32_t c[BPT], size[BPT], sum = 0, bsum = 0;
         #pragma unroll
         for (int j = 0; j < BPT; ++j) {
             c[j] = 0;
             #pragma unroll
             for (int v = 0; v < kWaves; ++v) c[j] += wcnt[v][b0 + j];
             sum += c[j];
+            size[j] = btot[seg * NB + b0 + j];
+            bsum += size[j];
         }
-        const int32_t incl = wave_incl_scan(sum);
-        if (lane == 63) wtot[wave] = incl;
+        const int32_t incl = wave_incl_scan(sum), bincl = wave_incl_scan(bsum);
+        if (lane == 63) { wtot[wave] = incl; btsum[wave] = bincl; }
         __syncthreads();
-        int32_t ex = incl - sum;
-        for (int v = 0; v < wave; ++v) ex += wtot[v];
+        int32_t ex = incl - sum, at = bincl - bsum;
+        for (int v = 0; v < wave; ++v) { ex += wtot[v]; at += btsum[v]; }
         #pragma unroll
         for (int j = 0; j < BPT; ++j) {
             const int b = b0 + j;
@@ -983,7 +1167,9 @@ __global__ __launch_bounds__(kSsThreads) void k_ss_scatter(const double* __restr
                 wcnt[v][b] = run;
                 run += a;
             }
-            gbase[b] = base + bstart[seg * NB + b] + cnt[(int64_t)tile * NB + b];
+            if (lt == 0) bstart[seg * NB + b] = at;
+            gbase[b] = base + at + cnt[(int64_t)tile * NB + b];
+            at += size[j];
             ex += c[j];
         }
     }
@@ -1043,41 +1229,45 @@ __global__ __launch_bounds__(kSsLocalThreads) void k_ss_local(SortSegs S, const 
         }
         return;
     }
-    uint64_t kr[kSsRounds];
-    int32_t vr[kSsRounds];
+    uint64_t kr[kSsLocalRounds];
+    int32_t vr[kSsLocalRounds];
     if (size <= kSsCap) {
         const int rounds = ss_rounds(size);
         #pragma unroll
-        for (int q = 0; q < kSsRounds; ++q) {
+        for (int q = 0; q < kSsLocalRounds; ++q) {
             const int i = (wave * rounds + q) * 64 + lane;
             const bool in = q < rounds && i < size;
             kr[q] = in ? kin[start + i] : 0ull;
             vr[q] = in ? vin[start + i] : 0;
         }
+        if (bin_sort<kWaves>(kr, vr, rounds, size, L.key, L.val, L.bin, L.bl,
+                             [&](int i, uint64_t k, int32_t v) { kout[start + i] = k; vout[start + i] = v; }))
+            return;
+        __syncthreads();
         ss_block_sort(kr, vr, size, L);
         #pragma unroll
-        for (int q = 0; q < kSsRounds; ++q) {
+        for (int q = 0; q < kSsLocalRounds; ++q) {
             const int i = (wave * rounds + q) * 64 + lane;
             if (q < rounds && i < size) { kout[start + i] = kr[q]; vout[start + i] = vr[q]; }
         }
         return;
     }
     // A bucket beyond the LDS: LSD passes through global memory, chunk by
-    // chunk (kSsCap keys, kSsRounds rounds per wave) in order, between
+    // chunk (kSsCap keys, kSsLocalRounds rounds per wave) in order, between
     // (kin, vin) and (kout, vout); a chunk's keys are written straight to
     // their places.  Data written by an earlier pass is read with
     // cache-coherent loads.
-    int dg[kSsRounds], rk[kSsRounds];
+    int dg[kSsLocalRounds], rk[kSsLocalRounds];
     uint64_t kmin = ~0ull, kmax = 0ull;
     for (int32_t c0 = 0; c0 < size; c0 += kSsCap) {
         const int nv = size - c0 < kSsCap ? size - c0 : kSsCap;
         #pragma unroll
-        for (int q = 0; q < kSsRounds; ++q) {
-            const int i = (wave * kSsRounds + q) * 64 + lane;
+        for (int q = 0; q < kSsLocalRounds; ++q) {
+            const int i = (wave * kSsLocalRounds + q) * 64 + lane;
             kr[q] = i < nv ? kin[start + c0 + i] : 0ull;
         }
         uint64_t lo, hi;
-        ss_key_range(kr, kSsRounds, nv, L.red, lo, hi);
+        ss_key_range(kr, kSsLocalRounds, nv, L.red, lo, hi);
         kmin = lo < kmin ? lo : kmin;
         kmax = hi > kmax ? hi : kmax;
     }
@@ -1091,41 +1281,41 @@ __global__ __launch_bounds__(kSsLocalThreads) void k_ss_local(SortSegs S, const 
         for (int32_t c0 = 0; c0 < size; c0 += kSsCap) {
             const int nv = size - c0 < kSsCap ? size - c0 : kSsCap;
             #pragma unroll
-            for (int q = 0; q < kSsRounds; ++q) {
-                const int i = (wave * kSsRounds + q) * 64 + lane;
+            for (int q = 0; q < kSsLocalRounds; ++q) {
+                const int i = (wave * kSsLocalRounds + q) * 64 + lane;
                 kr[q] = i < nv ? load_coherent(ks + start + c0 + i) : 0ull;
             }
-            ss_rank_digits(kr, 8 * p, kSsRounds, nv, L.wcnt, dg, rk);   // wcnt accumulates over the chunks
+            ss_rank_digits(kr, 8 * p, kSsLocalRounds, nv, L.wcnt, dg, rk);   // wcnt accumulates over the chunks
         }
         __syncthreads();
         {
             int32_t c = 0;
-            #pragma unroll
-            for (int v = 0; v < kWaves; ++v) c += L.wcnt[v][threadIdx.x];
+            if (threadIdx.x < 256)
+                for (int v = 0; v < kWaves; ++v) c += L.wcnt[v][threadIdx.x];
             const int32_t incl = wave_incl_scan(c);
             if (lane == 63) L.wtot[wave] = incl;
             __syncthreads();
             int32_t ex = incl - c;
             for (int v = 0; v < wave; ++v) ex += L.wtot[v];
-            gb[threadIdx.x] = ex;   // the digit's next free place in the bucket
+            if (threadIdx.x < 256) gb[threadIdx.x] = ex;   // the digit's next free place in the bucket
         }
         __syncthreads();
         for (int32_t c0 = 0; c0 < size; c0 += kSsCap) {
             const int nv = size - c0 < kSsCap ? size - c0 : kSsCap;
             #pragma unroll
-            for (int q = 0; q < kSsRounds; ++q) {
-                const int i = (wave * kSsRounds + q) * 64 + lane;
+            for (int q = 0; q < kSsLocalRounds; ++q) {
+                const int i = (wave * kSsLocalRounds + q) * 64 + lane;
                 kr[q] = i < nv ? load_coherent(ks + start + c0 + i) : 0ull;
                 vr[q] = i < nv ? load_coherent(vs + start + c0 + i) : 0;
             }
             for (int i = threadIdx.x; i < kWaves * 256; i += kSsLocalThreads) (&L.wcnt[0][0])[i] = 0;
             __syncthreads();
-            ss_rank_digits(kr, 8 * p, kSsRounds, nv, L.wcnt, dg, rk);
+            ss_rank_digits(kr, 8 * p, kSsLocalRounds, nv, L.wcnt, dg, rk);
             __syncthreads();
             const int32_t c = ss_digit_starts(L.wcnt, 0, L.wtot);   // chunk-local starts
             __syncthreads();
             #pragma unroll
-            for (int q = 0; q < kSsRounds; ++q) {
+            for (int q = 0; q < kSsLocalRounds; ++q) {
                 if (dg[q] >= 0) {
                     // the digit's next free place + the key's offset among the chunk's keys of that digit
                     const int32_t dst = gb[dg[q]] + (L.wcnt[wave][dg[q]] + rk[q]) - L.wcnt[0][dg[q]];
@@ -1134,7 +1324,7 @@ __global__ __launch_bounds__(kSsLocalThreads) void k_ss_local(SortSegs S, const 
                 }
             }
             __syncthreads();
-            gb[threadIdx.x] += c;
+            if (threadIdx.x < 256) gb[threadIdx.x] += c;
             __syncthreads();
         }
         uint64_t* tk = ks; ks = kd; kd = tk;
@@ -2126,11 +2316,10 @@ static SortSegs sort_segs(int32_t na, int32_t nb)
     return S;
 }
 
-// The 1024-slot splitter sort is taken up to 2^18 keys: measured faster than
-// the LSD sort there (200000 keys: plan 0.263 against 0.287 ms); at 1e6 its
-// sample and bucket sorts (ballot ranking, LDS round trips per round) cost
-// 342 us of GPU time against the LSD sort's 276.
-constexpr int32_t kSsLargeMax = 1 << 18;
+// The 1024-slot splitter sort is taken as far as its slots go: its launches
+// take 112 us for 2 x 1e6 keys, 128 with the gaps between them; the LSD sort's
+// 24 take 276 and 397.  Beyond 2^20 keys a bucket would outgrow the LDS.
+constexpr int32_t kSsLargeMax = 1 << 20;
 static_assert(kSsLargeMax <= SsCfg<1024>::kMaxLen, "splitter sort capacity");
 
 enum class SortPath { small, splitter64, splitter1024, lsd };
@@ -2167,11 +2356,13 @@ static hipError_t launch_splitter_sort(const double* r, int32_t na, const double
     int32_t* bstart = hist + C::kStartOff;
     int32_t* btot = hist + C::kTotOff;
     int32_t* cnt = hist + C::kCntOff;
-    hipLaunchKernelGGL(k_ss_sample<NB>, dim3(2), dim3(1024), 0, s, r, w, S, spl, nspl);
+    // k0 holds the sample's keys until the last kernel writes it
+    if (NB > 64) hipLaunchKernelGGL(k_ss_gather, dim3(C::kSample / 256, 2), dim3(256), 0, s, r, w, S, k0);
+    hipLaunchKernelGGL(k_ss_sample<NB>, dim3(2), dim3(1024), 0, s, r, w, k0, S, spl, nspl);
     hipLaunchKernelGGL(k_ss_count<NB>, dim3(tiles), dim3(kSsThreads), 0, s, r, w, S, spl, nspl, cnt, errs);
-    hipLaunchKernelGGL(k_ss_scan<NB>, dim3(2), dim3(NB), 0, s, S, cnt, bstart, btot);
-    hipLaunchKernelGGL(k_ss_scatter<NB>, dim3(tiles), dim3(kSsThreads), 0, s, r, w, S, spl, nspl, cnt, bstart, k1,
-                       v1);
+    hipLaunchKernelGGL(k_ss_scan<NB>, dim3(2 * NB / 64), dim3(64 * kSsScanWaves), 0, s, S, cnt, btot);
+    hipLaunchKernelGGL(k_ss_scatter<NB>, dim3(tiles), dim3(kSsThreads), 0, s, r, w, S, spl, nspl, cnt, btot, bstart,
+                       k1, v1);
     hipLaunchKernelGGL(k_ss_local<NB>, dim3(2 * NB), dim3(kSsLocalThreads), 0, s, S, nspl, bstart, btot, k1, v1,
                        k0, v0);
     return hipGetLastError();
