@@ -32,9 +32,21 @@ struct Arena {
     Panel* wlist;        // panels of points weighted on their own (pan_cap)
     LocalWork* lwork;    // the local blocks' rows by waves (lslot_cap)
     int32_t* dlist;      // direct blocks by the way they are applied (d_cap)
+    Node* stage;         // subtrees of the subdivision before they are numbered (node_cap); null: one workgroup
+    int32_t* sub;        // their roots and counts (kSubWords)
     int32_t pan_cap, lslot_cap;
     int32_t node_cap, l_cap, a_cap, d_cap, q_cap, litem_cap, aitem_cap, pad;
 };
+
+// Subtrees of a subdivision done side by side: the levels above them end
+// once a level has kSubFront nodes (so there are fewer than 2 kSubFront).
+constexpr int kSubFront = 128;
+constexpr int kSubTrees = 2 * kSubFront;
+// Words of Arena::sub: the number of subtrees and the blocks numbered above
+// them (nodes, local, asymptotic, direct), the level; from 8 on the roots
+// (j0, j1, k0, k1), then the counts (nodes, local, asymptotic, direct, level,
+// overflow, 2 unused).
+constexpr int kSubRoots = 8, kSubCounts = kSubRoots + 4 * kSubTrees, kSubWords = kSubCounts + 8 * kSubTrees;
 
 // Most partitions planned together (launch_planning_many).
 constexpr int kMaxPlanParts = 8;

@@ -1415,6 +1415,12 @@ __device__ __forceinline__ void staircases(const PlanArgs& a)
 // SplitIndices of Sec. 4.1 (candidate rows equispaced over the rows that hold
 // a local entry, minimal mixed area, ties to the smaller row).  Numbering is
 // deterministic: nodes in level order, children in (parent, position) order.
+//
+// A level is a chain of latencies (its nodes' headers, their candidates, the
+// scans, the stores: 5 us and more per 256 nodes), so for large transforms the
+// first workgroup stops at a level of kSubFront nodes or more, a workgroup
+// each subdivides the subtrees below (k_subtrees), and a third kernel numbers
+// them one after the other and writes their blocks (k_subtree_blocks).
 // ---------------------------------------------------------------------------
 // The split of one mixed node (Alg. 1) and the classes of its children.
 struct NodeSplit {
@@ -1425,7 +1431,9 @@ struct NodeSplit {
 // Candidate counts up to this are evaluated with all their loads in flight.
 constexpr int32_t kSplitUnroll = 16;
 
-// kj1 = K[R.j1], kj0 = K[R.j0], jc = Jc[R.k0], loaded by the caller.
+// kj1 = K[R.j1], kj0 = K[R.j0], jc = Jc[R.k0], loaded by the caller.  G
+// consecutive lanes (a power of two up to kSplitUnroll) share a node.
+template <int G>
 __device__ __forceinline__ NodeSplit split_node(const Rect& R, int32_t kj1, int32_t kj0, int32_t jc,
                                                 const int32_t* __restrict__ K, int64_t min_size, int32_t ncand)
 {
@@ -1443,12 +1451,18 @@ __device__ __forceinline__ NodeSplit split_node(const Rect& R, int32_t kj1, int3
         int32_t span = jl - R.j0;
         // more candidates than rows is every row (the exact optimum)
         int32_t nc = span > 0 ? (ncand <= span ? ncand : span + 1) : 1;
-        // candidate c is row j0 + floor(c span / (nc - 1)); the quotient is
-        // formed in double, exactly: c span < 2^53, and a non-integer quotient
-        // is at least 1/(nc-1) away from an integer
+        // candidate c is row j0 + floor(c span / (nc - 1)): the product with the
+        // divisor's reciprocal is within one of the quotient, and the remainder
+        // (exact: c span < 2^53) sets it right.  (A division per candidate
+        // made a level 7 us, of which this function 4.7.)
+        const double dspan = (double)span, div = (double)(nc > 1 ? nc - 1 : 1), rdiv = 1.0 / div;
+        const bool every = nc == span + 1;                  // every row
         auto row_of = [&](int32_t c) {
-            if (nc == span + 1) return R.j0 + c;            // every row
-            return span > 0 ? R.j0 + (int32_t)floor((double)c * (double)span / (double)(nc - 1)) : R.j0;
+            const double x = (double)c * dspan;
+            double q = floor(x * rdiv);
+            const double rem = __builtin_fma(-q, div, x);
+            q += rem < 0.0 ? -1.0 : rem >= div ? 1.0 : 0.0;
+            return R.j0 + (every ? c : (int32_t)q);
         };
         auto consider = [&](int32_t j, int32_t kraw) {
             int32_t k = kraw - 1;
@@ -1459,15 +1473,26 @@ __device__ __forceinline__ NodeSplit split_node(const Rect& R, int32_t kj1, int3
         };
         if (nc <= kSplitUnroll) {
             // all candidate loads in flight together, then taken in order
-            int32_t jv[kSplitUnroll], kv[kSplitUnroll];
+            constexpr int32_t kPer = kSplitUnroll / G;
+            const int32_t sub = threadIdx.x % G;
+            int32_t jv[kPer], kv[kPer];
             #pragma unroll
-            for (int32_t c = 0; c < kSplitUnroll; ++c) {
-                jv[c] = row_of(c < nc ? c : 0);
-                kv[c] = K[jv[c]];
+            for (int32_t q = 0; q < kPer; ++q) {
+                const int32_t c = sub + G * q;
+                jv[q] = row_of(c < nc ? c : 0);
+                kv[q] = K[jv[q]];
             }
             #pragma unroll
-            for (int32_t c = 0; c < kSplitUnroll; ++c)
-                if (c < nc) consider(jv[c], kv[c]);
+            for (int32_t q = 0; q < kPer; ++q)
+                if (sub + G * q < nc) consider(jv[q], kv[q]);
+            // the lanes' minima: rows increase with the candidate, so ties go
+            // to the smaller row
+            #pragma unroll
+            for (int32_t g = 1; g < G; g <<= 1) {
+                const int64_t om = __shfl_xor(best, g);
+                const int32_t oj = __shfl_xor(js, g), ok = __shfl_xor(ks, g);
+                if (om < best || (om == best && oj < js)) { best = om; js = oj; ks = ok; }
+            }
         } else {
             // batches of kSplitUnroll candidates with their loads in flight
             for (int32_t c0 = 0; c0 < nc; c0 += kSplitUnroll) {
@@ -1496,11 +1521,8 @@ __device__ __forceinline__ NodeSplit split_node(const Rect& R, int32_t kj1, int3
     return o;
 }
 
-// Nodes per thread per pass.  (Several per thread serialise their candidate
-// loads within the thread, and a pass waits for its slowest thread: one is
-// faster.)
-constexpr int kSubNpt = 1;
-// One workgroup does the whole subdivision.  256 threads rather than 1024:
+// Workgroups of the subdivision, a node a thread (several a thread would
+// serialise their candidate loads).  256 threads rather than 1024:
 // a 1024-thread workgroup needs a compute unit with sixteen free wave slots,
 // which the execution running beside the plan rarely leaves.
 constexpr int kSubThreads = 256;
@@ -1514,119 +1536,104 @@ __device__ __forceinline__ DBlock direct_block(int32_t j0, int32_t j1, int32_t k
     return DBlock{j0, j1, k0, k1, 0, 0, 0.0, 0.0, 0.0, 0.0};
 }
 
-__device__ __forceinline__ void subdivide(const PlanArgs& a)
+// Counts of a subdivision: nodes, blocks of each kind, levels; overflow = 1
+// where a table was too small, 2 where there are too many levels.
+struct SubCounts {
+    int32_t nodes, l, a, d, level, overflow;
+};
+
+__device__ __forceinline__ LBlock local_block(int32_t j0, int32_t j1, int32_t k0, int32_t k1, int32_t level)
+{
+    LBlock b;
+    b.j0 = j0; b.j1 = j1; b.k0 = k0; b.k1 = k1;
+    b.R = 0.0; b.item0 = 0; b.nitems = 0; b.level = level;
+    b.K = 0; b.pr = 0; b.slot0 = 0; b.D = 0.0; b.rw = 0.0;
+    return b;
+}
+
+__device__ __forceinline__ ABlock asymptotic_block(int32_t j0, int32_t j1, int32_t k0, int32_t k1, int32_t level)
+{
+    ABlock b = {};
+    b.j0 = j0; b.j1 = j1; b.k0 = k0; b.k1 = k1; b.level = level;
+    return b;
+}
+
+// The levels from the n_cur = 1 block in lq[0][0] on, counted on from c.
+// SUB: nodes alone, into nodes[0 .. node_cap), with the subtree's own numbers;
+// else nodes and blocks into A's tables, up to a level of `stop` nodes (whose
+// blocks are then in lq[*buf], *left of them).  q0, q1 (q_cap entries): queue
+// entries past the LDS.
+template <bool SUB>
+__device__ __forceinline__ void subdivide_levels(const PlanArgs& a, Rect (*lq)[kSubLds], int32_t (*wsum)[16],
+                                                 Node* __restrict__ nodes, int32_t node_cap, Rect* q0, Rect* q1,
+                                                 int32_t q_cap, int32_t stop, SubCounts& c, int32_t* left, int* buf)
 {
     const int32_t* __restrict__ K = a.K;
     const int32_t* __restrict__ Jc = a.Jc;
-    const int32_t* __restrict__ errs = a.errs;
-    Summary* __restrict__ sum = a.sum;
     const Arena& A = a.A;
-    const int32_t m = a.P.m, n = a.P.n, ncand = a.ncand, n_errs = a.n_errs;
+    const int32_t ncand = a.ncand;
     const int64_t min_size = a.min_size;
-    __shared__ int32_t wsum[4][16];
-    __shared__ Rect lq[2][kSubLds];
-    int tid = threadIdx.x;
-    // the summary starts clear (this is the first planning kernel to use it),
-    // with the input check's verdict
-    int bad = 0;
-    for (int32_t i = tid; i < n_errs; i += kSubThreads) bad |= errs[i];
-    bad = __syncthreads_or(bad);
-    if (tid == 0) {
-        *sum = Summary{};
-        sum->domain_error = bad ? 1 : 0;
-    }
-    Rect* cur = A.q0;
-    Rect* nxt = A.q1;
+    const int tid = threadIdx.x;
+    Rect* cur = q0;
+    Rect* nxt = q1;
     int cb = 0;                                      // LDS buffer of the current level
-    int32_t n_cur = (m > 0 && n > 0) ? 1 : 0;
-    if (tid == 0 && n_cur) lq[0][0] = Rect{0, m - 1, 0, n - 1};
-    int32_t n_nodes = 0, n_l = 0, n_a = 0, n_d = 0;
-    int32_t overflow = 0;
-    int32_t level = 0;
-    __syncthreads();
-    while (n_cur > 0) {
+    int32_t n_cur = 1;
+    int32_t n_nodes = c.nodes, n_l = c.l, n_a = c.a, n_d = c.d, level = c.level, overflow = 0;
+    while (n_cur > 0 && n_cur < stop) {
         ++level;
         int32_t n_next = 0;
-        for (int32_t c0 = 0; c0 < n_cur; c0 += kSubThreads * kSubNpt) {
-            const int32_t i0 = c0 + tid * kSubNpt;
-            Rect R[kSubNpt];
-            NodeSplit S[kSubNpt];
-            int32_t cnt[4] = {0, 0, 0, 0};
-            int32_t kj1[kSubNpt], kj0[kSubNpt], jc[kSubNpt];
-            #pragma unroll
-            for (int q = 0; q < kSubNpt; ++q) {
-                bool act = i0 + q < n_cur;
-                R[q] = act ? (i0 + q < kSubLds ? lq[cb][i0 + q] : cur[i0 + q]) : Rect{0, 0, 0, 0};
+        for (int32_t c0 = 0; c0 < n_cur; c0 += kSubThreads) {
+            // a short level: sixteen lanes a node (a level 7 us with one, 3.5 so)
+            const bool wide = n_cur <= kSubThreads / kSplitUnroll;
+            const int32_t i = wide ? tid / kSplitUnroll : c0 + tid;
+            bool act = i < n_cur;
+            const Rect R = act ? (i < kSubLds ? lq[cb][i] : cur[i - kSubLds]) : Rect{0, 0, 0, 0};
+            const int32_t kj1 = K[R.j1], kj0 = K[R.j0], jc = Jc[R.k0];   // all header loads in flight together
+            NodeSplit o;
+            int32_t v[4] = {0, 0, 0, 0};
+            if (act) {
+                if (wide) o = split_node<kSplitUnroll>(R, kj1, kj0, jc, K, min_size, ncand);
+                else o = split_node<1>(R, kj1, kj0, jc, K, min_size, ncand);
             }
-            #pragma unroll
-            for (int q = 0; q < kSubNpt; ++q) {   // all header loads in flight together
-                kj1[q] = K[R[q].j1];
-                kj0[q] = K[R[q].j0];
-                jc[q] = Jc[R[q].k0];
+            act = act && (!wide || tid % kSplitUnroll == 0);
+            if (act) {
+                v[0] = o.cl;
+                v[1] = o.ca;
+                v[2] = (int)o.ur_d + (int)o.ll_d;
+                v[3] = (int)o.ur_m + (int)o.ll_m;
             }
-            #pragma unroll
-            for (int q = 0; q < kSubNpt; ++q) {
-                bool act = i0 + q < n_cur;
-                if (act) {
-                    S[q] = split_node(R[q], kj1[q], kj0[q], jc[q], K, min_size, ncand);
-                    cnt[0] += S[q].cl;
-                    cnt[1] += S[q].ca;
-                    cnt[2] += (int)S[q].ur_d + (int)S[q].ll_d;
-                    cnt[3] += (int)S[q].ur_m + (int)S[q].ll_m;
-                }
-            }
-            int32_t v[4] = {cnt[0], cnt[1], cnt[2], cnt[3]};
             int32_t tot[4];
             block_scan<int32_t, 4, kSubThreads / 64>(v, tot, wsum);
             int32_t l_slot = n_l + v[0], a_slot = n_a + v[1], d_slot = n_d + v[2], m_slot = n_next + v[3];
             const int32_t next_base = n_nodes + n_cur;   // first node index of the next level
-            #pragma unroll
-            for (int q = 0; q < kSubNpt; ++q) {
-                if (i0 + q >= n_cur) continue;
-                const Rect& Rq = R[q];
-                const NodeSplit& o = S[q];
-                int32_t node = n_nodes + i0 + q;
+            if (act) {
+                const int32_t node = n_nodes + i;
                 Node nd;
-                nd.j0 = Rq.j0; nd.j1 = Rq.j1; nd.k0 = Rq.k0; nd.k1 = Rq.k1;
+                nd.j0 = R.j0; nd.j1 = R.j1; nd.k0 = R.k0; nd.k1 = R.k1;
                 nd.js = o.js; nd.ks = o.ks;
                 nd.lblk = o.cl ? l_slot : -1;
                 nd.ablk = o.ca ? a_slot : -1;
                 nd.level = level; nd.pad = 0;
                 nd.ur = -1; nd.ll = -1;
-                if (o.ur_m) {
-                    const Rect c = Rect{Rq.j0, o.js, o.ks + 1, Rq.k1};
-                    if (m_slot < kSubLds) lq[cb ^ 1][m_slot] = c;
-                    else if (m_slot < A.q_cap) nxt[m_slot] = c;
-                    nd.ur = next_base + m_slot;
-                    ++m_slot;
-                }
-                if (o.ur_d) { if (d_slot < A.d_cap) A.db[d_slot] = direct_block(Rq.j0, o.js, o.ks + 1, Rq.k1); nd.ur = encode_direct(d_slot); ++d_slot; }
-                if (o.ll_m) {
-                    const Rect c = Rect{o.js + 1, Rq.j1, Rq.k0, o.ks};
-                    if (m_slot < kSubLds) lq[cb ^ 1][m_slot] = c;
-                    else if (m_slot < A.q_cap) nxt[m_slot] = c;
-                    nd.ll = next_base + m_slot;
-                    ++m_slot;
-                }
-                if (o.ll_d) { if (d_slot < A.d_cap) A.db[d_slot] = direct_block(o.js + 1, Rq.j1, Rq.k0, o.ks); nd.ll = encode_direct(d_slot); ++d_slot; }
-                if (node < A.node_cap) A.nodes[node] = nd;
-                if (o.cl) {
-                    if (l_slot < A.l_cap) {
-                        LBlock b;
-                        b.j0 = Rq.j0; b.j1 = o.js; b.k0 = Rq.k0; b.k1 = o.ks;
-                        b.R = 0.0; b.item0 = 0; b.nitems = 0; b.level = level;
-                        b.K = 0; b.pr = 0; b.slot0 = 0; b.D = 0.0; b.rw = 0.0;
-                        A.lb[l_slot] = b;
-                    }
-                    ++l_slot;
-                }
-                if (o.ca) {
-                    if (a_slot < A.a_cap) {
-                        ABlock b = {};
-                        b.j0 = o.js + 1; b.j1 = Rq.j1; b.k0 = o.ks + 1; b.k1 = Rq.k1; b.level = level;
-                        A.ab[a_slot] = b;
-                    }
-                    ++a_slot;
+                auto queue = [&](const Rect& child) {
+                    if (m_slot < kSubLds) lq[cb ^ 1][m_slot] = child;
+                    else if (m_slot - kSubLds < q_cap) nxt[m_slot - kSubLds] = child;
+                    return next_base + m_slot++;
+                };
+                auto direct = [&](int32_t j0, int32_t j1, int32_t k0, int32_t k1) {
+                    if constexpr (!SUB)
+                        if (d_slot < A.d_cap) A.db[d_slot] = direct_block(j0, j1, k0, k1);
+                    return encode_direct(d_slot++);
+                };
+                if (o.ur_m) nd.ur = queue(Rect{R.j0, o.js, o.ks + 1, R.k1});
+                if (o.ur_d) nd.ur = direct(R.j0, o.js, o.ks + 1, R.k1);
+                if (o.ll_m) nd.ll = queue(Rect{o.js + 1, R.j1, R.k0, o.ks});
+                if (o.ll_d) nd.ll = direct(o.js + 1, R.j1, R.k0, o.ks);
+                if (node < node_cap) nodes[node] = nd;
+                if constexpr (!SUB) {
+                    if (o.cl && l_slot < A.l_cap) A.lb[l_slot] = local_block(R.j0, o.js, R.k0, o.ks, level);
+                    if (o.ca && a_slot < A.a_cap)
+                        A.ab[a_slot] = asymptotic_block(o.js + 1, R.j1, o.ks + 1, R.k1, level);
                 }
             }
             n_l += tot[0];
@@ -1635,20 +1642,145 @@ __device__ __forceinline__ void subdivide(const PlanArgs& a)
             n_next += tot[3];
         }
         n_nodes += n_cur;
-        if (n_next > A.q_cap || n_nodes > A.node_cap) {
-            overflow = 1;
-            n_next = n_next > A.q_cap ? A.q_cap : n_next;
-        }
+        if (n_next - kSubLds > q_cap || n_nodes > node_cap) overflow = 1;
         if (level >= kMaxLevels) overflow = 2;
         Rect* t = cur; cur = nxt; nxt = t;
         cb ^= 1;
         n_cur = overflow ? 0 : n_next;
         __syncthreads();
     }
-    if (overflow != 2 && (n_l > A.l_cap || n_a > A.a_cap || n_d > A.d_cap)) overflow = 1;
+    c = SubCounts{n_nodes, n_l, n_a, n_d, level, overflow};
+    *left = n_cur;
+    *buf = cb;
+}
+
+__device__ __forceinline__ void store_counts(Summary* __restrict__ sum, const Arena& A, const SubCounts& c)
+{
+    sum->n_nodes = c.nodes; sum->n_l = c.l; sum->n_a = c.a; sum->n_d = c.d;
+    sum->levels = c.level;
+    sum->overflow = c.overflow != 2 && (c.nodes > A.node_cap || c.l > A.l_cap || c.a > A.a_cap || c.d > A.d_cap)
+                        ? 1 : c.overflow;
+}
+
+__device__ __forceinline__ void subdivide(const PlanArgs& a)
+{
+    Summary* __restrict__ sum = a.sum;
+    const Arena& A = a.A;
+    const int32_t m = a.P.m, n = a.P.n, n_errs = a.n_errs;
+    __shared__ int32_t wsum[4][16];
+    __shared__ Rect lq[2][kSubLds];
+    const int tid = threadIdx.x;
+    // the summary starts clear (this is the first planning kernel to use it),
+    // with the input check's verdict
+    int bad = 0;
+    for (int32_t i = tid; i < n_errs; i += kSubThreads) bad |= a.errs[i];
+    bad = __syncthreads_or(bad);
     if (tid == 0) {
-        sum->n_nodes = n_nodes; sum->n_l = n_l; sum->n_a = n_a; sum->n_d = n_d;
-        sum->levels = level; sum->overflow = overflow;
+        *sum = Summary{};
+        sum->domain_error = bad ? 1 : 0;
+        lq[0][0] = Rect{0, m - 1, 0, n - 1};
+    }
+    __syncthreads();
+    SubCounts c{0, 0, 0, 0, 0, 0};
+    int32_t left = 0;
+    int buf = 0;
+    if (m > 0 && n > 0)
+        subdivide_levels<false>(a, lq, wsum, A.nodes, A.node_cap, A.q0, A.q1, A.q_cap, A.sub ? kSubFront : INT32_MAX,
+                                c, &left, &buf);
+    if (A.sub) {
+        // the subtrees' roots are numbered after the nodes above them
+        if (tid < left) {
+            const Rect R = lq[buf][tid];
+            int32_t* q = A.sub + kSubRoots + 4 * tid;
+            q[0] = R.j0; q[1] = R.j1; q[2] = R.k0; q[3] = R.k1;
+        }
+        if (tid == 0) {
+            A.sub[0] = left;
+            A.sub[1] = c.nodes; A.sub[2] = c.l; A.sub[3] = c.a; A.sub[4] = c.d; A.sub[5] = c.level;
+        }
+    }
+    if (tid == 0) store_counts(sum, A, c);
+}
+
+// Subtree blockIdx.x: its nodes, numbered on their own, into its share of the
+// staging table, its counts into A.sub.
+__global__ __launch_bounds__(kSubThreads) void k_subtrees(PlanArgs a)
+{
+    const Arena& A = a.A;
+    __shared__ int32_t wsum[4][16];
+    __shared__ Rect lq[2][kSubLds];
+    const int t = blockIdx.x;
+    if (t >= A.sub[0]) return;
+    const int32_t* q = A.sub + kSubRoots + 4 * t;
+    if (threadIdx.x == 0) lq[0][0] = Rect{q[0], q[1], q[2], q[3]};
+    __syncthreads();
+    const int32_t cap = A.node_cap / kSubTrees, qcap = A.q_cap / kSubTrees;
+    SubCounts c{0, 0, 0, 0, A.sub[5], 0};
+    int32_t left;
+    int buf;
+    subdivide_levels<true>(a, lq, wsum, A.stage + (int64_t)t * cap, cap, A.q0 + (int64_t)t * qcap,
+                           A.q1 + (int64_t)t * qcap, qcap, INT32_MAX, c, &left, &buf);
+    if (threadIdx.x == 0) {
+        int32_t* o = A.sub + kSubCounts + 8 * t;
+        o[0] = c.nodes; o[1] = c.l; o[2] = c.a; o[3] = c.d; o[4] = c.level; o[5] = c.overflow;
+    }
+}
+
+// Numbers subtree blockIdx.x after the subtrees before it and writes its nodes
+// and blocks.
+__global__ __launch_bounds__(kSubThreads) void k_subtree_blocks(PlanArgs a)
+{
+    static_assert(kSubThreads == kSubTrees, "a thread a subtree");
+    const Arena& A = a.A;
+    __shared__ int32_t wsum[4][16];
+    __shared__ int32_t first[4], top[2];
+    const int t = blockIdx.x, tid = threadIdx.x;
+    const int32_t trees = A.sub[0];
+    if (t >= trees) return;
+    const int32_t* o = A.sub + kSubCounts + 8 * tid;
+    const bool on = tid < trees;
+    int32_t v[4] = {on ? o[0] - 1 : 0, on ? o[1] : 0, on ? o[2] : 0, on ? o[3] : 0};   // nodes below the root
+    int32_t tot[4];
+    if (tid == 0) top[0] = top[1] = 0;
+    __syncthreads();
+    if (on) { atomicMax(&top[0], o[4]); atomicMax(&top[1], o[5]); }
+    block_scan<int32_t, 4, kSubThreads / 64>(v, tot, wsum);
+    if (tid == t)
+        for (int q = 0; q < 4; ++q) first[q] = v[q];
+    __syncthreads();
+    const int32_t roots = A.sub[1];
+    if (t == 0 && tid == 0)
+        store_counts(a.sum, A, SubCounts{roots + trees + tot[0], A.sub[2] + tot[1], A.sub[3] + tot[2],
+                                         A.sub[4] + tot[3], top[0], top[1]});
+    if (top[1]) return;
+    const int32_t node0 = roots + trees + first[0] - 1;   // node i > 0 of the subtree is node0 + i
+    const int32_t l0 = A.sub[2] + first[1], a0 = A.sub[3] + first[2], d0 = A.sub[4] + first[3];
+    const int32_t nodes = A.sub[kSubCounts + 8 * t];
+    const Node* __restrict__ stage = A.stage + (int64_t)t * (A.node_cap / kSubTrees);
+    for (int32_t i = tid; i < nodes; i += kSubThreads) {
+        Node nd = stage[i];
+        if (nd.lblk >= 0) {
+            nd.lblk += l0;
+            if (nd.lblk < A.l_cap) A.lb[nd.lblk] = local_block(nd.j0, nd.js, nd.k0, nd.ks, nd.level);
+        }
+        if (nd.ablk >= 0) {
+            nd.ablk += a0;
+            if (nd.ablk < A.a_cap) A.ab[nd.ablk] = asymptotic_block(nd.js + 1, nd.j1, nd.ks + 1, nd.k1, nd.level);
+        }
+        if (nd.ur >= 0) nd.ur += node0;
+        else if (nd.ur <= -2) {
+            const int32_t d = decode_direct(nd.ur) + d0;
+            if (d < A.d_cap) A.db[d] = direct_block(nd.j0, nd.js, nd.ks + 1, nd.k1);
+            nd.ur = encode_direct(d);
+        }
+        if (nd.ll >= 0) nd.ll += node0;
+        else if (nd.ll <= -2) {
+            const int32_t d = decode_direct(nd.ll) + d0;
+            if (d < A.d_cap) A.db[d] = direct_block(nd.js + 1, nd.j1, nd.k0, nd.ks);
+            nd.ll = encode_direct(d);
+        }
+        const int32_t node = i == 0 ? roots + t : node0 + i;
+        if (node < A.node_cap) A.nodes[node] = nd;
     }
 }
 
@@ -1781,8 +1913,10 @@ __device__ __forceinline__ void block_params(const PlanArgs& a)
         B.nitems = (ncol + P.spread_chunk - 1) / P.spread_chunk;
         if (lane == 0) A.ab[b] = B;
     }
+    long long entries = 0;
     for (int32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < n_d; b += gridDim.x * blockDim.x) {
         DBlock E = A.db[b];
+        entries += (long long)(E.j1 - E.j0 + 1) * (E.k1 - E.k0 + 1);
         const double rlo = P.rs[E.k0], rhi = P.rs[E.k1], wlo = P.ws[E.j0], whi = P.ws[E.j1];
         E.C = 0.5 * (rlo + rhi);
         E.D = 0.5 * (wlo + whi);
@@ -1802,6 +1936,10 @@ __device__ __forceinline__ void block_params(const PlanArgs& a)
             if (2.0 * (nb * (2.0 * K + 20.0) + 60.0 * K * K + 2.0 * K * mb) < 45.0 * mb * nb) E.K = (int32_t)K;
         }
         A.db[b] = E;
+    }
+    if (__ballot(entries != 0)) {
+        for (int o = 32; o >= 1; o >>= 1) entries += __shfl_xor(entries, o);
+        if ((threadIdx.x & 63) == 0) atomicAdd((unsigned long long*)&sum->d_ent, (unsigned long long)entries);
     }
     for (int32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < n_l; b += gridDim.x * blockDim.x) {
         LBlock L = A.lb[b];
@@ -1847,81 +1985,68 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
     const PlanDev& P = a.P;
     const Arena& A = a.A;
     Summary* __restrict__ sum = a.sum;
-    __shared__ int64_t wsum[3][16];
+    __shared__ int64_t wsum[4][16];
     __shared__ int32_t cls_cnt[kMaxFftLog2 + 1];
     __shared__ int32_t cls_first[kMaxFftLog2 + 1];
-    __shared__ long long red[9][kPlanScanThreads / 64];
+    __shared__ long long red[8][kPlanScanThreads / 64];
+    constexpr int32_t kFftKept = 1024;
+    __shared__ int4 kept[kFftKept];                  // FFT-path blocks: block, class, place in it
+    __shared__ int32_t n_kept;
     if (sum->overflow) return;
-    const int32_t n_l = sum->n_l, n_a = sum->n_a, n_d = sum->n_d;
+    const int32_t n_l = sum->n_l, n_a = sum->n_a;
     int tid = threadIdx.x;
     const int nch = P.nch;
     if (tid <= kMaxFftLog2) cls_cnt[tid] = 0;
+    if (tid == 0) n_kept = 0;
     __syncthreads();
     // membership statistics: rows / columns of local and asymptotic blocks,
-    // direct entries, grid cells and FFT points, and the row-side work of the
+    // grid cells and FFT points, and the row-side work of the
     // asymptotic blocks (rows x cells on the direct-sum path, rows on the FFT
     // path), gathered in the same passes
-    constexpr int kStats = 9;
-    long long st[kStats] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    constexpr int kVpt = 8;                          // blocks per thread per pass (2048 per pass)
+    constexpr int kStats = 8;
+    long long st[kStats] = {0, 0, 0, 0, 0, 0, 0, 0};
+    constexpr int kVpt = 4;                          // blocks of a kind per thread per pass (1024 per pass)
     int64_t l_items = 0;                             // items + 2^32 slots
-    for (int32_t c0 = 0; c0 < n_l; c0 += kPlanScanThreads * kVpt) {
-        const int32_t i0 = c0 + tid * kVpt;
-        int64_t v[kVpt][1];
-        #pragma unroll
-        for (int k = 0; k < kVpt; ++k) {
-            v[k][0] = 0;
-            if (i0 + k < n_l) {
-                const LBlock L = A.lb[i0 + k];
-                v[k][0] = L.nitems + ((int64_t)local_slots(L) << 32);
-                st[0] += L.j1 - L.j0 + 1;
-                st[1] += L.k1 - L.k0 + 1;
-            }
-        }
-        int64_t tot[1];
-        block_scan_vpt<1, kVpt, kPlanScanThreads / 64>(v, tot, wsum);
-        #pragma unroll
-        for (int k = 0; k < kVpt; ++k)
-            if (i0 + k < n_l) {
-                const int64_t x = l_items + v[k][0];
-                A.lb[i0 + k].item0 = (int32_t)(x & 0xffffffff);
-                A.lb[i0 + k].slot0 = (int32_t)(x >> 32);
-            }
-        l_items += tot[0];
-    }
-    const int32_t n_lslots = (int32_t)(l_items >> 32);
-    l_items &= 0xffffffff;
     int64_t a_items = 0, grid = 0;
     int64_t pans = 0;                                // panels of points + 2^32 panels of frequencies
-    for (int32_t c0 = 0; c0 < n_a; c0 += kPlanScanThreads * kVpt) {
+    const int32_t n_la = n_l > n_a ? n_l : n_a;
+    for (int32_t c0 = 0; c0 < n_la; c0 += kPlanScanThreads * kVpt) {
         const int32_t i0 = c0 + tid * kVpt;
-        int64_t v[kVpt][3];
-        bool fft[kVpt];
+        int64_t v[kVpt][4];
         int32_t n2[kVpt];
         #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
-            v[k][0] = v[k][1] = v[k][2] = 0;
-            fft[k] = false;
+            v[k][0] = v[k][1] = v[k][2] = v[k][3] = 0;
             n2[k] = 0;
+            if (i0 + k < n_l) {
+                const LBlock L = A.lb[i0 + k];
+                v[k][3] = L.nitems + ((int64_t)local_slots(L) << 32);
+                st[0] += L.j1 - L.j0 + 1;
+                st[1] += L.k1 - L.k0 + 1;
+            }
             if (i0 + k < n_a) {
                 const ABlock B = A.ab[i0 + k];
                 v[k][0] = B.nitems;
                 v[k][1] = B.K > 0 ? 0 : B.fft ? (int64_t)B.N2 : (int64_t)B.N1;
                 v[k][2] = B.K > 0 ? (int64_t)B.pc + ((int64_t)B.pr << 32) : 0;
-                fft[k] = B.fft != 0;
-                n2[k] = B.N2;
+                n2[k] = B.fft ? B.N2 : 0;
                 const long long rows = B.j1 - B.j0 + 1;
                 st[2] += rows;
                 st[3] += B.k1 - B.k0 + 1;
-                if (B.fft) { st[6] += B.N2; st[8] += rows; }
-                else if (B.K == 0) { st[5] += B.N1; st[7] += rows * B.N1; }
+                if (B.fft) { st[5] += B.N2; st[7] += rows; }
+                else if (B.K == 0) { st[4] += B.N1; st[6] += rows * B.N1; }
             }
         }
-        int64_t tot[3];
-        block_scan_vpt<3, kVpt, kPlanScanThreads / 64>(v, tot, wsum);
+        int64_t tot[4];
+        block_scan_vpt<4, kVpt, kPlanScanThreads / 64>(v, tot, wsum);
         #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
             const int32_t i = i0 + k;
+            if (i < n_l) {
+                const int64_t x = l_items + v[k][3];
+                A.lb[i].item0 = (int32_t)(x & 0xffffffff);
+                A.lb[i].slot0 = (int32_t)(x >> 32);
+            }
             if (i < n_a) {
                 A.ab[i].item0 = (int32_t)(a_items + v[k][0]);
                 A.ab[i].grid_off = (grid + v[k][1]) * nch;
@@ -1929,13 +2054,20 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
                 const int64_t pq = pans + v[k][2];
                 A.ab[i].cpan0 = (int32_t)(pq & 0xffffffff);
                 A.ab[i].rpan0 = (int32_t)(pq >> 32);
-                if (fft[k]) atomicAdd(&cls_cnt[31 - __clz(n2[k])], 1);
+                if (n2[k] > 0) {
+                    const int32_t c = 31 - __clz(n2[k]), at = atomicAdd(&cls_cnt[c], 1);
+                    const int32_t e = atomicAdd(&n_kept, 1);
+                    if (e < kFftKept) kept[e] = int4{i, c, at, 0};
+                }
             }
         }
         a_items += tot[0];
         grid += tot[1];
         pans += tot[2];
+        l_items += tot[3];
     }
+    const int32_t n_lslots = (int32_t)(l_items >> 32);
+    l_items &= 0xffffffff;
     if (tid == 0) A.gslot[n_a] = grid;
     __syncthreads();
     if (tid == 0) {
@@ -1950,19 +2082,23 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
         sum->n_fft = f;
     }
     __syncthreads();
-    // FFT-path blocks grouped by size class (order inside a class is immaterial)
-    for (int32_t i = tid; i < n_a; i += kPlanScanThreads) {
-        ABlock B = A.ab[i];
-        if (B.fft) {
-            int c = 31 - __clz(B.N2);
-            int32_t slot = cls_first[c] + atomicAdd(&cls_cnt[c], 1);
-            A.fft_list[slot] = i;
-            A.ab[i].fft_slot = slot;
+    // FFT-path blocks grouped by size class (order inside a class is
+    // immaterial): those kept in LDS, or (too many) all blocks once more
+    if (n_kept <= kFftKept) {
+        for (int32_t e = tid; e < n_kept; e += kPlanScanThreads) {
+            const int4 q = kept[e];
+            const int32_t slot = cls_first[q.y] + q.z;
+            A.fft_list[slot] = q.x;
+            A.ab[q.x].fft_slot = slot;
         }
-    }
-    for (int32_t i = tid; i < n_d; i += kPlanScanThreads) {
-        DBlock Db = A.db[i];
-        st[4] += (long long)(Db.j1 - Db.j0 + 1) * (Db.k1 - Db.k0 + 1);
+    } else {
+        for (int32_t i = tid; i < n_a; i += kPlanScanThreads)
+            if (A.ab[i].fft) {
+                const int c = 31 - __clz(A.ab[i].N2);
+                const int32_t slot = cls_first[c] + atomicAdd(&cls_cnt[c], 1);
+                A.fft_list[slot] = i;
+                A.ab[i].fft_slot = slot;
+            }
     }
     for (int q = 0; q < kStats; ++q) {
         long long x = st[q];
@@ -1971,12 +2107,12 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
     }
     __syncthreads();
     if (tid == 0) {
-        long long t[kStats] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+        long long t[kStats] = {0, 0, 0, 0, 0, 0, 0, 0};
         for (int q = 0; q < kStats; ++q)
             for (int w2 = 0; w2 < kPlanScanThreads / 64; ++w2) t[q] += red[q][w2];
         sum->l_row = t[0]; sum->l_col = t[1]; sum->a_row = t[2]; sum->a_col = t[3];
-        sum->d_ent = t[4]; sum->dft_cells = t[5]; sum->fft_points = t[6];
-        sum->dft_row_cells = t[7]; sum->fft_rows = t[8];
+        sum->dft_cells = t[4]; sum->fft_points = t[5];
+        sum->dft_row_cells = t[6]; sum->fft_rows = t[7];
         sum->n_litems = (int32_t)l_items; sum->n_aitems = (int32_t)a_items;
         sum->max_nch = nch;
         sum->grid_cells = grid;
@@ -2210,7 +2346,7 @@ __device__ __forceinline__ void item_scan(const PlanArgs& a)
     const Arena& A = a.A;
     Summary* __restrict__ sum = a.sum;
     const int32_t* __restrict__ a_cells = a.a_cells;
-    __shared__ int64_t wsum[4][16];
+    __shared__ int64_t wsum[2][16];
     __shared__ int32_t n_dense_total, n_dense_all;
     if (sum->overflow) return;
     const int32_t n_ai = sum->n_aitems;
@@ -2219,6 +2355,7 @@ __device__ __forceinline__ void item_scan(const PlanArgs& a)
     // the dense items' total first: the medium ones follow them in the list
     {
         int32_t nd = 0, all = 0;
+        #pragma unroll 8
         for (int32_t i = threadIdx.x; i < n_ai; i += kPlanScanThreads) {
             const int32_t c = a_cells[i];
             const int kind = (c >> 28) & 3;
@@ -2235,36 +2372,35 @@ __device__ __forceinline__ void item_scan(const PlanArgs& a)
     int64_t run = 0, run_dense = 0, run_med = 0, run_rank = 0;
     for (int32_t c0 = 0; c0 < n_ai; c0 += kPlanScanThreads * kVpt) {
         const int32_t i0 = c0 + threadIdx.x * kVpt;
-        int64_t v[kVpt][4];
+        int64_t v[kVpt][2];                          // cells; a pass's dense, medium and rank items, 16 bits each
         int cls[kVpt];                               // 1 dense, 2 medium, 0 vector, 3 an item of a rank block
+        static_assert(kPlanScanThreads * kVpt < (1 << 16), "counts of a pass");
         #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
             const int32_t c = i0 + k < n_ai ? a_cells[i0 + k] : (1 << 30);
             v[k][0] = c & ((1 << 28) - 1);
             cls[k] = (c >> 30) ? 3 : (c >> 28) & 3;
-            v[k][1] = cls[k] == 1 ? 1 : 0;
-            v[k][2] = cls[k] == 2 ? 1 : 0;
-            v[k][3] = cls[k] == 3 ? 1 : 0;
+            v[k][1] = cls[k] ? int64_t(1) << (16 * (cls[k] - 1)) : 0;
         }
-        int64_t tot[4];
-        block_scan_vpt<4, kVpt, kPlanScanThreads / 64>(v, tot, wsum);
+        int64_t tot[2];
+        block_scan_vpt<2, kVpt, kPlanScanThreads / 64>(v, tot, wsum);
         #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
             const int32_t i = i0 + k;
             if (i < n_ai && cls[k] != 3) {
                 A.aitems[i].off = (run + v[k][0]) * nch;
                 // dense from the front, then medium, the others from the back
-                const int64_t nd_before = run_dense + v[k][1], nm_before = run_med + v[k][2];
+                const int64_t nd_before = run_dense + (v[k][1] & 0xffff), nm_before = run_med + (v[k][1] >> 16 & 0xffff);
                 const int64_t pos = cls[k] == 1 ? nd_before
                                   : cls[k] == 2 ? nd_total + nm_before
-                                                : n_ai - 1 - (i - nd_before - nm_before - (run_rank + v[k][3]));
+                                                : n_ai - 1 - (i - nd_before - nm_before - (run_rank + (v[k][1] >> 32)));
                 A.alist[pos] = i;
             }
         }
         run += tot[0];
-        run_dense += tot[1];
-        run_med += tot[2];
-        run_rank += tot[3];
+        run_dense += tot[1] & 0xffff;
+        run_med += tot[1] >> 16 & 0xffff;
+        run_rank += tot[1] >> 32;
     }
     if (threadIdx.x == 0) {
         // the last pass counted its unused places as items of rank blocks
@@ -2426,13 +2562,17 @@ int sort_hist_len(int32_t na, int32_t nb)
     }
 }
 
-constexpr int kParamBlocks = 512, kItemBlocks = 512;
+constexpr int kParamBlocks = 1536, kItemBlocks = 512;
 
 hipError_t launch_planning(const PlanArgs& a, hipStream_t s)
 {
     const int32_t n = a.P.n, m = a.P.m;
     hipLaunchKernelGGL(k_staircases, dim3(cdiv(m, 256) + cdiv(n, 256)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_subdivide, dim3(1), dim3(kSubThreads), 0, s, a);
+    if (a.A.sub) {
+        hipLaunchKernelGGL(k_subtrees, dim3(kSubTrees), dim3(kSubThreads), 0, s, a);
+        hipLaunchKernelGGL(k_subtree_blocks, dim3(kSubTrees), dim3(kSubThreads), 0, s, a);
+    }
     hipLaunchKernelGGL(k_block_params, dim3(kParamBlocks), dim3(128), 0, s, a);
     hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(kPlanScanThreads), 0, s, a);
     hipLaunchKernelGGL(k_items, dim3(kItemBlocks), dim3(128), 0, s, a);
