@@ -822,10 +822,10 @@ __device__ __forceinline__ double rank_eval(const PlanDev& P, const ABlock& B, d
     double v;
     if constexpr (UNI) {
         const int qu = __builtin_amdgcn_readfirstlane(q);
-        if (__all(q == qu)) v = rank_series(P.rcoef + (int64_t)(B.rpan0 + qu) * kRankK, B.K, eta, cr, ci);
-        else v = rank_series(P.rcoef + (int64_t)(B.rpan0 + q) * kRankK, B.K, eta, cr, ci);
+        if (__all(q == qu)) v = rank_series(P.rcoef + (int64_t)(B.rpan0 + qu) * kRankK, B.rK, eta, cr, ci);
+        else v = rank_series(P.rcoef + (int64_t)(B.rpan0 + q) * kRankK, B.rK, eta, cr, ci);
     } else {
-        v = rank_series(P.rcoef + (int64_t)(B.rpan0 + q) * kRankK, B.K, eta, cr, ci);
+        v = rank_series(P.rcoef + (int64_t)(B.rpan0 + q) * kRankK, B.rK, eta, cr, ci);
     }
     return kSqrt2OverPi * rs * v;
 }
@@ -2104,7 +2104,7 @@ template <int NCH, bool UNI>
 __device__ double asym_eval(const PlanDev& P, int ablk, double om, const double2* __restrict__ grids)
 {
     const ABlock B = P.ab[ablk];
-    if (B.K > 0) return rank_eval<UNI>(P, B, om);
+    if (B.rK > 0) return rank_eval<UNI>(P, B, om);
     const int w = P.w;
     // gamma = 1/(om r0) and its square root (om r0 > z > 0 on an asymptotic block)
     const double rs = rsqrt_refined(om * B.r0);
@@ -2209,6 +2209,119 @@ __device__ double asym_eval(const PlanDev& P, int ablk, double om, const double2
     cis_dd(ph.hi, ph_lo, cr, ci);
     double amp = rs * scale;
     return kSqrt2OverPi * amp * __builtin_fma(cr, ar, -ci * ai);
+}
+
+// ---------------------------------------------------------------------------
+// Rows of FFT-path blocks through expansions.  Where a block has many more
+// rows than degrees of freedom, its part at frequency omega, without the
+// phase e^{i omega C}, is a K-term Chebyshev expansion on each of its panels
+// of frequencies (as in the rank blocks): the transform is interpolated at
+// the K nodes of a panel, and a row adds up a series instead of reading w
+// cells of every channel.  A node's loads, w neighbouring cells of a channel
+// at a time, are a chain of latencies over the channels, so four lanes share
+// a node, every fourth channel and tap each: a wave takes one of the four
+// shares of two neighbouring panels, kRankK lanes a panel.
+// 34 us for 6600 panels (1e6 x 1e6, order 0, 8 channels), where the row pass
+// falls from 123 to 73 us; at order 10 (12 channels) 41, and 138 to 74.
+// ---------------------------------------------------------------------------
+constexpr int kFftShares = 4;        // waves
+constexpr int kFftTaps = 8;          // taps loaded at once
+
+__device__ __forceinline__ void fft_nodes_body(const PlanDev& P, int bid)
+{
+    constexpr int kTaps = (kMaxEsWidth + kFftTaps - 1) / kFftTaps * kFftTaps;
+    __shared__ double s_psi[kTaps][64];
+    __shared__ double2 s_f[kFftShares][64];
+    const int lane = threadIdx.x & 63, share = threadIdx.x >> 6, g = lane / kRankK, x = lane - g * kRankK;
+    const Panel T = P.flist[bid];
+    const ABlock& B = P.ab[T.blk];
+    const int K = B.rK, q = T.q + g;
+    const bool on = g < kFftPanels && q < B.pr;
+    const double* __restrict__ tab = P.rank_tab + rank_tab_off(K);
+    // the share's cosines of coefficient x (of the panel's first node in lanes
+    // without one), loaded ahead
+    const int quarter = K / kFftShares, xc = x < K ? x : 0;
+    double cosine[kRankK / kFftShares];
+    #pragma unroll
+    for (int u = 0; u < kRankK / kFftShares; ++u)
+        cosine[u] = u < quarter ? tab[K * K + (share * quarter + u) * K + xc] : 0.0;
+    const int w = P.w, mask = B.N2 - 1;
+    const dd sp = two_sum(rank_mid(q, B.pr, B.rw), B.rw * tab[K + xc]);
+    const dd v = two_prod(sp.hi, B.Khi);
+    const double vl = v.lo + (sp.lo * B.Khi + sp.hi * B.Klo);
+    const int q0 = (int)ceil(v.hi - 0.5 * w);
+    const double sf = 2.0 * ((((double)q0 - v.hi) - vl) + 0.5 * w) - 1.0;
+    for (int tap = share; tap < kTaps; tap += kFftShares) {
+        double psi = 0.0;
+        if (tap < w) {
+            const double* cf = P.es_poly + tap * (kEsDeg + 1);
+            psi = cf[kEsDeg];
+            #pragma unroll
+            for (int d = kEsDeg - 1; d >= 0; --d) psi = __builtin_fma(psi, sf, cf[d]);
+        }
+        s_psi[tap][lane] = psi;
+    }
+    __syncthreads();
+    {
+        const double rs = rsqrt_refined((B.D + sp.hi) * B.r0), gam = rs * rs, gam2 = gam * gam, gam4 = gam2 * gam2;
+        double ar = 0.0, ai = 0.0;
+        for (int p = (P.nch - 1 - share) / kFftShares * kFftShares + share; p >= 0 && P.nch > share; p -= kFftShares) {
+            const double2* __restrict__ A = P.grids + B.grid_off + (int64_t)p * B.N2;
+            double br = 0.0, bi = 0.0;
+            for (int t0 = 0; t0 < w; t0 += kFftTaps) {
+                double2 c[kFftTaps];
+                #pragma unroll
+                for (int u = 0; u < kFftTaps; ++u) c[u] = A[(q0 + t0 + u) & mask];
+                #pragma unroll
+                for (int u = 0; u < kFftTaps; ++u) {
+                    const double psi = s_psi[t0 + u][lane];
+                    br = __builtin_fma(psi, c[u].x, br);
+                    bi = __builtin_fma(psi, c[u].y, bi);
+                }
+            }
+            ar = __builtin_fma(ar, gam4, br);
+            ai = __builtin_fma(ai, gam4, bi);
+        }
+        const double kap = fabs(sp.hi) * B.alpha;
+        const double own = (share & 1 ? gam : 1.0) * (share & 2 ? gam2 : 1.0);
+        const double sc = own * (2.0 * kPi / B.N2 * (B.h * rcp_refined(B.alpha * eshat(P, kap))));
+        s_f[share][lane] = make_double2(ar * sc, ai * sc);
+    }
+    __syncthreads();
+    // coefficient x, as rank_store_coefs, the shares a quarter of the nodes each
+    double vr = 0.0, vi = 0.0;
+    #pragma unroll
+    for (int u = 0; u < kRankK / kFftShares; ++u) {
+        const int h = g * kRankK + share * quarter + (u < quarter ? u : 0);
+        double fr = 0.0, fi = 0.0;
+        #pragma unroll
+        for (int e = 0; e < kFftShares; ++e) {
+            const double2 f = s_f[e][h & 63];
+            fr += f.x;
+            fi += f.y;
+        }
+        vr = __builtin_fma(fr, cosine[u], vr);
+        vi = __builtin_fma(fi, cosine[u], vi);
+    }
+    __syncthreads();
+    s_f[share][lane] = make_double2(vr, vi);
+    __syncthreads();
+    if (share == 0 && on && x < K) {
+        const double2 a = s_f[0][lane], b = s_f[1][lane], c = s_f[2][lane], d = s_f[3][lane];
+        static_assert(kFftShares == 4, "four shares added up");
+        const double f = (x == 0 ? 1.0 : 2.0) / K;
+        P.rcoef[(int64_t)(B.rpan0 + q) * kRankK + x] =
+            make_double2(((a.x + b.x) + (c.x + d.x)) * f, ((a.y + b.y) + (c.y + d.y)) * f);
+    }
+}
+
+__global__ __launch_bounds__(256) void k_fft_nodes(PlanDev P) { fft_nodes_body(P, blockIdx.x); }
+
+__global__ __launch_bounds__(256) void k_fft_nodes_many(const PlanDev* __restrict__ plans,
+                                                        const WorkSeg* __restrict__ segs, int nseg)
+{
+    const WorkSeg w = find_seg(segs, nseg);
+    fft_nodes_body(plan_of(plans, w.t), w.g0);
 }
 
 // ---------------------------------------------------------------------------
@@ -2598,9 +2711,9 @@ __device__ __forceinline__ double direct_row(const PlanDev& P, int d, int j, dou
 // asymptotic block, then the lower-left child; a direct child ends the walk
 // and adds the row's part from k_direct_blocks.  g is written once, in the
 // caller's order.
-// NCH: the plan's channels, or 0 where every asymptotic block is a rank block
-// (no grid): then one instance serves every order, so that a batch's
-// transforms share a launch.
+// NCH: the plan's channels, or 0 where the rows of every asymptotic block go
+// through expansions (no row reads a grid): then one instance serves every
+// order, so that a batch's transforms share a launch.
 template <int NCH>
 __device__ __forceinline__ void rows_body(const PlanDev& P, int bid, double* g)
 {
@@ -2737,8 +2850,8 @@ static void dispatch_channels(int nch, F&& f)
     }
 }
 
-// The row pass's channel count: 0 without grids.
-static int rows_channels(const PlanDev& P) { return P.grid_cells > 0 ? P.nch : 0; }
+// The row pass's channel count: 0 where no row reads a grid.
+static int rows_channels(const PlanDev& P) { return P.n_gridrows > 0 ? P.nch : 0; }
 
 template <class F>
 static void dispatch_rows(int nch, F&& f)
@@ -2900,6 +3013,7 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
                            sizeof(double2) << P.small.max_log2n, s, P);
     for (int q = 0; q < ncls; ++q)
         if (cls[q].log2n > 12) launch_fft_large(P, cls[q], s);
+    if (S.n_fpan > 0) hipLaunchKernelGGL(k_fft_nodes, dim3(S.n_fpan), dim3(256), 0, s, P);
     mark(marks, 5, s);
     if (!forked) launch_direct(s);
     mark(marks, 6, s);
@@ -2939,7 +3053,7 @@ void small_fft_table(PlanDev& P, const FftClass* cls, int ncls)
 // ---------------------------------------------------------------------------
 enum BatchKind : int32_t {
     kZeroOut, kGather, kLmom, kLmomReduce, kLocalNodes, kRankMoments, kRankWeights, kRankTranslate, kSpreadMfma, kSpreadMfmaMed, kSpreadVec, kSpreadReduce, kFftSmall,
-    kFftPass0, kFftPass1, kFftPass2, kDirect, kRows
+    kFftPass0, kFftPass1, kFftPass2, kFftNodes, kDirect, kRows
 };
 
 void build_batch_schedule(const BatchTransform* tr, int count, const int* order, BatchSchedule& out)
@@ -3057,6 +3171,9 @@ void build_batch_schedule(const BatchTransform* tr, int count, const int* order,
         L.blocks = (int32_t)g;
         if (L.nseg > 0) out.launches.push_back(L);
     }
+    add(kFftNodes, 0, 0, 256, [&](const BatchTransform& T, size_t&) -> int64_t {
+        return live(*T.P) ? T.S->n_fpan : 0;
+    });
     add(kDirect, 0, 0, kDirectThreads, [&](const BatchTransform& T, size_t&) -> int64_t {
         return live(*T.P) ? direct_workgroups(*T.S) : 0;
     });
@@ -3168,6 +3285,7 @@ hipError_t launch_execute_many(const BatchSchedule& S, const void* table_dev, vo
         case kFftPass0:
         case kFftPass1: hipLaunchKernelGGL(k_fft_col_many, grid, block, L.lds, s, plans, fs, L.nseg); break;
         case kFftPass2: hipLaunchKernelGGL(k_fft_row_many, grid, block, L.lds, s, plans, fs, L.nseg); break;
+        case kFftNodes: hipLaunchKernelGGL(k_fft_nodes_many, grid, block, 0, s, plans, sg, L.nseg); break;
         case kDirect: hipLaunchKernelGGL(k_direct_blocks_many, grid, block, 0, st, plans, sg, L.nseg); break;
         case kRows:
             dispatch_rows(L.variant, [&](auto k) {

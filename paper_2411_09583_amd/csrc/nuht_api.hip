@@ -1321,6 +1321,7 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
     slab.add(A.cpans, (size_t)A.pan_cap);
     slab.add(A.tlist, (size_t)A.pan_cap);
     slab.add(A.wlist, (size_t)A.pan_cap);
+    slab.add(A.flist, (size_t)A.pan_cap);
     slab.add(A.rlist, P.rank ? (size_t)A.aitem_cap : 0);
     // large transforms subdivide their subtrees side by side, unless a subtree
     // outgrew its share of the tables
@@ -1331,7 +1332,7 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
     NUHT_TRY(slab.commit(pp.tmp));
     P.nodes = A.nodes; P.lb = A.lb; P.ab = A.ab; P.db = A.db;
     P.litems = A.litems; P.aitems = A.aitems; P.alist = A.alist; P.fft_list = A.fft_list; P.gslot = A.gslot;
-    P.cpans = A.cpans; P.rlist = A.rlist; P.tlist = A.tlist; P.wlist = A.wlist;
+    P.cpans = A.cpans; P.rlist = A.rlist; P.tlist = A.tlist; P.wlist = A.wlist; P.flist = A.flist;
     P.lwork = A.lwork; P.dlist = A.dlist;
     P.tlist_cap = A.pan_cap; P.rlist_cap = A.aitem_cap;
     a.P = P; a.A = A; a.K = K; a.Jc = Jc; a.a_cells = a_cells;
@@ -1398,6 +1399,7 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     P.n_litems = S.n_litems; P.n_aitems = S.n_aitems; P.n_adense = S.n_adense; P.n_amed = S.n_amed;
     P.n_tsingle = S.n_tsingle; P.n_tmulti = S.n_tmulti; P.n_wmulti = S.n_wmulti;
     P.n_ritems = S.n_ritems; P.n_rsmall = S.n_rsmall;
+    P.n_fpan = S.n_fpan; P.n_gridrows = S.n_gridrows;
     P.n_lwork = S.n_lwork; P.n_dentry = S.n_dentry; P.n_drank = S.n_drank;
 
     // execution buffers
@@ -1414,8 +1416,8 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     if (S.n_cpan > 0) {
         slab.add(B.rmom, (size_t)kRankK * ((size_t)S.n_aitems + S.n_cpan));
         slab.add(B.rwts, (size_t)kRankK * S.n_cpan);
-        slab.add(B.rcoef, (size_t)kRankK * S.n_rpan);
     }
+    slab.add(B.rcoef, (size_t)kRankK * S.n_rpan);
     B.grid_cells = S.grid_cells;
     int64_t scratch = 0;
     for (int c = 6; c <= kMaxFftLog2; ++c) {

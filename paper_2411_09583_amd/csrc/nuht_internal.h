@@ -55,6 +55,9 @@ constexpr double kJtabWidth = 2.0;     // panel width (in x = omega r) of that t
 // block are cut into equal-width panels, at most kRankPanels of points.
 constexpr int kRankK = 24;
 constexpr int kRankPanels = 40;
+// Neighbouring panels of an FFT-path block's frequencies expanded by one
+// workgroup.
+constexpr int kFftPanels = 2;
 // The narrowest ES kernel at which plans have rank blocks: the expansions are
 // good to eps / 100 and the ES transforms to about 10^(1-w), so the two forms
 // of a block agree to 1e-9 or better from this width (eps <= 1e-8) on; wider
@@ -123,7 +126,9 @@ struct ABlock {
     int32_t level, fft_slot;  // fft_slot: position in the FFT size-class list
     // rank blocks (K > 0): expansion length, panels of points and frequencies
     // with their half-widths and first panel numbers
-    int32_t K, pc, pr, cpan0, rpan0, pad;
+    // (rK: terms of the rows' expansions, K in a rank block; an FFT-path block
+    // (K = 0) may have them too, its transform then read at their nodes alone)
+    int32_t K, pc, pr, cpan0, rpan0, rK;
     double cw, rw;
 };
 
@@ -181,6 +186,8 @@ struct Summary {
     int32_t n_cpan, n_rpan;    // panels of the rank blocks
     int32_t n_tsingle, n_tmulti;   // their panels of frequencies: of blocks translated by one wave, of others
     int32_t n_wmulti;              // panels of points of those others
+    int32_t n_fpan;                // groups of kFftPanels panels of frequencies of FFT-path blocks
+    int32_t n_gridrows;            // asymptotic blocks whose rows read the grids
     int32_t n_lslots, n_lwork;     // slots of the local blocks' rows; waves that fill them
     int32_t n_dentry, n_drank;     // direct blocks applied entry by entry, through expansions
     int64_t l_row, l_col, a_row, a_col, d_ent;
@@ -250,7 +257,8 @@ struct PlanDev {
     double jtab_x0;
     int32_t jtab_np, pad2;
     int32_t n_nodes, n_l, n_a, n_d, n_litems, n_aitems, n_adense, n_amed;
-    int32_t n_tsingle, n_tmulti, n_wmulti, n_ritems, n_rsmall, n_lwork;
+    int32_t n_tsingle, n_tmulti, n_wmulti, n_ritems, n_rsmall, n_lwork, n_fpan, n_gridrows;
+    const Panel* flist;              // panels of frequencies of FFT-path blocks, the first of each group
     const LocalWork* lwork;          // the local blocks' rows by waves
     const int32_t* dlist;            // direct blocks: entry by entry from the front, expansions from the back
     int32_t n_dentry, n_drank;

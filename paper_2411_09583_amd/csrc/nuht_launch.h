@@ -30,6 +30,7 @@ struct Arena {
     RankItem* rlist;     // items of rank blocks (aitem_cap)
     Panel* tlist;        // panels of frequencies to translate (pan_cap)
     Panel* wlist;        // panels of points weighted on their own (pan_cap)
+    Panel* flist;        // panels of frequencies of FFT-path blocks, the first of each group (pan_cap)
     LocalWork* lwork;    // the local blocks' rows by waves (lslot_cap)
     int32_t* dlist;      // direct blocks by the way they are applied (d_cap)
     Node* stage;         // subtrees of the subdivision before they are numbered (node_cap); null: one workgroup

@@ -1834,10 +1834,16 @@ __device__ __forceinline__ int rank_panels(const PlanDev& P, double lo, double s
         const double half = span_half / pc;
         const double k = rank_terms(P, lo + half, half, other, xi / pc);
         if (k <= (double)kRankK) { *terms = k; return pc; }
-        pc += (pc + 1) / 2;
+        pc += pc < 64 ? (pc + 1) / 2 : pc / 8;
     }
     return 0;
 }
+
+// Rows a node of an FFT-path block's expansions has to replace.  At 1e6 rows
+// (order 0, 8 channels) a node takes 0.21 ns, and a row 0.054 ns less through
+// an expansion than from the grid: even at 4, with a launch more.
+constexpr int kRowsPerNode = 5;
+constexpr int32_t kRankRowPanels = 1 << 17;
 
 // Half-width of each of `panels` panels over a half-range: rounded up to 40
 // bits, so that the panels' middles (small integers times it) are exact and
@@ -1883,6 +1889,7 @@ __device__ __forceinline__ void block_params(const PlanArgs& a)
                 B.cw = rank_half_width(X, pc); B.rw = rank_half_width(S, pr);
             }
         }
+        const double S_rows = S;
         if (!(S > 1e-280)) S = 1e-280;
         // grid spacing: the largest power of two with S h <= pi / sigma
         double h = exp2(floor(log2(kPi / (sigma * S))));
@@ -1909,6 +1916,19 @@ __device__ __forceinline__ void block_params(const PlanArgs& a)
             B.Klo = h * (double)N2 * kInvTwoPiLo;
         }
         B.fft = fft; B.N2 = N2;
+        // rows of an FFT-path block through expansions on panels of
+        // frequencies, where they outnumber the nodes by kRowsPerNode
+        B.rK = B.K;
+        if (P.rank && fft && X > 1e-290 && S_rows > 1e-290) {
+            double kr = 1.0;
+            const int pr = rank_panels(P, wlo, S_rows, rlo, X * S_rows, kRankRowPanels, &kr);
+            const int K = ((int)ceil(kr) + 3) & ~3;
+            if (pr > 0 && (int64_t)kRowsPerNode * K * pr <= B.j1 - B.j0 + 1) {
+                B.rK = K;
+                B.pr = pr;
+                B.rw = rank_half_width(S_rows, pr);
+            }
+        }
         int32_t ncol = B.k1 - B.k0 + 1;
         B.nitems = (ncol + P.spread_chunk - 1) / P.spread_chunk;
         if (lane == 0) A.ab[b] = B;
@@ -1991,13 +2011,13 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
     __shared__ long long red[8][kPlanScanThreads / 64];
     constexpr int32_t kFftKept = 1024;
     __shared__ int4 kept[kFftKept];                  // FFT-path blocks: block, class, place in it
-    __shared__ int32_t n_kept;
+    __shared__ int32_t n_kept, n_gridrows;
     if (sum->overflow) return;
     const int32_t n_l = sum->n_l, n_a = sum->n_a;
     int tid = threadIdx.x;
     const int nch = P.nch;
     if (tid <= kMaxFftLog2) cls_cnt[tid] = 0;
-    if (tid == 0) n_kept = 0;
+    if (tid == 0) n_kept = n_gridrows = 0;
     __syncthreads();
     // membership statistics: rows / columns of local and asymptotic blocks,
     // grid cells and FFT points, and the row-side work of the
@@ -2028,7 +2048,8 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
                 const ABlock B = A.ab[i0 + k];
                 v[k][0] = B.nitems;
                 v[k][1] = B.K > 0 ? 0 : B.fft ? (int64_t)B.N2 : (int64_t)B.N1;
-                v[k][2] = B.K > 0 ? (int64_t)B.pc + ((int64_t)B.pr << 32) : 0;
+                v[k][2] = (int64_t)B.pc + ((int64_t)B.pr << 32);
+                if (B.rK == 0) atomicAdd(&n_gridrows, 1);
                 n2[k] = B.fft ? B.N2 : 0;
                 const long long rows = B.j1 - B.j0 + 1;
                 st[2] += rows;
@@ -2115,6 +2136,7 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
         sum->dft_row_cells = t[6]; sum->fft_rows = t[7];
         sum->n_litems = (int32_t)l_items; sum->n_aitems = (int32_t)a_items;
         sum->max_nch = nch;
+        sum->n_gridrows = n_gridrows;
         sum->grid_cells = grid;
         const int32_t n_cp = (int32_t)(pans & 0xffffffff), n_rp = (int32_t)(pans >> 32);
         sum->n_cpan = n_cp; sum->n_rpan = n_rp; sum->n_lslots = n_lslots;
@@ -2228,6 +2250,7 @@ __device__ __forceinline__ void items(const PlanArgs& a)
         bool ritem = false;                           // an item of a rank block
         bool tone = false, tmany = false;             // a panel of frequencies of a block of one wave / of another
         bool wmany = false;                           // a panel of points of another
+        bool fpan = false;                            // the first of a group of panels of an FFT-path block
         bool lwork = false;                           // the first slot of a wave of local rows
         bool drank = false, dentry = false;           // a direct block through expansions / entry by entry
         int32_t id = 0;
@@ -2315,8 +2338,9 @@ __device__ __forceinline__ void items(const PlanArgs& a)
             if (ip < n_rp) {
                 const ABlock B = A.ab[lo];
                 T.blk = lo; T.q = ip - B.rpan0;
-                tone = rank_one_wave(B);
-                tmany = !tone;
+                fpan = B.K == 0 && T.q % kFftPanels == 0;
+                tone = B.K > 0 && rank_one_wave(B);
+                tmany = B.K > 0 && !tone;
             }
         }
         const bool small = ritem && R.kb - R.ka <= kRankWaveCols;
@@ -2329,6 +2353,8 @@ __device__ __forceinline__ void items(const PlanArgs& a)
         if (drank) A.dlist[n_d - 1 - p7] = id;
         const int32_t p5 = wave_append(lwork, &sum->n_lwork);
         if (lwork) A.lwork[p5] = W;
+        const int32_t p8 = wave_append(fpan, &sum->n_fpan);
+        if (fpan) A.flist[p8] = T;
         const int32_t p1 = wave_append(tone, &sum->n_tsingle);
         if (tone) A.tlist[p1] = T;
         const int32_t p2 = wave_append(tmany, &sum->n_tmulti);

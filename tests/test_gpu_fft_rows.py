@@ -1,0 +1,62 @@
+"""GPU: rows of FFT-path blocks through expansions.
+
+One asymptotic block (frequencies above the crossover at every point) wide
+enough for the FFT path, with row counts around the one from which rows go
+through expansions, over orders (channel counts) and tolerances; the same
+block's rows read the grid with few frequencies, and a second plan without
+expansions (dft_max < 0) gives the other path's answer.
+
+Bars: the method's own eps |c|_1 against the direct sum; between the two ways
+of the same transform, 0.1 eps + 2e-14 of |c|_1 (the expansions are made to
+eps / 1000, and interpolating at most 24 nodes enlarges the type-3
+transform's own error, below eps / 30 where it is measured, by at most 3).
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import direct
+from oracle import params as oparams
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def nuht():
+    import paper_2411_09583_amd as lib
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    lib.load_library()
+    return lib
+
+
+def dev(x):
+    return torch.as_tensor(np.ascontiguousarray(x, dtype=np.float64), device="cuda")
+
+
+@pytest.mark.parametrize("xi", [700.0, 3000.0])
+@pytest.mark.parametrize("m", [1, 500, 2600, 8000, 40000])
+def test_rows_of_fft_blocks(nuht, xi, m):
+    n = 900
+    for nu, eps in ((0, 1e-12), (1, 1e-8), (6, 1e-10), (20, 1e-9), (45, 1e-10), (0.5, 1e-12), (4.5, 1e-13)):
+        z = oparams.any_parameters(nu, eps)[1]
+        rng = np.random.default_rng(int(xi) + m + int(2 * nu))
+        r = np.concatenate([[1.0, 2.0], rng.uniform(1.0, 2.0, n - 2)])
+        w = 1.5 * z + 2.0 * xi * rng.uniform(0.0, 1.0, m) * 2.0
+        w[0] = 1.5 * z
+        w[-1] = 1.5 * z + 4.0 * xi if m > 1 else w[0]
+        c = rng.standard_normal(n)
+        p = nuht.Plan(dev(r), dev(w), nu, eps)
+        q = nuht.Plan(dev(r), dev(w), nu, eps, dft_max=-1)
+        assert p.info()["n_asy"] == 1 and p.info()["n_local"] == 0
+        if m > 1:
+            assert p.info()["n_fft_blocks"] == 1
+        g, h = p.execute(dev(c)).cpu().numpy(), q.execute(dev(c)).cpu().numpy()
+        k = np.unique(np.linspace(0, m - 1, 400).astype(int))
+        ref = direct.dht(nu, r, c, w[k])
+        one = np.sum(np.abs(c))
+        err, diff = np.max(np.abs(g[k] - ref)) / one, np.max(np.abs(g - h)) / one
+        print("xi", xi, "m", m, "nu", nu, "eps", eps, "err", err, "between", diff, flush=True)
+        assert err <= eps
+        assert diff <= 0.1 * eps + 2e-14
+        p.close()
+        q.close()
