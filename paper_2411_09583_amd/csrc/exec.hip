@@ -846,8 +846,9 @@ __device__ __forceinline__ double rank_eval(const PlanDev& P, const ABlock& B, d
 // (sums of coefficients common to all lanes times powers of the point's
 // offset), all into LDS.
 // Phase 2: threads own (cell, slice) pairs; the points reaching cell l are
-// those with l - w < l0 <= l, a contiguous range (points are sorted), found by
-// binary search; slices of one cell are adjacent lanes and are summed with
+// those with l - w < l0 <= l, a contiguous range (points are sorted), from a
+// list of the first point of every cell (a binary search where the sub-chunk
+// spans more than kSpreadSpan cells); slices of one cell are adjacent lanes and are summed with
 // cross-lane shuffles after the last sub-chunk.
 //
 // Where points are sparse an item's cells take several turns of the threads.
@@ -855,10 +856,14 @@ __device__ __forceinline__ double rank_eval(const PlanDev& P, const ABlock& B, d
 // a turn, which also reaches the next turn's, is kept in LDS: every sub-chunk
 // goes through phase 1 about once, whatever the number of turns.  (All of an
 // item's sub-chunks in every turn took 462 us for the 1e6 log-spaced points of
-// order 0, one point a cell, and takes 98 so; 276 and 147 at the first 1e6
-// zeros of J_0.)
+// order 0, one point a cell, and take 98 so, 73 with the list in place of
+// searches; 276, 147 and 145 at the first 1e6 zeros of J_0.)  Where items are
+// few, P.spread_turns workgroups share an item, every so many turns each (of
+// fewer cells where the item has few): 20000 points of a radial transform 57
+// -> 18 us, 5229 of order 18 70 -> 18, 1e5 of order 0 58 -> 35.
 // ---------------------------------------------------------------------------
 constexpr int kSpreadSub = 256;
+constexpr int kSpreadSpan = 512;     // first cells of a sub-chunk that are listed (1 KB; 4 KB cost a workgroup a CU)
 
 // T is the type of the weights, kernel values and channel sums: double, or
 // float in the FP32-spreading mode (positions and phases stay double-double
@@ -937,7 +942,8 @@ __device__ __forceinline__ void spread_body(const PlanDev& P, int bid)
     SpreadPoint<T>* s_pt = reinterpret_cast<SpreadPoint<T>*>(spread_lds);
     T* s_k = reinterpret_cast<T*>(s_pt + kSpreadSub);
     // the items not spread on the matrix cores, from the back of the order
-    const Item I = P.aitems[P.alist[P.n_aitems - 1 - bid]];
+    const int share = P.spread_turns;
+    const Item I = P.aitems[P.alist[P.n_aitems - 1 - bid / share]];
     const ABlock B = P.ab[I.blk];
     const int tid = threadIdx.x;
     const int w = P.w;
@@ -945,14 +951,18 @@ __device__ __forceinline__ void spread_body(const PlanDev& P, int bid)
     const double inv_h = 1.0 / B.h;      // exact: h is a power of two
     const int sub_n = I.sub_n;
     int slices = 1;
-    while (slices < 64 && slices * 2 * sub_n <= 256) slices <<= 1;
+    // (FP32 sums keep the slices of one workgroup, and so their order)
+    const int threads = std::is_same<T, float>::value ? 256 : 256 * share;
+    while (slices < 64 && slices * 2 * sub_n <= threads) slices <<= 1;
     const int cells_par = 256 / slices;
     auto cell_of = [&](int k) {
         double frac;
         return first_cell(two_sum(P.rs[k], -B.C), inv_h, hw, frac);
     };
     int k_begin = I.ka, in_lds = -1;     // first sub-chunk that reaches the turn's cells; the one in LDS
-    for (int cbase = 0; cbase < sub_n; cbase += cells_par) {
+    __shared__ uint16_t s_start[kSpreadSpan];
+    int l_first = 0, l_last = 0;         // first cells of its first and last point
+    for (int cbase = bid % share * cells_par; cbase < sub_n; cbase += share * cells_par) {
         const int l_lo = I.sub_lo + cbase;
         const int l_hi = I.sub_lo + (cbase + cells_par < sub_n ? cbase + cells_par : sub_n) - 1;
         while (k_begin + kSpreadSub < I.kb && cell_of(k_begin + kSpreadSub - 1) <= l_lo - w) k_begin += kSpreadSub;
@@ -1002,15 +1012,27 @@ __device__ __forceinline__ void spread_body(const PlanDev& P, int bid)
                 }
                 in_lds = k0;
                 __syncthreads();
+                // the first point from each cell on
+                l_first = s_pt[0].l0;
+                l_last = s_pt[np - 1].l0;
+                if (l_last - l_first < kSpreadSpan) {
+                    if (tid < np)
+                        for (int a = tid > 0 ? s_pt[tid - 1].l0 + 1 : l_first; a <= s_pt[tid].l0; ++a)
+                            s_start[a - l_first] = (uint16_t)tid;
+                    __syncthreads();
+                }
             }
             if (cell < sub_n) {
                 // points with l0 in (l - w, l]
-                int lo = 0, hi = np;
-                while (lo < hi) { int mid = (lo + hi) >> 1; if (s_pt[mid].l0 <= l - w) lo = mid + 1; else hi = mid; }
-                int first = lo;
-                hi = np;
-                while (lo < hi) { int mid = (lo + hi) >> 1; if (s_pt[mid].l0 <= l) lo = mid + 1; else hi = mid; }
-                int last = lo;
+                auto points_to = [&](int b) {            // points with l0 <= b
+                    if (b < l_first) return 0;
+                    if (b >= l_last) return np;
+                    if (l_last - l_first < kSpreadSpan) return (int)s_start[b + 1 - l_first];
+                    int lo = 0, hi = np;
+                    while (lo < hi) { int mid = (lo + hi) >> 1; if (s_pt[mid].l0 <= b) lo = mid + 1; else hi = mid; }
+                    return lo;
+                };
+                const int first = points_to(l - w), last = points_to(l);
                 for (int i = first + sl; i < last; i += slices) {
                     const SpreadPoint<T> rec = s_pt[i];
                     T phi = s_k[i * w + (l - rec.l0)];
@@ -2803,9 +2825,9 @@ static void launch_spread(const PlanDev& P, const Summary& S, hipStream_t s)
     }
     if (n_rest > 0) {
         if (P.fp32)
-            hipLaunchKernelGGL((k_spread<NCH, float>), dim3(n_rest), dim3(256), spread_lds_bytes<float>(P.w), s, P);
+            hipLaunchKernelGGL((k_spread<NCH, float>), dim3(n_rest * P.spread_turns), dim3(256), spread_lds_bytes<float>(P.w), s, P);
         else
-            hipLaunchKernelGGL((k_spread<NCH, double>), dim3(n_rest), dim3(256), spread_lds_bytes<double>(P.w), s, P);
+            hipLaunchKernelGGL((k_spread<NCH, double>), dim3(n_rest * P.spread_turns), dim3(256), spread_lds_bytes<double>(P.w), s, P);
     }
 }
 
@@ -3131,7 +3153,7 @@ void build_batch_schedule(const BatchTransform* tr, int count, const int* order,
         add(kSpreadVec, nch, fp32, 256, [&](const BatchTransform& T, size_t& lds) -> int64_t {
             if (!same(*T.P)) return 0;
             lds = fp32 ? spread_lds_bytes<float>(T.P->w) : spread_lds_bytes<double>(T.P->w);
-            return T.S->n_aspread - T.S->n_adense - T.S->n_amed;
+            return (int64_t)(T.S->n_aspread - T.S->n_adense - T.S->n_amed) * T.P->spread_turns;
         });
     }
     for (int fp32 = 0; fp32 <= 1; ++fp32)

@@ -1400,6 +1400,7 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     P.n_tsingle = S.n_tsingle; P.n_tmulti = S.n_tmulti; P.n_wmulti = S.n_wmulti;
     P.n_ritems = S.n_ritems; P.n_rsmall = S.n_rsmall;
     P.n_fpan = S.n_fpan; P.n_gridrows = S.n_gridrows;
+    P.spread_turns = spread_turns(S.n_aspread - S.n_adense - S.n_amed);
     P.n_lwork = S.n_lwork; P.n_dentry = S.n_dentry; P.n_drank = S.n_drank;
 
     // execution buffers

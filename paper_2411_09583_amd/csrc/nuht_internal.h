@@ -36,6 +36,10 @@ inline int64_t default_min_size(int64_t n, int64_t m) {
     while (s < kMinSizeHi && (double)(2 * s) <= a) s *= 2;
     return s;
 }
+// Workgroups per vector spreading item, of n items: an item is a chain of
+// sub-chunks and of turns of its cells, so few items are shared to fill the
+// chip.
+inline int32_t spread_turns(int32_t n) { int32_t t = 1; while (t < 8 && 2 * t * (int64_t)n <= 1024) t *= 2; return t; }
 constexpr int kMaxEsWidth = 18;        // largest ES kernel width
 constexpr int kEshatTerms = 16;        // terms of the polynomial for the ES kernel's Fourier transform
 constexpr int kEsDeg = 13;             // degree of the per-cell polynomial pieces of the ES kernel
@@ -234,7 +238,8 @@ struct PlanDev {
     double hank[2 * 20 + 2];         // a_p(nu), p = 0 .. 2M+1 (Hankel coefficients)
     double chan[kMaxChannels];       // channel factors (-1)^(p/2) a_p(nu) for p < 2M (odd p carry a factor i), 0 above
     double eshat[kEshatTerms];       // ES^ on [0, kappa_max]: monomial coefficients in s = 2 (kappa / kappa_max)^2 - 1
-    int32_t spread_chunk, pad3;      // points per spreading work item
+    int32_t spread_chunk;            // points per spreading work item
+    int32_t spread_turns;            // workgroups that share a vector item's cells (spread_turns)
     double kappa_max, eshat_s;       // eshat_s = 2 / kappa_max^2
     const double* rs;                // sorted points (n)
     const double* ws;                // sorted frequencies (m)
