@@ -2971,7 +2971,10 @@ static void launch_fft_large(const PlanDev& P, const FftClass& K, hipStream_t s)
 }
 
 // Transforms of at most this many points and frequencies run on one stream.
-constexpr int64_t kForkMin = 1 << 14;
+constexpr int64_t kForkMin = 1 << 13;
+// Above this many, and where there are grids, the rank blocks leave the main
+// stream too.
+constexpr int64_t kRankForkMin = 1 << 14;
 
 hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers& B, const FftClass* cls, int ncls,
                           const IoArgs& io, hipStream_t s, hipEvent_t* marks, const ExecFork* fork)
@@ -2985,43 +2988,60 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
     hipLaunchKernelGGL(k_gather, dim3(cdiv64(P.n, 256)), dim3(256), 0, s, P, io.c, io.c_slot,
                        io.scale_by_points ? 1 : 0);
     mark(marks, 1, s);
-    // the local moments and direct blocks read only the gathered weights; a
-    // small transform's kernels are shorter than the fork's events and waits
-    // take the host (a pass at 500 x 500: 56 us on one stream, 77 forked; plan
-    // and pass at 2000 x 2000: 173 and 220)
-    const bool forked = fork && fork->side && (S.n_litems > 0 || P.n_d > 0) && (int64_t)P.n + P.m > kForkMin;
-    const hipStream_t ls = forked ? fork->side : s;
-    if (forked) {
-        hipError_t e = hipEventRecord(fork->ev_fork, s);
-        if (e == hipSuccess) e = hipStreamWaitEvent(ls, fork->ev_fork, 0);
-        if (e != hipSuccess) return e;
-    }
-    if (S.n_litems > 0) {
+    // the local moments, the rank blocks and the direct blocks read only the
+    // gathered weights and run beside the grids' kernels.  A small transform's
+    // kernels are shorter than the fork's events and waits take the host: plan
+    // and pass at 2000 x 2000 173 us on one stream, 220 forked; passes of
+    // 5229 x 10761 and back, order 18, 277 and 222, but 244 with the rank
+    // blocks on the side stream (the host's launches of which hold the grids'
+    // up); passes of 20000 x 20000 and back 268 us with those on the main
+    // stream, 233 on the side one.  Without grids the rank blocks are the main
+    // stream's work.
+    const bool forked = fork && fork->side && (S.n_litems > 0 || P.n_d > 0) &&
+                        (int64_t)P.n + P.m > kForkMin;
+    const bool rank_aside = forked && P.grid_cells > 0 && (int64_t)P.n + P.m > kRankForkMin;
+    const hipStream_t ls = forked ? fork->side : s, ks = rank_aside ? fork->side : s;
+    auto launch_local = [&] {
+        if (S.n_litems == 0) return;
         if (lmom_width(P.L) == 32) hipLaunchKernelGGL(k_lmom<32>, dim3(S.n_litems), dim3(64), 0, ls, P);
         else hipLaunchKernelGGL(k_lmom<64>, dim3(S.n_litems), dim3(64), 0, ls, P);
         if (S.n_litems > S.n_l)   // some block has several items
             hipLaunchKernelGGL(k_lmom_reduce, dim3(lmom_reduce_blocks(P, S)), dim3(256), 0, ls, P);
         launch_local_nodes(P, ls);
-    }
-    auto launch_direct = [&](hipStream_t st) {
-        if (P.n_d > 0) {
-            hipLaunchKernelGGL(k_direct_blocks, dim3(direct_workgroups(S)), dim3(kDirectThreads), 0, st, P);
-        }
+    };
+    auto launch_rank_moments = [&] {
+        if (rank_moments_blocks(S) > 0)
+            hipLaunchKernelGGL(k_rank_moments, dim3(rank_moments_blocks(S)), dim3(64 * kRankWaves), 0, ks, P);
+    };
+    auto launch_rank_rows = [&] {
+        if (S.n_cpan == 0) return;
+        hipLaunchKernelGGL(k_rank_weights, dim3(rank_weights_blocks(S)), dim3(256), 0, ks, P);
+        if (S.n_tmulti > 0)
+            hipLaunchKernelGGL(k_rank_translate, dim3(S.n_tmulti), dim3(kRankTransThreads), 0, ks, P);
+    };
+    auto launch_direct = [&] {
+        if (P.n_d > 0) hipLaunchKernelGGL(k_direct_blocks, dim3(direct_workgroups(S)), dim3(kDirectThreads), 0, ls, P);
     };
     if (forked) {
-        launch_direct(ls);
-        const hipError_t e = hipEventRecord(fork->ev_join, ls);
+        hipError_t e = hipEventRecord(fork->ev_fork, s);
+        if (e == hipSuccess) e = hipStreamWaitEvent(ls, fork->ev_fork, 0);
         if (e != hipSuccess) return e;
     }
+    if (!rank_aside) launch_local();
+    if (forked && !rank_aside) launch_direct();
     mark(marks, 2, s);
-    if (rank_moments_blocks(S) > 0)
-        hipLaunchKernelGGL(k_rank_moments, dim3(rank_moments_blocks(S)), dim3(64 * kRankWaves), 0, s, P);
+    if (!rank_aside) launch_rank_moments();
     dispatch_channels(P.nch, [&](auto k) { launch_spread<decltype(k)::value>(P, S, s); });
     mark(marks, 3, s);
-    if (S.n_cpan > 0) {
-        hipLaunchKernelGGL(k_rank_weights, dim3(rank_weights_blocks(S)), dim3(256), 0, s, P);
-        if (S.n_tmulti > 0)
-            hipLaunchKernelGGL(k_rank_translate, dim3(S.n_tmulti), dim3(kRankTransThreads), 0, s, P);
+    if (rank_aside) {
+        launch_rank_moments();
+        launch_local();
+    }
+    launch_rank_rows();
+    if (rank_aside) launch_direct();
+    if (forked) {
+        const hipError_t e = hipEventRecord(fork->ev_join, ls);
+        if (e != hipSuccess) return e;
     }
     if (P.grid_cells > 0) {
         if (P.fp32)
@@ -3037,7 +3057,7 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
         if (cls[q].log2n > 12) launch_fft_large(P, cls[q], s);
     if (S.n_fpan > 0) hipLaunchKernelGGL(k_fft_nodes, dim3(S.n_fpan), dim3(256), 0, s, P);
     mark(marks, 5, s);
-    if (!forked) launch_direct(s);
+    if (!forked) launch_direct();
     mark(marks, 6, s);
     if (forked) {
         const hipError_t e = hipStreamWaitEvent(s, fork->ev_join, 0);
@@ -3228,10 +3248,11 @@ hipError_t launch_execute_many(const BatchSchedule& S, const void* table_dev, vo
     const FftSeg* fsegs = (const FftSeg*)(base + S.fsegs_off);
     const double* const* cin = (const double* const*)c_table;
     double* const* gout = (double* const*)g_table;
-    // with `fork`: the local moments and direct blocks on its side stream,
-    // forked at the first of them (after the gather) and joined before the
-    // local rows (or at the end)
-    bool forked = false, joined = false;
+    // with `fork`: the local moments, the direct blocks and (where there are
+    // grids) the rank blocks on its side stream, forked at the first of them (after the gather) and
+    // joined before the row pass (or at the end)
+    bool forked = false, joined = false, grids = false;
+    for (const BatchLaunch& L : S.launches) grids |= L.kind == kSpreadReduce;
     auto join = [&]() -> hipError_t {
         hipError_t e = hipEventRecord(fork->ev_join, fork->side);
         if (e == hipSuccess) e = hipStreamWaitEvent(s, fork->ev_join, 0);
@@ -3240,7 +3261,8 @@ hipError_t launch_execute_many(const BatchSchedule& S, const void* table_dev, vo
     };
     for (const BatchLaunch& L : S.launches) {
         const dim3 grid(L.blocks), block(L.threads);
-        const bool side_kind = L.kind == kLmom || L.kind == kLmomReduce || L.kind == kLocalNodes || L.kind == kDirect;
+        const bool side_kind = L.kind == kLmom || L.kind == kLmomReduce || L.kind == kLocalNodes || L.kind == kDirect ||
+                               (grids && (L.kind == kRankMoments || L.kind == kRankWeights || L.kind == kRankTranslate));
         hipStream_t st = s;
         if (fork && side_kind && !joined) {
             if (!forked) {
@@ -3272,10 +3294,10 @@ hipError_t launch_execute_many(const BatchSchedule& S, const void* table_dev, vo
             else hipLaunchKernelGGL(k_local_nodes_many<3>, grid, block, L.lds, st, plans, sg, L.nseg);
             break;
         case kRankMoments:
-            hipLaunchKernelGGL(k_rank_moments_many, grid, block, 0, s, plans, sg, L.nseg);
+            hipLaunchKernelGGL(k_rank_moments_many, grid, block, 0, st, plans, sg, L.nseg);
             break;
-        case kRankWeights: hipLaunchKernelGGL(k_rank_weights_many, grid, block, 0, s, plans, sg, L.nseg); break;
-        case kRankTranslate: hipLaunchKernelGGL(k_rank_translate_many, grid, block, 0, s, plans, sg, L.nseg); break;
+        case kRankWeights: hipLaunchKernelGGL(k_rank_weights_many, grid, block, 0, st, plans, sg, L.nseg); break;
+        case kRankTranslate: hipLaunchKernelGGL(k_rank_translate_many, grid, block, 0, st, plans, sg, L.nseg); break;
         case kSpreadMfma:
         case kSpreadMfmaMed:
             dispatch_channels(L.variant, [&](auto k) {

@@ -1316,6 +1316,8 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
     slab.add(A.alist, (size_t)A.aitem_cap);
     slab.add(A.fft_list, (size_t)A.a_cap);
     slab.add(A.gslot, (size_t)A.a_cap + 1);
+    slab.add(A.ascan, (size_t)A.a_cap);
+    slab.add(A.lscan, (size_t)A.l_cap);
     slab.add(A.lwork, (size_t)A.lslot_cap);
     slab.add(A.dlist, (size_t)A.d_cap);
     slab.add(A.cpans, (size_t)A.pan_cap);
@@ -1378,7 +1380,7 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     S = h->sum;
     if (S.overflow == 2) return NUHT_ECAPACITY;   // subdivision deeper than kMaxLevels
     if (S.grid_error) return NUHT_ECAPACITY;
-    if (S.overflow) {
+    if (S.overflow || S.scan_overflow) {
         if (++pp.attempt >= 6) return NUHT_ECAPACITY;
         int64_t need = std::max<int64_t>({(int64_t)S.n_nodes, (int64_t)S.n_l, (int64_t)S.n_a, (int64_t)S.n_d / 2,
                                           (int64_t)S.n_cpan / 2, (int64_t)S.n_rpan / 2, (int64_t)S.n_lslots / 2});

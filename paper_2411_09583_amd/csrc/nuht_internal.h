@@ -180,7 +180,8 @@ struct Item {
 // Written by the planning kernels, read once by the host.
 struct Summary {
     int32_t n_nodes, n_l, n_a, n_d;
-    int32_t levels, overflow;
+    int32_t levels, overflow;  // overflow: of the subdivision's tables (1) or levels (2)
+    int32_t scan_overflow;     // of the tables of items, panels and slots
     int32_t n_litems, n_aitems;
     int32_t n_fft, max_nch;
     int32_t n_adense, n_amed;  // dense and medium spread items (the first n_adense, then n_amed, of the item list)

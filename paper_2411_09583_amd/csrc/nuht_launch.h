@@ -14,7 +14,19 @@ struct Rect {
 // Device tables of one partition, with their capacities.  The planning
 // kernels write them; if any capacity is exceeded they report overflow in the
 // Summary and the host retries with larger tables.
+// What the scan over the blocks needs of one, side by side (an ABlock or LBlock
+// itself spans one or two cache lines).
+struct alignas(16) AScan {
+    int32_t items, slots, pc, pr;       // slots: of its grid
+    int32_t rows, cols, fft, gridrows;  // fft: log2 N2 of an FFT-path block, 0 of a direct-sum one, -1 of a rank block
+};
+struct alignas(16) LScan {
+    int32_t items, slots, rows, cols;
+};
+
 struct Arena {
+    AScan* ascan;        // per asymptotic block (a_cap)
+    LScan* lscan;        // per local block (l_cap)
     Node* nodes;
     LBlock* lb;
     ABlock* ab;

@@ -1931,7 +1931,11 @@ __device__ __forceinline__ void block_params(const PlanArgs& a)
         }
         int32_t ncol = B.k1 - B.k0 + 1;
         B.nitems = (ncol + P.spread_chunk - 1) / P.spread_chunk;
-        if (lane == 0) A.ab[b] = B;
+        if (lane == 0) {
+            A.ab[b] = B;
+            A.ascan[b] = AScan{B.nitems, B.K > 0 ? 0 : fft ? N2 : N1, B.pc, B.pr, B.j1 - B.j0 + 1, ncol,
+                               B.K > 0 ? -1 : fft ? 31 - __clz(N2) : 0, B.rK == 0 ? 1 : 0};
+        }
     }
     long long entries = 0;
     for (int32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < n_d; b += gridDim.x * blockDim.x) {
@@ -1987,162 +1991,178 @@ __device__ __forceinline__ void block_params(const PlanArgs& a)
             if ((int64_t)L.K * L.pr > L.j1 - L.j0 + 1) L.K = 0;
         }
         A.lb[b] = L;
+        A.lscan[b] = LScan{L.nitems, local_slots(L), L.j1 - L.j0 + 1, ncol};
     }
 }
 
 // ---------------------------------------------------------------------------
-// Offsets and totals (one workgroup): exclusive scans over the blocks of item
-// counts and grid slots, the FFT size classes, membership statistics.
-// The block and item scans run as one workgroup of kPlanScanThreads (at most
-// 128 VGPRs per wave): a workgroup this small fits on a compute unit as soon
-// as one workgroup of a running transform's kernels retires there, where a
-// 1024-thread one waits for a whole compute unit to drain.
+// Offsets and totals: exclusive scans over the blocks of item counts and grid
+// slots, the FFT size classes, membership statistics.  A workgroup takes a run
+// of blocks: it first adds up all blocks (and those before its run), then
+// scans its own, so that none waits for another (one workgroup over 12000
+// blocks of each kind took 117 us).  The workgroups, as that of the scan over
+// the items, are of kPlanScanThreads (at most 128 VGPRs per wave): a workgroup
+// this small fits on a compute unit as soon as one workgroup of a running
+// transform's kernels retires there, where a 1024-thread one waits for a whole
+// compute unit to drain.
 // ---------------------------------------------------------------------------
 constexpr int kPlanScanThreads = 256;
+constexpr int kPlanScanBlocks = 16;                  // workgroups of the scan over the blocks
 
 __device__ __forceinline__ void plan_scan(const PlanArgs& a)
 {
     const PlanDev& P = a.P;
     const Arena& A = a.A;
     Summary* __restrict__ sum = a.sum;
+    constexpr int kVpt = 4;                          // blocks of a kind per thread per pass (1024 per pass)
+    constexpr int kWaves = kPlanScanThreads / 64;
     __shared__ int64_t wsum[4][16];
-    __shared__ int32_t cls_cnt[kMaxFftLog2 + 1];
-    __shared__ int32_t cls_first[kMaxFftLog2 + 1];
-    __shared__ long long red[8][kPlanScanThreads / 64];
-    constexpr int32_t kFftKept = 1024;
-    __shared__ int4 kept[kFftKept];                  // FFT-path blocks: block, class, place in it
-    __shared__ int32_t n_kept, n_gridrows;
+    __shared__ int32_t cls_all[kMaxFftLog2 + 1], cls_next[kMaxFftLog2 + 1];
+    constexpr int kSums = 8 + 8;                     // all blocks: six sums, grid rows, then statistics
+    __shared__ int64_t red[kSums + 6][kWaves];
     if (sum->overflow) return;
     const int32_t n_l = sum->n_l, n_a = sum->n_a;
-    int tid = threadIdx.x;
-    const int nch = P.nch;
-    if (tid <= kMaxFftLog2) cls_cnt[tid] = 0;
-    if (tid == 0) n_kept = n_gridrows = 0;
-    __syncthreads();
-    // membership statistics: rows / columns of local and asymptotic blocks,
-    // grid cells and FFT points, and the row-side work of the
-    // asymptotic blocks (rows x cells on the direct-sum path, rows on the FFT
-    // path), gathered in the same passes
-    constexpr int kStats = 8;
-    long long st[kStats] = {0, 0, 0, 0, 0, 0, 0, 0};
-    constexpr int kVpt = 4;                          // blocks of a kind per thread per pass (1024 per pass)
-    int64_t l_items = 0;                             // items + 2^32 slots
-    int64_t a_items = 0, grid = 0;
-    int64_t pans = 0;                                // panels of points + 2^32 panels of frequencies
     const int32_t n_la = n_l > n_a ? n_l : n_a;
-    for (int32_t c0 = 0; c0 < n_la; c0 += kPlanScanThreads * kVpt) {
+    constexpr int32_t kPass = kPlanScanThreads * kVpt;
+    const int32_t run = ((n_la + kPlanScanBlocks - 1) / kPlanScanBlocks + kPass - 1) / kPass * kPass;
+    const int32_t first = (int32_t)blockIdx.x * run;
+    if (first >= n_la && first > 0) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int nch = P.nch;
+    if (tid <= kMaxFftLog2) cls_all[tid] = cls_next[tid] = 0;
+    __syncthreads();
+    // all[]: items and slots of the local blocks; items, grid slots, panels of
+    // points and of frequencies of the asymptotic ones; blocks whose rows read
+    // the grids; then rows and columns of either kind, direct-sum cells, FFT
+    // points, direct-sum row cells, FFT rows.  before[]: the first six over the
+    // blocks before the run.
+    int64_t all[kSums], before[6];
+    #pragma unroll
+    for (int q = 0; q < kSums; ++q) all[q] = 0;
+    #pragma unroll
+    for (int q = 0; q < 6; ++q) before[q] = 0;
+    #pragma unroll 2
+    for (int32_t i = tid; i < n_l; i += kPlanScanThreads) {
+        const LScan L = A.lscan[i];
+        all[0] += L.items; all[1] += L.slots; all[8] += L.rows; all[9] += L.cols;
+        if (i < first) { before[0] += L.items; before[1] += L.slots; }
+    }
+    #pragma unroll 2
+    for (int32_t i = tid; i < n_a; i += kPlanScanThreads) {
+        const AScan B = A.ascan[i];
+        all[2] += B.items; all[3] += B.slots; all[4] += B.pc; all[5] += B.pr; all[6] += B.gridrows;
+        all[10] += B.rows; all[11] += B.cols;
+        if (B.fft > 0) { all[13] += B.slots; all[15] += B.rows; }
+        else if (B.fft == 0) { all[12] += B.slots; all[14] += (int64_t)B.rows * B.slots; }
+        if (i < first) { before[2] += B.items; before[3] += B.slots; before[4] += B.pc; before[5] += B.pr; }
+        if (B.fft > 0) {
+            atomicAdd(&cls_all[B.fft], 1);
+            if (i < first) atomicAdd(&cls_next[B.fft], 1);
+        }
+    }
+    #pragma unroll
+    for (int q = 0; q < kSums; ++q) {
+        int64_t x = all[q];
+        for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
+        if (lane == 0) red[q][wave] = x;
+    }
+    if (first > 0) {
+        #pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            int64_t x = before[q];
+            for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
+            if (lane == 0) red[kSums + q][wave] = x;
+        }
+    }
+    __syncthreads();
+    auto total = [&](int q) {
+        int64_t x = 0;
+        for (int v = 0; v < kWaves; ++v) x += red[q][v];
+        return x;
+    };
+    if (blockIdx.x == 0) {
+        if (tid <= kMaxFftLog2) {
+            int32_t f = 0;
+            for (int c = 0; c < tid; ++c) f += cls_all[c];
+            sum->fft_first[tid] = f;
+            sum->fft_count[tid] = cls_all[tid];
+            if (tid == kMaxFftLog2) sum->n_fft = f + cls_all[tid];
+        }
+        if (tid == 64) {
+            const int64_t l_items = total(0), l_slots = total(1), a_items = total(2), grid = total(3), n_cp = total(4),
+                          n_rp = total(5);
+            A.gslot[n_a] = grid;
+            sum->l_row = total(8); sum->l_col = total(9); sum->a_row = total(10); sum->a_col = total(11);
+            sum->dft_cells = total(12); sum->fft_points = total(13);
+            sum->dft_row_cells = total(14); sum->fft_rows = total(15);
+            sum->n_litems = (int32_t)l_items; sum->n_aitems = (int32_t)a_items;
+            sum->max_nch = nch;
+            sum->n_gridrows = (int32_t)total(6);
+            sum->grid_cells = grid;
+            sum->n_cpan = (int32_t)n_cp; sum->n_rpan = (int32_t)n_rp; sum->n_lslots = (int32_t)l_slots;
+            // (read by the kernels that follow, not by the other workgroups of this one)
+            if (l_items > A.litem_cap || a_items > A.aitem_cap || n_cp > A.pan_cap || n_rp > A.pan_cap ||
+                l_slots > A.lslot_cap)
+                sum->scan_overflow = 1;
+        }
+    }
+    int64_t l_items = 0, l_slots = 0, a_items = 0, grid = 0, cpan = 0, rpan = 0;
+    if (first > 0) {
+        l_items = total(kSums); l_slots = total(kSums + 1); a_items = total(kSums + 2);
+        grid = total(kSums + 3); cpan = total(kSums + 4); rpan = total(kSums + 5);
+    }
+    const int32_t end = first + run < n_la ? first + run : n_la;
+    for (int32_t c0 = first; c0 < end; c0 += kPass) {
         const int32_t i0 = c0 + tid * kVpt;
-        int64_t v[kVpt][4];
-        int32_t n2[kVpt];
+        int64_t v[kVpt][4];                          // items and slots; items; grid slots; panels (2^32 apart)
+        int32_t fft[kVpt];
         #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
             v[k][0] = v[k][1] = v[k][2] = v[k][3] = 0;
-            n2[k] = 0;
+            fft[k] = 0;
             if (i0 + k < n_l) {
-                const LBlock L = A.lb[i0 + k];
-                v[k][3] = L.nitems + ((int64_t)local_slots(L) << 32);
-                st[0] += L.j1 - L.j0 + 1;
-                st[1] += L.k1 - L.k0 + 1;
+                const LScan L = A.lscan[i0 + k];
+                v[k][0] = L.items + ((int64_t)L.slots << 32);
             }
             if (i0 + k < n_a) {
-                const ABlock B = A.ab[i0 + k];
-                v[k][0] = B.nitems;
-                v[k][1] = B.K > 0 ? 0 : B.fft ? (int64_t)B.N2 : (int64_t)B.N1;
-                v[k][2] = (int64_t)B.pc + ((int64_t)B.pr << 32);
-                if (B.rK == 0) atomicAdd(&n_gridrows, 1);
-                n2[k] = B.fft ? B.N2 : 0;
-                const long long rows = B.j1 - B.j0 + 1;
-                st[2] += rows;
-                st[3] += B.k1 - B.k0 + 1;
-                if (B.fft) { st[5] += B.N2; st[7] += rows; }
-                else if (B.K == 0) { st[4] += B.N1; st[6] += rows * B.N1; }
+                const AScan B = A.ascan[i0 + k];
+                v[k][1] = B.items;
+                v[k][2] = B.slots;
+                v[k][3] = B.pc + ((int64_t)B.pr << 32);
+                fft[k] = B.fft;
             }
         }
         int64_t tot[4];
-        block_scan_vpt<4, kVpt, kPlanScanThreads / 64>(v, tot, wsum);
+        block_scan_vpt<4, kVpt, kWaves>(v, tot, wsum);
         #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
             const int32_t i = i0 + k;
             if (i < n_l) {
-                const int64_t x = l_items + v[k][3];
-                A.lb[i].item0 = (int32_t)(x & 0xffffffff);
-                A.lb[i].slot0 = (int32_t)(x >> 32);
+                A.lb[i].item0 = (int32_t)(l_items + (v[k][0] & 0xffffffff));
+                A.lb[i].slot0 = (int32_t)(l_slots + (v[k][0] >> 32));
             }
             if (i < n_a) {
-                A.ab[i].item0 = (int32_t)(a_items + v[k][0]);
-                A.ab[i].grid_off = (grid + v[k][1]) * nch;
-                A.gslot[i] = grid + v[k][1];
-                const int64_t pq = pans + v[k][2];
-                A.ab[i].cpan0 = (int32_t)(pq & 0xffffffff);
-                A.ab[i].rpan0 = (int32_t)(pq >> 32);
-                if (n2[k] > 0) {
-                    const int32_t c = 31 - __clz(n2[k]), at = atomicAdd(&cls_cnt[c], 1);
-                    const int32_t e = atomicAdd(&n_kept, 1);
-                    if (e < kFftKept) kept[e] = int4{i, c, at, 0};
+                A.ab[i].item0 = (int32_t)(a_items + v[k][1]);
+                A.ab[i].grid_off = (grid + v[k][2]) * nch;
+                A.gslot[i] = grid + v[k][2];
+                A.ab[i].cpan0 = (int32_t)(cpan + (v[k][3] & 0xffffffff));
+                A.ab[i].rpan0 = (int32_t)(rpan + (v[k][3] >> 32));
+                if (fft[k] > 0) {
+                    // FFT-path blocks grouped by size class (order inside a
+                    // class is immaterial)
+                    int32_t slot = atomicAdd(&cls_next[fft[k]], 1);
+                    for (int c = 0; c < fft[k]; ++c) slot += cls_all[c];
+                    A.fft_list[slot] = i;
+                    A.ab[i].fft_slot = slot;
                 }
             }
         }
-        a_items += tot[0];
-        grid += tot[1];
-        pans += tot[2];
-        l_items += tot[3];
-    }
-    const int32_t n_lslots = (int32_t)(l_items >> 32);
-    l_items &= 0xffffffff;
-    if (tid == 0) A.gslot[n_a] = grid;
-    __syncthreads();
-    if (tid == 0) {
-        int32_t f = 0;
-        for (int c = 0; c <= kMaxFftLog2; ++c) {
-            cls_first[c] = f;
-            sum->fft_first[c] = f;
-            sum->fft_count[c] = cls_cnt[c];
-            f += cls_cnt[c];
-            cls_cnt[c] = 0;
-        }
-        sum->n_fft = f;
-    }
-    __syncthreads();
-    // FFT-path blocks grouped by size class (order inside a class is
-    // immaterial): those kept in LDS, or (too many) all blocks once more
-    if (n_kept <= kFftKept) {
-        for (int32_t e = tid; e < n_kept; e += kPlanScanThreads) {
-            const int4 q = kept[e];
-            const int32_t slot = cls_first[q.y] + q.z;
-            A.fft_list[slot] = q.x;
-            A.ab[q.x].fft_slot = slot;
-        }
-    } else {
-        for (int32_t i = tid; i < n_a; i += kPlanScanThreads)
-            if (A.ab[i].fft) {
-                const int c = 31 - __clz(A.ab[i].N2);
-                const int32_t slot = cls_first[c] + atomicAdd(&cls_cnt[c], 1);
-                A.fft_list[slot] = i;
-                A.ab[i].fft_slot = slot;
-            }
-    }
-    for (int q = 0; q < kStats; ++q) {
-        long long x = st[q];
-        for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
-        if ((tid & 63) == 0) red[q][tid >> 6] = x;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        long long t[kStats] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int q = 0; q < kStats; ++q)
-            for (int w2 = 0; w2 < kPlanScanThreads / 64; ++w2) t[q] += red[q][w2];
-        sum->l_row = t[0]; sum->l_col = t[1]; sum->a_row = t[2]; sum->a_col = t[3];
-        sum->dft_cells = t[4]; sum->fft_points = t[5];
-        sum->dft_row_cells = t[6]; sum->fft_rows = t[7];
-        sum->n_litems = (int32_t)l_items; sum->n_aitems = (int32_t)a_items;
-        sum->max_nch = nch;
-        sum->n_gridrows = n_gridrows;
-        sum->grid_cells = grid;
-        const int32_t n_cp = (int32_t)(pans & 0xffffffff), n_rp = (int32_t)(pans >> 32);
-        sum->n_cpan = n_cp; sum->n_rpan = n_rp; sum->n_lslots = n_lslots;
-        if (l_items > A.litem_cap || a_items > A.aitem_cap || n_cp > A.pan_cap || n_rp > A.pan_cap ||
-            n_lslots > A.lslot_cap)
-            sum->overflow = 1;
+        l_items += tot[0] & 0xffffffff;
+        l_slots += tot[0] >> 32;
+        a_items += tot[1];
+        grid += tot[2];
+        cpan += tot[3] & 0xffffffff;
+        rpan += tot[3] >> 32;
     }
 }
 
@@ -2237,7 +2257,7 @@ __device__ __forceinline__ void items(const PlanArgs& a)
     const Arena& A = a.A;
     Summary* __restrict__ sum = a.sum;
     int32_t* __restrict__ a_cells = a.a_cells;
-    if (sum->overflow) return;
+    if (sum->overflow || sum->scan_overflow) return;
     const int32_t n_l = sum->n_l, n_a = sum->n_a, n_d = sum->n_d;
     const int32_t n_li = sum->n_litems, n_ai = sum->n_aitems, n_cp = sum->n_cpan, n_rp = sum->n_rpan, n_ls = sum->n_lslots;
     const int w = P.w;
@@ -2374,7 +2394,7 @@ __device__ __forceinline__ void item_scan(const PlanArgs& a)
     const int32_t* __restrict__ a_cells = a.a_cells;
     __shared__ int64_t wsum[2][16];
     __shared__ int32_t n_dense_total, n_dense_all;
-    if (sum->overflow) return;
+    if (sum->overflow || sum->scan_overflow) return;
     const int32_t n_ai = sum->n_aitems;
     const int nch = P.nch;
     constexpr int kVpt = 8;                          // items per thread per pass (2048 per pass)
@@ -2600,7 +2620,7 @@ hipError_t launch_planning(const PlanArgs& a, hipStream_t s)
         hipLaunchKernelGGL(k_subtree_blocks, dim3(kSubTrees), dim3(kSubThreads), 0, s, a);
     }
     hipLaunchKernelGGL(k_block_params, dim3(kParamBlocks), dim3(128), 0, s, a);
-    hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(kPlanScanThreads), 0, s, a);
+    hipLaunchKernelGGL(k_plan_scan, dim3(kPlanScanBlocks), dim3(kPlanScanThreads), 0, s, a);
     hipLaunchKernelGGL(k_items, dim3(kItemBlocks), dim3(128), 0, s, a);
     hipLaunchKernelGGL(k_item_scan, dim3(1), dim3(kPlanScanThreads), 0, s, a);
     return hipGetLastError();
@@ -2613,7 +2633,7 @@ hipError_t launch_planning_many(const PlanArgs* args_dev, int count, int64_t nm,
     hipLaunchKernelGGL(k_staircases_many, dim3(cdiv(nm, 256) + 1, count), dim3(256), 0, s, args_dev);
     hipLaunchKernelGGL(k_subdivide_many, dim3(1, count), dim3(kSubThreads), 0, s, args_dev);
     hipLaunchKernelGGL(k_block_params_many, dim3(kParamBlocks, count), dim3(128), 0, s, args_dev);
-    hipLaunchKernelGGL(k_plan_scan_many, dim3(1, count), dim3(kPlanScanThreads), 0, s, args_dev);
+    hipLaunchKernelGGL(k_plan_scan_many, dim3(kPlanScanBlocks, count), dim3(kPlanScanThreads), 0, s, args_dev);
     hipLaunchKernelGGL(k_items_many, dim3(kItemBlocks, count), dim3(128), 0, s, args_dev);
     hipLaunchKernelGGL(k_item_scan_many, dim3(1, count), dim3(kPlanScanThreads), 0, s, args_dev);
     return hipGetLastError();
