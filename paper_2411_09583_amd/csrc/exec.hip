@@ -1340,8 +1340,8 @@ __global__ __launch_bounds__(256) void k_spread_mfma_many(const PlanDev* __restr
 }
 
 // ---------------------------------------------------------------------------
-// Grid assembly: each grid slot sums the item partials that cover it, in item
-// order, and multiplies channel p by its factor beta_p (the Hankel coefficient
+// Grid assembly: each grid slot sums the item partials that cover it and
+// multiplies channel p by its factor beta_p (the Hankel coefficient
 // with the sign and the factor i the combination step gives it), so that the
 // row pass only sums the channels weighted by powers of 1/(om r0).
 // Direct-sum-path grids are stored cell-major [cell][channel].  FFT
@@ -1349,6 +1349,14 @@ __global__ __launch_bounds__(256) void k_spread_mfma_many(const PlanDev* __restr
 // psi^(l) = alpha2 ES^(|l| alpha2), alpha2 = w pi / N2 (the deconvolution of the
 // type-2 step) and placed at FFT index l mod N2, channel-major [channel][N2];
 // all other FFT inputs are zero.
+//
+// A thread takes a slot with all its channels: the items that cover it are
+// found, and the deconvolution computed, once, and a thread's loads and the
+// wave's stores are contiguous (95 us at the 1e6 zeros of J_0, 6 channels of
+// 2^22 points; 196 with a thread a slot and channel).  Where a block's points
+// crowd its cells (grid_crowded) dozens of items cover each, and the block's
+// slots take a thread a channel (at 1e6 x 1e6 uniform points 19 us, 122
+// without).  A crowded slot of another block is added up by the whole wave.
 // ---------------------------------------------------------------------------
 // Partial i as double2: PT is double2, or float2 in the FP32-spreading mode
 // (widened here, so the grids are assembled in FP64).
@@ -1359,103 +1367,169 @@ __device__ __forceinline__ double2 load_partial(const double2* __restrict__ part
     return make_double2((double)v.x, (double)v.y);
 }
 
+constexpr int kReduceItems = 4;      // items of a slot in flight
+constexpr int kReduceLight = 32;     // items of a slot up to which its own thread adds them up
+constexpr int kReduceChannels = 8;   // channels of a slot in flight
+
 template <typename PT>
 __device__ __forceinline__ void spread_reduce_body(const PlanDev& P, int bid)
 {
     const double2* __restrict__ part = P.part;
     double2* __restrict__ grids = P.grids;
-    int64_t t = (int64_t)bid * blockDim.x + threadIdx.x;
-    const int nch = P.nch;
-    const int64_t total = P.grid_cells * nch;
-    // Block owning a slot: the last block b with gslot[b] <= slot.  The wave
-    // searches once for the slot of its first lane (uniform, through the scalar
-    // unit); a wave spans at most 64 slots, so each lane then steps forward
-    // over the few blocks that start inside that span.
-    int64_t t0 = (int64_t)bid * blockDim.x + (threadIdx.x & ~63);
-    int64_t slot0 = __builtin_amdgcn_readfirstlane((int32_t)((t0 < total ? t0 : total - 1) / nch));
+    const int nch = P.nch, lane = threadIdx.x & 63;
+    const int64_t total = P.grid_units;
+    const int64_t unit = (int64_t)bid * blockDim.x + threadIdx.x;
+    // Block owning a unit: the last block b with gunit[b] <= unit.  The wave
+    // searches once for its first lane's unit (uniform, through the scalar
+    // unit), and each lane then steps forward over the few blocks that start
+    // inside the wave's 64 units.
+    const int64_t unit0 = unit - lane;
+    if (unit0 >= total) return;
     int32_t lo = 0, hi = P.n_a - 1;
+    const int64_t probe = ((int64_t)__builtin_amdgcn_readfirstlane((int32_t)(unit0 >> 32)) << 32) |
+                          (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)unit0);
     while (lo < hi) {
         int32_t mid = (lo + hi + 1) >> 1;
-        if (P.gslot[mid] <= slot0) lo = mid; else hi = mid - 1;
+        if (P.gunit[mid] <= probe) lo = mid; else hi = mid - 1;
     }
-    // the wave's last slot: when it lies in the same block as the first, the
+    const bool on = unit < total;
+    // when the wave's last unit lies in the same block as the first, the
     // block's fields are read once through the scalar unit
-    const int64_t tl = t0 + 63 < total ? t0 + 63 : total - 1;
-    const int64_t slot_last = __builtin_amdgcn_readfirstlane((int32_t)(tl / nch));
-    const bool one_block = P.gslot[lo + 1] > slot_last;
-    if (t >= total) return;
-    int64_t slot = t / nch;
-    int p = (int)(t % nch);
-    while (P.gslot[lo + 1] <= slot) ++lo;
-    const ABlock B = one_block ? P.ab[__builtin_amdgcn_readfirstlane(lo)] : P.ab[lo];
-    int64_t local = slot - P.gslot[lo];
+    const int64_t last = unit0 + 63 < total ? unit0 + 63 : total - 1;
+    const bool one_block = P.gunit[lo + 1] > last;
+    int32_t blk = lo;
+    if (!one_block && on)
+        while (P.gunit[blk + 1] <= unit) ++blk;
+    struct Fields { int64_t grid_off; int32_t fft, N2, llo, N1, item0, nitems; };
+    auto fields = [&](const ABlock& B) { return Fields{B.grid_off, B.fft, B.N2, B.llo, B.N1, B.item0, B.nitems}; };
+    const Fields B = one_block ? fields(P.ab[__builtin_amdgcn_readfirstlane(lo)]) : fields(P.ab[blk]);
+    int64_t local = unit - P.gunit[blk];
+    const bool by_channel = nch > 1 && P.gunit[blk + 1] - P.gunit[blk] != P.gslot[blk + 1] - P.gslot[blk];
+    int own = 0;                                     // the thread's channel
+    if (by_channel) {
+        own = (int)(local % nch);
+        local /= nch;
+    }
     int32_t l;
     if (B.fft) l = local < B.N2 / 2 ? (int32_t)local : (int32_t)(local - B.N2);
     else l = B.llo + (int32_t)local;
-    double sr = 0.0, si = 0.0;
-    if (l >= B.llo && l < B.llo + B.N1) {
+    int32_t a = 0, b = 0;
+    if (on && l >= B.llo && l < B.llo + B.N1) {
         // Items covering cell l: both ends of the items' cell ranges increase
         // with the item index, so they form one run [a, b): a is the first item
-        // ending after l, b the first starting after l.  With the run known the
-        // partials are loaded several at a time and still added in item order.
+        // ending after l, b the first starting after l.
         const int32_t i0 = B.item0, i1 = B.item0 + B.nitems;
-        int32_t a = i0, hi = i1;
-        while (a < hi) {
-            int32_t mid = (a + hi) >> 1;
+        a = i0;
+        int32_t top = i1;
+        while (a < top) {
+            int32_t mid = (a + top) >> 1;
             const Item& I = P.aitems[mid];
-            if (I.sub_lo + I.sub_n <= l) a = mid + 1; else hi = mid;
+            if (I.sub_lo + I.sub_n <= l) a = mid + 1; else top = mid;
         }
-        // b: up to four steps forward from a (where points are spread out a
-        // cell lies in the subgrids of one or two items), then a binary
-        // search over the rest (where a block's points crowd a few cells,
-        // dozens of items cover each)
-        int32_t b = a;
-        for (int k = 0; k < 4 && b < i1 && P.aitems[b].sub_lo <= l; ++k) ++b;
-        if (b < i1 && P.aitems[b].sub_lo <= l) {
-            hi = i1;
-            ++b;
-            while (b < hi) {
-                int32_t mid = (b + hi) >> 1;
-                if (P.aitems[mid].sub_lo <= l) b = mid + 1; else hi = mid;
+        // b: a few steps forward from a (where points are spread out a cell
+        // lies in the subgrids of one or two items), then a binary search
+        b = a;
+        for (int k = 0; k <= kReduceItems && b < i1 && P.aitems[b].sub_lo <= l; ++k) ++b;
+        if (b - a > kReduceItems) {
+            top = i1;
+            while (b < top) {
+                int32_t mid = (b + top) >> 1;
+                if (P.aitems[mid].sub_lo <= l) b = mid + 1; else top = mid;
             }
-        }
-        int32_t it = a;
-        for (; it + 16 <= b; it += 16) {
-            double2 v[16];
-            #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const Item& I = P.aitems[it + q];
-                v[q] = load_partial<PT>(part, I.off + (int64_t)(l - I.sub_lo) * nch + p);
-            }
-            #pragma unroll
-            for (int q = 0; q < 16; ++q) { sr += v[q].x; si += v[q].y; }
-        }
-        for (; it + 4 <= b; it += 4) {
-            double2 v[4];
-            #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const Item& I = P.aitems[it + q];
-                v[q] = load_partial<PT>(part, I.off + (int64_t)(l - I.sub_lo) * nch + p);
-            }
-            #pragma unroll
-            for (int q = 0; q < 4; ++q) { sr += v[q].x; si += v[q].y; }
-        }
-        for (; it < b; ++it) {
-            const Item& I = P.aitems[it];
-            double2 v = load_partial<PT>(part, I.off + (int64_t)(l - I.sub_lo) * nch + p);
-            sr += v.x;
-            si += v.y;
         }
     }
-    // channel factor: real for even p, i times real for odd p
-    double f = P.chan[p];
-    double2 v = (p & 1) ? make_double2(-si * f, sr * f) : make_double2(sr * f, si * f);
+    // 1 / psi^(l) on the FFT path
+    double scale = 1.0;
     if (B.fft) {
-        double a2 = P.w * kPi / B.N2;
-        double s = 1.0 / (a2 * eshat(P, fabs((double)l) * a2));
-        grids[B.grid_off + (int64_t)p * B.N2 + local] = make_double2(v.x * s, v.y * s);
-    } else {
-        grids[B.grid_off + local * nch + p] = v;
+        const double a2 = P.w * kPi / B.N2;
+        scale = 1.0 / (a2 * eshat(P, fabs((double)l) * a2));
+    }
+    // channel factor: real for even p, i times real for odd p
+    auto store = [&](int p, double sr, double si, const Fields& F, int64_t at, double sc) {
+        const double f = P.chan[p];
+        const double2 v = (p & 1) ? make_double2(-si * f, sr * f) : make_double2(sr * f, si * f);
+        if (F.fft) grids[F.grid_off + (int64_t)p * F.N2 + at] = make_double2(v.x * sc, v.y * sc);
+        else grids[F.grid_off + at * nch + p] = v;
+    };
+    if (on && by_channel) {
+        // partials several at a time, added in item order
+        double sr = 0.0, si = 0.0;
+        int32_t it = a;
+        auto add = [&](auto count) {
+            constexpr int N = decltype(count)::value;
+            double2 v[N];
+            #pragma unroll
+            for (int q = 0; q < N; ++q) {
+                const Item& I = P.aitems[it + q];
+                v[q] = load_partial<PT>(part, I.off + (int64_t)(l - I.sub_lo) * nch + own);
+            }
+            #pragma unroll
+            for (int q = 0; q < N; ++q) { sr += v[q].x; si += v[q].y; }
+            it += N;
+        };
+        while (it + 16 <= b) add(std::integral_constant<int, 16>());
+        while (it + 4 <= b) add(std::integral_constant<int, 4>());
+        while (it < b) add(std::integral_constant<int, 1>());
+        store(own, sr, si, B, local, scale);
+    }
+    const bool crowded = !by_channel && b - a > kReduceLight;
+    if (on && !by_channel && !crowded) {
+        for (int p0 = 0; p0 < nch; p0 += kReduceChannels) {
+            double sr[kReduceChannels], si[kReduceChannels];
+            #pragma unroll
+            for (int u = 0; u < kReduceChannels; ++u) sr[u] = si[u] = 0.0;
+            for (int32_t it = a; it < b; it += kReduceItems) {
+                int64_t from[kReduceItems];
+                #pragma unroll
+                for (int k = 0; k < kReduceItems; ++k) {
+                    from[k] = 0;
+                    if (it + k < b) {
+                        const Item& I = P.aitems[it + k];
+                        from[k] = I.off + (int64_t)(l - I.sub_lo) * nch;
+                    }
+                }
+                #pragma unroll
+                for (int k = 0; k < kReduceItems; ++k)
+                    if (it + k < b) {
+                        #pragma unroll
+                        for (int u = 0; u < kReduceChannels; ++u)
+                            if (p0 + u < nch) {
+                                const double2 v = load_partial<PT>(part, from[k] + p0 + u);
+                                sr[u] += v.x;
+                                si[u] += v.y;
+                            }
+                    }
+            }
+            #pragma unroll
+            for (int u = 0; u < kReduceChannels; ++u)
+                if (p0 + u < nch) store(p0 + u, sr[u], si[u], B, local, scale);
+        }
+    }
+    // crowded slots, one after the other: lane (g, p) adds items a + g,
+    // a + g + groups, .. of channel p
+    const int groups = 64 / nch, g = lane / nch, p = lane - g * nch;
+    for (uint64_t left = __ballot(on && crowded); left; left &= left - 1) {
+        const int h = __builtin_ctzll(left);
+        const int32_t ah = __shfl(a, h), bh = __shfl(b, h), lh = __shfl(l, h);
+        double sr = 0.0, si = 0.0;
+        if (g < groups) {
+            #pragma unroll 4
+            for (int32_t it = ah + g; it < bh; it += groups) {
+                const Item& I = P.aitems[it];
+                const double2 v = load_partial<PT>(part, I.off + (int64_t)(lh - I.sub_lo) * nch + p);
+                sr += v.x;
+                si += v.y;
+            }
+        }
+        double tr = sr, ti = si;
+        for (int q = 1; q < groups; ++q) {
+            tr += __shfl(sr, q * nch + p);
+            ti += __shfl(si, q * nch + p);
+        }
+        const Fields F{__shfl(B.grid_off, h), __shfl(B.fft, h), __shfl(B.N2, h), 0, 0, 0, 0};
+        const int64_t at = __shfl(local, h);
+        const double sc = __shfl(scale, h);
+        if (g == 0) store(p, tr, ti, F, at, sc);
     }
 }
 
@@ -3045,9 +3119,9 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
     }
     if (P.grid_cells > 0) {
         if (P.fp32)
-            hipLaunchKernelGGL(k_spread_reduce<float2>, dim3(cdiv64(P.grid_cells * P.nch, 256)), dim3(256), 0, s, P);
+            hipLaunchKernelGGL(k_spread_reduce<float2>, dim3(cdiv64(P.grid_units, 256)), dim3(256), 0, s, P);
         else
-            hipLaunchKernelGGL(k_spread_reduce<double2>, dim3(cdiv64(P.grid_cells * P.nch, 256)), dim3(256), 0, s, P);
+            hipLaunchKernelGGL(k_spread_reduce<double2>, dim3(cdiv64(P.grid_units, 256)), dim3(256), 0, s, P);
     }
     mark(marks, 4, s);
     if (P.small.n > 0 && P.small.wg0[P.small.n] > 0)
@@ -3178,7 +3252,7 @@ void build_batch_schedule(const BatchTransform* tr, int count, const int* order,
     }
     for (int fp32 = 0; fp32 <= 1; ++fp32)
         add(kSpreadReduce, 0, fp32, 256, [&](const BatchTransform& T, size_t&) -> int64_t {
-            return live(*T.P) && T.P->fp32 == fp32 ? cdiv64(T.P->grid_cells * T.P->nch, 256) : 0;
+            return live(*T.P) && T.P->fp32 == fp32 ? cdiv64(T.P->grid_units, 256) : 0;
         });
     add(kFftSmall, 0, 0, 256, [&](const BatchTransform& T, size_t& lds) -> int64_t {
         const SmallFfts& F = T.P->small;

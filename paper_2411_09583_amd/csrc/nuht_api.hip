@@ -1316,6 +1316,7 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
     slab.add(A.alist, (size_t)A.aitem_cap);
     slab.add(A.fft_list, (size_t)A.a_cap);
     slab.add(A.gslot, (size_t)A.a_cap + 1);
+    slab.add(A.gunit, (size_t)A.a_cap + 1);
     slab.add(A.ascan, (size_t)A.a_cap);
     slab.add(A.lscan, (size_t)A.l_cap);
     slab.add(A.lwork, (size_t)A.lslot_cap);
@@ -1333,7 +1334,7 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
     }
     NUHT_TRY(slab.commit(pp.tmp));
     P.nodes = A.nodes; P.lb = A.lb; P.ab = A.ab; P.db = A.db;
-    P.litems = A.litems; P.aitems = A.aitems; P.alist = A.alist; P.fft_list = A.fft_list; P.gslot = A.gslot;
+    P.litems = A.litems; P.aitems = A.aitems; P.alist = A.alist; P.fft_list = A.fft_list; P.gslot = A.gslot; P.gunit = A.gunit;
     P.cpans = A.cpans; P.rlist = A.rlist; P.tlist = A.tlist; P.wlist = A.wlist; P.flist = A.flist;
     P.lwork = A.lwork; P.dlist = A.dlist;
     P.tlist_cap = A.pan_cap; P.rlist_cap = A.aitem_cap;
@@ -1401,6 +1402,7 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     P.n_litems = S.n_litems; P.n_aitems = S.n_aitems; P.n_adense = S.n_adense; P.n_amed = S.n_amed;
     P.n_tsingle = S.n_tsingle; P.n_tmulti = S.n_tmulti; P.n_wmulti = S.n_wmulti;
     P.n_ritems = S.n_ritems; P.n_rsmall = S.n_rsmall;
+    P.grid_units = S.grid_units;
     P.n_fpan = S.n_fpan; P.n_gridrows = S.n_gridrows;
     P.spread_turns = spread_turns(S.n_aspread - S.n_adense - S.n_amed);
     P.n_lwork = S.n_lwork; P.n_dentry = S.n_dentry; P.n_drank = S.n_drank;

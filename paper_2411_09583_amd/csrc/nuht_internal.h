@@ -106,6 +106,11 @@ struct LBlock {
     double D, rw;
 };
 
+// Whether a grid of N1 cells is assembled by a thread a cell and channel: the
+// items, w + 2 cells wider than their points, cover a cell more than three
+// times on average.  (Else a thread a cell: see k_spread_reduce.)
+__host__ __device__ inline bool grid_crowded(int32_t N1, int32_t nitems, int32_t w) { return (int64_t)nitems * (w + 2) > 2 * (int64_t)N1; }
+
 // Slots of a local block's rows, and those evaluated by one wave.
 __host__ __device__ inline int32_t local_slots(const LBlock& B) { return B.K > 0 ? B.pr : (B.j1 - B.j0 + kRankK) / kRankK; }
 __host__ __device__ inline int32_t local_wave_slots(int32_t K) { return K > 0 ? 64 / K : 64 / kRankK; }
@@ -197,6 +202,7 @@ struct Summary {
     int32_t n_dentry, n_drank;     // direct blocks applied entry by entry, through expansions
     int64_t l_row, l_col, a_row, a_col, d_ent;
     int64_t grid_cells;     // sum N1 (all asymptotic blocks)
+    int64_t grid_units;     // threads that assemble the grids
     int64_t dft_cells;      // sum N1 over direct-sum-path blocks
     int64_t fft_points;     // sum N2 over FFT-path blocks
     int64_t part_cells;     // sum of item subgrid sizes
@@ -255,6 +261,8 @@ struct PlanDev {
     const int32_t* alist;            // spreading order: dense items from the front, the others from the back
     const int32_t* fft_list;         // FFT-path blocks grouped by size class
     const int64_t* gslot;            // first grid slot of each asymptotic block; gslot[n_a] = all slots
+    const int64_t* gunit;            // first unit of its grid's assembly; gunit[n_a] = grid_units
+    int64_t grid_units;
     const double* es_poly;           // ES kernel pieces, w x (kEsDeg + 1) monomial coefficients
     const double* half_tab;          // half-integer orders: [panel][l][degree] local coefficients
     double half_inv_h;               // 1 / panel width

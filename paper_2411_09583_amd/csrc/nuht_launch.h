@@ -19,6 +19,7 @@ struct Rect {
 struct alignas(16) AScan {
     int32_t items, slots, pc, pr;       // slots: of its grid
     int32_t rows, cols, fft, gridrows;  // fft: log2 N2 of an FFT-path block, 0 of a direct-sum one, -1 of a rank block
+    int64_t units, pad;                 // threads that assemble its grid
 };
 struct alignas(16) LScan {
     int32_t items, slots, rows, cols;
@@ -38,6 +39,7 @@ struct Arena {
     int32_t* alist;      // spreading order of the asymptotic items (aitem_cap)
     int32_t* fft_list;
     int64_t* gslot;      // first grid slot of each asymptotic block, then the total (a_cap + 1)
+    int64_t* gunit;      // first unit of its grid's assembly, then the total (a_cap + 1)
     Panel* cpans;        // panels of the rank blocks' points (pan_cap)
     RankItem* rlist;     // items of rank blocks (aitem_cap)
     Panel* tlist;        // panels of frequencies to translate (pan_cap)

@@ -1934,7 +1934,8 @@ __device__ __forceinline__ void block_params(const PlanArgs& a)
         if (lane == 0) {
             A.ab[b] = B;
             A.ascan[b] = AScan{B.nitems, B.K > 0 ? 0 : fft ? N2 : N1, B.pc, B.pr, B.j1 - B.j0 + 1, ncol,
-                               B.K > 0 ? -1 : fft ? 31 - __clz(N2) : 0, B.rK == 0 ? 1 : 0};
+                               B.K > 0 ? -1 : fft ? 31 - __clz(N2) : 0, B.rK == 0 ? 1 : 0,
+                               B.K > 0 ? 0 : (int64_t)(fft ? N2 : N1) * (grid_crowded(N1, B.nitems, w) ? P.nch : 1), 0};
         }
     }
     long long entries = 0;
@@ -2016,10 +2017,10 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
     Summary* __restrict__ sum = a.sum;
     constexpr int kVpt = 4;                          // blocks of a kind per thread per pass (1024 per pass)
     constexpr int kWaves = kPlanScanThreads / 64;
-    __shared__ int64_t wsum[4][16];
+    __shared__ int64_t wsum[5][16];
     __shared__ int32_t cls_all[kMaxFftLog2 + 1], cls_next[kMaxFftLog2 + 1];
-    constexpr int kSums = 8 + 8;                     // all blocks: six sums, grid rows, then statistics
-    __shared__ int64_t red[kSums + 6][kWaves];
+    constexpr int kSums = 8 + 8;                     // all blocks: seven sums, grid rows, then statistics
+    __shared__ int64_t red[kSums + 7][kWaves];
     if (sum->overflow) return;
     const int32_t n_l = sum->n_l, n_a = sum->n_a;
     const int32_t n_la = n_l > n_a ? n_l : n_a;
@@ -2032,15 +2033,15 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
     if (tid <= kMaxFftLog2) cls_all[tid] = cls_next[tid] = 0;
     __syncthreads();
     // all[]: items and slots of the local blocks; items, grid slots, panels of
-    // points and of frequencies of the asymptotic ones; blocks whose rows read
-    // the grids; then rows and columns of either kind, direct-sum cells, FFT
-    // points, direct-sum row cells, FFT rows.  before[]: the first six over the
+    // points and of frequencies and assembly units of the asymptotic ones;
+    // blocks whose rows read the grids; then rows and columns of either kind, direct-sum cells, FFT
+    // points, direct-sum row cells, FFT rows.  before[]: the first seven over the
     // blocks before the run.
-    int64_t all[kSums], before[6];
+    int64_t all[kSums], before[7];
     #pragma unroll
     for (int q = 0; q < kSums; ++q) all[q] = 0;
     #pragma unroll
-    for (int q = 0; q < 6; ++q) before[q] = 0;
+    for (int q = 0; q < 7; ++q) before[q] = 0;
     #pragma unroll 2
     for (int32_t i = tid; i < n_l; i += kPlanScanThreads) {
         const LScan L = A.lscan[i];
@@ -2050,11 +2051,11 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
     #pragma unroll 2
     for (int32_t i = tid; i < n_a; i += kPlanScanThreads) {
         const AScan B = A.ascan[i];
-        all[2] += B.items; all[3] += B.slots; all[4] += B.pc; all[5] += B.pr; all[6] += B.gridrows;
+        all[2] += B.items; all[3] += B.slots; all[4] += B.pc; all[5] += B.pr; all[6] += B.units; all[7] += B.gridrows;
         all[10] += B.rows; all[11] += B.cols;
         if (B.fft > 0) { all[13] += B.slots; all[15] += B.rows; }
         else if (B.fft == 0) { all[12] += B.slots; all[14] += (int64_t)B.rows * B.slots; }
-        if (i < first) { before[2] += B.items; before[3] += B.slots; before[4] += B.pc; before[5] += B.pr; }
+        if (i < first) { before[2] += B.items; before[3] += B.slots; before[4] += B.pc; before[5] += B.pr; before[6] += B.units; }
         if (B.fft > 0) {
             atomicAdd(&cls_all[B.fft], 1);
             if (i < first) atomicAdd(&cls_next[B.fft], 1);
@@ -2068,7 +2069,7 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
     }
     if (first > 0) {
         #pragma unroll
-        for (int q = 0; q < 6; ++q) {
+        for (int q = 0; q < 7; ++q) {
             int64_t x = before[q];
             for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
             if (lane == 0) red[kSums + q][wave] = x;
@@ -2092,12 +2093,13 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
             const int64_t l_items = total(0), l_slots = total(1), a_items = total(2), grid = total(3), n_cp = total(4),
                           n_rp = total(5);
             A.gslot[n_a] = grid;
+            A.gunit[n_a] = sum->grid_units = total(6);
             sum->l_row = total(8); sum->l_col = total(9); sum->a_row = total(10); sum->a_col = total(11);
             sum->dft_cells = total(12); sum->fft_points = total(13);
             sum->dft_row_cells = total(14); sum->fft_rows = total(15);
             sum->n_litems = (int32_t)l_items; sum->n_aitems = (int32_t)a_items;
             sum->max_nch = nch;
-            sum->n_gridrows = (int32_t)total(6);
+            sum->n_gridrows = (int32_t)total(7);
             sum->grid_cells = grid;
             sum->n_cpan = (int32_t)n_cp; sum->n_rpan = (int32_t)n_rp; sum->n_lslots = (int32_t)l_slots;
             // (read by the kernels that follow, not by the other workgroups of this one)
@@ -2106,19 +2108,20 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
                 sum->scan_overflow = 1;
         }
     }
-    int64_t l_items = 0, l_slots = 0, a_items = 0, grid = 0, cpan = 0, rpan = 0;
+    int64_t l_items = 0, l_slots = 0, a_items = 0, grid = 0, cpan = 0, rpan = 0, unit = 0;
     if (first > 0) {
         l_items = total(kSums); l_slots = total(kSums + 1); a_items = total(kSums + 2);
         grid = total(kSums + 3); cpan = total(kSums + 4); rpan = total(kSums + 5);
+        unit = total(kSums + 6);
     }
     const int32_t end = first + run < n_la ? first + run : n_la;
     for (int32_t c0 = first; c0 < end; c0 += kPass) {
         const int32_t i0 = c0 + tid * kVpt;
-        int64_t v[kVpt][4];                          // items and slots; items; grid slots; panels (2^32 apart)
+        int64_t v[kVpt][5];                          // items and slots; items; grid slots; panels (2^32 apart); units
         int32_t fft[kVpt];
         #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
-            v[k][0] = v[k][1] = v[k][2] = v[k][3] = 0;
+            v[k][0] = v[k][1] = v[k][2] = v[k][3] = v[k][4] = 0;
             fft[k] = 0;
             if (i0 + k < n_l) {
                 const LScan L = A.lscan[i0 + k];
@@ -2129,11 +2132,12 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
                 v[k][1] = B.items;
                 v[k][2] = B.slots;
                 v[k][3] = B.pc + ((int64_t)B.pr << 32);
+                v[k][4] = B.units;
                 fft[k] = B.fft;
             }
         }
-        int64_t tot[4];
-        block_scan_vpt<4, kVpt, kWaves>(v, tot, wsum);
+        int64_t tot[5];
+        block_scan_vpt<5, kVpt, kWaves>(v, tot, wsum);
         #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
             const int32_t i = i0 + k;
@@ -2145,6 +2149,7 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
                 A.ab[i].item0 = (int32_t)(a_items + v[k][1]);
                 A.ab[i].grid_off = (grid + v[k][2]) * nch;
                 A.gslot[i] = grid + v[k][2];
+                A.gunit[i] = unit + v[k][4];
                 A.ab[i].cpan0 = (int32_t)(cpan + (v[k][3] & 0xffffffff));
                 A.ab[i].rpan0 = (int32_t)(rpan + (v[k][3] >> 32));
                 if (fft[k] > 0) {
@@ -2163,6 +2168,7 @@ __device__ __forceinline__ void plan_scan(const PlanArgs& a)
         grid += tot[2];
         cpan += tot[3] & 0xffffffff;
         rpan += tot[3] >> 32;
+        unit += tot[4];
     }
 }
 
