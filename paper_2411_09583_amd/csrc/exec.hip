@@ -1348,12 +1348,13 @@ __global__ __launch_bounds__(256) void k_spread_mfma_many(const PlanDev* __restr
 // path: mode l of the spread grid is divided by the inner kernel's transform
 // psi^(l) = alpha2 ES^(|l| alpha2), alpha2 = w pi / N2 (the deconvolution of the
 // type-2 step) and placed at FFT index l mod N2, channel-major [channel][N2];
-// all other FFT inputs are zero.
+// all other FFT inputs are zero (of FFTs above kSmallFft they are not written:
+// half of the traffic of the assembly, and of the first pass's reads).
 //
 // A thread takes a slot with all its channels: the items that cover it are
 // found, and the deconvolution computed, once, and a thread's loads and the
-// wave's stores are contiguous (95 us at the 1e6 zeros of J_0, 6 channels of
-// 2^22 points; 196 with a thread a slot and channel).  Where a block's points
+// wave's stores are contiguous (101 us at the 1e6 zeros of J_0, 6 channels of
+// 2^22 points, and 76 without the zeros; 196 with a thread a slot and channel).  Where a block's points
 // crowd its cells (grid_crowded) dozens of items cover each, and the block's
 // slots take a thread a channel (at 1e6 x 1e6 uniform points 19 us, 122
 // without).  A crowded slot of another block is added up by the whole wave.
@@ -1367,6 +1368,7 @@ __device__ __forceinline__ double2 load_partial(const double2* __restrict__ part
     return make_double2((double)v.x, (double)v.y);
 }
 
+constexpr int32_t kSmallFft = 4096;  // FFTs up to this are one kernel (k_fft_small), which reads all inputs
 constexpr int kReduceItems = 4;      // items of a slot in flight
 constexpr int kReduceLight = 32;     // items of a slot up to which its own thread adds them up
 constexpr int kReduceChannels = 8;   // channels of a slot in flight
@@ -1414,7 +1416,10 @@ __device__ __forceinline__ void spread_reduce_body(const PlanDev& P, int bid)
     if (B.fft) l = local < B.N2 / 2 ? (int32_t)local : (int32_t)(local - B.N2);
     else l = B.llo + (int32_t)local;
     int32_t a = 0, b = 0;
-    if (on && l >= B.llo && l < B.llo + B.N1) {
+    const bool spread = l >= B.llo && l < B.llo + B.N1;
+    // (the first pass of a large FFT takes the other inputs as zero)
+    const bool write = on && (spread || !B.fft || B.N2 <= kSmallFft);
+    if (on && spread) {
         // Items covering cell l: both ends of the items' cell ranges increase
         // with the item index, so they form one run [a, b): a is the first item
         // ending after l, b the first starting after l.
@@ -1451,7 +1456,7 @@ __device__ __forceinline__ void spread_reduce_body(const PlanDev& P, int bid)
         if (F.fft) grids[F.grid_off + (int64_t)p * F.N2 + at] = make_double2(v.x * sc, v.y * sc);
         else grids[F.grid_off + at * nch + p] = v;
     };
-    if (on && by_channel) {
+    if (write && by_channel) {
         // partials several at a time, added in item order
         double sr = 0.0, si = 0.0;
         int32_t it = a;
@@ -1473,7 +1478,7 @@ __device__ __forceinline__ void spread_reduce_body(const PlanDev& P, int bid)
         store(own, sr, si, B, local, scale);
     }
     const bool crowded = !by_channel && b - a > kReduceLight;
-    if (on && !by_channel && !crowded) {
+    if (write && !by_channel && !crowded) {
         for (int p0 = 0; p0 < nch; p0 += kReduceChannels) {
             double sr[kReduceChannels], si[kReduceChannels];
             #pragma unroll
@@ -1685,6 +1690,7 @@ __device__ void lds_fft_lines(double2* sm, int logL, int lines, int ls, const do
 // e = (b_lo & lo_mask) (b_hi + kmul k).
 struct FftCol {
     int32_t logL, logLines, logBlo, to_scratch;
+    int32_t from_grid, pad;  // the pass that reads the assembled grid (written within the spread cells alone)
     int64_t in_es, in_hs, out_es, out_hs, lo_mask, kmul;
 };
 
@@ -1736,7 +1742,12 @@ __device__ __forceinline__ void fft_col_body(const PlanDev& P, int bid, const Ff
     #pragma unroll
     for (int u = 0; u < kPer; ++u) {
         int e = threadIdx.x + u * 256;
-        if (e < tile) v[u] = xs[(int64_t)(e >> C.logLines) * C.in_es + (e & (lines - 1))];
+        const int64_t at = (int64_t)(e >> C.logLines) * C.in_es + (e & (lines - 1));
+        v[u] = make_double2(0.0, 0.0);
+        if (e < tile) {
+            const int64_t i = blo0 + bhi * C.in_hs + at;
+            if (!C.from_grid || i < B.llo + B.N1 || i >= N + B.llo) v[u] = xs[at];
+        }
     }
     fft_stage_twiddles(tw, T, C.logL);
     #pragma unroll
@@ -3016,11 +3027,11 @@ static bool fft_pass(const FftClass& K, int nch, int pass, FftPass& F, int& bloc
         if (logNb == 0) return false;
         c.logL = logNb; c.logLines = fft_log_lines(logNb); c.logBlo = logN1 + logNa; c.to_scratch = 0;
         c.in_es = N1 * Na; c.in_hs = 0; c.out_es = N1 * Na; c.out_hs = 0;
-        c.lo_mask = ~(N1 - 1); c.kmul = 1;
+        c.lo_mask = ~(N1 - 1); c.kmul = 1; c.from_grid = 1;
     } else if (pass == 1) {
         c.logL = logNa; c.logLines = fft_log_lines(logNa); c.logBlo = logN1; c.to_scratch = 1;
         c.in_es = N1; c.in_hs = N1 * Na; c.out_es = N1 * Nb; c.out_hs = N1;
-        c.lo_mask = ~int64_t(0); c.kmul = Nb;
+        c.lo_mask = ~int64_t(0); c.kmul = Nb; c.from_grid = logNb == 0 ? 1 : 0;
     } else {
         c.logL = logN1; c.logLines = fft_log_lines(logN1);
         blocks = ntr * (int)((int64_t(1) << (logN - logN1)) >> c.logLines);

@@ -60,3 +60,25 @@ def test_rows_of_fft_blocks(nuht, xi, m):
         assert diff <= 0.1 * eps + 2e-14
         p.close()
         q.close()
+
+
+@pytest.mark.parametrize("xi", [700.0, 3000.0, 40000.0])
+def test_passes_of_one_plan(nuht, xi):
+    # grids are written within their spread cells alone, and read at the
+    # frequencies' cells: later passes find an earlier one's transform there
+    n, m, nu, eps = 500, 3000, 3, 1e-11
+    z = oparams.any_parameters(nu, eps)[1]
+    rng = np.random.default_rng(int(xi))
+    for low, high in ((1.0, 2.0), (1.9, 2.0)):        # cells over half of the grid, and few
+        r = np.concatenate([[low, high], rng.uniform(low, high, n - 2)])
+        w = 1.5 * z + 4.0 * xi / (high - low) * 0.5 * np.concatenate([[0.0, 1.0], rng.uniform(0.0, 1.0, m - 2)])
+        p = nuht.Plan(dev(r), dev(w), nu, eps)
+        assert p.info()["n_fft_blocks"] == 1
+        k = np.unique(np.concatenate([[0, 1], np.linspace(0, m - 1, 200).astype(int)]))
+        for scale in (1e6, 1.0, 1e-6):
+            c = scale * rng.standard_normal(n)
+            g = p.execute(dev(c)).cpu().numpy()
+            err = np.max(np.abs(g[k] - direct.dht(nu, r, c, w[k]))) / np.sum(np.abs(c))
+            print("xi", xi, low, scale, "err", err, flush=True)
+            assert err <= eps
+        p.close()
