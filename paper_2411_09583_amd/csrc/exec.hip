@@ -1798,6 +1798,10 @@ __device__ __forceinline__ void fft_row_body(const PlanDev& P, int bid, const Ff
     int slot = tr / nch, ch = tr - slot * nch;
     const ABlock B = P.ab[P.fft_list[first + slot]];
     const int64_t k20 = (int64_t)grp << logLines;
+    // the cells that the block's frequencies reach (half of them or fewer: the
+    // grid is twice as fine as they need); the others are not written
+    const double span = fmax(P.ws[B.j1] - B.D, B.D - P.ws[B.j0]) * B.Khi;
+    const int64_t reach = (int64_t)ceil(span) + P.w + 2;
     const double2* xs = scratch + scratch_off + (int64_t)tr * N + (k20 << logL);
     double2* ys = grids + B.grid_off + (int64_t)ch * N + k20;
     constexpr int kPer = kFftTilePts / 256;
@@ -1820,7 +1824,8 @@ __device__ __forceinline__ void fft_row_body(const PlanDev& P, int bid, const Ff
         int e = threadIdx.x + u * 256;
         if (e < tile) {
             int k1 = e >> logLines, li = e & (lines - 1);
-            ys[(int64_t)k1 * N2 + li] = sm[li * ls + k1];
+            const int64_t k = k20 + li + (int64_t)k1 * N2;
+            if (k <= reach || k >= N - reach) ys[(int64_t)k1 * N2 + li] = sm[li * ls + k1];
         }
     }
 }
