@@ -11,8 +11,8 @@ stream; inputs are resident in GPU memory before the timed region.  value =
 synchronised on both sides.
 
 Also reported: execute-only throughput (plans reused), per-stage times from
-HIP events recorded on the transform's stream inside the timed region, the
-roofline of the dominant kernel, and the CPU oracle (direct O(nm) sum) timed
+HIP events recorded on the transform's stream (two stages inside the timed
+region, the others after it), the roofline of an execution, and the CPU oracle (direct O(nm) sum) timed
 on a bounded sample of the same workload.
 
 Prints one JSON line on stdout; progress goes to stderr.
@@ -31,7 +31,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 ORDERS = (0, 1, 10)
-DOMINANT_STAGES = ("spread", "rows_asymptotic")    # the candidates for the dominant kernel
+TIMED_STAGES = ("spread", "rows_asymptotic")       # timed inside the timed region
 SEEDS = {0: 2, 1: 3, 10: 4}
 EPS = 1e-12
 N = M_OUT = 1_000_000
@@ -41,27 +41,6 @@ PEAK_HBM = 8.0e12            # bytes/s
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
-
-
-def read_traffic(kernel):
-    """HBM bytes per launch of `kernel` (for the spreading stage, its two
-    kernels together) from FETCH_SIZE and WRITE_SIZE counters scaled by a
-    plain copy of known size, read from the committed counter summary if it
-    was taken on the current kernel sources; else None."""
-    path = os.path.join(ROOT, "profiles", f"{kernel}_traffic_large_uniform.txt")
-    if not os.path.exists(path):
-        return None
-    rec = {}
-    with open(path) as f:
-        for line in f:
-            if ":" in line and not line.startswith((" ", "#")):
-                k, v = line.split(":", 1)
-                rec[k.strip()] = v.strip()
-    if rec.get("sources_sha256") != sources_sha256():
-        return None
-    fetch, write = float(rec["fetch_bytes_per_launch"]), float(rec["write_bytes_per_launch"])
-    return dict(fetch_bytes=fetch, write_bytes=write, bytes=fetch + write,
-                source=os.path.relpath(path, ROOT))
 
 
 def read_step_traffic():
@@ -558,11 +537,10 @@ def main():
     torch.cuda.synchronize()
     log("warmup done")
 
-    # Inside the timed region events bracket only the two stages that can be
-    # the dominant kernel (the spreading and the asymptotic rows), whose
-    # live durations the roofline uses; the other stages are timed in an
-    # untimed pass afterwards, so that the timed steps carry few events.
-    prof = StageProfile(nuht, stages=DOMINANT_STAGES)
+    # Inside the timed region events bracket only two stages (the spreading
+    # and the rows); the other stages are timed in an untimed pass afterwards,
+    # so that the timed steps carry few events.
+    prof = StageProfile(nuht, stages=TIMED_STAGES)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for _ in range(args.steps):
@@ -582,11 +560,10 @@ def main():
                           "ms_per_step": ms_per_step, "value": value}), flush=True)
         return
 
-    # per-stage times: the dominant-kernel candidates from events recorded
-    # inside the timed region, the others from an untimed pass with every
-    # stage profiled
+    # per-stage times: two stages from events recorded inside the timed region,
+    # the others from an untimed pass with every stage profiled
     infos = prof.infos
-    live_ms = {k: prof.total[k] / args.steps for k in DOMINANT_STAGES}   # per step (3 transforms)
+    live_ms = {k: prof.total[k] / args.steps for k in TIMED_STAGES}   # per step (3 transforms)
     prof_all = StageProfile(nuht)
     all_steps = 5
     for _ in range(all_steps):
@@ -623,70 +600,34 @@ def main():
                                   direct_entries=inf["direct_entries"], fft_points=inf["fft_points"])
     exec_total = sum(v["execute_ms"] for v in per_order.values())
     log("per order:", json.dumps(per_order))
-    log("stage ms per step:", json.dumps(stage_ms), "(live in the timed steps:", ", ".join(DOMINANT_STAGES),
-        "; untimed pass:", json.dumps({k: untimed_ms[k] for k in DOMINANT_STAGES}), ")")
+    log("stage ms per step:", json.dumps(stage_ms), "(live in the timed steps:", ", ".join(TIMED_STAGES),
+        "; untimed pass:", json.dumps({k: untimed_ms[k] for k in TIMED_STAGES}), ")")
 
-    # Roofline of the dominant kernel among those with an algorithmic flop
-    # count (FP64 operations the method's arithmetic needs, per launch; phase
-    # evaluations and index arithmetic are not counted):
-    #   spreading   (k_spread_mfma on dense items, k_spread on the others; one
-    #               stage) every (point, tap) pair inside the kernel support (w taps
-    #               per point membership): the kernel value from its degree-13
-    #               polynomial piece (13 multiply-adds, 26 flops), then 2M complex
-    #               channels x (2 add + 2 mul) and the kernel-weight product:
-    #               26 + 8M + 2 (without the kernel evaluation: 8M + 2)
-    #   k_rows_asy  every (row, cell) pair of a direct-sum-path block: channel
-    #               sum (2M-1) x 4, one complex multiply-add of Horner's rule over
-    #               the cells 8: 8M + 4; every (row, tap) pair of an FFT-path
-    #               block: (2M-1) x 4 + 4 = 8M, plus the tap's kernel value
-    def flops(stage, inf, with_kernel=True):
-        M, w = inf["M"], inf["es_width"]
-        kv = 26.0 if with_kernel else 0.0
-        if stage == "spread":
-            return inf["asy_col_members"] * w * (kv + 8.0 * M + 2.0)
-        return inf["dft_row_cells"] * (8.0 * M + 4.0) + inf["fft_row_members"] * w * (kv + 8.0 * M)
+    # Roofline of an execution: the FP64 operations that the method cannot do
+    # without, over the time of the executions alone.  Every point and every
+    # frequency goes through one local expansion (8 + 2 digits terms, 4
+    # operations each) and one type-3 transform per asymptotic term (2M complex
+    # channels, a kernel digits + 3 wide, 4 operations a tap and channel).
+    # What a kernel spends beyond that (several blocks per point, phases,
+    # kernel values) is not counted, and neither is it counted per kernel: most
+    # blocks go through Chebyshev expansions of lengths that the plan chooses
+    # block by block, so no plan statistic gives a stage's operations except
+    # the local moments' (4 (L + 1) per local column membership).
+    digits = -np.log10(EPS)
 
-    kern = {"spread": "k_spread_mfma+k_spread", "rows_asymptotic": "k_rows_asy"}
-    tfile = {"spread": "spread_stage", "rows_asymptotic": "k_rows_asy"}   # traffic summaries
-    dom = max(kern, key=lambda st: stage_ms[st])
-    fl = sum(flops(dom, infos[nu]) for nu in ORDERS)             # one launch per order per step
-    fl_ch = sum(flops(dom, infos[nu], False) for nu in ORDERS)
-    achieved = fl / (stage_ms[dom] * 1e-3)
-    traffic = read_traffic(tfile[dom])
-    roofline = dict(bound="alu", kernel=kern[dom], achieved=achieved / 1e12, peak=PEAK_FP64 / 1e12,
-                    unit="TFLOP/s", frac=achieved / PEAK_FP64, traffic=traffic,
-                    flops_per_step=fl, launches_per_step=len(ORDERS),
-                    frac_without_kernel_evaluation=fl_ch / (stage_ms[dom] * 1e-3) / PEAK_FP64,
-                    ms_per_step={k: stage_ms[k] for k in kern})
-    # In the timed steps the local moments and direct blocks run on the
-    # library's side stream beside the spreading chain, so the dominant
-    # stage's event-timed duration includes sharing the GPU with them; the
-    # untimed pass (every stage timed) runs all stages on one stream, which
-    # gives the kernel's own rate.
-    one_ms = untimed_ms[dom]
-    roofline["one_stream"] = dict(ms_per_step=one_ms, achieved=fl / (one_ms * 1e-3) / 1e12,
-                                  frac=fl / (one_ms * 1e-3) / PEAK_FP64)
-    if traffic is not None:
-        gbs = len(ORDERS) * traffic["bytes"] / (stage_ms[dom] * 1e-3)
-        roofline.update(traffic_GBps=gbs / 1e9, hbm_frac=gbs / PEAK_HBM)
-    # The other stages with an algorithmic count, each over its own event-timed
-    # duration (the asymptotic rows live in the timed steps, the direct blocks
-    # and local moments in the untimed profiled pass): the asymptotic rows (as
-    # above); the direct
-    # blocks at 200 flops per entry (one J_nu(omega r) and its multiply-add,
-    # the survey's per-entry estimate; the table evaluation spends ~34); the
-    # local moments at 4 (L + 1) flops per local column membership (a
-    # Chebyshev step and a multiply-add per moment).
-    stage_flops = {
-        "spread": fl,
-        "rows_asymptotic": sum(flops("rows_asymptotic", infos[nu]) for nu in ORDERS),
-        "direct": sum(200.0 * infos[nu]["direct_entries"] for nu in ORDERS),
-        "local_moments": sum(4.0 * (infos[nu]["L"] + 1) * infos[nu]["local_col_members"] for nu in ORDERS),
-    }
-    roofline["stages"] = {
-        st: dict(flops_per_step=f, ms_per_step=stage_ms[st], achieved=f / (stage_ms[st] * 1e-3) / 1e12,
-                 frac=f / (stage_ms[st] * 1e-3) / PEAK_FP64)
-        for st, f in stage_flops.items() if stage_ms[st] > 0}
+    def flops(inf):
+        return (N + M_OUT) * (4.0 * (8.0 + 2.0 * digits) + 8.0 * inf["M"] * (digits + 3.0))
+
+    fl = sum(flops(infos[nu]) for nu in ORDERS)
+    achieved = fl / (exec_total * 1e-3)
+    roofline = dict(bound="alu", kernel="execution (all stages)", achieved=achieved / 1e12, peak=PEAK_FP64 / 1e12,
+                    unit="TFLOP/s", frac=achieved / PEAK_FP64, traffic=None,
+                    flops_per_step=fl, launches_per_step=len(ORDERS), ms_per_step=exec_total)
+    lm = sum(4.0 * (infos[nu]["L"] + 1) * infos[nu]["local_col_members"] for nu in ORDERS)
+    if stage_ms["local_moments"] > 0:
+        rate = lm / (stage_ms["local_moments"] * 1e-3)
+        roofline["stages"] = {"local_moments": dict(flops_per_step=lm, ms_per_step=stage_ms["local_moments"],
+                                                    achieved=rate / 1e12, frac=rate / PEAK_FP64)}
     step_traffic = read_step_traffic()
     if step_traffic is not None:
         gbs = step_traffic["bytes_per_step"] / (ms_per_step * 1e-3)
@@ -764,8 +705,8 @@ def main():
         "execute_only_value": len(ORDERS) * (N + M_OUT) / (exec_total * 1e-3),
         "per_order": per_order,
         "stage_ms_per_step": stage_ms,
-        "stage_ms_source": {"timed_region": list(DOMINANT_STAGES),
-                            "untimed_pass": [k for k in stage_ms if k not in DOMINANT_STAGES]},
+        "stage_ms_source": {"timed_region": list(TIMED_STAGES),
+                            "untimed_pass": [k for k in stage_ms if k not in TIMED_STAGES]},
         "roofline": roofline,
         "cpu_baseline": cpu,
         "accuracy": accuracy,

@@ -211,10 +211,11 @@ int nuht_plan_half(nuht_plan_t *plan, int nu2, double eps,
  *   c_dev: n weights in the caller's point order (as passed to nuht_plan).
  *   g_dev: m outputs in the caller's frequency order; overwritten.
  * Asynchronous on `stream`; allocates nothing.  The local moments and direct
- * blocks, which read only the gathered weights, run on a side stream the
- * library keeps per device and rejoin `stream` before the local rows, so the
- * call is ordered on `stream` as one sequence of kernels.  While `stream` is
- * being captured into a graph, or while the local-moment, direct or
+ * blocks (and, beside grids, the blocks applied through Chebyshev expansions),
+ * which read only the gathered weights, run on a side stream the library keeps
+ * per device and rejoin `stream` before the rows, so the call is ordered on
+ * `stream` as one sequence of kernels; small transforms stay on `stream`.
+ * While `stream` is being captured into a graph, or while the local-moment, direct or
  * local-row stages are timed (nuht_profile_stages), every stage runs on
  * `stream`.
  */
@@ -352,8 +353,9 @@ int nuht_batch_destroy(nuht_batch_t batch);
  * Stage timing (diagnostics).  nuht_profile(plan, 1) clears and starts it:
  * every later nuht_execute / nuht_adjoint on the plan records HIP events on its
  * own stream between its NUHT_NSTAGES stages (0 gather of c, 1 local moments,
- * 2 ES spreading, 3 grid assembly, 4 FFTs, 5 direct blocks, 6 asymptotic rows,
- * 7 local rows and output).
+ * 2 ES spreading (and moments of the expansions), 3 grid assembly (and the
+ * expansions' translation), 4 FFTs, 5 direct blocks, 6 rows and output;
+ * 7 is empty: the asymptotic and local rows are one kernel).
  * nuht_profile(plan, 0)
  * stops it.  nuht_profile_stages(plan, mask) does the same for the stages
  * whose bits are set in mask (bit i: stage i; 0 stops), recording events only

@@ -1748,7 +1748,7 @@ static int run(nuht_plan_t p, const Partition& Pt, const double* in, double* out
     io.scale_by_points = scale;
     // The fork needs the plan's events and the side stream; it is left out
     // while `s` is being captured into a graph (the capture stays one stream)
-    // and while the local moments, direct blocks or local rows are timed
+    // and while the local moments, direct blocks or rows are timed
     // (their intervals are taken on `s`).
     ExecFork fork;
     const ExecFork* fk = nullptr;
