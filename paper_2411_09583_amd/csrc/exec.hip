@@ -447,7 +447,10 @@ __device__ __forceinline__ double rank_moments_wave(const PlanDev& P, const Rank
 
 // A large item (four waves) within one or two panels: the waves share each
 // panel's points.  Over more panels: a panel per wave in turn.  A small item's
-// wave takes its panels one after the other.
+// wave takes its panels one after the other, kRankWavePanels at most: a panel
+// is more than a microsecond however few its points, and 300 log-spaced points
+// of order 1.5 in one block of 40 panels kept one wave busy for 50 us of a
+// pass of 121 (about 40 us less with four waves).
 // The K-term instance for an item's block.
 template <class F>
 __device__ __forceinline__ void rank_dispatch(int K, F&& f)
@@ -3061,7 +3064,11 @@ static void launch_fft_large(const PlanDev& P, const FftClass& K, hipStream_t s)
 }
 
 // Transforms of at most this many points and frequencies run on one stream.
-constexpr int64_t kForkMin = 1 << 13;
+// At half-integer orders z is so small that the direct entries lie below the
+// table of J_nu and run a recurrence each, so the fork pays earlier: 155 us a
+// pass on one stream and 116 forked at 2500 x 400, order 1.5, but 86 and 93 at
+// 300 x 300, where the host's launches are the longer.
+constexpr int64_t kForkMin = 1 << 13, kHalfForkMin = 1 << 11;
 // Above this many, and where there are grids, the rank blocks leave the main
 // stream too.
 constexpr int64_t kRankForkMin = 1 << 14;
@@ -3088,7 +3095,7 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
     // stream, 233 on the side one.  Without grids the rank blocks are the main
     // stream's work.
     const bool forked = fork && fork->side && (S.n_litems > 0 || P.n_d > 0) &&
-                        (int64_t)P.n + P.m > kForkMin;
+                        (int64_t)P.n + P.m > (P.half ? kHalfForkMin : kForkMin);
     const bool rank_aside = forked && P.grid_cells > 0 && (int64_t)P.n + P.m > kRankForkMin;
     const hipStream_t ls = forked ? fork->side : s, ks = rank_aside ? fork->side : s;
     auto launch_local = [&] {

@@ -67,8 +67,10 @@ constexpr int kFftPanels = 2;
 // of a block agree to 1e-9 or better from this width (eps <= 1e-8) on; wider
 // tolerances keep the ES transforms, whose own error is part of their results.
 constexpr int kRankMinWidth = 11;
-// Items of at most this many columns take one wave, larger ones four.
+// Items of at most this many columns over at most this many panels take one
+// wave, larger ones four.
 constexpr int kRankWaveCols = 256;
+constexpr int kRankWavePanels = 4;
 // Blocks with one panel of points and at most this many items are translated
 // by the wave that adds up their moments.
 constexpr int kRankSingleItems = 16;
@@ -192,7 +194,7 @@ struct Summary {
     int32_t n_adense, n_amed;  // dense and medium spread items (the first n_adense, then n_amed, of the item list)
     int32_t n_aspread;         // spread items (the items of blocks that are not rank blocks)
     int32_t n_dense_info;      // items of all asymptotic blocks that are dense or medium by their cells
-    int32_t n_ritems, n_rsmall;    // items of rank blocks: of more than kRankWaveCols columns, of at most that many
+    int32_t n_ritems, n_rsmall;    // items of rank blocks: of four waves (kRankWaveCols, kRankWavePanels), of one
     int32_t n_cpan, n_rpan;    // panels of the rank blocks
     int32_t n_tsingle, n_tmulti;   // their panels of frequencies: of blocks translated by one wave, of others
     int32_t n_wmulti;              // panels of points of those others

@@ -2369,7 +2369,7 @@ __device__ __forceinline__ void items(const PlanArgs& a)
                 tmany = B.K > 0 && !tone;
             }
         }
-        const bool small = ritem && R.kb - R.ka <= kRankWaveCols;
+        const bool small = ritem && R.kb - R.ka <= kRankWaveCols && R.nq <= kRankWavePanels;
         const int32_t p0 = wave_append(ritem && !small, &sum->n_ritems), p4 = wave_append(small, &sum->n_rsmall);
         if (ritem) A.rlist[small ? A.aitem_cap - 1 - p4 : p0] = R;
         const int32_t p3 = wave_append(wmany, &sum->n_wmulti);

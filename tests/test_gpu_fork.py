@@ -72,3 +72,20 @@ def test_forked_streams_keep_order(nuht):
         assert torch.allclose(outs_b[k], ref_b * scale, rtol=1e-14, atol=1e-300 + 1e-14 * float(ref_b.abs().max()))
     pa.close()
     pb.close()
+
+
+@pytest.mark.parametrize("n,m", [(300, 300), (2500, 400), (350, 7000)])
+def test_small_half_order_forked_equals_serial(nuht, n, m):
+    print("fork half", n, m, flush=True)
+    r, w, c = workloads.uniform(n, m, 1.0, 0.25 * max(n, m), seed=90 + n)
+    r, w, c = (torch.as_tensor(a, device="cuda") for a in (r, w, c))
+    p = nuht.Plan(r, w, 1.5, 1e-12)
+    g_fork = p.execute(c)
+    g_again = p.execute(c)
+    p.profile(True, stages=["local_moments"])
+    g_serial = p.execute(c)
+    p.profile(False)
+    torch.cuda.synchronize()
+    p.close()
+    assert torch.equal(g_fork, g_serial)
+    assert torch.equal(g_again, g_serial)

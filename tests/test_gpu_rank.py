@@ -83,3 +83,12 @@ def test_rank_widths(nuht, xi):
             assert info["n_fft_blocks"] == 0
         elif xi >= 400.0:   # over 40 panels at every tolerance
             assert info["n_fft_blocks"] == 1
+
+
+@pytest.mark.parametrize("n", [5, 64, 255, 256])
+def test_rank_few_points_many_panels(nuht, n):
+    # items of one wave's columns over more panels than one wave takes, and
+    # about as many as it takes
+    for xi in (3.0, 12.0, 25.0, 130.0):
+        check(nuht, n, 300, xi, 1.5, 1e-12, 3000 + n + int(xi))
+        check(nuht, n, 300, xi, 2, 1e-10, 3500 + n + int(xi))
