@@ -295,31 +295,44 @@ __global__ __launch_bounds__(64) void k_lmom_many(const PlanDev* __restrict__ pl
 // order.  A block can hold a thousand items (the top-level local block spans
 // most columns) and a sum's loads are a chain of latencies, so a wave takes
 // eight moments and eight lanes share each: lane group s adds items s, s + 8,
-// .., four loads in flight, and the groups' sums are combined pairwise.
+// .., four loads in flight, and the groups' sums are combined pairwise.  The
+// moments of a partition (blocks times L + 1) can outnumber what 32 bits count
+// in lanes, so a workgroup takes every kLmomReduceMax-th group of 32 beyond.
+constexpr int64_t kLmomReduceMax = 1 << 20;
+
+__host__ __device__ inline int64_t lmom_reduce_blocks(int64_t n_l, int64_t L)
+{
+    const int64_t b = (n_l * (L + 1) + 31) / 32;
+    return b < kLmomReduceMax ? b : kLmomReduceMax;
+}
+
 __device__ __forceinline__ void lmom_reduce_body(const PlanDev& P, int bid)
 {
     const int lane = threadIdx.x & 63, sub = lane >> 3;
     const int32_t Lp = P.L + 1;
-    const int32_t t = ((bid * (int32_t)blockDim.x + (int32_t)threadIdx.x) >> 6) * 8 + (lane & 7);
-    if (t >= P.n_l * Lp) return;                     // all eight lanes of a moment
-    const int32_t b = t / Lp;
-    const int32_t l = t - b * Lp;
-    const int32_t nitems = P.lb[b].nitems;
-    if (nitems == 1) return;                         // stored by its item
-    const double* __restrict__ col = P.lpart + (int64_t)P.lb[b].item0 * Lp + l;
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
-    int32_t it = sub;
-    for (; it + 24 < nitems; it += 32) {
+    const int64_t total = (int64_t)P.n_l * Lp, step = 32 * lmom_reduce_blocks(P.n_l, P.L);
+    // (all eight lanes of a moment leave the loop together)
+    for (int64_t t = (int64_t)bid * 32 + (threadIdx.x >> 6) * 8 + (lane & 7); t < total; t += step) {
+        // (a 32-bit division wherever the counts allow it)
+        const int32_t b = total <= INT32_MAX ? (int32_t)t / Lp : (int32_t)(t / Lp);
+        const int32_t l = (int32_t)(t - (int64_t)b * Lp);
+        const int32_t nitems = P.lb[b].nitems;
+        if (nitems == 1) continue;                   // stored by its item
+        const double* __restrict__ col = P.lpart + (int64_t)P.lb[b].item0 * Lp + l;
+        double a[4] = {0.0, 0.0, 0.0, 0.0};
+        int32_t it = sub;
+        for (; it + 24 < nitems; it += 32) {
+            #pragma unroll
+            for (int q = 0; q < 4; ++q) a[q] += col[(int64_t)(it + 8 * q) * Lp];
+        }
         #pragma unroll
-        for (int q = 0; q < 4; ++q) a[q] += col[(int64_t)(it + 8 * q) * Lp];
+        for (int q = 0; q < 3; ++q)
+            if (it + 8 * q < nitems) a[q] += col[(int64_t)(it + 8 * q) * Lp];
+        double s = (a[0] + a[1]) + (a[2] + a[3]);
+        #pragma unroll
+        for (int o = 8; o < 64; o <<= 1) s += __shfl_xor(s, o);
+        if (sub == 0) P.lmom[t] = moment_as_used(P, l, s);
     }
-    #pragma unroll
-    for (int q = 0; q < 3; ++q)
-        if (it + 8 * q < nitems) a[q] += col[(int64_t)(it + 8 * q) * Lp];
-    double s = (a[0] + a[1]) + (a[2] + a[3]);
-    #pragma unroll
-    for (int o = 8; o < 64; o <<= 1) s += __shfl_xor(s, o);
-    if (sub == 0) P.lmom[t] = moment_as_used(P, l, s);
 }
 
 __global__ void k_lmom_reduce(PlanDev P) { lmom_reduce_body(P, blockIdx.x); }
@@ -2902,7 +2915,6 @@ __global__ void k_direct_all(PlanDev P, const double* __restrict__ r, const doub
 
 // ---------------------------------------------------------------------------
 static inline int cdiv64(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
-static inline int lmom_reduce_blocks(const PlanDev& P, const Summary& S) { return cdiv64((int64_t)S.n_l * (P.L + 1), 32); }
 
 template <int NCH>
 static void launch_spread(const PlanDev& P, const Summary& S, hipStream_t s)
@@ -3103,7 +3115,7 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
         if (lmom_width(P.L) == 32) hipLaunchKernelGGL(k_lmom<32>, dim3(S.n_litems), dim3(64), 0, ls, P);
         else hipLaunchKernelGGL(k_lmom<64>, dim3(S.n_litems), dim3(64), 0, ls, P);
         if (S.n_litems > S.n_l)   // some block has several items
-            hipLaunchKernelGGL(k_lmom_reduce, dim3(lmom_reduce_blocks(P, S)), dim3(256), 0, ls, P);
+            hipLaunchKernelGGL(k_lmom_reduce, dim3(lmom_reduce_blocks(S.n_l, P.L)), dim3(256), 0, ls, P);
         launch_local_nodes(P, ls);
     };
     auto launch_rank_moments = [&] {
@@ -3232,7 +3244,7 @@ void build_batch_schedule(const BatchTransform* tr, int count, const int* order,
             return live(*T.P) && lmom_width(T.P->L) == width ? T.S->n_litems : 0;
         });
     add(kLmomReduce, 0, 0, 256, [&](const BatchTransform& T, size_t&) -> int64_t {
-        return live(*T.P) && T.S->n_litems > T.S->n_l ? lmom_reduce_blocks(*T.P, *T.S) : 0;
+        return live(*T.P) && T.S->n_litems > T.S->n_l ? lmom_reduce_blocks(T.S->n_l, T.P->L) : 0;
     });
     for (int mode = 0; mode < 4; ++mode)
         add(kLocalNodes, mode, 0, 64, [&](const BatchTransform& T, size_t& lds) -> int64_t {
