@@ -69,14 +69,15 @@ typedef struct nuht_plan_s *nuht_plan_t;
  *                     positions and phases stay double-double, grids are
  *                     assembled in FP64 and every other step is FP64.  Allowed
  *                     for eps >= 1e-7 (else NUHT_EPRECISION).
- *   dft_max           asymptotic blocks whose spread grid has at most this
- *                     many cells are evaluated by a direct sum over the grid
- *                     instead of an FFT and interpolation (0 -> built-in default,
- *                     negative -> always use the FFT path).  In FP64 plans with
- *                     eps at or below about 1e-8 and dft_max >= 0, blocks of a
+ *   dft_max           how asymptotic blocks are applied.  Positive: blocks whose
+ *                     spread grid has at most this many cells by a direct sum
+ *                     over the grid, the others by an FFT and interpolation.
+ *                     Negative: every block by FFT.  0: the built-in choice: in
+ *                     FP64 plans with eps at or below about 1e-8, blocks of a
  *                     small (r range) x (omega range) are applied through
- *                     Chebyshev expansions in r and omega instead (to eps /
- *                     1000) and have no spread grid.
+ *                     Chebyshev expansions in r and omega (to eps / 1000) and
+ *                     have no spread grid; the others, and every block of the
+ *                     other plans, as with 48.
  *   spread_chunk      points per spreading work item, 64 .. 16384 (0 -> 1024).
  *   tune              nonzero: nuht_plan_many picks min_size, dft_max,
  *                     spread_chunk and split_candidates per size class with
@@ -298,9 +299,11 @@ int nuht_plan_order(nuht_plan_t plan, double *r_sorted, int32_t *perm_r, double 
                     int32_t *perm_omega, void *stream);
 
 /*
- * nuht_tune -- pick the spreading work-item size, min_size, dft_max and (unless
- * the plan uses the exact split) split_candidates for this plan's geometry and
- * order: coordinate descent over a few candidates of each, every candidate
+ * nuht_tune -- pick the spreading work-item size, min_size, dft_max (unless it
+ * is 0 and the plan applies blocks through Chebyshev expansions: it then stays
+ * 0, as nothing else would be left for it to decide) and (unless the plan uses
+ * the exact split) split_candidates for this plan's geometry and order:
+ * coordinate descent over a few candidates of each, every candidate
  * planned on the plan's sorted geometry and timed over `reps` executes
  * (0 -> 3) with HIP events on `stream` (c_dev: n weights, or NULL for all
  * ones; the timing does not depend on the values).  With a tuning cache (the

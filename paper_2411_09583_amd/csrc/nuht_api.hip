@@ -1182,8 +1182,9 @@ static int fill_params(PlanDev& P, int nu2, double eps_req, const nuht_opts& o)
     for (int p = 0; p < kMaxChannels; ++p)
         P.chan[p] = p < 2 * M ? (((p >> 1) & 1) ? -P.hank[p] : P.hank[p]) : 0.0;
     // rank blocks where the ES transforms are accurate enough for the two
-    // forms to agree; a caller who asks for FFTs everywhere (dft_max < 0) gets them
-    P.rank = (!P.fp32 && P.w >= kRankMinWidth && o.dft_max >= 0) ? 1 : 0;
+    // forms to agree; a caller who says how the blocks use their grids
+    // (dft_max other than 0) gets grids everywhere
+    P.rank = (!P.fp32 && P.w >= kRankMinWidth && o.dft_max == 0) ? 1 : 0;
     P.rank_const = 1;
     for (int p = 1; p < 2 * M; ++p)
         if (P.chan[p] != 0.0) P.rank_const = 0;
@@ -2107,13 +2108,15 @@ int nuht_plan_set_order(nuht_plan_t p, int nu, void* stream)
 
 // ---------------------------------------------------------------------------
 // Autotuning: the spreading work-item size (points per item), the direct-block
-// threshold min_size, the direct-sum/FFT threshold dft_max and the number of
-// candidate rows of SplitIndices (unless the exact split was asked for), by
-// coordinate descent over a few candidates each, every candidate planned on
-// the plan's own sorted geometry and timed over `reps` executes (after one
-// warm-up) with HIP events on `s`.
+// threshold min_size, the direct-sum/FFT threshold dft_max (where the plan has
+// no rank blocks, which take the place of the grids it decides on) and the
+// number of candidate rows of SplitIndices (unless the exact split was asked
+// for), by coordinate descent over a few candidates each, every candidate
+// planned on the plan's own sorted geometry and timed over `reps` executes
+// (after one warm-up) with HIP events on `s`.
 // ---------------------------------------------------------------------------
-static int tune_plan(nuht_plan_t p, const double* c_dev, int reps, nuht_opts* best, double* best_ms, hipStream_t s)
+static int tune_plan(nuht_plan_t p, const double* c_dev, int reps, bool tune_dft, nuht_opts* best, double* best_ms,
+                     hipStream_t s)
 {
     if (reps < 1) reps = 3;
     DevBuf ones, out;
@@ -2130,7 +2133,7 @@ static int tune_plan(nuht_plan_t p, const double* c_dev, int reps, nuht_opts* be
     nuht_opts cur = saved;
     if (cur.spread_chunk == 0) cur.spread_chunk = kSpreadChunk;
     if (cur.min_size == 0) cur.min_size = default_min_size(p->n, p->m);
-    if (cur.dft_max == 0) cur.dft_max = 48;
+    if (tune_dft && cur.dft_max == 0) cur.dft_max = 48;
     if (cur.split_candidates == 0) cur.split_candidates = 16;
     int rc = NUHT_OK;
     auto time_opts = [&](const nuht_opts& o, double* ms) -> int {
@@ -2160,6 +2163,7 @@ static int tune_plan(nuht_plan_t p, const double* c_dev, int reps, nuht_opts* be
     const int splits[] = {8, 16, 32};
     const int nparam = cur.split_candidates == -1 ? 3 : 4;
     for (int param = 0; param < nparam && rc == NUHT_OK; ++param) {
+        if (param == 2 && !tune_dft) continue;
         int ncand = (param == 0 || param == 1) ? 4 : 3;
         for (int q = 0; q < ncand && rc == NUHT_OK; ++q) {
             nuht_opts o = cur;
@@ -2293,11 +2297,15 @@ static int tune_cached(nuht_plan_t p, const double* c_dev, int reps, nuht_opts* 
     if (!cur) return NUHT_EINVAL;
     const std::string key = tune_key(p, cur->P);
     nuht_opts o = p->opts;
+    // dft_max is tuned where it decides something: a plan with rank blocks
+    // keeps its 0 (an entry's value would take them away, and its 0 stands for
+    // no value)
+    const bool tune_dft = !cur->P.rank;
     TuneEntry e;
     if (!p->cache_path.empty() && cache_lookup(p->cache_path, key, e)) {
         o.spread_chunk = (int32_t)e.spread_chunk;
         o.min_size = e.min_size;
-        o.dft_max = (int32_t)e.dft_max;
+        if (tune_dft && e.dft_max != 0) o.dft_max = (int32_t)e.dft_max;
         if (o.split_candidates != -1) o.split_candidates = (int32_t)e.split_candidates;
         o.tune = 0;
         *best = o;
@@ -2305,7 +2313,7 @@ static int tune_cached(nuht_plan_t p, const double* c_dev, int reps, nuht_opts* 
         return NUHT_OK;
     }
     double ms = 0.0;
-    NUHT_TRY(tune_plan(p, c_dev, reps, &o, &ms, s));
+    NUHT_TRY(tune_plan(p, c_dev, reps, tune_dft, &o, &ms, s));
     if (!p->cache_path.empty()) {
         e.key = key;
         e.spread_chunk = o.spread_chunk; e.min_size = o.min_size; e.dft_max = o.dft_max;
