@@ -1828,10 +1828,11 @@ static int check_plan_args(int nu2, double eps, int64_t n, const double* r_dev, 
 
 // A plan with its geometry: storage allocated, input check and sort launched
 // on `s` (no partition yet, no synchronisation).
-// s: the stream the plan works on (its planning stream); wait_on, if set, is
-// the caller's stream, after whose queued work the inputs are read.
+// s: the stream the plan works on (its planning stream), which reads the inputs
+// after the work queued on the caller's stream `from` (the null stream
+// included).  With from == s that order is there already.
 static int plan_create(nuht_plan_t* out, int nu2, double eps, int64_t n, const double* r_dev, int64_t m,
-                       const double* omega_dev, const nuht_opts& o, hipStream_t s, hipStream_t wait_on)
+                       const double* omega_dev, const nuht_opts& o, hipStream_t s, hipStream_t from)
 {
     *out = nullptr;
     NUHT_TRY(check_plan_args(nu2, eps, n, r_dev, m, omega_dev, o));
@@ -1863,8 +1864,8 @@ static int plan_create(nuht_plan_t* out, int nu2, double eps, int64_t n, const d
         if (p->ev_join) (void)hipEventDestroy(p->ev_join);
         p->ev_fork = p->ev_join = nullptr;
     }
-    if (wait_on) {
-        if (hipEventRecord(p->ev_use, wait_on) != hipSuccess) return fail(NUHT_EHIP);
+    if (from != s) {
+        if (hipEventRecord(p->ev_use, from) != hipSuccess) return fail(NUHT_EHIP);
         if (hipStreamWaitEvent(s, p->ev_use, 0) != hipSuccess) return fail(NUHT_EHIP);
     }
     {
@@ -2449,7 +2450,7 @@ int nuht_plan_many(nuht_batch_t* out, int count, const int* nu, double eps, cons
     b->plans.assign(count, nullptr);
     for (int i = 0; i < count; ++i) {
         int rc = plan_create(&b->plans[i], 2 * nu[i], eps, n[i], r_dev[i], m[i], omega_dev[i], o,
-                             b->aux[b->stream_of[i]], nullptr);
+                             b->aux[b->stream_of[i]], b->aux[b->stream_of[i]]);
         if (rc != NUHT_OK) return fail(rc);
     }
     if (o.tune) {
