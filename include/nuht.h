@@ -149,8 +149,8 @@ typedef struct {
     int64_t min_size;                 /* options in use (after defaults and tuning) */
     int32_t dft_max, spread_chunk;
     int32_t spread_items;             /* column work items of the asymptotic blocks */
-    int32_t dense_items;              /* of which dense: spread on the matrix cores unless their
-                                         block is applied through Chebyshev expansions */
+    int32_t dense_items;              /* of which dense by their cells, whether spread or not
+                                         (nuht_plan_spreading counts what is spread where) */
     int32_t split_candidates;         /* candidate rows of SplitIndices in use (-1: exact) */
     int32_t half_order;               /* 1: the order is nu + 1/2 (nuht_plan_half) */
 } nuht_info;
@@ -285,6 +285,16 @@ int nuht_plan_set_order(nuht_plan_t plan, int nu, void *stream);
 
 /* nuht_plan_info -- parameters and partition statistics of the current order. */
 int nuht_plan_info(nuht_plan_t plan, nuht_info *info);
+
+/*
+ * nuht_plan_spreading -- how the column work items of the current order's
+ * asymptotic blocks (nuht_info.spread_items) run, in counts[4]: spread on the
+ * matrix cores as dense items (their points reach the grid from at most 6
+ * first cells), spread there as medium items (at most 40, up to 16 channels),
+ * spread on the vector units, and not spread (their block is applied through
+ * Chebyshev expansions).  NUHT_EINVAL for a null plan or array.
+ */
+int nuht_plan_spreading(nuht_plan_t plan, int32_t *counts);
 
 /*
  * nuht_plan_order -- the plan's sorted geometry.  The method works on points

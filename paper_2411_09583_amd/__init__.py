@@ -61,7 +61,8 @@ class NuhtInfo(ctypes.Structure):
 # every symbol include/nuht.h declares
 EXPORTS = ("nuht_plan", "nuht_plan_half", "nuht_execute", "nuht_adjoint", "nuht_gradient", "nuht_gradient_noalloc",
            "nuht_plan_set_order",
-           "nuht_plan_info", "nuht_plan_order", "nuht_tune", "nuht_plan_many", "nuht_execute_many", "nuht_batch_info",
+           "nuht_plan_info", "nuht_plan_spreading", "nuht_plan_order", "nuht_tune", "nuht_plan_many",
+           "nuht_execute_many", "nuht_batch_info",
            "nuht_batch_destroy", "nuht_destroy", "nuht_strerror", "nuht_direct", "nuht_profile",
            "nuht_profile_stages", "nuht_profile_read",
            "nuht_fb_plan", "nuht_fb_analysis", "nuht_fb_synthesis", "nuht_fb_helmholtz", "nuht_fb_destroy")
@@ -96,6 +97,7 @@ def load_library():
     lib.nuht_batch_destroy.argtypes = [vp]
     lib.nuht_plan_set_order.argtypes = [vp, ctypes.c_int, vp]
     lib.nuht_plan_info.argtypes = [vp, ctypes.POINTER(NuhtInfo)]
+    lib.nuht_plan_spreading.argtypes = [vp, ctypes.POINTER(ctypes.c_int32)]
     lib.nuht_plan_order.argtypes = [vp, vp, vp, vp, vp, vp]
     lib.nuht_destroy.argtypes = [vp]
     lib.nuht_strerror.argtypes = [ctypes.c_int]
@@ -111,7 +113,7 @@ def load_library():
     lib.nuht_fb_helmholtz.argtypes = [vp, ctypes.c_double, vp, vp, vp, vp, vp]
     lib.nuht_fb_destroy.argtypes = [vp]
     for name in ("nuht_plan", "nuht_plan_half", "nuht_execute", "nuht_adjoint", "nuht_gradient", "nuht_gradient_noalloc",
-                 "nuht_plan_set_order", "nuht_plan_info", "nuht_plan_order",
+                 "nuht_plan_set_order", "nuht_plan_info", "nuht_plan_spreading", "nuht_plan_order",
                  "nuht_tune", "nuht_plan_many", "nuht_execute_many", "nuht_batch_info", "nuht_batch_destroy",
                  "nuht_destroy", "nuht_direct", "nuht_profile", "nuht_profile_stages", "nuht_profile_read",
                  "nuht_fb_plan",
@@ -244,6 +246,14 @@ class Plan:
         inf = NuhtInfo()
         _check(load_library().nuht_plan_info(self._h, ctypes.byref(inf)))
         return {f: getattr(inf, f) for f, _ in NuhtInfo._fields_}
+
+    def spreading(self) -> dict:
+        """How the column work items of the asymptotic blocks run (see
+        nuht_plan_spreading): dense and medium items on the matrix cores,
+        items on the vector units, and items that are not spread."""
+        counts = (ctypes.c_int32 * 4)()
+        _check(load_library().nuht_plan_spreading(self._h, counts))
+        return dict(zip(("dense", "medium", "vector", "not_spread"), counts))
 
     def order(self):
         """The plan's sorted geometry (nuht_plan_order): r sorted, the caller

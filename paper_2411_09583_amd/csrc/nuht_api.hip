@@ -2672,6 +2672,19 @@ int nuht_plan_info(nuht_plan_t p, nuht_info* info)
     return NUHT_OK;
 }
 
+int nuht_plan_spreading(nuht_plan_t p, int32_t* counts)
+{
+    if (!p || !counts) return NUHT_EINVAL;
+    const Partition* cur = current_forward(p);
+    if (!cur) return NUHT_EINVAL;
+    const Summary& S = cur->sum;
+    counts[0] = S.n_adense;
+    counts[1] = S.n_amed;
+    counts[2] = S.n_aspread - S.n_adense - S.n_amed;
+    counts[3] = S.n_aitems - S.n_aspread;
+    return NUHT_OK;
+}
+
 int nuht_profile_stages(nuht_plan_t p, uint32_t mask)
 {
     if (!p) return NUHT_EINVAL;
