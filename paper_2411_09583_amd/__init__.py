@@ -67,6 +67,8 @@ EXPORTS = ("nuht_plan", "nuht_plan_half", "nuht_execute", "nuht_adjoint", "nuht_
            "nuht_profile_stages", "nuht_profile_read",
            "nuht_fb_plan", "nuht_fb_analysis", "nuht_fb_synthesis", "nuht_fb_helmholtz", "nuht_fb_destroy")
 
+# the stages nuht_profile times; all rows are one kernel, which runs as
+# "rows_asymptotic", so "rows_local" is empty
 STAGES = ("gather", "local_moments", "spread", "grid_assembly", "fft", "direct", "rows_asymptotic", "rows_local")
 
 _lib = None

@@ -3167,11 +3167,11 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
     if (S.n_fpan > 0) hipLaunchKernelGGL(k_fft_nodes, dim3(S.n_fpan), dim3(256), 0, s, P);
     mark(marks, 5, s);
     if (!forked) launch_direct();
-    mark(marks, 6, s);
     if (forked) {
         const hipError_t e = hipStreamWaitEvent(s, fork->ev_join, 0);
         if (e != hipSuccess) return e;
     }
+    mark(marks, 6, s);                               // after the wait: the rows' interval holds them alone
     dispatch_rows(rows_channels(P), [&](auto k) {
         hipLaunchKernelGGL(k_rows<decltype(k)::value>, dim3(cdiv64(P.m, 256)), dim3(256), 0, s, P, io.g, io.g_slot);
     });

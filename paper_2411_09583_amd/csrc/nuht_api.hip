@@ -1749,11 +1749,13 @@ static int run(nuht_plan_t p, const Partition& Pt, const double* in, double* out
     io.scale_by_points = scale;
     // The fork needs the plan's events and the side stream; it is left out
     // while `s` is being captured into a graph (the capture stays one stream)
-    // and while the local moments, direct blocks or rows are timed
-    // (their intervals are taken on `s`).
+    // and while a stage is timed that has kernels on the side stream: local
+    // moments, spreading (with the expansions' moments), grid assembly (with
+    // their translation), direct blocks.  The rows start after the join, so
+    // their interval on `s` holds them alone, forked or not.
     ExecFork fork;
     const ExecFork* fk = nullptr;
-    constexpr uint32_t kSerialStages = (1u << 1) | (1u << 5) | (1u << 7);
+    constexpr uint32_t kSerialStages = (1u << 1) | (1u << 2) | (1u << 3) | (1u << 5);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
         (void)hipGetLastError();
