@@ -1252,6 +1252,7 @@ struct PendingPart {
     hipStream_t s = nullptr;
     int32_t cap = 0, icap = 0;
     int attempt = 0;
+    bool apart = true;   // subtrees of the subdivision side by side (subtrees_apart)
     Arena A{};
     Partition tmp;   // the current attempt's tables
     PendingPart() = default;
@@ -1264,6 +1265,12 @@ struct PendingPart {
 // uniform, 71 against 472 at 2 x 1e6 exponential (12000 nodes), but 56 against
 // 43 at 2 x 1e5.
 static bool subtrees_apart(int64_t n, int64_t m) { return n + m > (1 << 19); }
+
+// Planning passes of a partition before its tables are taken to be beyond
+// reach: one for the tables of the blocks, whose counts go on when one
+// overflows, one for a subtree's share, one for the tables of items; where a
+// level's queue overflows they double, from (n + m) / 32 on.
+constexpr int kPlanAttempts = 9;
 
 static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Geometry& G, int nu, hipStream_t s,
                         bool first, bool alone, PlanArgs& a)
@@ -1281,6 +1288,7 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
         Pt.sum = Summary{};
         pp.tmp.release();
         pp.attempt = 0;
+        pp.apart = true;
         pp.Pt = &Pt; pp.G = &G; pp.s = s;
         int64_t tot = (int64_t)G.n + G.m;
         pp.cap = (int32_t)std::min<int64_t>(tot / 32 + 4096, 1 << 28);
@@ -1329,7 +1337,8 @@ static int part_prepare(nuht_plan_t pl, PendingPart& pp, Partition& Pt, const Ge
     slab.add(A.rlist, P.rank ? (size_t)A.aitem_cap : 0);
     // large transforms subdivide their subtrees side by side, unless a subtree
     // outgrew its share of the tables
-    if (subtrees_apart(G.n, G.m) && pp.attempt == 0 && alone) {
+    pp.apart = pp.apart && alone && subtrees_apart(G.n, G.m);
+    if (pp.apart) {
         slab.add(A.stage, (size_t)A.node_cap);
         slab.add(A.sub, (size_t)kSubWords);
     }
@@ -1380,17 +1389,29 @@ static int part_finish(PendingPart& pp, const HostStage* h, bool* again)
     if (h->sum.domain_error) return NUHT_EDOMAIN;
     Summary& S = Pt.sum;
     S = h->sum;
-    if (S.overflow == 2) return NUHT_ECAPACITY;   // subdivision deeper than kMaxLevels
+    if (S.overflow == kOverLevels) return NUHT_ECAPACITY;   // subdivision deeper than kMaxLevels
     if (S.grid_error) return NUHT_ECAPACITY;
     if (S.overflow || S.scan_overflow) {
-        if (++pp.attempt >= 6) return NUHT_ECAPACITY;
+        if (++pp.attempt >= kPlanAttempts) return NUHT_ECAPACITY;
+        *again = true;
         int64_t need = std::max<int64_t>({(int64_t)S.n_nodes, (int64_t)S.n_l, (int64_t)S.n_a, (int64_t)S.n_d / 2,
                                           (int64_t)S.n_cpan / 2, (int64_t)S.n_rpan / 2, (int64_t)S.n_lslots / 2});
+        if (pp.apart && need < pp.cap && (S.overflow == kOverShare || S.overflow == kOverQueue)) {
+            // the tables do, but not a subtree's share of them: by one workgroup
+            pp.apart = false;
+            return NUHT_OK;
+        }
+        if (S.overflow == kOverTables) {
+            // the counts are whole; every local block has an item or more
+            const int32_t cap = (int32_t)std::min<int64_t>(need + need / 8 + 1024, 1 << 29);
+            pp.icap = (int32_t)std::min<int64_t>(pp.icap + 2 * (int64_t)std::max(cap - pp.cap, 0), 1 << 29);
+            pp.cap = cap;
+            return NUHT_OK;
+        }
         if (need >= pp.cap) pp.cap = (int32_t)std::min<int64_t>(2 * need + 1024, 1 << 29);
         int64_t ineed = std::max<int64_t>((int64_t)S.n_litems, (int64_t)S.n_aitems);
         if (ineed >= pp.icap) pp.icap = (int32_t)std::min<int64_t>(2 * ineed + 1024, 1 << 29);
         if (need < pp.cap && ineed < pp.icap) { pp.cap *= 2; pp.icap *= 2; }
-        *again = true;
         return NUHT_OK;
     }
     // keep this attempt's tables

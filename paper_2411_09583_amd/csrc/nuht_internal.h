@@ -184,10 +184,15 @@ struct Item {
     int64_t off;          // spread items: partial-subgrid offset (complex elements)
 };
 
+// What a subdivision overflowed: a table (the counting goes on), the levels, a
+// subtree's share of tables that hold the whole, or the queue of a level (the
+// counts are those so far).
+constexpr int32_t kOverTables = 1, kOverLevels = 2, kOverShare = 3, kOverQueue = 4;
+
 // Written by the planning kernels, read once by the host.
 struct Summary {
     int32_t n_nodes, n_l, n_a, n_d;
-    int32_t levels, overflow;  // overflow: of the subdivision's tables (1) or levels (2)
+    int32_t levels, overflow;  // overflow: kOver*
     int32_t scan_overflow;     // of the tables of items, panels and slots
     int32_t n_litems, n_aitems;
     int32_t n_fft, max_nch;

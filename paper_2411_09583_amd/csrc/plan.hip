@@ -1536,8 +1536,8 @@ __device__ __forceinline__ DBlock direct_block(int32_t j0, int32_t j1, int32_t k
     return DBlock{j0, j1, k0, k1, 0, 0, 0.0, 0.0, 0.0, 0.0};
 }
 
-// Counts of a subdivision: nodes, blocks of each kind, levels; overflow = 1
-// where a table was too small, 2 where there are too many levels.
+// Counts of a subdivision: nodes, blocks of each kind, levels, and what
+// overflowed (kOver*).
 struct SubCounts {
     int32_t nodes, l, a, d, level, overflow;
 };
@@ -1642,13 +1642,14 @@ __device__ __forceinline__ void subdivide_levels(const PlanArgs& a, Rect (*lq)[k
             n_next += tot[3];
         }
         n_nodes += n_cur;
-        if (n_next - kSubLds > q_cap || n_nodes > node_cap) overflow = 1;
-        if (level >= kMaxLevels) overflow = 2;
+        if (n_next - kSubLds > q_cap) overflow = kOverQueue;
+        if (level >= kMaxLevels) overflow = kOverLevels;
         Rect* t = cur; cur = nxt; nxt = t;
         cb ^= 1;
         n_cur = overflow ? 0 : n_next;
         __syncthreads();
     }
+    if (!overflow && n_nodes > node_cap) overflow = kOverTables;
     c = SubCounts{n_nodes, n_l, n_a, n_d, level, overflow};
     *left = n_cur;
     *buf = cb;
@@ -1658,8 +1659,9 @@ __device__ __forceinline__ void store_counts(Summary* __restrict__ sum, const Ar
 {
     sum->n_nodes = c.nodes; sum->n_l = c.l; sum->n_a = c.a; sum->n_d = c.d;
     sum->levels = c.level;
-    sum->overflow = c.overflow != 2 && (c.nodes > A.node_cap || c.l > A.l_cap || c.a > A.a_cap || c.d > A.d_cap)
-                        ? 1 : c.overflow;
+    const bool stopped = c.overflow == kOverLevels || c.overflow == kOverQueue;
+    sum->overflow = !stopped && (c.nodes > A.node_cap || c.l > A.l_cap || c.a > A.a_cap || c.d > A.d_cap)
+                        ? kOverTables : c.overflow;
 }
 
 __device__ __forceinline__ void subdivide(const PlanArgs& a)
@@ -1710,11 +1712,12 @@ __global__ __launch_bounds__(kSubThreads) void k_subtrees(PlanArgs a)
     __shared__ int32_t wsum[4][16];
     __shared__ Rect lq[2][kSubLds];
     const int t = blockIdx.x;
-    if (t >= A.sub[0]) return;
+    const int32_t trees = A.sub[0];
+    if (t >= trees) return;
     const int32_t* q = A.sub + kSubRoots + 4 * t;
     if (threadIdx.x == 0) lq[0][0] = Rect{q[0], q[1], q[2], q[3]};
     __syncthreads();
-    const int32_t cap = A.node_cap / kSubTrees, qcap = A.q_cap / kSubTrees;
+    const int32_t cap = A.node_cap / trees, qcap = A.q_cap / trees;
     SubCounts c{0, 0, 0, 0, A.sub[5], 0};
     int32_t left;
     int buf;
@@ -1751,12 +1754,12 @@ __global__ __launch_bounds__(kSubThreads) void k_subtree_blocks(PlanArgs a)
     const int32_t roots = A.sub[1];
     if (t == 0 && tid == 0)
         store_counts(a.sum, A, SubCounts{roots + trees + tot[0], A.sub[2] + tot[1], A.sub[3] + tot[2],
-                                         A.sub[4] + tot[3], top[0], top[1]});
+                                         A.sub[4] + tot[3], top[0], top[1] == kOverTables ? kOverShare : top[1]});
     if (top[1]) return;
     const int32_t node0 = roots + trees + first[0] - 1;   // node i > 0 of the subtree is node0 + i
     const int32_t l0 = A.sub[2] + first[1], a0 = A.sub[3] + first[2], d0 = A.sub[4] + first[3];
     const int32_t nodes = A.sub[kSubCounts + 8 * t];
-    const Node* __restrict__ stage = A.stage + (int64_t)t * (A.node_cap / kSubTrees);
+    const Node* __restrict__ stage = A.stage + (int64_t)t * (A.node_cap / trees);
     for (int32_t i = tid; i < nodes; i += kSubThreads) {
         Node nd = stage[i];
         if (nd.lblk >= 0) {
