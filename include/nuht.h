@@ -214,8 +214,9 @@ int nuht_plan_half(nuht_plan_t *plan, int nu2, double eps,
  * Asynchronous on `stream`; allocates nothing.  The local moments and direct
  * blocks (and, beside grids, the blocks applied through Chebyshev expansions),
  * which read only the gathered weights, run on a side stream the library keeps
- * per device and rejoin `stream` before the rows, so the call is ordered on
- * `stream` as one sequence of kernels; small transforms stay on `stream`.
+ * per device and rejoin `stream` before the rows (or, where long direct blocks
+ * run beside the rows, after them), so the call is ordered on `stream` as one
+ * sequence of kernels; small transforms stay on `stream`.
  * While `stream` is being captured into a graph, or while a stage is timed that
  * would have kernels on the side stream (nuht_profile_stages: stages 1, 2, 3
  * and 5), every stage runs on `stream`.
@@ -368,15 +369,15 @@ int nuht_batch_destroy(nuht_batch_t batch);
  * own stream between its NUHT_NSTAGES stages (0 gather of c, 1 local moments
  * and the local rows' expansions, 2 ES spreading and moments of the blocks
  * applied through expansions, 3 grid assembly and those blocks' translation,
- * 4 FFTs, 5 direct blocks, 6 rows of every kind and output; 7 is empty: all rows
- * are one kernel).  nuht_profile(plan, 0) stops it.  nuht_profile_stages(plan,
+ * 4 FFTs, 5 direct blocks, 6 rows of every kind and output, 7 the rows' parts
+ * from the direct blocks where they are added after the rows, empty else).  nuht_profile(plan, 0) stops it.  nuht_profile_stages(plan,
  * mask) does the same for the stages whose bits are set in mask (bit i: stage
  * i; 0 stops), recording events only at their boundaries, so that timing a few
  * stages disturbs the execution less; NUHT_EINVAL for bits beyond
  * NUHT_NSTAGES.  While any of stages 1, 2, 3 and 5 is timed, the execution
  * stays on its stream, so that the interval holds the stage's kernels and no
- * others; stages 0, 4 and 6 are timed as they run, 4 beside the side stream's
- * kernels, 6 after both streams have joined.  nuht_profile_read synchronises on
+ * others; stages 0, 4, 6 and 7 are timed as they run, 4 beside the side stream's
+ * kernels, 6 after the rows' inputs have joined, 7 from the rows' end on.  nuht_profile_read synchronises on
  * the last recorded event and writes the per-stage totals in milliseconds to
  * stage_ms[NUHT_NSTAGES] (0 for stages not timed) and the number of profiled
  * calls to *calls (may be NULL).

@@ -2842,8 +2842,9 @@ __device__ __forceinline__ double direct_row(const PlanDev& P, int d, int j, dou
 // NCH: the plan's channels, or 0 where the rows of every asymptotic block go
 // through expansions (no row reads a grid): then one instance serves every
 // order, so that a batch's transforms share a launch.
+// direct = false leaves the direct blocks to k_direct_rows.
 template <int NCH>
-__device__ __forceinline__ void rows_body(const PlanDev& P, int bid, double* g)
+__device__ __forceinline__ void rows_body(const PlanDev& P, int bid, double* g, bool direct)
 {
     const double2* __restrict__ grids = P.grids;
     const int j = bid * blockDim.x + threadIdx.x;
@@ -2875,7 +2876,7 @@ __device__ __forceinline__ void rows_body(const PlanDev& P, int bid, double* g)
             child = nd.ll;
         }
         if (child <= -2) {
-            acc += direct_row(P, decode_direct(child), j, om);
+            if (direct) acc += direct_row(P, decode_direct(child), j, om);
             break;
         }
         node = child;
@@ -2885,9 +2886,19 @@ __device__ __forceinline__ void rows_body(const PlanDev& P, int bid, double* g)
 
 template <int NCH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_rows(PlanDev P, double* g,
-                                                                                     double* const* g_slot)
+                                                                                     double* const* g_slot, int direct)
 {
-    rows_body<NCH>(P, blockIdx.x, g_slot ? *g_slot : g);
+    rows_body<NCH>(P, blockIdx.x, g_slot ? *g_slot : g, direct != 0);
+}
+
+// The rows' parts from the direct blocks, added to what k_rows wrote without
+// them (the last term of a row's sum, so the same result), a workgroup a block.
+__global__ __launch_bounds__(256) void k_direct_rows(PlanDev P, double* g, double* const* g_slot)
+{
+    double* out = g_slot ? *g_slot : g;
+    const int32_t j0 = P.db[blockIdx.x].j0, j1 = P.db[blockIdx.x].j1;
+    for (int32_t j = j0 + (int32_t)threadIdx.x; j <= j1; j += blockDim.x)
+        out[P.perm_w[j]] += P.sign * direct_row(P, blockIdx.x, j, P.ws[j]);
 }
 
 template <int NCH>
@@ -2895,7 +2906,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const PlanDev* __restrict__ plans, const WorkSeg* __restrict__ segs, int nseg, double* const* g_table)
 {
     const WorkSeg w = find_seg(segs, nseg);
-    rows_body<NCH>(plan_of(plans, w.t), w.g0, g_table[w.t]);
+    rows_body<NCH>(plan_of(plans, w.t), w.g0, g_table[w.t], true);
 }
 
 // Brute-force reference: one thread per frequency, all points.
@@ -3084,6 +3095,17 @@ constexpr int64_t kForkMin = 1 << 13, kHalfForkMin = 1 << 11;
 // Above this many, and where there are grids, the rank blocks leave the main
 // stream too.
 constexpr int64_t kRankForkMin = 1 << 14;
+// A direct block of more than this many entries below the table of J_nu, a
+// recurrence each (half-integer orders and high ones), keeps k_direct_blocks
+// busy for longer than the other stages of most transforms, 100 to 280 us: then
+// the rank blocks stay on the main stream whatever the sizes, and the rows do
+// not wait for the direct blocks.
+constexpr int32_t kDirectHeavy = 2048;
+// The other executions whose rows do not wait for the direct blocks: few rows,
+// whose pass is a chain of latencies as long as the main stream's whole work
+// where that has no FFT, of this many points and frequencies or more (without
+// rank blocks, with them).
+constexpr int64_t kLateRows = 1024, kLateMin = 1 << 14, kLateRankMin = 1 << 17;
 
 hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers& B, const FftClass* cls, int ncls,
                           const IoArgs& io, hipStream_t s, hipEvent_t* marks, const ExecFork* fork)
@@ -3108,7 +3130,21 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
     // stream's work.
     const bool forked = fork && fork->side && (S.n_litems > 0 || P.n_d > 0) &&
                         (int64_t)P.n + P.m > (P.half ? kHalfForkMin : kForkMin);
-    const bool rank_aside = forked && P.grid_cells > 0 && (int64_t)P.n + P.m > kRankForkMin;
+    // The rows wait for the local rows' expansions and, as a rule, for the
+    // direct blocks.  Where those are the side stream's long work, the rows run
+    // beside them instead and the direct blocks' parts are added at the end
+    // (us, at the start of the two-pass rows that one pass replaced, with the
+    // wait, without it):
+    //   5.5 radial 30000 x 500 (direct 236 us): 317, 359, 286
+    //   1.5 uniform 100000 x 100000: 310, 342, 299
+    //   40 radial 30000 x 500: 513, 441, 306
+    //   0 radial 300000 x 500 at 1e-6: 114, 143, 115
+    // Elsewhere the addition costs its launch: 500 x 300000 at 1e-6 101 with the
+    // wait, 107 without; 30000 x 30000 uniform 130 and 143.
+    const bool heavy = forked && S.d_area > kDirectHeavy;
+    const bool rank_aside = forked && !heavy && P.grid_cells > 0 && (int64_t)P.n + P.m > kRankForkMin;
+    const bool late = heavy || (forked && P.n_d > 0 && S.n_fft == 0 && P.m <= kLateRows &&
+                                (int64_t)P.n + P.m > (P.rank ? kLateRankMin : kLateMin));
     const hipStream_t ls = forked ? fork->side : s, ks = rank_aside ? fork->side : s;
     auto launch_local = [&] {
         if (S.n_litems == 0) return;
@@ -3136,8 +3172,14 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
         if (e == hipSuccess) e = hipStreamWaitEvent(ls, fork->ev_fork, 0);
         if (e != hipSuccess) return e;
     }
-    if (!rank_aside) launch_local();
-    if (forked && !rank_aside) launch_direct();
+    // what the rows wait for ends on the side stream: with late, before the direct blocks
+    auto join_rows = [&](bool here) { return here ? hipEventRecord(fork->ev_join, ls) : hipSuccess; };
+    hipError_t e_join = hipSuccess;
+    if (!rank_aside) {
+        launch_local();
+        e_join = join_rows(late);
+        if (forked) launch_direct();
+    }
     mark(marks, 2, s);
     if (!rank_aside) launch_rank_moments();
     dispatch_channels(P.nch, [&](auto k) { launch_spread<decltype(k)::value>(P, S, s); });
@@ -3147,11 +3189,12 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
         launch_local();
     }
     launch_rank_rows();
-    if (rank_aside) launch_direct();
-    if (forked) {
-        const hipError_t e = hipEventRecord(fork->ev_join, ls);
-        if (e != hipSuccess) return e;
+    if (rank_aside) {
+        if (e_join == hipSuccess) e_join = join_rows(late);
+        launch_direct();
     }
+    if (e_join == hipSuccess) e_join = late ? hipEventRecord(fork->ev_fork, ls) : join_rows(forked);
+    if (e_join != hipSuccess) return e_join;
     if (P.grid_cells > 0) {
         if (P.fp32)
             hipLaunchKernelGGL(k_spread_reduce<float2>, dim3(cdiv64(P.grid_units, 256)), dim3(256), 0, s, P);
@@ -3173,9 +3216,15 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
     }
     mark(marks, 6, s);                               // after the wait: the rows' interval holds them alone
     dispatch_rows(rows_channels(P), [&](auto k) {
-        hipLaunchKernelGGL(k_rows<decltype(k)::value>, dim3(cdiv64(P.m, 256)), dim3(256), 0, s, P, io.g, io.g_slot);
+        hipLaunchKernelGGL(k_rows<decltype(k)::value>, dim3(cdiv64(P.m, 256)), dim3(256), 0, s, P, io.g, io.g_slot,
+                           late ? 0 : 1);
     });
     mark(marks, 7, s);
+    if (late) {
+        const hipError_t e = hipStreamWaitEvent(s, fork->ev_fork, 0);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_direct_rows, dim3(P.n_d), dim3(256), 0, s, P, io.g, io.g_slot);
+    }
     mark(marks, 8, s);
     return hipGetLastError();
 }

@@ -207,6 +207,7 @@ struct Summary {
     int32_t n_gridrows;            // asymptotic blocks whose rows read the grids
     int32_t n_lslots, n_lwork;     // slots of the local blocks' rows; waves that fill them
     int32_t n_dentry, n_drank;     // direct blocks applied entry by entry, through expansions
+    int32_t d_area, pad;           // largest of the former that reaches below the J_nu table
     int64_t l_row, l_col, a_row, a_col, d_ent;
     int64_t grid_cells;     // sum N1 (all asymptotic blocks)
     int64_t grid_units;     // threads that assemble the grids

@@ -1964,6 +1964,10 @@ __device__ __forceinline__ void block_params(const PlanArgs& a)
             if (2.0 * (nb * (2.0 * K + 20.0) + 60.0 * K * K + 2.0 * K * mb) < 45.0 * mb * nb) E.K = (int32_t)K;
         }
         A.db[b] = E;
+        if (E.K == 0 && (P.jtab_np == 0 || wlo * rlo < P.jtab_x0)) {
+            const int64_t area = (int64_t)(E.j1 - E.j0 + 1) * (E.k1 - E.k0 + 1);
+            atomicMax(&sum->d_area, area < INT32_MAX ? (int32_t)area : INT32_MAX);
+        }
     }
     if (__ballot(entries != 0)) {
         for (int o = 32; o >= 1; o >>= 1) entries += __shfl_xor(entries, o);
