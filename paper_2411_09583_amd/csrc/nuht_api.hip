@@ -1887,7 +1887,11 @@ static int plan_create(nuht_plan_t* out, int nu2, double eps, int64_t n, const d
         if (p->ev_join) (void)hipEventDestroy(p->ev_join);
         p->ev_fork = p->ev_join = nullptr;
     }
-    if (from != s) {
+    // (an idle stream holds nothing to wait for: the event and the wait take 40
+    // us of an otherwise idle GPU's time)
+    const bool busy = from != s && hipStreamQuery(from) != hipSuccess;
+    (void)hipGetLastError();
+    if (busy) {
         if (hipEventRecord(p->ev_use, from) != hipSuccess) return fail(NUHT_EHIP);
         if (hipStreamWaitEvent(s, p->ev_use, 0) != hipSuccess) return fail(NUHT_EHIP);
     }
