@@ -12,7 +12,8 @@
  * J_nu(omega_j r_k) is split along omega r = z by Alg. 1 (Sec. 4.1); local
  * blocks are applied with the Wimp expansion (Sec. 3.1), asymptotic blocks with
  * 2M type-3 NUFFTs of Hankel's expansion (Sec. 3.2), and a few small direct
- * blocks entry by entry.
+ * blocks entry by entry.  (Where Chebyshev expansions in both variables give a
+ * block to well below eps at less cost, it goes through those.)
  *
  * Conventions for every entry point:
  *  - Pointers named *_dev are device pointers (HIP global memory) of FP64
@@ -247,8 +248,8 @@ int nuht_adjoint(nuht_plan_t plan, const double *y_dev, double *cbar_dev, void *
  * domega may be NULL (not computed); c_dev may be NULL when neither dr nor
  * domega is asked for.  Outputs are in the caller's order and overwritten.
  * Orders nu -+ 1 need |nu| <= 100.  The partitions of the orders used are
- * built on the first call (one synchronisation each) and kept in the plan
- * (up to four orders), as are two n- and two m-sized temporaries; later calls
+ * built on the first call (together, with one synchronisation) and kept in the
+ * plan (up to four orders), as are two n- and two m-sized temporaries; later calls
  * are asynchronous on `stream` and allocate nothing.
  */
 int nuht_gradient(nuht_plan_t plan, const double *c_dev, const double *gbar_dev,

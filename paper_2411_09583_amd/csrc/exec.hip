@@ -1,6 +1,7 @@
 // exec.hip -- execution of a planned transform (Alg. 2): local blocks by the
 // Wimp expansion (Sec. 3.1), asymptotic blocks by type-3 NUFFTs of Hankel's
-// expansion (Sec. 3.2), direct blocks entry by entry.
+// expansion (Sec. 3.2) or, the smaller ones, Chebyshev expansions in both
+// variables, direct blocks entry by entry or through such expansions.
 //
 // Column side (reductions over points):  gather c -> local moments ->
 //   ES spreading of 2M weight channels onto each asymptotic block's grid.
@@ -458,12 +459,6 @@ __device__ __forceinline__ double rank_moments_wave(const PlanDev& P, const Rank
     return wave_sums<2 * KC>(acc, s, lane);
 }
 
-// A large item (four waves) within one or two panels: the waves share each
-// panel's points.  Over more panels: a panel per wave in turn.  A small item's
-// wave takes its panels one after the other, kRankWavePanels at most: a panel
-// is more than a microsecond however few its points, and 300 log-spaced points
-// of order 1.5 in one block of 40 panels kept one wave busy for 50 us of a
-// pass of 121 (about 40 us less with four waves).
 // The K-term instance for an item's block.
 template <class F>
 __device__ __forceinline__ void rank_dispatch(int K, F&& f)
@@ -476,6 +471,13 @@ __device__ __forceinline__ void rank_dispatch(int K, F&& f)
 
 // Workgroups 0 .. n_ritems - 1: a large item each; then four small items
 // each, one per wave.
+//
+// A large item (four waves) within one or two panels: the waves share each
+// panel's points.  Over more panels: a panel per wave in turn.  A small item's
+// wave takes its panels one after the other, kRankWavePanels at most: a panel
+// is more than a microsecond however few its points, and 300 log-spaced points
+// of order 1.5 in one block of 40 panels kept one wave busy for 50 us of a
+// pass of 121 (about 40 us less with four waves).
 __device__ __forceinline__ void rank_moments_body(const PlanDev& P, int bid)
 {
     __shared__ double s_m[kRankWaves][2 * kRankK];
@@ -1370,10 +1372,11 @@ __global__ __launch_bounds__(256) void k_spread_mfma_many(const PlanDev* __restr
 // A thread takes a slot with all its channels: the items that cover it are
 // found, and the deconvolution computed, once, and a thread's loads and the
 // wave's stores are contiguous (101 us at the 1e6 zeros of J_0, 6 channels of
-// 2^22 points, and 76 without the zeros; 196 with a thread a slot and channel).  Where a block's points
-// crowd its cells (grid_crowded) dozens of items cover each, and the block's
-// slots take a thread a channel (at 1e6 x 1e6 uniform points 19 us, 122
-// without).  A crowded slot of another block is added up by the whole wave.
+// 2^21 points and less, and 76 without the zeros; 196 with a thread a slot and
+// channel).  Where a block's points crowd its cells (grid_crowded) dozens of
+// items cover each, and the block's slots take a thread a channel (at 1e6 x 1e6
+// uniform points 19 us, 122 without).  A crowded slot of another block is added
+// up by the whole wave.
 // ---------------------------------------------------------------------------
 // Partial i as double2: PT is double2, or float2 in the FP32-spreading mode
 // (widened here, so the grids are assembled in FP64).

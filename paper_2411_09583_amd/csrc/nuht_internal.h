@@ -22,12 +22,16 @@ constexpr int kMaxFftLog2 = 24;        // largest FFT of an asymptotic block: 2^
 inline __host__ __device__ int32_t local_chunk(int32_t n) { return n <= (1 << 17) ? 256 : n <= (1 << 19) ? 512 : 1024; }
 constexpr int kSpreadChunk = 1024;     // default points per spreading work item (a plan option)
 // Default direct-block threshold of Alg. 1 for an n x m transform.  The
-// paper leaves min_size to numerical experiments (its example: 1024).  On
-// MI355X, with the direct entries read from a J_nu table, the fastest
-// threshold grows with the matrix: 1024 for n m below about 5e5, 2048 near
-// 1e6, 8192 from about 1e7 on (uniform, radial, exponential, Fourier-Bessel
-// and batched workloads).  The rule takes the power of two at or below
-// n m / 256, within [1024, 8192].
+// paper leaves min_size to numerical experiments (its example: 1024).  The rule
+// takes the power of two at or below n m / 256, within [1024, 8192]; it was
+// found when every direct block was applied entry by entry, and most are
+// applied through expansions now.  An execution's time over that of the best of
+// 256 .. 131072 (geometric mean over orders 0, 10, 40 and 3/2, tolerances 1e-6
+// to 1e-12 and three layouts), with the rule's threshold and the best fixed one:
+// 500 x 500 1.07 and 1.04 (256), 1000 x 1000 1.02, 2000 x 2000 1.11 and 1.02
+// (2048), 5000 x 5000 1.04 and 1.02 (16384), 1e5 x 1e5 1.09, 3e5 x 3e5 1.13 and
+// 1.11 (4096), 1e6 x 1e6 1.12 and 1.10 (16384); far off only where points
+// outnumber frequencies many times, 30000 x 500 1.24 and 1.03 (256).
 constexpr int64_t kMinSizeLo = 1024;
 constexpr int64_t kMinSizeHi = 8192;
 inline int64_t default_min_size(int64_t n, int64_t m) {
@@ -62,10 +66,12 @@ constexpr int kRankPanels = 40;
 // Neighbouring panels of an FFT-path block's frequencies expanded by one
 // workgroup.
 constexpr int kFftPanels = 2;
-// The narrowest ES kernel at which plans have rank blocks: the expansions are
-// good to eps / 100 and the ES transforms to about 10^(1-w), so the two forms
-// of a block agree to 1e-9 or better from this width (eps <= 1e-8) on; wider
-// tolerances keep the ES transforms, whose own error is part of their results.
+// The narrowest ES kernel at which plans have rank blocks (eps up to about
+// 1e-8).  The expansions are good to max(eps / 1000, 2e-16) and the ES transforms
+// to about 10^(1-w), so the two forms of a block agree to 1e-9 or better from
+// this width on.  That is no limit of the expansions, which are the more exact
+// form everywhere: looser plans keep the grids that they had, and so their
+// results.
 constexpr int kRankMinWidth = 11;
 // Items of at most this many columns over at most this many panels take one
 // wave, larger ones four.

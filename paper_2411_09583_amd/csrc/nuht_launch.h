@@ -127,7 +127,7 @@ struct FftClass {
 
 // Execution stages, timed between consecutive events of `marks` (kStages + 1
 // events, or null; a null entry records nothing).
-constexpr int kStages = 8;   // gather, local moments and row expansions, spread, grid assembly, FFT, direct, rows, (none)
+constexpr int kStages = 8;   // gather, local moments and row expansions, spread, grid assembly, FFT, direct, rows, late direct parts
 // Input and output of one transform.  When the slots are set, the kernels
 // read the input and output pointers from those device locations at run time
 // (so a captured graph serves any buffers); otherwise c and g are used.  With
@@ -146,7 +146,9 @@ struct IoArgs {
 // (local moments, direct blocks, and beside grids the rank blocks): after the
 // gather `s` records ev_fork, `side` waits for it and runs them, records
 // ev_join, and `s` waits for ev_join before the rows, the first stage to read
-// their results.
+// their results.  Where the rows run beside the direct blocks, ev_join is
+// recorded before these, ev_fork once more after them, and `s` waits for that
+// before their parts are added.
 struct ExecFork {
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
