@@ -1553,6 +1553,15 @@ static void before_free(nuht_plan_t p)
     if (p->used && p->ps && p->ev_use) (void)hipStreamWaitEvent(p->ps, p->ev_use, 0);
 }
 
+// The same for partitions that are released while the plan lives: memory freed
+// in the planning stream's order may be handed, at once, to a plan of another
+// thread and used on that one's stream, so the host waits for the last use
+// (the partitions built in their place make it wait anyway).
+static void wait_for_use(nuht_plan_t p)
+{
+    if (p->used && p->ev_use && hipEventSynchronize(p->ev_use) != hipSuccess) (void)hipGetLastError();
+}
+
 static void note_use(nuht_plan_t p, hipStream_t s)
 {
     if (p->ev_use && hipEventRecord(p->ev_use, s) == hipSuccess) p->used = true;
@@ -1707,7 +1716,7 @@ static nuht_plan_s::OrderParts* order_parts(nuht_plan_t p, int nu)
                 (victim == p->orders.size() || p->orders[i]->used < p->orders[victim]->used))
                 victim = i;
         if (victim < p->orders.size()) {
-            before_free(p);
+            wait_for_use(p);
             p->orders.erase(p->orders.begin() + victim);
         }
     }
@@ -2367,6 +2376,7 @@ int nuht_tune(nuht_plan_t p, const double* c_dev, int reps, nuht_opts* best, dou
     o.margin = p->opts.margin;
     o.tune_cache = nullptr;
     p->opts = o;
+    wait_for_use(p);   // executions on other streams
     p->orders.clear();
     Partition* Pt = nullptr;
     NUHT_TRY(get_partition(p, p->nu2_req, false, s, &Pt));
