@@ -3135,15 +3135,15 @@ hipError_t launch_execute(const PlanDev& P, const Summary& S, const ExecBuffers&
                         (int64_t)P.n + P.m > (P.half ? kHalfForkMin : kForkMin);
     // The rows wait for the local rows' expansions and, as a rule, for the
     // direct blocks.  Where those are the side stream's long work, the rows run
-    // beside them instead and the direct blocks' parts are added at the end
-    // (us, at the start of the two-pass rows that one pass replaced, with the
-    // wait, without it):
-    //   5.5 radial 30000 x 500 (direct 236 us): 317, 359, 286
-    //   1.5 uniform 100000 x 100000: 310, 342, 299
-    //   40 radial 30000 x 500: 513, 441, 306
-    //   0 radial 300000 x 500 at 1e-6: 114, 143, 115
-    // Elsewhere the addition costs its launch: 500 x 300000 at 1e-6 101 with the
-    // wait, 107 without; 30000 x 30000 uniform 130 and 143.
+    // beside them instead and the direct blocks' parts are added at the end.
+    // Microseconds a pass with rows that wait, and with rows that do not:
+    //   order 5.5, radial, 30000 x 500 (direct blocks 236)   359   286
+    //   order 3/2, uniform, 100000 x 100000                  342   299
+    //   order 40, radial, 30000 x 500                        441   306
+    //   order 0, radial, 300000 x 500, at 1e-6               143   115
+    // Elsewhere the addition only costs its launch:
+    //   order 0, uniform, 500 x 300000, at 1e-6              101   107
+    //   order 0, uniform, 30000 x 30000, at 1e-6             130   143
     const bool heavy = forked && S.d_area > kDirectHeavy;
     const bool rank_aside = forked && !heavy && P.grid_cells > 0 && (int64_t)P.n + P.m > kRankForkMin;
     const bool late = heavy || (forked && P.n_d > 0 && S.n_fft == 0 && P.m <= kLateRows &&
